@@ -89,8 +89,10 @@ int check_backward_support(int L, int dtype, bool want_dbias) {
     return FWA_OK;
 }
 
-// Row statistics the large-window backward leaves for its dBias kernel: [N, heads, 2, 16 nb] floats
-size_t large_stats_bytes(int64_t N, int L, int heads) {
+// Part of the published workspace size of a large-window call with dBias that the kernels no longer use (two floats
+// per padded query and head; the row statistics now travel inside dV and dK, see fwa_backward_large.hip).  Sizes
+// that callers have stored, and the set of calls that fit fwa_backward_noalloc's scratch, stay what they were.
+size_t large_reserved_bytes(int64_t N, int L, int heads) {
     const size_t nb = (size_t)(L + 15) / 16;
     return (size_t)N * heads * 2 * 16 * nb * sizeof(float);
 }
@@ -229,7 +231,7 @@ size_t fwa_backward_workspace_bytes(int64_t N, int L, int C, int heads, int dtyp
         // room for the fp32 copy of a bf16 bias whether or not the call will pass one
         const size_t copy = large_bias_copy_bytes(L, heads);
         if (!want_dbias) return copy;
-        return copy + large_stats_bytes(N, L, heads) +
+        return copy + large_reserved_bytes(N, L, heads) +
                (size_t)fwa::backward_large_slots(N, heads, L) * heads * nb * nb * 256 * sizeof(float);
     }
     if (!want_dbias) return 0;
@@ -341,14 +343,14 @@ int backward_impl(const void* q, const void* k, const void* v, const void* d_o, 
     a.slots = C / heads != fwa::kHeadDim ? fwa::backward_wide_slots(N, heads)
               : large                    ? fwa::backward_large_slots(N, heads, L)
                                          : fwa::backward_slots(N, heads, a.per_window ? 1 : a.nW);
-    // workspace: [fp32 copy of a bf16 bias (large windows only)] [row statistics (large windows
-    // with dBias)] [partial sums of dBias]; a call needs the parts it uses
+    // workspace: [fp32 copy of a bf16 bias (large windows only)] [partial sums of dBias]; a call needs the
+    // parts it uses
     const bool copy_bias = large && bias && bias_dtype == FWA_BF16;
     const size_t copy_room = large ? large_bias_copy_bytes(L, heads) : 0;
     if (static_scratch) {
         // the parts at their exact sizes for this call, out of the library's own array
         const size_t nb = (size_t)(L + 15) / 16;
-        const size_t exact = (copy_bias ? copy_room : 0) + (dbias && large ? large_stats_bytes(N, L, heads) : 0) +
+        const size_t exact = (copy_bias ? copy_room : 0) + (dbias && large ? large_reserved_bytes(N, L, heads) : 0) +
                              (dbias ? (size_t)a.slots * heads * nb * nb * 256 * sizeof(float) : 0);
         if (exact > FWA_NOALLOC_SCRATCH_BYTES) return FWA_ERR_WORKSPACE;
         workspace = nullptr;
@@ -370,11 +372,6 @@ int backward_impl(const void* q, const void* k, const void* v, const void* d_o, 
         ws += copy_room;
     }
     a.partial = dbias ? reinterpret_cast<float*>(ws) : nullptr;
-    a.stats = nullptr;
-    if (dbias && large) {  // [row statistics][partial sums]
-        a.stats = reinterpret_cast<float*>(ws);
-        a.partial = reinterpret_cast<float*>(ws + large_stats_bytes(N, L, heads));
-    }
     a.bias = bias; a.bias_bf16 = bias && bias_dtype == FWA_BF16;
     a.ldq = (int)ld_qkv; a.ldg = (int)ld_do; a.ldd = (int)ld_dqkv; a.f16 = dtype == FWA_F16;
     // the one-wave-per-tile kernel takes fp32 biases only

@@ -1,127 +1,394 @@
 // Backward (paper Algorithm 2) for 64 < L <= 256: the score matrix of a tile no longer fits
 // the registers of a few waves, so it is produced twice, block by block, in the two
-// orientations the two kinds of output need, and never leaves the registers.
+// orientations the two kinds of output need, by two kernels, and never leaves the registers.
 //
-// A workgroup of W = 4 (NB <= 10) or 8 waves (NB = ceil(L / 16) blocks of 16 rows; a multiple of
-// the 4 SIMDs, so that two 4-wave workgroups or one 8-wave workgroup load a CU evenly) owns one head,
-// parks the K, V, Q, dO slabs of the current window in LDS and walks the windows
-// bw, bw + G, ...  Per window:
-//
-//   pass 1, wave <-> 16-query blocks qb = wave, wave + W, ... ("query on the lane": lane (g, n), slot r of key block
-//   jb stands for query 16 qb + n and key 16 jb + 4g + r):
+//   rows kernel, wave <-> one block of 16 queries ("query on the lane": lane (g, n), slot r of key block jb stands for
+//   query 16 qb + n and key 16 jb + 4g + r):
 //       S^T = K Q^T for all key blocks, + bias + mask, row max, exp, row sum
 //       delta_i = sum_j P_ij dP_ij with dP^T = V dO^T produced block by block
-//       M_i = max_i + log2(sum_i) and delta_i go to LDS for pass 2
 //       dQ rows of the block: dS^T is already the operand of dQ^T = K^T dS^T (dP recomputed
 //       block by block; K^T through the transposing LDS read)
-//   pass 2, wave <-> 16-key blocks jb = wave, wave + W, ... ("key on the lane": lane (g, n), slot r of query block qb
+//       M_i = max_i + log2(sum_i) and -delta_i of the block's rows for the other kernel
+//   keys kernel, wave <-> one block of 16 keys ("key on the lane": lane (g, n), slot r of query block qb
 //   stands for query 16 qb + 4g + r and key 16 jb + n):
 //       S = Q K^T and dP = dO V^T block by block, P = exp2(score - M_i), dS = P (dP - delta_i):
 //       the accumulator layout is exactly the operand layout of dV^T = dO^T P and dK^T = Q^T dS
-//       with the queries on the k-slots, so P and dS go straight back into the matrix cores.
+//       with the queries on the k-slots, so P and dS go straight back into the matrix cores;
+//       with DB, dS is added to dBias[all queries][the wave's keys], held in registers across windows.
 //
 // Nothing is transposed and no L x L tile is ever stored; the price is a second S / dP / exp.
 // P and dS enter the matrix cores as hi + lo bf16 pairs (16 significant bits), as in the
 // kernels for small windows.
 //
-// Additive term: in pass 2 a lane needs B[i][j] for 4 queries and one key, 16 lanes cover 16
-// consecutive keys: dword loads, 64 contiguous bytes per 16 lanes.  In pass 1 a lane needs 4
-// consecutive keys of one query row and neighbouring lanes sit in different rows, which the
-// memory pipeline serves a lane at a time; there the wave copies 16 rows x 64 columns at a time
-// with row-contiguous 16-byte loads into a private LDS patch and picks its values from there.
+// Both kernels are persistent: a wave keeps its block for life and its workgroup walks the windows bw, bw + G, ...
+// What bounds them is vector instructions (8 to 10 per score besides the exponential, six of them in the keys kernel
+// for the two hi/lo splits), so everything that does not change from window to window stays out of the loop:
+// (bias + mask[w mod nW]) * log2e of the block's 16 x L scores sits in registers (G is a multiple of the mask
+// period), -delta_i enters as the accumulator the product dO V^T starts from.  Reading the additive term per window
+// instead (the form for dense masks whose period no G is a multiple of) costs its loads, the LDS patch that turns
+// rows into lanes, and three to four more instructions per score.  Measured, N = 1024 windows of 16 x 16 tokens,
+// 4 heads, bias + labels + dBias: rows 210 -> 154 us, keys 283 -> 185 us (kernels of their own that read the term per
+// window and parked the slabs out of registers between two barriers), the whole call 465 -> 339 us; N = 315 windows
+// of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 59 us.  Vector instructions issue in
+// 60-64 % of the cycles now, the matrix cores are busy for 25 %, the LDS for 40-48 %.
+//
+// The statistics M_i, -delta_i (8 bytes per query) travel from one kernel to the other inside the outputs that the
+// second one overwrites: the 16 floats of a query block are as long as the 64-byte slice of the head in one token
+// row, and every workgroup of the keys kernel finds the statistics of all query blocks in the rows of its own first
+// key block -- M in dV, -delta in dK, query block qb in row 16 part + qb -- which it alone reads, and overwrites
+// when it has.  So neither kernel needs scratch memory but for the dBias partial sums.
 #include "fwa_device.h"
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
-
-#include <type_traits>
 
 namespace fwa {
 namespace {
 
 struct LargeGeom {
-    uint32_t heads, G;
+    uint32_t heads, parts, G;
     uint32_t xcd_q, xcd_r;
 };
 
-constexpr int large_waves(int nb) { return nb <= 10 ? 4 : 8; }
-// Slab rows of the kernel below in 16-byte units: 64 bytes of data and no padding.  Row-operand and transposing
-// reads run at the same rate as with 16 bytes of padding (measured), and the smaller workgroup lets a CU hold a third
-// one where registers allow (pass 1 alone at L = 100: 294 -> 261 us with dBias).
+// Slab rows in 16-byte units: 64 bytes of data and no padding.  Row-operand and transposing
+// reads run at the same rate as with 16 bytes of padding (measured).
 constexpr uint32_t kLargeStride = 4;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
 __device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
     const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
     return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
 }
 
-// HB: no bias (0) or an fp32 bias (1; a bf16 bias arrives as an fp32 copy made once per call); HM: no mask (0), a dense mask (1), or region
-// labels from which the mask values are formed in registers (2).  What is absent costs neither
-// loads nor registers.
-// P2 = false: pass 1 only (dQ, and the row statistics to the workspace); dK, dV and dBias are then
-// left to bwd_bf16_large_keys_kernel.
-template <int NB, int HB, int HM, bool P2>
-__global__ void __launch_bounds__(64 * large_waves(NB)) bwd_bf16_large_kernel(BwdArgs p, LargeGeom gm) {
-    constexpr bool BM = HB != 0 || HM != 0;
-    constexpr int W = large_waves(NB);
+// The key blocks of a head are spread over the workgroups ("parts") of the keys kernel in turns: wave v of part
+// `part` owns key block part + parts * v.  The first block of a part is then always one of the first four, i.e. a
+// full one, whose 16 rows have room for the statistics of 16 query blocks.
+constexpr int keys_parts(int nb) { return (nb + 3) / 4; }
+constexpr int keys_waves(int nb) { return (nb + keys_parts(nb) - 1) / keys_parts(nb); }
+
+// M and -delta of query block qb (lane (g, n) holds those of query 16 qb + n, the same for all g) to every part of
+// the keys kernel: lane row g serves part g.
+template <int NB>
+__device__ __forceinline__ void store_stats(const BwdArgs& p, size_t tile_d, uint32_t row_d, int qb, int n, int g, float M,
+                                            float neg_delta) {
+    constexpr uint32_t PARTS = (uint32_t)keys_parts(NB);
+    // rows 16 part + qb of the head's slice, all below 16 PARTS <= L
+    const uint32_t bytes = (16u * PARTS - 1u) * row_d + 64u;
+    const uint32_t off = (uint32_t)g < PARTS ? (uint32_t)(16 * g + qb) * row_d + 4u * (uint32_t)n : 0xfffffff0u;
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, M), make_rsrc((char*)p.dv + tile_d, bytes), off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, neg_delta), make_rsrc((char*)p.dk + tile_d, bytes), off, 0, 0);
+}
+
+// 16 output rows of a wave (64 bytes each: channels 0..15 in `lo`, 16..31 in `hi`, accumulator order) leave through
+// 16 x 80 bytes of LDS of the wave's own: written there, read back 16 bytes per lane, one store of 64-byte row
+// pieces instead of two of 32.
+__device__ __forceinline__ void store_rows(char* cell, const u32x2 lo, const u32x2 hi, const __amdgpu_buffer_rsrc_t dst,
+                                           int blk, uint32_t row_d, int lane) {
+    const int n = lane & 15, g = lane >> 4;
+    *reinterpret_cast<u32x2*>(cell + n * 80 + g * 8) = lo;
+    *reinterpret_cast<u32x2*>(cell + n * 80 + 32 + g * 8) = hi;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t r = (uint32_t)(lane >> 2), c = (uint32_t)(lane & 3);
+    const u32x4 rows = *reinterpret_cast<const u32x4*>(cell + r * 80 + c * 16);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_raw_buffer_store_b128(rows, dst, (uint32_t)(16 * blk + r) * row_d + 16u * c, 0, 0);
+}
+
+// What follows the scores in the query orientation, shared by the two rows kernels: s holds the scaled scores (with
+// the additive term, -inf beyond L), m their maximum over the lane's keys; on return the block's dQ rows are packed in
+// lo2, hi2, and M, neg_delta are its statistics.  lk, lv: the K and V slabs; opd / trs: the lane's offsets for row
+// operands / transposing reads.  Matrix products are issued one step ahead of the vector work that needs them, and
+// the scheduling barriers keep the compiler from collecting them at one end of a loop (2-3 % at L = 196).
+// `between(i)` is called in between, i = 0, 1, ..., NB - 1 (a place for the next window's loads).
+template <int NB, class Between>
+__device__ __forceinline__ void rows_block(f32x4 (&s)[NB], float m, const bf16x8 gop, const uint4* lk, const uint4* lv,
+                                           uint32_t opd, uint32_t trs, float scale, float& M, float& neg_delta,
+                                           u32x2& lo2, u32x2& hi2, Between between) {
     constexpr int NB2 = (NB + 1) / 2;
+    constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    auto v_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]); };
+    m = max_over_g(m);
+    // s keeps exp(score - max), not normalised: P = s / sum enters delta here and dQ at the very
+    // end (one factor per output element instead of one per score)
+    float sum = 0.f, delta = 0.f;
+    f32x4 dp[2];
+    dp[0] = mfma_bf16(v_rows(0), gop, zero);
+    bf16x8 ov = v_rows(1);
+#pragma unroll
+    for (int jb = 0; jb < NB; ++jb) {
+        __builtin_amdgcn_sched_barrier(0);
+        between(jb);
+        if (jb + 1 < NB) dp[(jb + 1) & 1] = mfma_bf16(ov, gop, zero);
+        if (jb + 2 < NB) ov = v_rows(jb + 2);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float e = __builtin_amdgcn_exp2f(s[jb][r] - m);
+            s[jb][r] = e;
+            sum += e;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) delta = fmaf(s[jb][r], dp[jb & 1][r], delta);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 o0 = v_rows(0), o1 = v_rows(1);
+    sum = sum_over_g(sum);
+    const float inv = __builtin_amdgcn_rcpf(sum);
+    delta = sum_over_g(delta) * inv;
+    M = m + __builtin_amdgcn_logf(sum);  // p_ij = exp2(score_ij - M_i)
+    neg_delta = -delta;
+    const f32x4 nd = {neg_delta, neg_delta, neg_delta, neg_delta};
+    // dQ^T = K^T dS^T over pairs of key blocks
+    f32x4 q0 = zero, q1 = zero;  // dQ[16 qb + n][4g + r], dQ[16 qb + n][16 + 4g + r]
+    const uint16_t* lk16 = reinterpret_cast<const uint16_t*>(lk) + trs;
+    f32x4 da[2], db[2];  // dP - delta of the two blocks of a pair
+    da[0] = mfma_bf16(o0, gop, nd);
+    db[0] = mfma_bf16(o1, gop, nd);
+    if (NB > 2) o0 = v_rows(2);
+    if (NB > 3) o1 = v_rows(3);
+    bf16x8 tk0, tk1, dh, dl;
+#pragma unroll
+    for (int kp = 0; kp < NB2; ++kp) {
+        const bool two = 2 * kp + 1 < NB;
+        const int cur = kp & 1;
+        __builtin_amdgcn_sched_barrier(0);
+        if (2 * kp + 2 < NB) da[cur ^ 1] = mfma_bf16(o0, gop, nd);
+        if (2 * kp + 3 < NB) db[cur ^ 1] = mfma_bf16(o1, gop, nd);
+        if (kp > 0) {
+            q0 = mfma_bf16(tk0, dh, q0);
+            q1 = mfma_bf16(tk1, dh, q1);
+            q0 = mfma_bf16(tk0, dl, q0);
+            q1 = mfma_bf16(tk1, dl, q1);
+        }
+        if (2 * kp + 4 < NB) o0 = v_rows(2 * kp + 4);
+        if (2 * kp + 5 < NB) o1 = v_rows(2 * kp + 5);
+        tk0 = operand_tr(lk16 + (32 * kp) * SROW, 16 * SROW, two);
+        tk1 = operand_tr(lk16 + (32 * kp) * SROW + 16, 16 * SROW, two);
+        bf16x4 hi[2], lo[2];
+        hi[1] = lo[1] = as_bf16x4(uint2{0u, 0u});
+        split_hi_lo(s[2 * kp] * da[cur], hi[0], lo[0]);  // dS, times the row sum
+        if (two) split_hi_lo(s[two ? 2 * kp + 1 : 0] * db[cur], hi[1], lo[1]);
+        dh = pair_operand(hi[0], hi[1]), dl = pair_operand(lo[0], lo[1]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    q0 = mfma_bf16(tk0, dh, q0);
+    q1 = mfma_bf16(tk1, dh, q1);
+    q0 = mfma_bf16(tk0, dl, q0);
+    q1 = mfma_bf16(tk1, dl, q1);
+    const float qs = scale * inv;  // the lane's query row: dQ_i = scale / sum_i * (the products above)
+    lo2 = u32x2{pack_bf16(q0[0] * qs, q0[1] * qs), pack_bf16(q0[2] * qs, q0[3] * qs)};
+    hi2 = u32x2{pack_bf16(q1[0] * qs, q1[1] * qs), pack_bf16(q1[2] * qs, q1[3] * qs)};
+}
+// -inf for the keys of the last block beyond L; the running maximum m takes a block's scores in
+template <int NB>
+__device__ __forceinline__ void pad_and_max(f32x4& x, int jb, int L, int g, float& m) {
+    if (jb == NB - 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (16 * (NB - 1) + 4 * g + r >= L) x[r] = -INFINITY;
+    }
+    m = fmaxf(fmaxf(m, x[0]), x[1]);
+    m = fmaxf(fmaxf(m, x[2]), x[3]);
+}
+
+// ------------------------------------------------------------------ rows kernel
+// W waves = W consecutive query blocks of the head (the head is split over two workgroups when NB > 12), K and V of
+// the head in a double-buffered LDS slab, the wave's own Q and dO rows straight from global memory as operands.  One
+// barrier per window.
+// BM: there is an additive term.  PW: the mask comes as labels whose period does not divide G; the bias alone stays
+// in registers, the labels of a window travel with its slabs and the mask is formed per score.
+constexpr int rows_parts(int nb) { return nb <= 12 ? 1 : 2; }
+constexpr int rows_waves(int nb) { return (nb + rows_parts(nb) - 1) / rows_parts(nb); }
+
+template <int NB>
+constexpr size_t rows_lds() {
+    return (size_t)2 * 2 * 16 * NB * kLargeStride * 16 + (size_t)2 * 16 * NB * 4 + (size_t)rows_waves(NB) * 16 * 80;
+}
+
+template <int NB, bool BM, bool PW>
+__global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdArgs p, LargeGeom gm) {
+    constexpr int W = rows_waves(NB);
     constexpr int ROWS = 16 * NB;
     constexpr int PASSES = (ROWS + 16 * W - 1) / (16 * W);  // the workgroup moves 16 W slab rows per pass
-    constexpr uint32_t STRIDE = kLargeStride;                // slab row in 16-byte units
-    constexpr uint32_t SROW = STRIDE * 8;                    // the same in bf16 elements
-    constexpr uint32_t SG = 68;                              // patch row: 64 floats + 4 of padding
-    extern __shared__ __attribute__((aligned(16))) uint4 lds[];
+    constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
+    constexpr uint32_t SLAB = ROWS * STRIDE;                // in uint4
+    extern __shared__ __attribute__((aligned(16))) uint4 lds[];  // [2 buffers][K, V][ROWS][STRIDE], labels [2][ROWS], output cells
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int* const llab = reinterpret_cast<int*>(lds + 4 * SLAB);
+    char* const cell = reinterpret_cast<char*>(llab + 2 * ROWS) + wave * (16 * 80);
+    // workgroups that share 128-byte lines (the parts of a head, the heads of a window) are neighbours: one XCD
+    const uint32_t lb = xcd_logical_block(blockIdx.x, gm.xcd_q, gm.xcd_r);
+    const uint32_t part = lb % gm.parts, bh = lb / gm.parts;
+    const uint32_t h = bh % gm.heads, bw = bh / gm.heads;
+    const int qb = (int)(part * W + wave);
+    const bool active = qb < NB;
+    const int L = p.L;
+    const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
+    const float sl2 = p.scale * kLog2e;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+
+    const uint32_t tile_bytes = (uint32_t)(L - 1) * row_bytes + 2u * kHeadDim;
+    const uint32_t tile_bytes_g = (uint32_t)(L - 1) * row_g + 2u * kHeadDim;
+    const uint32_t tile_bytes_d = (uint32_t)(L - 1) * row_d + 2u * kHeadDim;
+    const uint32_t off_q = (uint32_t)(16 * qb + n) * row_bytes + 16u * g;
+    const uint32_t off_g = (uint32_t)(16 * qb + n) * row_g + 16u * g;
+    const uint32_t trs = (4u * g + (n >> 2)) * SROW + 4u * (n & 3);
+    const uint32_t opd = (uint32_t)n * STRIDE + g;
+
+    // K and V go straight from memory into LDS, into the buffer that the current window does not use; the wave's own
+    // Q and dO rows (and PW: the labels, 4 tid .. 4 tid + 3) wait in registers.  Rows beyond L are never loaded:
+    // zeros from the start.
+    static_assert(4 * SLAB * 16 <= 65536, "direct loads reach the first 64 KB");
+    const uint32_t off_slab = ((uint32_t)lane >> 2) * row_bytes + ((uint32_t)lane & 3u) * 16u;
+    u32x4 nq = {0u, 0u, 0u, 0u}, ng = nq;
+    i32x4 nlab = {0, 0, 0, 0};
+    // No branches in here (they would cut the window into pieces): without a next window `on` is false, the
+    // descriptors are empty and nothing is fetched.
+    auto request_slab = [&](uint32_t w, uint32_t buf, int t, bool on) {  // 16 rows of K and V: block W t + wave
+        const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
+        // a wave beyond the last block moves that one too
+        const uint32_t blk = NB % W == 0 || wave + t * W < (uint32_t)NB ? wave + t * W : (uint32_t)NB - 1u;
+        const uint32_t to = lds_offset(lds) + buf * (2 * SLAB * 16) + blk * 1024u;
+        const uint32_t skip = 16u * blk * row_bytes;  // of the rows in front, fewer than L
+        load_to_lds((const char*)p.k + tile + skip, on ? tile_bytes - skip : 0u, off_slab, to);
+        load_to_lds((const char*)p.v + tile + skip, on ? tile_bytes - skip : 0u, off_slab, to + SLAB * 16);
+    };
+    auto request_rest = [&](uint32_t w, bool on) {
+        const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
+        const size_t tile_g = ((size_t)w * L * p.ldg + (size_t)h * kHeadDim) * 2u;
+        nq = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.q + tile, on ? tile_bytes : 0u), off_q, 0, 0);
+        ng = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.d_o + tile_g, on ? tile_bytes_g : 0u), off_g, 0, 0);
+        if (PW)  // wave 0's are parked; tokens beyond L lie outside the descriptor: label 0
+            nlab = load_i32x4(make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, on && wave == 0 ? (uint32_t)L * 4u : 0u), (uint32_t)tid * 16u);
+    };
+    auto park_labels = [&](uint32_t buf) {
+        if (PW && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab + buf * ROWS)[tid] = nlab;
+    };
+    for (uint32_t i = (uint32_t)(4 * L + tid); i < SLAB; i += 64u * W) {  // rows L .. ROWS - 1 of the four slabs
+        const uint4 z = {0u, 0u, 0u, 0u};
+        lds[i] = lds[SLAB + i] = lds[2 * SLAB + i] = lds[3 * SLAB + i] = z;
+    }
+    const uint32_t end = (uint32_t)p.N, step = gm.G;
+    if (bw < end) {  // in flight while the additive term is fetched
+#pragma unroll
+        for (int t = 0; t < PASSES; ++t) request_slab(bw, 0u, t, true);
+        request_rest(bw, true);
+    }
+    f32x4 add[NB];
+    if (BM) {
+        const BiasSrc rb = bias_of_head(p, h);
+        // rows beyond L (and the whole block of an idle wave) fall outside the descriptors: zeros
+        const MaskSrc msk = PW ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
+        addend_at(rb, msk, active ? (uint32_t)(16 * qb + n) : (uint32_t)L, 4u * g, (uint32_t)L).template fill<NB, false>(add, kLog2e);
+    }
+    const float mv = p.mask_value * kLog2e;
+    park_labels(0u);
+    lds_loads_done();
+    __syncthreads();
+
+    uint32_t buf = 0u;
+    for (uint32_t w = bw; w < end; w += step, buf ^= 1u) {
+        const uint4* const lk = lds + buf * (2 * SLAB);
+        const uint4* const lv = lk + SLAB;
+        const bf16x8 qop = as_bf16x8(nq), gop = as_bf16x8(ng);
+        const bool has_next = w + step < end;
+        float M, nd;
+        u32x2 lo, hi;
+        if (active) {
+            f32x4 s[NB];
+            float m = -INFINITY;
+            const int* const lab = llab + buf * ROWS;
+            const AddendRegsLabels<NB> with_labels = {add, lab, PW ? lab[16 * qb + n] : 0, mv, g};
+            // all K operands are asked for at once (they are as large as the scores that replace them), and the
+            // products run two blocks ahead of the vector work on them
+            bf16x8 ok[NB];
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb) ok[jb] = __builtin_bit_cast(bf16x8, lk[opd + 16 * jb * STRIDE]);
+#pragma unroll
+            for (int jb = 0; jb < NB + 2; ++jb) {
+                if (jb < NB) s[jb] = mfma_bf16(ok[jb], qop, zero);
+                if (jb >= 2) {
+                    const int c = jb - 2;
+                    const f32x4 t = PW ? with_labels.block(c) : (BM ? add[c] : zero);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s[c][r] = BM ? fmaf(s[c][r], sl2, t[r]) : s[c][r] * sl2;
+                    pad_and_max<NB>(s[c], c, L, g, m);
+                }
+                if (jb & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+            rows_block<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, [&](int i) {
+                // the next window's loads one pair at a time: issued in one go they queue at the CU's address unit
+                // and hold the wave up
+#pragma unroll
+                for (int t = 0; t < PASSES; ++t)
+                    if (i == 2 * t) request_slab(w + step, buf ^ 1u, t, has_next);
+                if (i == 3) request_rest(w + step, has_next);
+            });
+        } else {  // an idle wave moves its share all the same
+#pragma unroll
+            for (int t = 0; t < PASSES; ++t) request_slab(w + step, buf ^ 1u, t, has_next);
+        }
+        // The next window's slabs are in LDS before this wave passes the barrier; the
+        // wait stands in front of the stores, so that it does not wait for those.
+        lds_loads_done();
+        park_labels(buf ^ 1u);
+        if (active) {
+            const size_t tile_d = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
+            store_stats<NB>(p, tile_d, row_d, qb, n, g, M, nd);
+            store_rows(cell, lo, hi, make_rsrc((char*)p.dq + tile_d, tile_bytes_d), qb, row_d, lane);
+        }
+        __syncthreads();  // the next window is in place, and every wave is done with this one's buffer
+    }
+}
+
+// The rows kernel for dense masks whose period no G is a multiple of: 4 (NB <= 10) or 8 waves walk the query blocks
+// of a head, and rows of (bias + mask) are fetched for every window.  A lane needs 4 consecutive keys of one query
+// row and neighbouring lanes sit in different rows, which the memory pipeline serves a lane at a time; so the wave
+// copies 16 rows x 64 columns at a time with row-contiguous 16-byte loads into a private LDS patch and picks its
+// values from there.
+constexpr int stream_waves(int nb) { return nb <= 10 ? 4 : 8; }
+constexpr uint32_t kPatchRow = 68;  // 64 floats + 4 of padding
+
+template <int NB>
+constexpr size_t stream_lds() {
+    return (size_t)4 * 16 * NB * kLargeStride * 16 + (size_t)stream_waves(NB) * 16 * kPatchRow * 4;
+}
+
+template <int NB, bool HB>
+__global__ void __launch_bounds__(64 * stream_waves(NB)) bwd_bf16_rows_stream_kernel(BwdArgs p, LargeGeom gm) {
+    constexpr int W = stream_waves(NB);
+    constexpr int ROWS = 16 * NB;
+    constexpr int PASSES = (ROWS + 16 * W - 1) / (16 * W);
+    constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8, SG = kPatchRow;
+    extern __shared__ __attribute__((aligned(16))) uint4 lds[];  // slabs [K][V][Q][dO], each [ROWS][STRIDE]; one patch per wave
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lb = xcd_logical_block(blockIdx.x, gm.xcd_q, gm.xcd_r);  // heads of a window: one XCD
     const uint32_t h = lb % gm.heads, bw = lb / gm.heads;
     const int L = p.L;
-    // token rows are p.ldq (q, k, v), p.ldg (d_o), p.ldd (dq, dk, dv) elements apart; window w starts at row w L
     const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
     const float sl2 = p.scale * kLog2e;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-
-    // LDS: slabs [K][V][Q][dO], each [ROWS][STRIDE] uint4; M[ROWS], delta[ROWS]; one patch per wave
     uint4* const lk = lds;
     uint4* const lv = lds + ROWS * STRIDE;
     uint4* const lq = lds + 2 * ROWS * STRIDE;
     uint4* const lg = lds + 3 * ROWS * STRIDE;
-    float* const stM = reinterpret_cast<float*>(lds + 4 * ROWS * STRIDE);
-    float* const stD = stM + ROWS;
-    float* const patch = stD + ROWS + wave * (16 * SG);
-
+    float* const patch = reinterpret_cast<float*>(lds + 4 * ROWS * STRIDE) + wave * (16 * SG);
     const uint32_t ll = (uint32_t)L * L * 4u;
     const float* const bias32 = static_cast<const float*>(p.bias);
-    const __amdgpu_buffer_rsrc_t rb =
-        HB == 1 ? make_rsrc(bias32 + (size_t)h * L * L, ll) : make_rsrc(nullptr, 0);
-
-    const uint32_t srow = (uint32_t)tid >> 2, scol = (uint32_t)tid & 3u;  // slab movement: (row, 16 B column)
+    const uint32_t srow = (uint32_t)tid >> 2, scol = (uint32_t)tid & 3u;
     const uint32_t tile_bytes = (uint32_t)(L - 1) * row_bytes + 2u * kHeadDim;
-    const uint32_t trs = (4u * g + (n >> 2)) * SROW + 4u * (n & 3);  // transposing-read base inside a slab
-    const uint32_t opd = (uint32_t)n * STRIDE + g;                   // row operand of block b: slab[opd + 16 b STRIDE]
     const uint32_t tile_bytes_g = (uint32_t)(L - 1) * row_g + 2u * kHeadDim;
     const uint32_t tile_bytes_d = (uint32_t)(L - 1) * row_d + 2u * kHeadDim;
-    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-    // 16 output rows of this wave (64 bytes each: channels 0..15 in `lo`, 16..31 in `hi`, accumulator
-    // order) leave through the wave's patch area, free whenever a block's results are ready: written
-    // there, read back 16 bytes per lane, one store of 64-byte row pieces instead of two of 32.
-    auto store_rows = [&](const u32x2_t lo, const u32x2_t hi, const __amdgpu_buffer_rsrc_t dst, int blk) {
-        char* const cell = reinterpret_cast<char*>(patch);
-        *reinterpret_cast<u32x2_t*>(cell + n * 80 + g * 8) = lo;
-        *reinterpret_cast<u32x2_t*>(cell + n * 80 + 32 + g * 8) = hi;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t r = (uint32_t)(lane >> 2), c = (uint32_t)(lane & 3);
-        const u32x4 rows = *reinterpret_cast<const u32x4*>(cell + r * 80 + c * 16);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_raw_buffer_store_b128(rows, dst, (uint32_t)(16 * blk + r) * row_d + 16u * c, 0, 0);
-    };
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const uint32_t trs = (4u * g + (n >> 2)) * SROW + 4u * (n & 3);
+    const uint32_t opd = (uint32_t)n * STRIDE + g;
 
     // The slabs of the next window are requested into registers by every wave right before its last stores of the
-    // current one -- the big temporaries of the passes are dead by then --, so that their way through memory
-    // overlaps with those stores and with the wait for the slowest wave; they are parked between the two barriers
-    // that separate the windows.
+    // current one -- the big temporaries are dead by then --, and parked between the two barriers between windows.
     u32x4 pk[PASSES], pv[PASSES], pq[PASSES], pg[PASSES];
     auto request = [&](uint32_t w) {
         const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
@@ -161,339 +428,101 @@ __global__ void __launch_bounds__(64 * large_waves(NB)) bwd_bf16_large_kernel(Bw
         const bool has_next = w + gm.G < (uint32_t)p.N;
         __syncthreads();  // the slabs are in place
         // dead until the request at the end of this window: said so, or the compiler carries the old values
-        // through both passes on behalf of the path on which no request happens
+        // through the window on behalf of the path on which no request happens
 #pragma unroll
         for (int t = 0; t < PASSES; ++t) pk[t] = pv[t] = pq[t] = pg[t] = u32x4{0u, 0u, 0u, 0u};
-        // the labels of the window's tokens when the mask comes as labels
-        const __amdgpu_buffer_rsrc_t rl =
-            HM == 2 ? make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, (uint32_t)L * 4u) : make_rsrc(nullptr, 0);
 
-        // ---------------- pass 1: query blocks wave, wave + W ----------------
         for (int qb = (int)wave; qb < NB; qb += W) {
             const bf16x8 qop = __builtin_bit_cast(bf16x8, lq[opd + 16 * qb * STRIDE]);
             const bf16x8 gop = __builtin_bit_cast(bf16x8, lg[opd + 16 * qb * STRIDE]);
             // rows 16 qb .. 16 qb + 15 of (bias + mask), 64 columns at a time: lane -> (row 4t + lane / 16,
             // columns 4 (lane % 16) ..), 256 contiguous bytes per 16 lanes; rows beyond L lie outside the
-            // descriptors and read as zero, columns beyond L are overwritten with -inf below.  The first
+            // descriptors and read as zero, columns beyond L are overwritten with -inf later.  The first
             // patch is requested before the products are formed, each further one a patch ahead.
             const uint32_t prow = (uint32_t)lane >> 4, pcol = 4u * ((uint32_t)lane & 15u);
             constexpr int CH = (NB + 3) / 4;
             f32x4 tb[2][4], tm[2][4];
-            i32x4 tk[2];  // with labels: those of a patch's 4 columns ...
-            int tq[4];    // ... and of the lane's 4 patch rows
             const uint32_t qrow = (uint32_t)(16 * qb) * L * 4u;  // < ll: the block starts inside the tile
-            const __amdgpu_buffer_rsrc_t rbq = HB == 1 ? make_rsrc(bias32 + (size_t)h * L * L + (size_t)16 * qb * L, ll - qrow) : rb;
+            const __amdgpu_buffer_rsrc_t rbq =
+                HB ? make_rsrc(bias32 + (size_t)h * L * L + (size_t)16 * qb * L, ll - qrow) : make_rsrc(nullptr, 0);
             const __amdgpu_buffer_rsrc_t rmq =
-                HM == 1 ? make_rsrc(p.mask + (size_t)(w % (uint32_t)p.nW) * L * L + (size_t)16 * qb * L, ll - qrow) : rb;
-            if (HM == 2) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) tq[t] = load_i32(rl, (uint32_t)(16 * qb + 4 * t + prow) * 4u);
-            }
+                make_rsrc(p.mask + (size_t)(w % (uint32_t)p.nW) * L * L + (size_t)16 * qb * L, ll - qrow);
             auto request_patch = [&](int ch, int slot) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const uint32_t off = ((uint32_t)(4 * t + prow) * L + pcol) * 4u + 256u * ch;
-                    if (HB == 1) tb[slot][t] = load_f32x4(rbq, off);
-                    if (HM == 1) tm[slot][t] = load_f32x4(rmq, off);
+                    if (HB) tb[slot][t] = load_f32x4(rbq, off);
+                    tm[slot][t] = load_f32x4(rmq, off);
                 }
-                if (HM == 2) tk[slot] = load_i32x4(rl, (pcol + 64u * ch) * 4u);
             };
-            if (BM) request_patch(0, 0);
+            request_patch(0, 0);
             f32x4 s[NB];
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb)
                 s[jb] = mfma_bf16(__builtin_bit_cast(bf16x8, lk[opd + 16 * jb * STRIDE]), qop, zero);
-            if (BM) {
 #pragma unroll
-                for (int ch = 0; ch < CH; ++ch) {
-                    const int cur = ch & 1;
-                    if (ch + 1 < CH) request_patch(ch + 1, cur ^ 1);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const f32x4 mk = HM == 2 ? mask_of_labels(tq[t], tk[cur], p.mask_value) : tm[cur][t];
-                        const f32x4 bq = tb[cur][t];
-                        *reinterpret_cast<f32x4*>(patch + (4 * t + prow) * SG + pcol) =
-                            (HB && HM ? bq + mk : (HB ? bq : mk)) * kLog2e;
-                    }
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        const int jb = 4 * ch + b;
-                        if (jb < NB) {
-                            const f32x4 a = *reinterpret_cast<const f32x4*>(patch + n * SG + 16 * b + 4 * g);
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) s[jb][r] = fmaf(s[jb][r], sl2, a[r]);
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            } else {
-#pragma unroll
-                for (int jb = 0; jb < NB; ++jb) s[jb] *= sl2;
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (16 * (NB - 1) + 4 * g + r >= L) s[NB - 1][r] = -INFINITY;
-            float m = s[0][0];
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) {
-                m = fmaxf(fmaxf(m, s[jb][0]), s[jb][1]);
-                m = fmaxf(fmaxf(m, s[jb][2]), s[jb][3]);
-            }
-            m = max_over_g(m);
-            float sum = 0.f;
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float e = __builtin_amdgcn_exp2f(s[jb][r] - m);
-                    s[jb][r] = e;
-                    sum += e;
-                }
-            sum = sum_over_g(sum);
-            const float inv = __builtin_amdgcn_rcpf(sum);
-            // s keeps exp(score - max), not normalised: P = s * inv enters delta here and dQ at the very
-            // end (one factor per output element instead of one per score)
-            float delta = 0.f;
-#pragma unroll
-            for (int jb = 0; jb < NB; ++jb) {
-                const f32x4 dp = mfma_bf16(__builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]), gop, zero);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) delta = fmaf(s[jb][r], dp[r], delta);
-            }
-            delta = sum_over_g(delta) * inv;
-            if (g == 0) {
-                const float Mi = m + __builtin_amdgcn_logf(sum);  // p_ij = exp2(score_ij - M_i)
-                stM[16 * qb + n] = Mi;
-                stD[16 * qb + n] = delta;
-                if (p.stats) {  // kept for the dBias kernel, which redoes pass 2 only
-                    float* gs = p.stats + ((size_t)w * p.heads + h) * (2 * ROWS) + 16 * qb + n;
-                    gs[0] = Mi;
-                    gs[ROWS] = delta;
-                }
-            }
-            // dQ^T = K^T dS^T over pairs of key blocks; the operands of the next pair are fetched ahead
-            f32x4 q0 = zero, q1 = zero;  // dQ[16 qb + n][4g + r], dQ[16 qb + n][16 + 4g + r]
-            const uint16_t* lk16 = reinterpret_cast<const uint16_t*>(lk) + trs;
-            bf16x8 ov[2][2], tk0[2], tk1[2];
-            auto fetch1 = [&](int kp, int slot) {
-                const bool two = 2 * kp + 1 < NB;
-                ov[slot][0] = __builtin_bit_cast(bf16x8, lv[opd + 16 * (2 * kp) * STRIDE]);
-                if (two) ov[slot][1] = __builtin_bit_cast(bf16x8, lv[opd + 16 * (2 * kp + 1) * STRIDE]);
-                tk0[slot] = operand_tr(lk16 + (32 * kp) * SROW, 16 * SROW, two);
-                tk1[slot] = operand_tr(lk16 + (32 * kp) * SROW + 16, 16 * SROW, two);
-            };
-            fetch1(0, 0);
-#pragma unroll
-            for (int kp = 0; kp < NB2; ++kp) {
-                const bool two = 2 * kp + 1 < NB;
-                const int cur = kp & 1;
-                if (kp + 1 < NB2) fetch1(kp + 1, cur ^ 1);
+            for (int ch = 0; ch < CH; ++ch) {
+                const int cur = ch & 1;
+                if (ch + 1 < CH) request_patch(ch + 1, cur ^ 1);
                 __builtin_amdgcn_sched_barrier(0);
-                bf16x4 hi[2], lo[2];
-                hi[1] = lo[1] = as_bf16x4(uint2{0u, 0u});
-                f32x4 dp[2];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    if (u == 1 && !two) break;
-                    dp[u] = mfma_bf16(ov[cur][u], gop, zero);
+                for (int t = 0; t < 4; ++t)
+                    *reinterpret_cast<f32x4*>(patch + (4 * t + prow) * SG + pcol) = (HB ? tb[cur][t] + tm[cur][t] : tm[cur][t]) * kLog2e;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const int jb = 4 * ch + b;
+                    if (jb < NB) {
+                        const f32x4 a = *reinterpret_cast<const f32x4*>(patch + n * SG + 16 * b + 4 * g);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) s[jb][r] = fmaf(s[jb][r], sl2, a[r]);
+                    }
                 }
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    if (u == 1 && !two) break;
-                    const int jb = 2 * kp + u;
-                    f32x4 ds;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) ds[r] = s[jb][r] * (dp[u][r] - delta);
-                    split_hi_lo(ds, hi[u], lo[u]);
-                }
-                const bf16x8 dh = pair_operand(hi[0], hi[1]), dl = pair_operand(lo[0], lo[1]);
-                q0 = mfma_bf16(tk0[cur], dh, q0);
-                q1 = mfma_bf16(tk1[cur], dh, q1);
-                q0 = mfma_bf16(tk0[cur], dl, q0);
-                q1 = mfma_bf16(tk1[cur], dl, q1);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            const float qs = p.scale * inv;  // the lane's query row: dQ_i = scale / sum_i * (the products above)
-            const u32x2 lo2 = {pack_bf16(q0[0] * qs, q0[1] * qs), pack_bf16(q0[2] * qs, q0[3] * qs)};
-            const u32x2 hi2 = {pack_bf16(q1[0] * qs, q1[1] * qs), pack_bf16(q1[2] * qs, q1[3] * qs)};
-            if (!P2 && has_next && qb + W >= NB) request(w + gm.G);  // the wave's last block of this window
-            store_rows(lo2, hi2, make_rsrc((char*)p.dq + tile_d, tile_bytes_d), qb);
+            float M, nd;
+            u32x2 lo, hi;
+            float m = -INFINITY;
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb) pad_and_max<NB>(s[jb], jb, L, g, m);
+            rows_block<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, [](int) {});
+            if (has_next && qb + W >= NB) request(w + gm.G);  // the wave's last block of this window
+            store_stats<NB>(p, tile_d, row_d, qb, n, g, M, nd);
+            store_rows(reinterpret_cast<char*>(patch), lo, hi, make_rsrc((char*)p.dq + tile_d, tile_bytes_d), qb, row_d, lane);
         }
         __syncthreads();
-
-        // ---------------- pass 2: key blocks wave, wave + W, ..., two at a time ----------------
-        // A wave that owns two key blocks works on both at once: every operand it fetches for a query
-        // block (Q and dO rows, their transposes, the statistics) then serves two key blocks, which
-        // halves the LDS traffic of this pass, and the two blocks are independent chains of work.
-        auto pass2 = [&](auto nk_tag, const int jb0) {
-            constexpr int NK = decltype(nk_tag)::value;  // key blocks jb0 (and jb0 + W)
-            bf16x8 kop[NK], vop[NK];
-            f32x4 v0[NK], v1[NK], k0[NK], k1[NK];  // dV, dK [16 jb + n][4g + r] and [..][16 + 4g + r]
-            int lkey[NK];
-#pragma unroll
-            for (int t = 0; t < NK; ++t) {
-                const int jb = jb0 + t * W;
-                kop[t] = __builtin_bit_cast(bf16x8, lk[opd + 16 * jb * STRIDE]);
-                vop[t] = __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]);
-                v0[t] = v1[t] = k0[t] = k1[t] = zero;
-                lkey[t] = HM == 2 ? load_i32(rl, (uint32_t)(16 * jb + n) * 4u) : 0;
-            }
-            // A key beyond L (a lane of the last key block) is not masked out: what it computes -- from
-            // zero rows of K and V, possibly an overflow -- stays in its own column of every product,
-            // i.e. in rows of dV and dK beyond L, which the stores drop.
-            const uint16_t* lg16 = reinterpret_cast<const uint16_t*>(lg) + trs;
-            const uint16_t* lq16 = reinterpret_cast<const uint16_t*>(lq) + trs;
-            uint32_t aoff[4];  // additive term of query 4g + r and key 16 jb0 + n; key block t: + 64 W t bytes
-#pragma unroll
-            for (int r = 0; r < 4; ++r) aoff[r] = ((uint32_t)(4 * g + r) * L + 16u * jb0 + n) * 4u;
-            // Row operands, statistics (LDS) and additive terms (L2) are fetched one query block ahead of
-            // their use, the transposed operands one pair of query blocks ahead; the scheduling barriers
-            // keep the compiler from hoisting more than that.
-            bf16x8 oq[2], og[2], tg0[2], tg1[2], tx0[2], tx1[2];
-            f32x4 oM[2], oD[2], ab[2][NK], am[2][NK];
-            i32x4 al[2];
-            auto fetch_q = [&](int qb, int slot) {
-                oq[slot] = __builtin_bit_cast(bf16x8, lq[opd + 16 * qb * STRIDE]);
-                og[slot] = __builtin_bit_cast(bf16x8, lg[opd + 16 * qb * STRIDE]);
-                oM[slot] = *reinterpret_cast<const f32x4*>(stM + 16 * qb + 4 * g);
-                oD[slot] = *reinterpret_cast<const f32x4*>(stD + 16 * qb + 4 * g);
-                if (BM) {
-                    // rows beyond L lie outside the descriptors (which start at the first row of the query
-                    // block, so that the 4 lane offsets serve every block)
-                    const uint32_t qrow = (uint32_t)(16 * qb) * L;
-                    const __amdgpu_buffer_rsrc_t rbq = HB == 1 ? make_rsrc(bias32 + (size_t)h * L * L + qrow, ll - 4u * qrow) : rb;
-                    const __amdgpu_buffer_rsrc_t rmq =
-                        HM == 1 ? make_rsrc(p.mask + (size_t)(w % (uint32_t)p.nW) * L * L + qrow, ll - 4u * qrow) : rb;
-#pragma unroll
-                    for (int t = 0; t < NK; ++t)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            if (HB == 1) ab[slot][t][r] = load_f32(rbq, aoff[r] + 64u * W * t);
-                            if (HM == 1) am[slot][t][r] = load_f32(rmq, aoff[r] + 64u * W * t);
-                        }
-                    // with labels: those of the 4 query rows, compared with the key's where the term is used
-                    if (HM == 2) al[slot] = load_i32x4(rl, (uint32_t)(16 * qb + 4 * g) * 4u);
-                }
-            };
-            auto fetch_t = [&](int qp, int slot) {  // dO^T and Q^T of the 32 queries (channel on the lane)
-                const bool two = 2 * qp + 1 < NB;
-                tg0[slot] = operand_tr(lg16 + (32 * qp) * SROW, 16 * SROW, two);
-                tg1[slot] = operand_tr(lg16 + (32 * qp) * SROW + 16, 16 * SROW, two);
-                tx0[slot] = operand_tr(lq16 + (32 * qp) * SROW, 16 * SROW, two);
-                tx1[slot] = operand_tr(lq16 + (32 * qp) * SROW + 16, 16 * SROW, two);
-            };
-            fetch_q(0, 0);
-            fetch_t(0, 0);
-#pragma unroll
-            for (int qp = 0; qp < NB2; ++qp) {
-                const bool two = 2 * qp + 1 < NB;
-                const int tcur = qp & 1;
-                if (qp + 1 < NB2) fetch_t(qp + 1, tcur ^ 1);
-                bf16x4 ph[NK][2], pl[NK][2], sh[NK][2], sl[NK][2];
-#pragma unroll
-                for (int t = 0; t < NK; ++t) ph[t][1] = pl[t][1] = sh[t][1] = sl[t][1] = as_bf16x4(uint2{0u, 0u});
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    if (u == 1 && !two) break;
-                    const int qb = 2 * qp + u, cur = qb & 1;
-                    if (qb + 1 < NB) fetch_q(qb + 1, cur ^ 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    f32x4 sc[NK], dp[NK];
-#pragma unroll
-                    for (int t = 0; t < NK; ++t) {
-                        sc[t] = mfma_bf16(oq[cur], kop[t], zero);  // sc[r] = <q_i, k_j>, i = 16 qb + 4g + r, j = 16 jb + n
-                        dp[t] = mfma_bf16(og[cur], vop[t], zero);
-                    }
-#pragma unroll
-                    for (int t = 0; t < NK; ++t) {
-                        f32x4 pr, ds;
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            float x;
-                            if (BM) {
-                                const float mk = HM == 2 ? (al[cur][r] == lkey[t] ? 0.f : p.mask_value) : am[cur][t][r];
-                                const float bv = ab[cur][t][r];
-                                const float add = HB && HM ? bv + mk : (HB ? bv : mk);
-                                x = fmaf(sc[t][r], sl2, fmaf(add, kLog2e, -oM[cur][r]));
-                            } else {
-                                x = fmaf(sc[t][r], sl2, -oM[cur][r]);
-                            }
-                            pr[r] = __builtin_amdgcn_exp2f(x);
-                            ds[r] = pr[r] * (dp[t][r] - oD[cur][r]);
-                        }
-                        split_hi_lo(pr, ph[t][u], pl[t][u]);
-                        split_hi_lo(ds, sh[t][u], sl[t][u]);
-                    }
-                }
-#pragma unroll
-                for (int t = 0; t < NK; ++t) {
-                    const bf16x8 PH = pair_operand(ph[t][0], ph[t][1]), PL = pair_operand(pl[t][0], pl[t][1]);
-                    const bf16x8 SH = pair_operand(sh[t][0], sh[t][1]), SL = pair_operand(sl[t][0], sl[t][1]);
-                    v0[t] = mfma_bf16(tg0[tcur], PH, v0[t]);
-                    v1[t] = mfma_bf16(tg1[tcur], PH, v1[t]);
-                    k0[t] = mfma_bf16(tx0[tcur], SH, k0[t]);
-                    k1[t] = mfma_bf16(tx1[tcur], SH, k1[t]);
-                    v0[t] = mfma_bf16(tg0[tcur], PL, v0[t]);
-                    v1[t] = mfma_bf16(tg1[tcur], PL, v1[t]);
-                    k0[t] = mfma_bf16(tx0[tcur], SL, k0[t]);
-                    k1[t] = mfma_bf16(tx1[tcur], SL, k1[t]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            // The wave's last key blocks of this window (with 8 waves it comes through here once per window;
-            // with 4, up to twice, and asks after the loop below instead).
-            if (W == 8 && has_next) request(w + gm.G);
-#pragma unroll
-            for (int t = 0; t < NK; ++t) {
-                const int jb = jb0 + t * W;
-                const u32x2 va = {pack_bf16(v0[t][0], v0[t][1]), pack_bf16(v0[t][2], v0[t][3])};
-                const u32x2 vb = {pack_bf16(v1[t][0], v1[t][1]), pack_bf16(v1[t][2], v1[t][3])};
-                const u32x2 ka = {pack_bf16(k0[t][0] * p.scale, k0[t][1] * p.scale), pack_bf16(k0[t][2] * p.scale, k0[t][3] * p.scale)};
-                const u32x2 kb = {pack_bf16(k1[t][0] * p.scale, k1[t][1] * p.scale), pack_bf16(k1[t][2] * p.scale, k1[t][3] * p.scale)};
-                store_rows(va, vb, make_rsrc((char*)p.dv + tile_d, tile_bytes_d), jb);
-                store_rows(ka, kb, make_rsrc((char*)p.dk + tile_d, tile_bytes_d), jb);
-            }
-        };
-        for (int jb0 = (int)wave; P2 && jb0 < NB; jb0 += 2 * W) {
-            if (jb0 + W < NB)
-                pass2(std::integral_constant<int, 2>{}, jb0);
-            else
-                pass2(std::integral_constant<int, 1>{}, jb0);
-        }
-        if (P2 && W == 4 && has_next) request(w + gm.G);
-        if (P2) __syncthreads();  // every wave has left the slabs (without pass 2: the barrier after pass 1)
         if (has_next) park();
     }
 }
 
-// dK, dV and dBias for 64 < L <= 256 when dBias is wanted.  The dBias accumulator is L x L fp32 per
-// head (256 KB at L = 256): half of a CU's register file, which the two passes of the kernel above
-// need themselves.  So a call with dBias runs that kernel with pass 1 only (dQ; the row statistics
-// M_i, delta_i go to the workspace, 8 bytes per query) and this one for pass 2: a wave owns ONE key
-// block of one head for its whole life -- the key blocks of a head are spread over one workgroup
-// (up to 8 blocks) or two (9 to 16) -- produces S and dP block by block in the "key on the lane"
-// orientation, P = exp2(score - M_i), dS = P (dP - delta_i), feeds both back into the matrix cores
-// for its dV and dK rows exactly as pass 2 above, and adds dS into dBias[all queries][its keys],
-// held in registers (at most 64) across the windows bw, bw + G, ...  The sums are written out once,
-// in register order, as one of G partial sums per head; the reduce kernel adds the slots in a fixed
-// order.  Only Q and dO (all rows) go through LDS; the wave takes the K and V rows of its key block
-// straight from global memory.
-// The key blocks of a head are spread over workgroups of at most 4 waves (one wave per SIMD), of which a CU
-// holds two: while one loads or waits at a barrier the other computes.
-constexpr int keys_parts(int nb) { return (nb + 3) / 4; }
-constexpr int keys_waves(int nb) { return (nb + keys_parts(nb) - 1) / keys_parts(nb); }
+// ------------------------------------------------------------------ keys kernel
+// At most 4 waves per workgroup (one per SIMD), of which a CU holds two: while one loads or waits at a barrier the
+// other computes.  Only Q and dO (all rows) go through LDS; the wave takes the K and V rows of its key block straight
+// from global memory.  With DB the dBias accumulator is L x L fp32 per head (256 KB at L = 256), half of a CU's
+// register file, spread over the waves of the head's workgroups; the sums are written out once, in register order, as
+// one of G partial sums per head, and the reduce kernel adds the slots in a fixed order.
+enum { kTermNone = 0,    // no additive term
+       kTermKept = 1,    // (bias + mask) * log2e of all queries and the wave's keys in registers, G a multiple of the period
+       kTermLabels = 2,  // bias * log2e in registers, the mask from the labels of each window
+       kTermStream = 3,  // a dense mask read for every window, and the bias too where the registers are needed for dBias
+       kTermStreamMask = 4 };  // a dense mask alone, read for every window
 
-template <int NB, int HB, int HM>
-__global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_large_keys_kernel(BwdArgs p, LargeGeom gm) {
-    constexpr bool BM = HB != 0 || HM != 0;
-    constexpr int PARTS = keys_parts(NB);
+template <int NB>
+constexpr size_t keys_lds() {  // two buffers of: Q, dO slabs; then two of: M, -delta, labels; the waves' output cells
+    return (size_t)2 * 2 * 16 * NB * kLargeStride * 16 + (size_t)2 * 3 * 16 * NB * 4 + (size_t)keys_waves(NB) * 16 * 80;
+}
+
+template <int NB, int TERM, bool DB>
+__global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(BwdArgs p, LargeGeom gm) {
+    constexpr bool KEEP = TERM == kTermKept || TERM == kTermLabels;
+    constexpr bool STREAM = TERM == kTermStream || TERM == kTermStreamMask;
+    constexpr bool PW = TERM == kTermLabels;
+    constexpr bool KEEPB = TERM == kTermStream && (!DB || NB <= 12);  // the bias in registers all the same
+    constexpr bool HB = TERM == kTermStream && !KEEPB;
+    constexpr uint32_t PARTS = (uint32_t)keys_parts(NB);
     constexpr int W = keys_waves(NB);
-    constexpr int NB2 = (NB + 1) / 2;
     constexpr int ROWS = 16 * NB;
     constexpr int PASSES = (ROWS + 16 * W - 1) / (16 * W);
-    constexpr uint32_t STRIDE = 5;         // slab row: 64 bytes of data + 16 of padding
-    constexpr uint32_t SROW = STRIDE * 8;  // the same in bf16 elements
+    constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
     extern __shared__ __attribute__((aligned(16))) uint4 lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
@@ -501,220 +530,253 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_large_keys_ke
     // the parts of a head and the heads of a window are neighbours in the logical order: one XCD
     const uint32_t lb = xcd_logical_block(blockIdx.x, gm.xcd_q, gm.xcd_r);
     const uint32_t part = lb % PARTS, h = (lb / PARTS) % gm.heads, bw = lb / (PARTS * gm.heads);
-    const int jb = (int)(part * W + wave);  // this wave's key block
-    const bool active = jb < NB;            // wave-uniform
+    const int jb = (int)(part + PARTS * wave);  // this wave's key block
+    const bool active = jb < NB;                // wave-uniform
     const int L = p.L;
     const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
     const float sl2 = p.scale * kLog2e;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 
-    // LDS: slabs [Q][dO], each [ROWS][STRIDE] uint4; M[ROWS], delta[ROWS]; 16 rows x 80 bytes per wave for its output rows
-    constexpr uint32_t SET = 2 * ROWS * STRIDE + ROWS / 2;  // in uint4
-    char* const cell = reinterpret_cast<char*>(lds + SET) + wave * (16 * 80);
+    // two buffers: window w is computed out of one while the slabs of w + G are on their way into the other
+    constexpr uint32_t SLAB = ROWS * STRIDE;                              // in uint4
+    constexpr uint32_t ST = 3 * ROWS;                                     // M, -delta, labels of a window, in dwords
+    float* const stats = reinterpret_cast<float*>(lds + 4 * SLAB);
+    char* const cell = reinterpret_cast<char*>(stats + 2 * ST) + wave * (16 * 80);
 
     const uint32_t ll = (uint32_t)L * L * 4u;
     const float* const bias32 = static_cast<const float*>(p.bias);
-    const uint32_t srow = (uint32_t)tid >> 2, scol = (uint32_t)tid & 3u;
     const uint32_t tile_bytes = (uint32_t)(L - 1) * row_bytes + 2u * kHeadDim;
     const uint32_t tile_bytes_g = (uint32_t)(L - 1) * row_g + 2u * kHeadDim;
     const uint32_t tile_bytes_d = (uint32_t)(L - 1) * row_d + 2u * kHeadDim;
     const uint32_t trs = (4u * g + (n >> 2)) * SROW + 4u * (n & 3);
     const uint32_t opd = (uint32_t)n * STRIDE + g;
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    auto store_rows = [&](const u32x2 lo, const u32x2 hi, const __amdgpu_buffer_rsrc_t dst) {
-        *reinterpret_cast<u32x2*>(cell + n * 80 + g * 8) = lo;
-        *reinterpret_cast<u32x2*>(cell + n * 80 + 32 + g * 8) = hi;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const uint32_t r = (uint32_t)(lane >> 2), c = (uint32_t)(lane & 3);
-        const u32x4 rows = *reinterpret_cast<const u32x4*>(cell + r * 80 + c * 16);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_raw_buffer_store_b128(rows, dst, (uint32_t)(16 * jb + r) * row_d + 16u * c, 0, 0);
-    };
 
     f32x4 dbacc[NB];  // dS summed over the windows: queries 16 qb + 4g + r, key 16 jb + n
+    if (DB) {
 #pragma unroll
-    for (int qb = 0; qb < NB; ++qb) dbacc[qb] = zero;
-    uint32_t aoff[4];  // additive term of query 4g + r (of a query block) and this lane's key
-#pragma unroll
-    for (int r = 0; r < 4; ++r) aoff[r] = ((uint32_t)(4 * g + r) * L + 16u * jb + n) * 4u;
+        for (int qb = 0; qb < NB; ++qb) dbacc[qb] = zero;
+    }
 
-    // The Q and dO slabs, the statistics and the wave's own K and V rows of the next window are requested into
-    // registers at the end of an iteration, in front of its stores, and go from there into LDS between the two
-    // barriers that separate the windows.
-    constexpr int PASSES_ = PASSES;
-    constexpr int SPASSES = (ROWS / 2 + 64 * W - 1) / (64 * W);
-    u32x4 pq[PASSES_], pg[PASSES_], st4[SPASSES], pk, pv;
-    auto request = [&](uint32_t w) {
+    // The Q and dO slabs of the next window go straight from memory into the other LDS buffer (no registers, no LDS
+    // writes), requested at the top of a window; its statistics (wave 0: M, wave 1: -delta, 16 bytes per lane), its
+    // labels and the wave's own K and V rows wait in registers.  Rows beyond L are never loaded: zeros from the start.
+    static_assert(W >= 3, "wave 2 fetches the labels");
+    const uint32_t off_q = ((uint32_t)lane >> 2) * row_bytes + ((uint32_t)lane & 3u) * 16u, off_g = ((uint32_t)lane >> 2) * row_g + ((uint32_t)lane & 3u) * 16u;
+    static_assert(4 * SLAB * 16 <= 65536, "direct loads reach the first 64 KB");
+    u32x4 pst = {0u, 0u, 0u, 0u}, pk = pst, pv = pst;
+    // No branches in here (they would cut the block loop into pieces): without a next window `on` is false, the
+    // descriptors are empty and nothing is fetched.
+    const uint32_t off_st = wave < 2 ? (16u * part + ((uint32_t)lane >> 2)) * row_d + 16u * ((uint32_t)lane & 3u) : 16u * (uint32_t)lane;
+    auto request_slab = [&](uint32_t w, uint32_t buf, int t, bool on) {  // 16 rows of Q and dO: block W t + wave
         const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
         const size_t tile_g = ((size_t)w * L * p.ldg + (size_t)h * kHeadDim) * 2u;
-        const __amdgpu_buffer_rsrc_t rk = make_rsrc((const char*)p.k + tile, tile_bytes);
-        const __amdgpu_buffer_rsrc_t rv = make_rsrc((const char*)p.v + tile, tile_bytes);
-        const __amdgpu_buffer_rsrc_t rq = make_rsrc((const char*)p.q + tile, tile_bytes);
-        const __amdgpu_buffer_rsrc_t rg = make_rsrc((const char*)p.d_o + tile_g, tile_bytes_g);
-        const __amdgpu_buffer_rsrc_t rs =
-            make_rsrc(p.stats + ((size_t)w * p.heads + h) * (2 * ROWS), (uint32_t)(2 * ROWS * 4));
-#pragma unroll
-        for (int t = 0; t < PASSES; ++t) {  // rows beyond L arrive as zeros
-            pq[t] = __builtin_amdgcn_raw_buffer_load_b128(rq, (16 * W * t + srow) * row_bytes + scol * 16u, 0, 0);
-            pg[t] = __builtin_amdgcn_raw_buffer_load_b128(rg, (16 * W * t + srow) * row_g + scol * 16u, 0, 0);
-        }
-        // 2 ROWS floats of statistics: 16 bytes per thread
-#pragma unroll
-        for (int t = 0; t < SPASSES; ++t) st4[t] = __builtin_amdgcn_raw_buffer_load_b128(rs, (uint32_t)(tid + 64 * W * t) * 16u, 0, 0);
-        // the wave's own K and V rows as operands: row 16 jb + n, channels 8g .. 8g + 7
-        pk = __builtin_amdgcn_raw_buffer_load_b128(rk, (uint32_t)(16 * jb + n) * row_bytes + 16u * g, 0, 0);
-        pv = __builtin_amdgcn_raw_buffer_load_b128(rv, (uint32_t)(16 * jb + n) * row_bytes + 16u * g, 0, 0);
+        // a wave beyond the last block moves that one too
+        const uint32_t blk = NB % W == 0 || wave + t * W < (uint32_t)NB ? wave + t * W : (uint32_t)NB - 1u;
+        const uint32_t to = lds_offset(lds) + buf * (2 * SLAB * 16) + blk * 1024u;
+        const uint32_t skip = 16u * blk;  // rows, below L
+        load_to_lds((const char*)p.q + tile + skip * row_bytes, on ? tile_bytes - skip * row_bytes : 0u, off_q, to);
+        load_to_lds((const char*)p.d_o + tile_g + skip * row_g, on ? tile_bytes_g - skip * row_g : 0u, off_g, to + SLAB * 16);
     };
-    auto park = [&]() {
-        uint4* const sq = lds;
-        uint4* const sg = sq + ROWS * STRIDE;
-#pragma unroll
-        for (int t = 0; t < PASSES; ++t) {
-            const uint32_t row = 16 * W * t + srow;
-            if (row < (uint32_t)ROWS) {
-                sq[row * STRIDE + scol] = __builtin_bit_cast(uint4, pq[t]);
-                sg[row * STRIDE + scol] = __builtin_bit_cast(uint4, pg[t]);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < SPASSES; ++t)
-            if (tid + 64 * W * t < ROWS / 2) sq[2 * ROWS * STRIDE + tid + 64 * W * t] = __builtin_bit_cast(uint4, st4[t]);
-    };
-    if (bw < (uint32_t)p.N) {
-        request(bw);
-        park();
-    }
-    __syncthreads();
-    const uint4* const lq = lds;
-    const uint4* const lg = lq + ROWS * STRIDE;
-    const float* const stM = reinterpret_cast<const float*>(lq + 2 * ROWS * STRIDE);
-    const float* const stD = stM + ROWS;
-    const uint16_t* const lg16 = reinterpret_cast<const uint16_t*>(lg) + trs;
-    const uint16_t* const lq16 = reinterpret_cast<const uint16_t*>(lq) + trs;
-
-    for (uint32_t w = bw; w < (uint32_t)p.N; w += gm.G) {
+    auto request_rest = [&](uint32_t w, bool on) {
+        const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
         const size_t tile_d = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
-        const __amdgpu_buffer_rsrc_t rl =
-            HM == 2 ? make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, (uint32_t)L * 4u) : make_rsrc(nullptr, 0);
+        // waves 0, 1: floats 4 lane .. 4 lane + 3 of M resp. -delta, i.e. row 16 part + lane / 4 of the head's slice
+        // of dV resp. dK; wave 2 with PW: labels 4 lane .. 4 lane + 3 (0 beyond L)
+        const char* src = (wave == 0 ? static_cast<const char*>(p.dv) : static_cast<const char*>(p.dk)) + tile_d;
+        uint32_t bytes = wave < 2 ? (16u * PARTS - 1u) * row_d + 64u : 0u;
+        if (PW) {
+            const char* const lab = reinterpret_cast<const char*>(p.labels + (size_t)(w % (uint32_t)p.nW) * L);
+            src = wave == 2 ? lab : src;
+            bytes = wave == 2 ? (uint32_t)L * 4u : bytes;
+        }
+        pst = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(src, on ? bytes : 0u), off_st, 0, 0);
+        // the wave's own K and V rows as operands: row 16 jb + n, channels 8g .. 8g + 7
+        const uint32_t off = (uint32_t)(16 * jb + n) * row_bytes + 16u * g, own = on ? tile_bytes : 0u;
+        pk = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.k + tile, own), off, 0, 0);
+        pv = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.v + tile, own), off, 0, 0);
+    };
+    auto park = [&](uint32_t buf) {
+        // M, -delta and labels lie one behind the other: ROWS / 4 = 4 NB <= 64 units of 16 bytes each
+        if (wave < (PW ? 3u : 2u) && lane < ROWS / 4) reinterpret_cast<u32x4*>(stats + buf * ST + wave * ROWS)[lane] = pst;
+    };
+    for (uint32_t i = (uint32_t)(4 * L + tid); i < SLAB; i += 64u * W) {  // rows L .. ROWS - 1 of the four slabs
+        const uint4 z = {0u, 0u, 0u, 0u};
+        lds[i] = lds[SLAB + i] = lds[2 * SLAB + i] = lds[3 * SLAB + i] = z;
+    }
+    if (bw < (uint32_t)p.N) {  // in flight while the additive term is fetched
+#pragma unroll
+        for (int t = 0; t < PASSES; ++t) request_slab(bw, 0u, t, true);
+        request_rest(bw, true);
+    }
+    f32x4 add[NB];  // (bias + mask) * log2e, resp. bias * log2e, in the layout of dbacc
+    if (KEEP || KEEPB) {
+        const MaskSrc msk = PW || KEEPB ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
+        const __amdgpu_buffer_rsrc_t rb = p.bias ? make_rsrc(bias32 + (size_t)h * L * L, ll) : make_rsrc(nullptr, 0);
+        // rows beyond L lie outside the descriptors: zeros.  A key beyond L reads into the next row: what it makes
+        // of that stays in its own column of every product, i.e. in rows of dV, dK and columns of dBias beyond L,
+        // which the stores and the reduce kernel drop.
+#pragma unroll
+        for (int qb = 0; qb < NB; ++qb) {
+            const uint32_t off = ((uint32_t)(16 * qb + 4 * g) * L + 16u * jb + n) * 4u;
+            const f32x4 mk = mask_rows4(msk, (uint32_t)(16 * qb + 4 * g), 16u * jb + n, (uint32_t)L);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) add[qb][r] = (load_f32(rb, off + 4u * L * r) + mk[r]) * kLog2e;
+        }
+    }
+    uint32_t aoff[4];  // STREAM: additive term of query 4g + r (of a query block) and this lane's key
+#pragma unroll
+    for (int r = 0; r < 4; ++r) aoff[r] = ((uint32_t)(4 * g + r) * L + 16u * jb + n) * 4u;
+    const float mv = p.mask_value * kLog2e;
+    if (bw < (uint32_t)p.N) park(0u);
+    lds_loads_done();
+    __syncthreads();
+
+    uint32_t buf = 0u;
+    for (uint32_t w = bw; w < (uint32_t)p.N; w += gm.G, buf ^= 1u) {
+        const uint4* const lq = lds + buf * (2 * SLAB);
+        const uint4* const lg = lq + SLAB;
+        const float* const stM = stats + buf * ST;
+        const float* const stD = stM + ROWS;  // -delta
+        const int* const llab = reinterpret_cast<const int*>(stD + ROWS);
+        const uint16_t* const lg16 = reinterpret_cast<const uint16_t*>(lg) + trs;
+        const uint16_t* const lq16 = reinterpret_cast<const uint16_t*>(lq) + trs;
+        const size_t tile_d = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
         const bf16x8 kop = as_bf16x8(pk), vop = as_bf16x8(pv);
         const bool has_next = w + gm.G < (uint32_t)p.N;
         u32x2 va = {0u, 0u}, vb = {0u, 0u}, ka = {0u, 0u}, kb = {0u, 0u};  // the wave's 16 rows of dV and dK, packed
 
         if (active) {
-            const int lkey = HM == 2 ? load_i32(rl, (uint32_t)(16 * jb + n) * 4u) : 0;
+            const int lkey = PW ? llab[16 * jb + n] : 0;
             f32x4 v0 = zero, v1 = zero, k0 = zero, k1 = zero;  // dV, dK [16 jb + n][4g + r] and [..][16 + 4g + r]
-            // operands of a query block one block ahead of their use, transposed operands one pair ahead
-            bf16x8 oq[2], og[2], tg0[2], tg1[2], tx0[2], tx1[2];
-            f32x4 oM[2], oD[2], ab[2], am[2];
+            // The products S, dP of a query block are issued one block ahead of the block's vector work, from operands
+            // fetched two blocks ahead, and the dV, dK products of a pair of blocks during the next block's: so every
+            // stretch of vector instructions has matrix instructions beside it that do not depend on it.
+            bf16x8 oq, og, tg0, tg1, tx0, tx1, PH, PL, SH, SL;
+            f32x4 oM[2], oD, sc[2], dp[2], ab[2], am[2];
             i32x4 al[2];
-            auto fetch_q = [&](int qb, int slot) {
-                oq[slot] = __builtin_bit_cast(bf16x8, lq[opd + 16 * qb * STRIDE]);
-                og[slot] = __builtin_bit_cast(bf16x8, lg[opd + 16 * qb * STRIDE]);
-                oM[slot] = *reinterpret_cast<const f32x4*>(stM + 16 * qb + 4 * g);
-                oD[slot] = *reinterpret_cast<const f32x4*>(stD + 16 * qb + 4 * g);
-                if (BM) {
-                    // descriptors start at the first row of the query block, so that the 4 lane offsets
-                    // serve every block; rows beyond L lie outside them
-                    const uint32_t qrow = (uint32_t)(16 * qb) * L;
-                    const __amdgpu_buffer_rsrc_t rbq =
-                        HB == 1 ? make_rsrc(bias32 + (size_t)h * L * L + qrow, ll - 4u * qrow) : make_rsrc(nullptr, 0);
-                    const __amdgpu_buffer_rsrc_t rmq =
-                        HM == 1 ? make_rsrc(p.mask + (size_t)(w % (uint32_t)p.nW) * L * L + qrow, ll - 4u * qrow)
-                                : make_rsrc(nullptr, 0);
+            auto fetch_q = [&](int qb) {
+                oq = __builtin_bit_cast(bf16x8, lq[opd + 16 * qb * STRIDE]);
+                og = __builtin_bit_cast(bf16x8, lg[opd + 16 * qb * STRIDE]);
+                oD = *reinterpret_cast<const f32x4*>(stD + 16 * qb + 4 * g);
+            };
+            auto fetch_m = [&](int qb) {
+                oM[qb & 1] = *reinterpret_cast<const f32x4*>(stM + 16 * qb + 4 * g);
+                if (PW) al[qb & 1] = *reinterpret_cast<const i32x4*>(llab + 16 * qb + 4 * g);
+            };
+            auto fetch_term = [&](int qb) {
+                // descriptors start at the first row of the query block, so that the 4 lane offsets
+                // serve every block; rows beyond L lie outside them
+                const uint32_t qrow = (uint32_t)(16 * qb) * L;
+                const __amdgpu_buffer_rsrc_t rbq =
+                    HB ? make_rsrc(bias32 + (size_t)h * L * L + qrow, ll - 4u * qrow) : make_rsrc(nullptr, 0);
+                const __amdgpu_buffer_rsrc_t rmq =
+                    make_rsrc(p.mask + (size_t)(w % (uint32_t)p.nW) * L * L + qrow, ll - 4u * qrow);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        if (HB == 1) ab[slot][r] = load_f32(rbq, aoff[r]);
-                        if (HM == 1) am[slot][r] = load_f32(rmq, aoff[r]);
-                    }
-                    if (HM == 2) al[slot] = load_i32x4(rl, (uint32_t)(16 * qb + 4 * g) * 4u);
+                for (int r = 0; r < 4; ++r) {
+                    if (HB) ab[qb & 1][r] = load_f32(rbq, aoff[r]);
+                    am[qb & 1][r] = load_f32(rmq, aoff[r]);
                 }
             };
-            auto fetch_t = [&](int qp, int slot) {  // dO^T and Q^T of the 32 queries (channel on the lane)
-                const bool two = 2 * qp + 1 < NB;
-                tg0[slot] = operand_tr(lg16 + (32 * qp) * SROW, 16 * SROW, two);
-                tg1[slot] = operand_tr(lg16 + (32 * qp) * SROW + 16, 16 * SROW, two);
-                tx0[slot] = operand_tr(lq16 + (32 * qp) * SROW, 16 * SROW, two);
-                tx1[slot] = operand_tr(lq16 + (32 * qp) * SROW + 16, 16 * SROW, two);
+            auto products = [&](int qb) {
+                sc[qb & 1] = mfma_bf16(oq, kop, zero);  // <q_i, k_j>, i = 16 qb + 4g + r, j = 16 jb + n
+                dp[qb & 1] = mfma_bf16(og, vop, oD);    // dP - delta
             };
-            fetch_q(0, 0);
-            fetch_t(0, 0);
-#pragma unroll
-            for (int qp = 0; qp < NB2; ++qp) {
+            auto fetch_t = [&](int qp) {  // dO^T and Q^T of the 32 queries (channel on the lane)
                 const bool two = 2 * qp + 1 < NB;
-                const int tcur = qp & 1;
-                if (qp + 1 < NB2) fetch_t(qp + 1, tcur ^ 1);
-                bf16x4 ph[2], pl[2], sh[2], sl[2];
-                ph[1] = pl[1] = sh[1] = sl[1] = as_bf16x4(uint2{0u, 0u});
+                tg0 = operand_tr(lg16 + (32 * qp) * SROW, 16 * SROW, two);
+                tg1 = operand_tr(lg16 + (32 * qp) * SROW + 16, 16 * SROW, two);
+                tx0 = operand_tr(lq16 + (32 * qp) * SROW, 16 * SROW, two);
+                tx1 = operand_tr(lq16 + (32 * qp) * SROW + 16, 16 * SROW, two);
+            };
+            auto accumulate = [&]() {
+                v0 = mfma_bf16(tg0, PH, v0);
+                v1 = mfma_bf16(tg1, PH, v1);
+                k0 = mfma_bf16(tx0, SH, k0);
+                k1 = mfma_bf16(tx1, SH, k1);
+                v0 = mfma_bf16(tg0, PL, v0);
+                v1 = mfma_bf16(tg1, PL, v1);
+                k0 = mfma_bf16(tx0, SL, k0);
+                k1 = mfma_bf16(tx1, SL, k1);
+            };
+            fetch_q(0);
+            fetch_m(0);
+            if (STREAM) fetch_term(0);
+            products(0);
+            fetch_q(1);
+            if (STREAM) fetch_term(1);
+            bf16x4 ph[2], pl[2], sh[2], sl[2];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    if (u == 1 && !two) break;
-                    const int qb = 2 * qp + u, cur = qb & 1;
-                    if (qb + 1 < NB) fetch_q(qb + 1, cur ^ 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                    const f32x4 sc = mfma_bf16(oq[cur], kop, zero);  // <q_i, k_j>, i = 16 qb + 4g + r, j = 16 jb + n
-                    const f32x4 dp = mfma_bf16(og[cur], vop, zero);
-                    f32x4 pr, ds;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float x;
-                        if (BM) {
-                            const float mk = HM == 2 ? (al[cur][r] == lkey ? 0.f : p.mask_value) : am[cur][r];
-                            const float bv = ab[cur][r];
-                            const float add = HB && HM ? bv + mk : (HB ? bv : mk);
-                            x = fmaf(sc[r], sl2, fmaf(add, kLog2e, -oM[cur][r]));
-                        } else {
-                            x = fmaf(sc[r], sl2, -oM[cur][r]);
-                        }
-                        // a key beyond L is not masked out: its column of every product lands in rows of dV, dK
-                        // and columns of dBias beyond L, which the stores and the reduce kernel drop
-                        pr[r] = __builtin_amdgcn_exp2f(x);
-                        ds[r] = pr[r] * (dp[r] - oD[cur][r]);
-                    }
-                    dbacc[qb] += ds;
-                    split_hi_lo(pr, ph[u], pl[u]);
-                    split_hi_lo(ds, sh[u], sl[u]);
-                }
-                const bf16x8 PH = pair_operand(ph[0], ph[1]), PL = pair_operand(pl[0], pl[1]);
-                const bf16x8 SH = pair_operand(sh[0], sh[1]), SL = pair_operand(sl[0], sl[1]);
-                v0 = mfma_bf16(tg0[tcur], PH, v0);
-                v1 = mfma_bf16(tg1[tcur], PH, v1);
-                k0 = mfma_bf16(tx0[tcur], SH, k0);
-                k1 = mfma_bf16(tx1[tcur], SH, k1);
-                v0 = mfma_bf16(tg0[tcur], PL, v0);
-                v1 = mfma_bf16(tg1[tcur], PL, v1);
-                k0 = mfma_bf16(tx0[tcur], SL, k0);
-                k1 = mfma_bf16(tx1[tcur], SL, k1);
+            for (int qb = 0; qb < NB; ++qb) {
+                const int u = qb & 1;
                 __builtin_amdgcn_sched_barrier(0);
+                // the next window's loads one pair at a time between the blocks: issued in one go they queue at the
+                // CU's address unit and hold the wave up
+#pragma unroll
+                for (int t = 0; t < PASSES; ++t)
+                    if (qb == t * (NB / 2) / PASSES) request_slab(w + gm.G, buf ^ 1u, t, has_next);
+                if (qb == NB / 2) request_rest(w + gm.G, has_next);
+                if (qb + 1 < NB) products(qb + 1);
+                if (u == 0 && qb > 0) accumulate();
+                if (u == 1 || qb == NB - 1) fetch_t(qb / 2);
+                if (qb + 1 < NB) fetch_m(qb + 1);
+                if (qb + 2 < NB) fetch_q(qb + 2);
+                f32x4 pr, ds;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float x;
+                    if (TERM == kTermNone) {
+                        x = fmaf(sc[u][r], sl2, -oM[u][r]);
+                    } else {
+                        float t;
+                        if (STREAM) t = KEEPB ? fmaf(am[u][r], kLog2e, add[qb][r]) : (HB ? ab[u][r] + am[u][r] : am[u][r]) * kLog2e;
+                        else t = PW ? add[qb][r] + (al[u][r] == lkey ? 0.f : mv) : add[qb][r];
+                        x = fmaf(sc[u][r], sl2, t) - oM[u][r];
+                    }
+                    pr[r] = __builtin_amdgcn_exp2f(x);
+                    ds[r] = pr[r] * dp[u][r];
+                }
+                if (DB) dbacc[qb] += ds;
+                split_hi_lo(pr, ph[u], pl[u]);
+                split_hi_lo(ds, sh[u], sl[u]);
+                if (STREAM && qb + 2 < NB) fetch_term(qb + 2);
+                if (u == 1 || qb == NB - 1) {
+                    if (u == 0) ph[1] = pl[1] = sh[1] = sl[1] = as_bf16x4(uint2{0u, 0u});
+                    PH = pair_operand(ph[0], ph[1]), PL = pair_operand(pl[0], pl[1]);
+                    SH = pair_operand(sh[0], sh[1]), SL = pair_operand(sl[0], sl[1]);
+                }
             }
+            __builtin_amdgcn_sched_barrier(0);
+            accumulate();
             va = u32x2{pack_bf16(v0[0], v0[1]), pack_bf16(v0[2], v0[3])};
             vb = u32x2{pack_bf16(v1[0], v1[1]), pack_bf16(v1[2], v1[3])};
             ka = u32x2{pack_bf16(k0[0] * p.scale, k0[1] * p.scale), pack_bf16(k0[2] * p.scale, k0[3] * p.scale)};
             kb = u32x2{pack_bf16(k1[0] * p.scale, k1[1] * p.scale), pack_bf16(k1[2] * p.scale, k1[3] * p.scale)};
+        } else {  // an idle wave moves its share all the same
+#pragma unroll
+            for (int t = 0; t < PASSES; ++t) request_slab(w + gm.G, buf ^ 1u, t, has_next);
+            request_rest(w + gm.G, has_next);
         }
-        // The next window is requested here, behind the last loads of this one's additive term and in front of
-        // its stores: memory operations of a wave complete in the order issued, so a request at the top of the
-        // window would hold up every small load behind it.
-        if (has_next) request(w + gm.G);
+        // The next window's slabs are in LDS before this wave passes the barrier; the wait stands in front of the
+        // stores, so that it does not wait for those.
+        lds_loads_done();
+        park(buf ^ 1u);
         if (active) {
-            store_rows(va, vb, make_rsrc((char*)p.dv + tile_d, tile_bytes_d));
-            store_rows(ka, kb, make_rsrc((char*)p.dk + tile_d, tile_bytes_d));
+            store_rows(cell, va, vb, make_rsrc((char*)p.dv + tile_d, tile_bytes_d), jb, row_d, lane);
+            store_rows(cell, ka, kb, make_rsrc((char*)p.dk + tile_d, tile_bytes_d), jb, row_d, lane);
         }
-        __syncthreads();  // every wave is done with the slabs
-        if (has_next) park();
-        __syncthreads();
+        __syncthreads();  // the next window is in place, and every wave is done with this one's buffer
     }
 
     // partial sums in register order: [slot][head][jb][qb][lane] float4, element r of lane (g, n) being
     // dS summed over windows for query 16 qb + 4g + r and key 16 jb + n
-    if (active) {
+    if (DB && active) {
         f32x4* dst = reinterpret_cast<f32x4*>(p.partial) + ((size_t)bw * p.heads + h) * (NB * NB * 64) + lane;
 #pragma unroll
         for (int qb = 0; qb < NB; ++qb) dst[(jb * NB + qb) * 64] = dbacc[qb];
     }
 }
 
+// ------------------------------------------------------------------ launches
 // Workgroups of `fn` one CU holds (LDS and registers decide), asked once per kernel; threads racing
 // through the first call ask twice and store the same figure.
 hipError_t workgroups_per_cu(const void* fn, unsigned block, size_t lds, std::atomic<int>& once, int& per_cu) {
@@ -731,84 +793,124 @@ hipError_t workgroups_per_cu(const void* fn, unsigned block, size_t lds, std::at
     return hipSuccess;
 }
 
-// dK, dV and the dBias partial sums; `slots` receives the number of partial sums per head
-template <int NB, int HB, int HM>
-hipError_t launch_large_keys(const BwdArgs& a, hipStream_t st, int& slots) {
-    constexpr int W = keys_waves(NB), HALVES = keys_parts(NB);
-    const void* fn = reinterpret_cast<const void*>(&bwd_bf16_large_keys_kernel<NB, HB, HM>);
-    const unsigned block = 64u * W;
-    const size_t lds = (size_t)2 * 16 * NB * 5 * 16 + (size_t)2 * 16 * NB * 4 + (size_t)W * 16 * 80;  // slabs, statistics, the waves' output cells
-    static std::atomic<int> once{0};
-    int per_cu = 1;
-    const hipError_t e = workgroups_per_cu(fn, block, lds, once, per_cu);
-    if (e != hipSuccess) return e;
+LargeGeom large_geom(const BwdArgs& a, int parts, long long G, unsigned& grid) {
     LargeGeom gm;
     gm.heads = (uint32_t)a.heads;
-    long long G = (long long)cu_count() * per_cu / ((long long)a.heads * HALVES);  // resident workgroups only
-    if (G > a.slots) G = a.slots;  // the workspace holds a.slots partial sums per head
-    if (G > a.N) G = a.N;
-    if (G < 1) G = 1;
+    gm.parts = (uint32_t)parts;
     gm.G = (uint32_t)G;
-    slots = (int)G;
-    const unsigned grid = gm.G * gm.heads * HALVES;
+    grid = gm.G * gm.heads * gm.parts;
     gm.xcd_q = grid / 8u;
     gm.xcd_r = grid % 8u;
-    hipLaunchKernelGGL((bwd_bf16_large_keys_kernel<NB, HB, HM>), dim3(grid), dim3(block), lds, st, a, gm);
+    return gm;
+}
+
+// Window positions walked in parallel, `resident` = as many as the chip holds at once.  Without a mask period: those,
+// at most one per window.  With one, a workgroup that keeps its additive term needs a multiple of it: the largest
+// that is resident, or, for a dense mask (`dense`), more than are resident at once, in several rounds, as long as
+// the cost in windows -- rounds times (windows per workgroup + about one and a half for fetching the term) -- stays
+// below that of the kernels that read the mask per window, 1.35 times as long per window (L = 256: 210 against 154 us
+// and 283 against 185).  0: those, or for labels the per-window form.  `most`: an upper limit (the dBias slots).
+long long walk_slots(long long resident, long long most, long long N, long long period, bool dense) {
+    if (resident < 1) resident = 1;
+    long long G = resident < most ? resident : most;
+    if (G > N) G = N;
+    const long long fit = G / period * period;
+    if (fit > 0 || !dense) return fit;
+    const double stream = 1.35 * (double)((N + G - 1) / G);
+    long long best = 0;
+    double best_cost = stream;
+    for (long long c = period; c <= N && c <= most && c <= 16 * resident; c += period) {
+        const double cost = (double)((c + resident - 1) / resident) * ((double)(N / c + (N % c != 0)) + 1.5);
+        if (cost < best_cost) best_cost = cost, best = c;
+    }
+    return best;
+}
+
+template <int NB, bool BM, bool PW>
+hipError_t launch_rows(const BwdArgs& a, long long period, hipStream_t st, bool& fits) {
+    const void* fn = reinterpret_cast<const void*>(&bwd_bf16_rows_kernel<NB, BM, PW>);
+    constexpr unsigned block = 64u * rows_waves(NB);
+    static std::atomic<int> once{0};
+    int per_cu = 1;
+    const hipError_t e = workgroups_per_cu(fn, block, rows_lds<NB>(), once, per_cu);
+    if (e != hipSuccess) return e;
+    const long long G = walk_slots((long long)cu_count() * per_cu / ((long long)a.heads * rows_parts(NB)), a.N, a.N, period, a.mask != nullptr);
+    fits = G > 0;
+    if (!fits) return hipSuccess;
+    unsigned grid;
+    const LargeGeom gm = large_geom(a, rows_parts(NB), G, grid);
+    hipLaunchKernelGGL((bwd_bf16_rows_kernel<NB, BM, PW>), dim3(grid), dim3(block), rows_lds<NB>(), st, a, gm);
     return hipGetLastError();
 }
 
-template <int NB, int HB, int HM, bool P2>
-hipError_t launch_large_one(const BwdArgs& a, hipStream_t st) {
-    constexpr int W = large_waves(NB);
-    const void* fn = reinterpret_cast<const void*>(&bwd_bf16_large_kernel<NB, HB, HM, P2>);
-    const unsigned block = 64u * W;
-    const size_t lds = (size_t)4 * 16 * NB * kLargeStride * 16 + (size_t)2 * 16 * NB * 4 + (size_t)W * 16 * 68 * 4;  // slabs, statistics, one patch per wave
+template <int NB, bool HB>
+hipError_t launch_rows_stream(const BwdArgs& a, hipStream_t st) {
+    const void* fn = reinterpret_cast<const void*>(&bwd_bf16_rows_stream_kernel<NB, HB>);
+    constexpr unsigned block = 64u * stream_waves(NB);
     static std::atomic<int> once{0};
     int per_cu = 1;
-    const hipError_t e = workgroups_per_cu(fn, block, lds, once, per_cu);
+    const hipError_t e = workgroups_per_cu(fn, block, stream_lds<NB>(), once, per_cu);
     if (e != hipSuccess) return e;
-    LargeGeom gm;
-    gm.heads = (uint32_t)a.heads;
-    long long G = (long long)cu_count() * per_cu / a.heads;  // one resident workgroup per slot and head
-    if (G < 1) G = 1;
-    if (G > a.N) G = a.N;
-    gm.G = (uint32_t)G;
-    const unsigned grid = gm.G * gm.heads;
-    gm.xcd_q = grid / 8u;
-    gm.xcd_r = grid % 8u;
-    hipLaunchKernelGGL((bwd_bf16_large_kernel<NB, HB, HM, P2>), dim3(grid), dim3(block), lds, st, a, gm);
+    unsigned grid;
+    const LargeGeom gm = large_geom(a, 1, walk_slots((long long)cu_count() * per_cu / a.heads, a.N, a.N, 1, false), grid);
+    hipLaunchKernelGGL((bwd_bf16_rows_stream_kernel<NB, HB>), dim3(grid), dim3(block), stream_lds<NB>(), st, a, gm);
     return hipGetLastError();
 }
 
-// Without dBias one kernel does both passes.  With it: pass 1 (dQ, statistics), then the keys kernel
-// (dK, dV, dBias partial sums), then the reduction of the partial sums.
-template <int NB, int HB, int HM>
-hipError_t launch_large_both(const BwdArgs& a, hipStream_t st) {
-    if (a.dbias == nullptr) return launch_large_one<NB, HB, HM, true>(a, st);
-    hipError_t e = launch_large_one<NB, HB, HM, false>(a, st);
+// dK, dV and, with DB, the dBias partial sums (`slots` receives their number per head) and their reduction
+template <int NB, int TERM, bool DB>
+hipError_t launch_keys_db(const BwdArgs& a, long long period, hipStream_t st, bool& fits) {
+    const void* fn = reinterpret_cast<const void*>(&bwd_bf16_keys_kernel<NB, TERM, DB>);
+    constexpr unsigned block = 64u * keys_waves(NB);
+    static std::atomic<int> once{0};
+    int per_cu = 1;
+    const hipError_t e = workgroups_per_cu(fn, block, keys_lds<NB>(), once, per_cu);
     if (e != hipSuccess) return e;
-    int slots = a.slots;
-    e = launch_large_keys<NB, HB, HM>(a, st, slots);
-    if (e != hipSuccess) return e;
+    const long long resident = (long long)cu_count() * per_cu / ((long long)a.heads * keys_parts(NB));
+    const long long most = DB ? a.slots : a.N;  // the workspace holds a.slots partial sums per head
+    const long long G = walk_slots(resident, most, a.N, period, a.mask != nullptr);
+    fits = G > 0;
+    if (!fits) return hipSuccess;
+    unsigned grid;
+    const LargeGeom gm = large_geom(a, keys_parts(NB), G, grid);
+    hipLaunchKernelGGL((bwd_bf16_keys_kernel<NB, TERM, DB>), dim3(grid), dim3(block), keys_lds<NB>(), st, a, gm);
+    const hipError_t l = hipGetLastError();
+    if (!DB || l != hipSuccess) return l;
     BwdArgs r = a;
-    r.slots = slots;
+    r.slots = (int)G;
     return launch_dbias_reduce(r, st, true);
 }
+template <int NB, int TERM>
+hipError_t launch_keys(const BwdArgs& a, long long period, hipStream_t st, bool& fits) {
+    return a.dbias ? launch_keys_db<NB, TERM, true>(a, period, st, fits) : launch_keys_db<NB, TERM, false>(a, period, st, fits);
+}
 
+// The additive term stays in registers where the number of window positions in flight can be a multiple of the mask
+// period (1 without a mask).  Beyond that labels let the kernels form the mask of each window, and a dense mask is
+// read per window.  The two kernels decide for themselves: they hold different numbers of workgroups.
 template <int NB>
 hipError_t launch_large_nb(const BwdArgs& a, hipStream_t st) {
     if (a.bias && a.bias_bf16) return hipErrorInvalidValue;  // the caller hands over an fp32 copy
-    if (a.bias) {
-        if (a.labels) return launch_large_both<NB, 1, 2>(a, st);
-        return a.mask ? launch_large_both<NB, 1, 1>(a, st) : launch_large_both<NB, 1, 0>(a, st);
+    const bool bm = a.bias || has_mask(a);
+    const long long period = mask_period(a);
+    bool fits = false;
+    hipError_t e = bm ? launch_rows<NB, true, false>(a, period, st, fits) : launch_rows<NB, false, false>(a, 1, st, fits);
+    if (e == hipSuccess && !fits) {
+        if (a.labels) e = launch_rows<NB, true, true>(a, 1, st, fits);
+        else e = a.bias ? launch_rows_stream<NB, true>(a, st) : launch_rows_stream<NB, false>(a, st);
     }
-    if (a.labels) return launch_large_both<NB, 0, 2>(a, st);
-    return a.mask ? launch_large_both<NB, 0, 1>(a, st) : launch_large_both<NB, 0, 0>(a, st);
+    if (e != hipSuccess) return e;
+    e = bm ? launch_keys<NB, kTermKept>(a, period, st, fits) : launch_keys<NB, kTermNone>(a, 1, st, fits);
+    if (e == hipSuccess && !fits) {
+        if (a.labels) e = launch_keys<NB, kTermLabels>(a, 1, st, fits);
+        else e = a.bias ? launch_keys<NB, kTermStream>(a, 1, st, fits) : launch_keys<NB, kTermStreamMask>(a, 1, st, fits);
+    }
+    return e;
 }
 
 }  // namespace
 
-// Slots of dBias partial sums for large windows: one resident workgroup of the dBias kernel per CU
+// Slots of dBias partial sums for large windows: one resident workgroup of the keys kernel per CU
 // when its slabs fill most of the LDS (more than 10 blocks of 16 rows), two otherwise
 int backward_large_slots(long long N, int heads, int L) {
     long long G = (L > 160 ? 1 : 2) * cu_count() / heads;

@@ -94,6 +94,25 @@ __device__ __forceinline__ int load_i32(__amdgpu_buffer_rsrc_t r, uint32_t voffs
     return (int)__builtin_amdgcn_raw_buffer_load_b32(r, voffset, 0, 0);
 }
 
+// 16 bytes per lane straight from global memory into LDS, lane l's at byte `lds_off` + 16 l of the workgroup's LDS
+//
+// (`lds_off` wave-uniform and below 64 KB; inactive lanes write nothing).  Written in assembly because the compiler
+// would wait for the load in front of every later LDS read, whatever that reads: the caller separates the two
+// with lds_loads_done() and a barrier.  `base` is wave-uniform; lanes whose offset lies at or
+// beyond `bytes` fetch nothing, and zeros at most are written for them (callers keep zeros there from the start).
+__device__ __forceinline__ uint32_t lds_offset(const void* p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t bytes, uint32_t voffset, uint32_t lds_off) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(base);
+    const u32x4 r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
+    uint32_t saved;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved) : "s"(lds_off), "v"(voffset), "s"(r) : "memory");
+}
+// every global load and store this wave has issued is complete
+__device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Unsigned division by a runtime constant with a host-made multiplier
 // (round-up method): n / d == (mulhi(n, mul) + n) >> shift for n < 2^31.
 struct FastDiv {

@@ -47,7 +47,6 @@ struct BwdArgs {
     void* dv;
     float* dbias;        // [heads, L, L] or nullptr
     float* partial;      // workspace for per-slot dS sums, or nullptr
-    float* stats;        // workspace [N, heads, 2, 16 * ceil(L / 16)] for the row statistics (L > 64 with dbias), or nullptr
     const void* bias;    // as in FwdArgs
     int bias_bf16;
     const float* mask;

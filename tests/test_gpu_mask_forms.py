@@ -1,0 +1,47 @@
+"""The forms in which the backward for windows of more than 64 tokens takes its additive term, each at the sizes
+where the choice between them falls, against the fp64 oracle: kept in registers (the number of workgroups in flight
+is a multiple of the mask period, or more workgroups than are resident are launched), the mask formed per window from
+labels, and a dense mask read per window.  The block counts cover odd ones, whose last workgroup has idle waves."""
+import numpy as np
+import pytest
+
+from paper_2501_06480_amd import synth
+from gpu_util import TOL, check_bf16_output, f32_device, max_abs, to_device, to_f64
+
+pytestmark = pytest.mark.gpu
+
+# name, L, heads, N, nW, bias, dbias
+CASES = [
+    ("period_of_one", 65, 2, 70, 1, True, True),
+    ("kept_idle_waves", 129, 3, 96, 8, True, True),
+    ("kept_last_part_one_block", 193, 2, 64, 4, True, False),
+    ("more_workgroups_than_resident", 65, 24, 960, 40, True, True),
+    ("beyond_L65", 65, 24, 100, 50, True, True),
+    ("beyond_L65_no_bias", 65, 24, 100, 50, False, True),
+    ("beyond_L81_no_dbias", 81, 24, 100, 50, True, False),
+    ("beyond_L177", 177, 16, 40, 40, True, True),
+    ("beyond_L256", 256, 12, 24, 24, True, True),
+    ("beyond_L256_mask_alone", 256, 12, 24, 24, False, False),
+]
+
+
+@pytest.mark.parametrize("name,L,heads,N,nW,use_bias,dbias", CASES, ids=[c[0] for c in CASES])
+def test_large_window_backward(oracle, name, L, heads, N, nW, use_bias, dbias):
+    import torch
+    import paper_2501_06480_amd as fwa
+    w = synth.Workload("forms_" + name, N, L, 32 * heads, heads, "bf16", 8100 + L, 0, backward=True)
+    x = synth.draw(w)
+    bias = synth.normal((heads, L, L), 8200 + L, 0.5) if use_bias else None
+    labels = synth.rng(8300 + L).integers(0, 3, (nW, L)).astype(np.int32)
+    mask = np.where(labels[:, :, None] == labels[:, None, :], 0.0, -3.0).astype(np.float32)
+    ref = oracle.backward(x["q"], x["k"], x["v"], x["d_o"], heads, w.scale, bias, mask)
+    q, k, v, g = (to_device(x, w, n) for n in ("q", "k", "v", "d_o"))
+    for form in ("dense", "labels"):
+        print(f"{name} {form}: L={L} heads={heads} N={N} nW={nW} bias={use_bias} dbias={dbias}", flush=True)
+        kw = {"mask": f32_device(mask)} if form == "dense" else {"labels": torch.from_numpy(labels).cuda(), "mask_value": -3.0}
+        got = fwa.fwa_backward(q, k, v, g, heads, w.scale, f32_device(bias), want_dbias=dbias, **kw)
+        torch.cuda.synchronize()
+        for what, a, b in zip(("dq", "dk", "dv"), got, ref):
+            check_bf16_output(to_f64(a), b, f"{name} {form} {what}")
+        if dbias:
+            assert max_abs(to_f64(got[3]), ref[3]) <= TOL["bf16"], (name, form)
