@@ -334,15 +334,16 @@ int backward_impl(const void* q, const void* k, const void* v, const void* d_o, 
     a.dq = dq; a.dk = dk; a.dv = dv; a.dbias = dbias;
     a.mask = mask; a.labels = labels; a.mask_value = mask_value;
     a.N = N; a.L = L; a.C = C; a.heads = heads; a.nW = (mask || labels) ? nW : 1; a.scale = scale;
-    // A mask period that no slot count of the cooperative kernel is a multiple of: with the mask as
-    // labels the kernel forms each window's mask itself and its workgroups walk the windows as if
-    // there were no period; with a dense mask the one-wave-per-tile kernel takes the call.
+    // A mask period that no slot count of the cooperative kernel is a multiple of: the kernel forms each
+    // window's mask from its labels, or fetches its tile, and its workgroups walk the windows as if there
+    // were no period.
     const bool large = L > fwa::kMaxBackwardL;
     const bool small = dtype == FWA_BF16 && C / heads == fwa::kHeadDim && !large;
-    a.per_window = small && labels && fwa::coop_slots(N, heads, a.nW) == 0 && fwa::coop_slots(N, heads, 1) > 0;
+    const bool periodic = fwa::coop_slots(N, heads, a.nW) > 0;
+    a.per_window = small && (labels || mask) && !periodic;
     a.slots = C / heads != fwa::kHeadDim ? fwa::backward_wide_slots(N, heads)
               : large                    ? fwa::backward_large_slots(N, heads, L)
-                                         : fwa::backward_slots(N, heads, a.per_window ? 1 : a.nW);
+                                         : fwa::backward_slots(N, heads, a.nW);
     // workspace: [fp32 copy of a bf16 bias (large windows only)] [partial sums of dBias]; a call needs the
     // parts it uses
     const bool copy_bias = large && bias && bias_dtype == FWA_BF16;
@@ -374,9 +375,8 @@ int backward_impl(const void* q, const void* k, const void* v, const void* d_o, 
     a.partial = dbias ? reinterpret_cast<float*>(ws) : nullptr;
     a.bias = bias; a.bias_bf16 = bias && bias_dtype == FWA_BF16;
     a.ldq = (int)ld_qkv; a.ldg = (int)ld_do; a.ldd = (int)ld_dqkv; a.f16 = dtype == FWA_F16;
-    // the one-wave-per-tile kernel takes fp32 biases only
-    if (a.bias_bf16 && small && !a.per_window && fwa::coop_slots(N, heads, a.nW) == 0)
-        return FWA_ERR_UNSUPPORTED;
+    // more head groups than the chip holds workgroups: fp32 biases only, as ever
+    if (a.bias_bf16 && small && !periodic && fwa::coop_slots(N, heads, 1) == 0) return FWA_ERR_UNSUPPORTED;
     const hipError_t e = dtype != FWA_F32 ? fwa::launch_backward_bf16(a, st) : fwa::launch_backward_f32(a, st);
     return e == hipSuccess ? FWA_OK : FWA_ERR_LAUNCH;
 }

@@ -1,8 +1,8 @@
 // Cooperative backward kernel (paper Algorithm 2) for L <= 64: four waves per
 // (window, head) tile, several heads per workgroup, persistent over windows.
 //
-// The single-wave kernel (fwa_backward.hip) needs the whole register file for one tile and
-// runs two waves per SIMD.  Here the tile is split:
+// One wave per tile would need the whole register file and run two waves per SIMD (built first: twice as
+// slow).  Here the tile is split:
 //
 //   phase A, wave qb (16 queries, "query on the lane"):
 //       S^T = K Q^T, softmax, dP^T = V dO^T, delta, dS          (K, V rows read from LDS)
@@ -33,16 +33,21 @@ struct CoopGeom {
     FastDiv groups;         // workgroups per window position
     FastDiv lanes_per_row;  // 4 * heads_per_block
     uint32_t heads_per_block;
+    uint32_t stride;        // slab row in 16-byte units
     uint32_t G;             // window positions walked in parallel (= dBias slots)
     uint32_t xcd_remap, xcd_q, xcd_r;
 };
 
 // KT < 4 promises that only the first KT of a lane's 4 columns in the last key block can be real
 // (L <= 16 (NB - 1) + KT, e.g. KT = 1 for L = 49): the others are zero without any arithmetic.
-// PW ("per window"): the mask comes as labels whose period G is no multiple of.  The registers then
-// hold bias * log2e alone; the labels of a window travel with its slabs into LDS and phase A forms
-// the mask per score (AddendRegsLabels).
-template <int NB, bool BM, bool DB, int KT, bool PW>
+// PW ("per window"): G is no multiple of the mask's period.  The registers then hold bias * log2e alone.
+// PW = 1, labels: those of a window travel with its slabs into LDS and phase A forms the mask per score
+// (AddendRegsLabels).  PW = 2, a dense mask: the tile of a window is fetched into LDS during phase B of the window
+// before, straight from memory and in whole lines (AddendRegsDense; every lane loading the values of its own row,
+// 16 bytes of a line each, took 93 us instead of 53 below).  Stage 1 of two 800 x 1333 images (2784
+// windows, 3 heads, bias, mask of 1392 windows, dBias): 53 us with the reduction, 52 as labels; a kernel with one
+// wave per tile that such calls took before, 102.
+template <int NB, bool BM, bool DB, int KT, int PW>
 __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf16_coop_kernel(BwdArgs p, CoopGeom gm) {
     constexpr int NB2 = (NB + 1) / 2;
     constexpr int ROWS = 16 * NB;
@@ -62,23 +67,24 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     const int L = p.L;
     // token rows are p.ldq (q, k, v), p.ldg (d_o), p.ldd (dq, dk, dv) elements apart; window w starts at row w L
     const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
-    const uint32_t stride = 4u * hpb + 1u;  // slab row stride in 16-byte units
+    const uint32_t stride = gm.stride;  // slab row stride in 16-byte units
     const float sl2 = p.scale * kLog2e;
     const bool active = role < NB;
 
-    // LDS: slabs [K][V][Q][dO], each [ROWS][stride] uint4; then per head four bf16 tiles.
-    uint4* const lk = lds;
-    uint4* const lv = lds + ROWS * stride;
-    uint4* const lq = lds + 2 * ROWS * stride;
-    uint4* const lg = lds + 3 * ROWS * stride;
+    // LDS: (PW == 2) the mask tile; slabs [K][V][Q][dO], each [ROWS][stride] uint4; then per head four bf16 tiles.
+    uint4* const lmask = lds;
+    uint4* const lk = lds + (PW == 2 ? mask_tile_bytes((uint32_t)L) / 16u : 0u);
+    uint4* const lv = lk + ROWS * stride;
+    uint4* const lq = lk + 2 * ROWS * stride;
+    uint4* const lg = lk + 3 * ROWS * stride;
     // P_hi, P_lo, dS_hi, dS_lo tiles of this head: [ROWS][64] bf16.  A row is 16 units of 4 keys; unit
     // (block b, quarter c) of row i sits at unit (b ^ (i & 3), c ^ ((i >> 2) & 3)): the 16 lanes of a
     // write (16 rows, one unit each) and of a transposing read (4 rows x 4 units) then touch 16
     // different units, i.e. every bank once.
     constexpr uint32_t XS = 64, XT = ROWS * XS;
-    uint16_t* const ex = reinterpret_cast<uint16_t*>(lds + 4 * ROWS * stride) + (size_t)hl * (4 * XT);
-    // PW: the labels of the window in LDS, behind the tiles of all heads
-    int* const llab = reinterpret_cast<int*>(reinterpret_cast<uint16_t*>(lds + 4 * ROWS * stride) + (size_t)hpb * (4 * XT));
+    uint16_t* const ex = reinterpret_cast<uint16_t*>(lk + 4 * ROWS * stride) + (size_t)hl * (4 * XT);
+    // PW == 1: the labels of the window in LDS, behind the tiles of all heads
+    int* const llab = reinterpret_cast<int*>(reinterpret_cast<uint16_t*>(lk + 4 * ROWS * stride) + (size_t)hpb * (4 * XT));
     const uint32_t srow = stride * 8u;  // slab row stride in bf16 elements
     // transposing-read base of this lane inside a slab (channel on the lane) and inside a tile
     const uint32_t trs = (4u * g + (n >> 2)) * srow + 32u * hl + 4u * (n & 3);
@@ -101,7 +107,7 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     const uint32_t goff_g = rip * row_g + col * 16u;
     const uint32_t loff = rip * stride + col;
     u32x4 pk, pv, pq, pg;
-    i32x4 plab = {0, 0, 0, 0};  // PW: labels 4 tid .. 4 tid + 3 of the requested window (0 beyond L)
+    i32x4 plab = {0, 0, 0, 0};  // PW == 1: labels 4 tid .. 4 tid + 3 of the requested window (0 beyond L)
     auto request = [&](uint32_t w) {
         const size_t slab = ((size_t)w * L * p.ldq + (size_t)hg * hpb * kHeadDim) * 2u;
         const size_t slab_g = ((size_t)w * L * p.ldg + (size_t)hg * hpb * kHeadDim) * 2u;
@@ -110,7 +116,7 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
         pv = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.v + slab, slab_bytes), goff, 0, 0);
         pq = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.q + slab, slab_bytes), goff, 0, 0);
         pg = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.d_o + slab_g, slab_bytes_g), goff_g, 0, 0);
-        if (PW && wv == 0) plab = load_i32x4(make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, (uint32_t)L * 4u), (uint32_t)tid * 16u);
+        if (PW == 1 && wv == 0) plab = load_i32x4(make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, (uint32_t)L * 4u), (uint32_t)tid * 16u);
     };
     auto park = [&]() {
         if (rip < (uint32_t)ROWS) {
@@ -119,7 +125,7 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
             lq[loff] = __builtin_bit_cast(uint4, pq);
             lg[loff] = __builtin_bit_cast(uint4, pg);
         }
-        if (PW && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab)[tid] = plab;
+        if (PW == 1 && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab)[tid] = plab;
     };
     if (bw < (uint32_t)p.N) request(bw);  // in flight while the additive term is fetched
     // additive score term of this wave's query rows, in registers (see the file comment)
@@ -130,7 +136,12 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
         addend_at(rb, msk, (uint32_t)(16 * role + n), 4u * g, (uint32_t)L).fill(add, kLog2e);
     }
     const float mv = p.mask_value * kLog2e;
+    auto request_mask = [&](uint32_t w) { request_mask_tile(p, w, lds_offset(lmask), wv, 4u * hpb, (uint32_t)lane); };
+    // this lane's query row of the mask tile; rows beyond L stay inside it (their results are dropped)
+    const float* const mask_row = reinterpret_cast<const float*>(lmask) + (16 * role + n < L ? 16 * role + n : L - 1) * L + 4 * g;
+    if (PW == 2 && bw < (uint32_t)p.N) request_mask(bw);
     if (bw < (uint32_t)p.N) park();
+    if (PW == 2) lds_loads_done();
 
     const uint32_t tile_bytes = (uint32_t)(L - 1) * row_d + 2u * kHeadDim;  // of an output tile
     const uint32_t off_half = (uint32_t)n * row_d + 8u * g;  // channels 4g..4g+3 of row n (+32 B: 16+4g..)
@@ -164,7 +175,10 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
             }
             // softmax of the block's rows: s <- exp(score - rowmax), inv = 1 / rowsum
             float inv;
-            if (BM && PW) {
+            if (BM && PW == 2) {
+                const AddendRegsDense<NB> addend = {add, mask_row};
+                inv = softmax_block<NB, true, AddendRegsDense<NB>, KT>(s, sl2, addend, L, g);
+            } else if (BM && PW == 1) {
                 const AddendRegsLabels<NB> addend = {add, llab, llab[16 * qb + n], mv, g};
                 inv = softmax_block<NB, true, AddendRegsLabels<NB>, KT>(s, sl2, addend, L, g);
             } else if (BM) {
@@ -235,6 +249,9 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
                 __builtin_amdgcn_raw_buffer_store_b64(dq_lo, rdq, off_half + 16 * role * row_d, 0, 0);
                 __builtin_amdgcn_raw_buffer_store_b64(dq_hi, rdq, off_half + 32 + 16 * role * row_d, 0, 0);
             }
+        }
+        if (PW == 2 && has_next) request_mask(w + gm.G);  // every wave has left phase A, the tile's only reader
+        if (active) {
             const int jb = role;
             f32x4 v0 = zero, v1 = zero, k0 = zero, k1 = zero;  // dV, dK [16 jb + n][4g + r] and [..][16 + 4g + r]
             const uint16_t* lg16 = reinterpret_cast<const uint16_t*>(lg) + trs;
@@ -262,7 +279,6 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
                 k0 = mfma_bf16(x0, sl, k0);
                 k1 = mfma_bf16(x1, sl, k1);
             }
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
             const u32x2 va = {pack_bf16(v0[0], v0[1]), pack_bf16(v0[2], v0[3])};
             const u32x2 vb = {pack_bf16(v1[0], v1[1]), pack_bf16(v1[2], v1[3])};
             const u32x2 ka = {pack_bf16(k0[0] * p.scale, k0[1] * p.scale), pack_bf16(k0[2] * p.scale, k0[3] * p.scale)};
@@ -284,6 +300,10 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lk[loff]), make_rsrc((char*)p.dk + slab_d, slab_bytes_d), goff_d, 0, 0);
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lv[loff]), make_rsrc((char*)p.dv + slab_d, slab_bytes_d), goff_d, 0, 0);
         }
+        if (PW == 2) {  // the mask tile has landed; the two stores above are younger and not waited for
+            if (rip < (uint32_t)ROWS) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+            else lds_loads_done();
+        }
         if (has_next) park();  // each thread overwrites the slab cells it has just read out
     }
 
@@ -295,10 +315,10 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     }
 }
 
-template <int NB, bool BM, bool DB, int KT, bool PW>
+template <int NB, bool BM, bool DB, int KT, int PW>
 hipError_t launch_coop_pw(const BwdArgs& a, const CoopGeom& gm, unsigned grid, unsigned block, size_t lds,
                           hipStream_t st) {
-    if (PW) lds += (size_t)16 * NB * 4;  // the window's labels
+    if (PW == 1) lds += (size_t)16 * NB * 4;  // the window's labels
     {
         const hipError_t e = allow_lds(reinterpret_cast<const void*>(&bwd_bf16_coop_kernel<NB, BM, DB, KT, PW>), lds);
         if (e != hipSuccess) return e;
@@ -311,9 +331,11 @@ template <int NB, bool BM, bool DB, int KT>
 hipError_t launch_coop_kt(const BwdArgs& a, const CoopGeom& gm, unsigned grid, unsigned block, size_t lds,
                           hipStream_t st) {
     if constexpr (BM) {
-        if (a.per_window) return launch_coop_pw<NB, true, DB, KT, true>(a, gm, grid, block, lds, st);
+        if (a.per_window)
+            return a.labels ? launch_coop_pw<NB, true, DB, KT, 1>(a, gm, grid, block, lds, st)
+                            : launch_coop_pw<NB, true, DB, KT, 2>(a, gm, grid, block, lds, st);
     }
-    return launch_coop_pw<NB, BM, DB, KT, false>(a, gm, grid, block, lds, st);
+    return launch_coop_pw<NB, BM, DB, KT, 0>(a, gm, grid, block, lds, st);
 }
 
 template <int NB, bool BM, bool DB>
@@ -333,7 +355,12 @@ hipError_t launch_coop_nb(const BwdArgs& a, int hpb, hipStream_t st) {
     gm.heads_per_block = (uint32_t)hpb;
     gm.G = (uint32_t)a.slots;
     const unsigned grid = gm.G * groups, block = 64u * kCoopWavesPerTile * (unsigned)hpb;
-    const size_t lds = (size_t)4 * 16 * NB * (4 * hpb + 1) * 16 + (size_t)hpb * 4 * (16 * NB) * 64 * 2;
+    // one unit of padding per slab row, but where a dense mask tile per window takes its place: at 3 heads and
+    // L = 56 .. 64 the workgroup then fills the 160 KB of LDS exactly
+    const size_t mask_lds = a.per_window && a.mask ? mask_tile_bytes((uint32_t)a.L) : 0;
+    const size_t tiles = (size_t)hpb * 4 * (16 * NB) * 64 * 2 + mask_lds;
+    gm.stride = (size_t)4 * 16 * NB * (4 * hpb + 1) * 16 + tiles <= 160 * 1024 ? 4u * (uint32_t)hpb + 1u : 4u * (uint32_t)hpb;
+    const size_t lds = (size_t)4 * 16 * NB * gm.stride * 16 + tiles;
     gm.xcd_remap = (hpb % 2 == 1 && groups > 1) ? 1u : 0u;
     gm.xcd_q = grid / 8u;
     gm.xcd_r = grid % 8u;

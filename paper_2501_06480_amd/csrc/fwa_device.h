@@ -83,10 +83,6 @@ __device__ __forceinline__ void store_f32x4(f32x4 v, __amdgpu_buffer_rsrc_t r, u
 __device__ __forceinline__ float load_f32(__amdgpu_buffer_rsrc_t r, uint32_t voffset) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voffset, 0, 0));
 }
-// one bf16 element (2-byte load) as fp32
-__device__ __forceinline__ float load_bf16(__amdgpu_buffer_rsrc_t r, uint32_t voffset) {
-    return __builtin_bit_cast(float, (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, voffset, 0, 0) << 16);
-}
 __device__ __forceinline__ i32x4 load_i32x4(__amdgpu_buffer_rsrc_t r, uint32_t voffset) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voffset, 0, 0));
 }
@@ -95,7 +91,6 @@ __device__ __forceinline__ int load_i32(__amdgpu_buffer_rsrc_t r, uint32_t voffs
 }
 
 // 16 bytes per lane straight from global memory into LDS, lane l's at byte `lds_off` + 16 l of the workgroup's LDS
-//
 // (`lds_off` wave-uniform and below 64 KB; inactive lanes write nothing).  Written in assembly because the compiler
 // would wait for the load in front of every later LDS read, whatever that reads: the caller separates the two
 // with lds_loads_done() and a barrier.  `base` is wave-uniform; lanes whose offset lies at or
@@ -169,23 +164,11 @@ __device__ __forceinline__ float sum_over_g(float x) {
     b = s32[1];
     return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
 }
-// sum over the 16 lanes (n = 0..15) that share the same g
-__device__ __forceinline__ float sum_over_n(float x) {
-    x += __shfl_xor(x, 1);
-    x += __shfl_xor(x, 2);
-    x += __shfl_xor(x, 4);
-    x += __shfl_xor(x, 8);
-    return x;
-}
-
 // (lo16(a), lo16(b)) and (hi16(a), hi16(b)) as one byte-permute each
 __device__ __forceinline__ uint32_t lower_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 __device__ __forceinline__ uint32_t upper_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));  // raw bf16 bits, operand of the K=16 matrix op
-__device__ __forceinline__ f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
+typedef short bf16x4 __attribute__((ext_vector_type(4)));  // raw bf16 bits
 __device__ __forceinline__ bf16x4 as_bf16x4(uint2 u) { return __builtin_bit_cast(bf16x4, u); }
 
 // fp32 values that are exactly bf16 (results of a product with a 0/1 matrix) -> packed bf16
@@ -201,7 +184,6 @@ __device__ __forceinline__ uint2 pack_exact_u2(const f32x4& x) {
     h.y = upper_halves(u[2], u[3]);
     return h;
 }
-__device__ __forceinline__ bf16x4 pack_exact(const f32x4& x) { return as_bf16x4(pack_exact_u2(x)); }
 
 // x = hi + lo with hi the upper 16 bits of x (a bf16 by truncation) and lo the
 // remainder rounded to bf16: together 16 significant bits.
@@ -221,16 +203,6 @@ __device__ __forceinline__ void split_hi_lo(const f32x4& x, bf16x4& hi, bf16x4& 
     l.y = pack_bf16(rem[2], rem[3]);
     hi = as_bf16x4(h);
     lo = as_bf16x4(l);
-}
-
-// B operand of the K=16 matrix op that is the 16x16 identity: slot e of lane (g, n) is 1.0 iff
-// 4g + e == n.  X (as A operand) times it returns X in the accumulator layout, i.e. with the
-// other index on the lane: lane (g', n') <- X[row 4g' + r][column n'].
-__device__ __forceinline__ bf16x4 identity_operand(int g, int n) {
-    uint2 u;
-    u.x = (4 * g + 0 == n ? 0x3f80u : 0u) | (4 * g + 1 == n ? 0x3f800000u : 0u);
-    u.y = (4 * g + 2 == n ? 0x3f80u : 0u) | (4 * g + 3 == n ? 0x3f800000u : 0u);
-    return as_bf16x4(u);
 }
 
 // A operand of the K=32 matrix op that is all ones: times the probability operand of a pair of key blocks it

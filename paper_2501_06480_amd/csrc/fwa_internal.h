@@ -59,8 +59,8 @@ struct BwdArgs {
     int nW;
     float scale;
     int slots;           // number of partial-sum slots per head in `partial`
-    int per_window;      // cooperative kernel for L <= 64: the mask is formed per window from the labels (a period
-                         // that no slot count is a multiple of); only the bias stays in registers
+    int per_window;      // cooperative kernel for L <= 64: the mask is formed or fetched per window (a period that
+                         // no slot count is a multiple of); only the bias stays in registers
     int ldq;             // elements between consecutive token rows of q, k, v (C when contiguous)
     int ldg;             // the same for d_o
     int ldd;             // the same for dq, dk, dv
@@ -97,7 +97,6 @@ int backward_slots(long long N, int heads, int nW);
 int backward_max_slots(long long N, int heads);
 int coop_slots(long long N, int heads, int nW);
 hipError_t launch_backward_bf16_coop(const BwdArgs& a, hipStream_t s);
-hipError_t launch_backward_bf16_single(const BwdArgs& a, hipStream_t s);
 hipError_t launch_backward_bf16_large(const BwdArgs& a, hipStream_t s);
 hipError_t launch_backward_bf16_wide(const BwdArgs& a, hipStream_t s);
 int backward_wide_slots(long long N, int heads);

@@ -60,13 +60,9 @@ __device__ __forceinline__ BiasSrc bias_of_head(const Args& p, uint32_t h) {
     if (p.bias_bf16) return BiasSrc{make_rsrc(p.bias, ((uint32_t)p.heads * L * L * 2u + 3u) & ~3u), h * L * L, true};
     return BiasSrc{make_rsrc(static_cast<const float*>(p.bias) + (size_t)h * L * L, L * L * 4u), 0u, false};
 }
-// One element of the tile (idx = i L + j) and four consecutive ones out of a 16-byte load that
-// started at the dword holding element idx (bf16: `odd` = idx is odd, the quad then starts in the
+// Four consecutive elements of the tile out of a 16-byte load that
+// started at the dword holding the first one, element idx = i L + j (bf16: `odd` = idx is odd, the quad then starts in the
 // upper half of the first dword).
-__device__ __forceinline__ float bias_elem(const BiasSrc& b, uint32_t idx) {
-    if (b.bf16) return load_bf16(b.r, 2u * (b.hbase + idx));
-    return load_f32(b.r, 4u * idx);
-}
 __device__ __forceinline__ f32x4 bf16_quad(const f32x4& raw, bool odd) {
     const u32x4 r = __builtin_bit_cast(u32x4, raw);
     const uint32_t sh = odd ? 16u : 0u;
@@ -197,6 +193,37 @@ template <class A>
 struct addend_per_block { static constexpr bool value = false; };
 template <int NB>
 struct addend_per_block<AddendRegsLabels<NB>> { static constexpr bool value = true; };
+// AddendRegsDense: the same with a dense mask, whose tile [L, L] of the current window the kernel has staged in LDS.
+// `row` points at M[i][4g] of the lane's query row; keys beyond L read what follows and are overwritten with -inf.
+template <int NB>
+struct AddendRegsDense {
+    const f32x4 (&a)[NB];
+    const float* row;
+    __device__ __forceinline__ f32x4 block(int jb) const {
+        f32x4 t;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t[r] = fmaf(row[16 * jb + r], kLog2e, a[jb][r]);
+        return t;
+    }
+    __device__ __forceinline__ void fill(f32x4 (&add)[NB], float) const {
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) add[jb] = block(jb);
+    }
+};
+template <int NB>
+struct addend_per_block<AddendRegsDense<NB>> { static constexpr bool value = true; };
+// LDS bytes of a staged mask tile: it is fetched in pieces of 1 KB per wave, and its last row is read up to column
+// 16 ceil(L / 16) - 1
+__host__ __device__ constexpr uint32_t mask_tile_bytes(uint32_t L) { return (L * L * 4u + 1023u) / 1024u * 1024u; }
+// Requests the dense mask tile of a window into LDS byte `to` (see load_to_lds): 1 KB pieces in turns over the
+// workgroup's `waves` waves, of which this is number `wave`.
+template <class Args>
+__device__ __forceinline__ void request_mask_tile(const Args& p, uint32_t w, uint32_t to, uint32_t wave, uint32_t waves, uint32_t lane) {
+    const uint32_t bytes = (uint32_t)p.L * (uint32_t)p.L * 4u;
+    const char* const src = reinterpret_cast<const char*>(p.mask) + (size_t)(w % (uint32_t)p.nW) * bytes;
+    for (uint32_t c = wave * 1024u; c < bytes; c += waves * 1024u) load_to_lds(src + c, bytes - c, lane * 16u, to + c);
+}
+
 struct AddendNone {
     template <int NB>
     __device__ __forceinline__ void fill(f32x4 (&add)[NB], float) const {

@@ -45,3 +45,27 @@ def test_large_window_backward(oracle, name, L, heads, N, nW, use_bias, dbias):
             check_bf16_output(to_f64(a), b, f"{name} {form} {what}")
         if dbias:
             assert max_abs(to_f64(got[3]), ref[3]) <= TOL["bf16"], (name, form)
+
+
+# The backward for windows of up to 64 tokens with a mask period that no slot count is a multiple of: labels parked in
+# LDS, or a dense tile fetched into LDS per window.  Tiles of less than, exactly and more than a 1 KB piece; 3 heads at
+# L = 55 and 56 (with and without room for the padding of the slab rows) and 64; 1, 2 and 3 heads per workgroup; idle
+# waves (L <= 48); the trimmed last key block (L = 17, 33, 49).
+# name, L, heads, N, nW, bias, dbias
+SMALL = [
+    ("L16", 16, 3, 600, 300, True, True),
+    ("L17_pairs", 17, 4, 280, 140, True, False),
+    ("L33_single_heads", 33, 24, 80, 40, True, True),
+    ("L49", 49, 3, 600, 300, True, True),
+    ("L49_mask_alone", 49, 2, 300, 300, False, True),
+    ("L55", 55, 3, 300, 300, True, True),
+    ("L56", 56, 3, 300, 300, True, True),
+    ("L64", 64, 3, 300, 300, True, False),
+    ("L64_pairs", 64, 8, 140, 70, True, True),
+    ("L64_one_head", 64, 1, 800, 800, True, True),
+]
+
+
+@pytest.mark.parametrize("name,L,heads,N,nW,use_bias,dbias", SMALL, ids=[c[0] for c in SMALL])
+def test_small_window_backward_long_periods(oracle, name, L, heads, N, nW, use_bias, dbias):
+    test_large_window_backward(oracle, name, L, heads, N, nW, use_bias, dbias)
