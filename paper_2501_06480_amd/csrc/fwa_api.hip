@@ -173,7 +173,7 @@ int forward_impl(const void* q, const void* k, const void* v, void* o, int64_t N
     a.ldq = (int)ld_qkv; a.ldo = (int)ld_o; a.f16 = dtype == FWA_F16;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool wide = C / heads != fwa::kHeadDim;
-    const hipError_t e = dtype == FWA_F32 ? (wide || L <= fwa::kMaxWideL ? fwa::launch_forward_f32_tile(a, st) : fwa::launch_forward_f32(a, st))
+    const hipError_t e = dtype == FWA_F32 ? fwa::launch_forward_f32(a, st)
                                            : (wide ? fwa::launch_forward_bf16_wide(a, st) : fwa::launch_forward_bf16(a, st));
     return e == hipSuccess ? FWA_OK : FWA_ERR_LAUNCH;
 }

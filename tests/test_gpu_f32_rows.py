@@ -1,0 +1,36 @@
+"""The fp32 forward for windows of more than 64 tokens: every choice of waves per workgroup (block counts 5 to 16, ragged
+last blocks), with the query blocks of a tile in one workgroup and, for few tiles, spread over several."""
+import numpy as np
+import pytest
+
+from paper_2501_06480_amd import synth
+from gpu_util import TOL, f32_device, max_abs, to_device, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L", [65, 81, 112, 113, 144, 145, 176, 177, 193, 209, 225, 256])
+@pytest.mark.parametrize("N,heads,form", [(1, 1, "none"), (2, 3, "dense"), (30, 5, "labels"), (2, 50, "bf16")])
+def test_forward(oracle, L, N, heads, form):
+    import torch
+    import paper_2501_06480_amd as fwa
+    w = synth.Workload(f"f32_rows_L{L}", N, L, 32 * heads, heads, "f32", 9100 + L, 0)
+    x = synth.draw(w)
+    nW = 2
+    bias = None if form == "none" else synth.normal((heads, L, L), 9200 + L, 0.5)
+    if form == "bf16":
+        bias = synth.bf16_round(bias)[0]
+    labels = synth.rng(9300 + L).integers(0, 3, (nW, L)).astype(np.int32)
+    mask = np.where(labels[:, :, None] == labels[:, None, :], 0.0, -3.0).astype(np.float32) if form in ("dense", "labels") else None
+    q, k, v = (to_device(x, w, n) for n in ("q", "k", "v"))
+    b = f32_device(bias)
+    print(f"L={L} N={N} heads={heads} {form}", flush=True)
+    kw = {}
+    if form == "dense":
+        kw["mask"] = f32_device(mask)
+    elif form == "labels":
+        kw.update(labels=torch.from_numpy(labels).cuda(), mask_value=-3.0)
+    o = fwa.fwa_forward(q, k, v, heads, w.scale, b.bfloat16() if form == "bf16" else b, **kw)
+    torch.cuda.synchronize()
+    want = oracle.forward(x["q"], x["k"], x["v"], heads, w.scale, bias, mask)
+    assert max_abs(to_f64(o), want) <= TOL["f32"]
