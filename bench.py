@@ -45,7 +45,7 @@ PREWARM_SECONDS = 0.3           # un-timed launches in front of the warm-up: the
 
 def ensure_built():
     from paper_2501_06480_amd import binding
-    if not os.path.exists(binding.library_path()):
+    if not all(os.path.exists(p) for p in (binding.library_path(), binding.native_path())):
         from paper_2501_06480_amd import build
         build.build(verbose=False)
 

@@ -1,9 +1,11 @@
-"""ctypes binding of the C-ABI library declared in ``include/fwa.h``.
+"""Python binding of the C-ABI library declared in ``include/fwa.h``.
 
 Argument marshalling only: every step of the attention path runs in the HIP
-kernels of ``libfwa.so``.  torch supplies device memory and the stream.  There
-is no CPU fallback: when the library has not been built, or a call is made
-without a GPU tensor, an exception is raised.
+kernels of ``libfwa.so``.  torch supplies device memory and the stream.  The
+marshalling of the tensor calls is native (``csrc/torch_binding.cpp``, built as
+``_fwa_torch``); the queries and the call that allocates nothing go through
+ctypes.  There is no CPU fallback: when the libraries have not been built, or a
+call is made without a GPU tensor, an exception is raised.
 """
 from __future__ import annotations
 
@@ -42,6 +44,11 @@ class FwaError(RuntimeError):
 
 def library_path() -> str:
     return _LIB_PATH
+
+
+def native_path() -> str:
+    """The native marshalling module beside the library."""
+    return os.path.join(_HERE, "_fwa_torch.so")
 
 
 def load_library():
@@ -113,25 +120,6 @@ def _dev_ptr(t, name: str, like=None, f32: bool = False) -> Optional[int]:
     return t.data_ptr()
 
 
-def _row_ptr(t, name: str, like=None):
-    """(device pointer, row stride in elements) of an [N, L, C] tensor whose channels are
-    contiguous and whose token rows are evenly spaced, e.g. a q/k/v view of a fused
-    [N, L, 3, heads, d] projection output.  A contiguous tensor has row stride C."""
-    if not getattr(t, "is_cuda", False):
-        raise TypeError(f"{name} must be a GPU tensor (there is no CPU path)")
-    if t.dim() != 3:
-        raise ValueError(f"{name} must be [N, L, C]")
-    if like is not None and (t.shape != like.shape or t.dtype != like.dtype or t.device != like.device):
-        raise ValueError(f"{name} must match q in shape, dtype and device")
-    N, L, C = t.shape
-    if t.is_contiguous():
-        return t.data_ptr(), C
-    s0, s1, s2 = t.stride()
-    if (C > 1 and s2 != 1) or (L > 1 and s1 < C) or (N > 1 and s0 != L * s1):
-        raise ValueError(f"{name}: channels must be contiguous and token rows evenly spaced (stride {t.stride()})")
-    return t.data_ptr(), (s1 if L > 1 else (s0 if N > 1 else C))
-
-
 _torch_mod = None
 
 
@@ -198,15 +186,29 @@ def _bias_ptr(bias, heads: int, L: int):
     return _dev_ptr(bias, "bias", f32=True), FWA_F32
 
 
-def _labels_ptr(labels, mask, L: int):
-    """(device pointer, nW) of int32 region labels [nW, L]; they stand in for a dense mask."""
-    if mask is not None:
-        raise ValueError("give the mask either as a dense tensor or as labels, not both")
-    if not getattr(labels, "is_cuda", False):
-        raise TypeError("labels must be a GPU tensor (there is no CPU path)")
-    if labels.dtype != _torch().int32 or labels.dim() != 2 or labels.shape[1] != L or not labels.is_contiguous():
-        raise ValueError("labels must be a contiguous int32 tensor [nW, L]")
-    return labels.data_ptr(), int(labels.shape[0])
+_native_mod = None
+
+
+def _native():
+    """The native marshalling module, linked against the ``libfwa.so`` beside it."""
+    global _native_mod
+    if _native_mod is None:
+        load_library()
+        _torch()
+        try:
+            from . import _fwa_torch
+        except ImportError as e:
+            raise RuntimeError(f"{os.path.join(_HERE, '_fwa_torch.so')} cannot be loaded ({e}): build it with "
+                               "`python -m paper_2501_06480_amd.build`. There is no fallback path.") from e
+        _native_mod = _fwa_torch
+    return _native_mod
+
+
+def _entry(what: str, tensors, bias, labels) -> str:
+    """Name of the C entry a call went through, for the message of an error."""
+    if labels is not None or (bias is not None and bias.dtype == _torch().bfloat16):
+        return what + "_labels"
+    return what if all(t is None or t.is_contiguous() for t in tensors) else what + "_strided"
 
 
 def fwa_forward(q, k, v, heads: int, scale: float, bias=None, mask=None, out=None, stream=None, labels=None,
@@ -215,48 +217,23 @@ def fwa_forward(q, k, v, heads: int, scale: float, bias=None, mask=None, out=Non
     q, k, v (and `out`) may be row-strided views, e.g. of a fused [N, L, 3, heads, d] tensor.
     The mask is a dense [nW, L, L] fp32 tensor, or int32 region `labels` [nW, L] from which the
     kernels form M[i][j] = 0 if labels agree else `mask_value`."""
-    lib = _lib if _lib is not None else load_library()
-    N, L, C = q.shape
-    if out is None:
+    call = (_native_mod or _native()).forward
+    if stream is None:
+        o = call(q, k, v, int(heads), float(scale), bias, mask, out, None, labels, float(mask_value))
+    else:
         with _alloc_on(stream, q.device):
-            o = _torch().empty_like(q, memory_format=_torch().contiguous_format)
-    else:
-        o = out
-    nW = 0 if mask is None else int(mask.shape[0])
-    bp, bias_code = _bias_ptr(bias, heads, L)
-    if mask is not None and tuple(mask.shape) != (nW, L, L):
-        raise ValueError("mask must be [nW, L, L]")
-    if bias_code == FWA_BF16 and mask is not None:
-        raise ValueError("a bf16 bias goes with a mask given as labels (or with no mask), not with a dense mask")
-    if labels is not None or bias_code == FWA_BF16:
-        lp, nW = _labels_ptr(labels, mask, L) if labels is not None else (None, 0)
-        (qp, ld), (kp, ldk), (vp, ldv), (op, ldo) = (_row_ptr(q, "q"), _row_ptr(k, "k", q), _row_ptr(v, "v", q),
-                                                    _row_ptr(o, "out", q))
-        if not ld == ldk == ldv:
-            raise ValueError("q, k and v must share one row stride")
-        with _on_device(q.device):
-            rc = lib.fwa_forward_labels(qp, kp, vp, op, N, L, C, int(heads), float(scale), ld, ldo,
-                                        bp, bias_code, lp, float(mask_value), nW, _dtype_code(q),
-                                        _stream_handle(stream, q.device))
-        if rc != FWA_OK:
-            raise FwaError(rc, "fwa_forward_labels")
-        return o
-    tail = (bp, _dev_ptr(mask, "mask", f32=True), nW, _dtype_code(q), _stream_handle(stream, q.device))
-    if q.is_contiguous() and k.is_contiguous() and v.is_contiguous() and o.is_contiguous():
-        args = (_dev_ptr(q, "q"), _dev_ptr(k, "k", q), _dev_ptr(v, "v", q), _dev_ptr(o, "out", q), N, L, C,
-                int(heads), float(scale)) + tail
-        fn, what = lib.fwa_forward, "fwa_forward"
-    else:
-        (qp, ld), (kp, ldk), (vp, ldv), (op, ldo) = (_row_ptr(q, "q"), _row_ptr(k, "k", q), _row_ptr(v, "v", q),
-                                                    _row_ptr(o, "out", q))
-        if not ld == ldk == ldv:
-            raise ValueError("q, k and v must share one row stride")
-        args = (qp, kp, vp, op, N, L, C, int(heads), float(scale), ld, ldo) + tail
-        fn, what = lib.fwa_forward_strided, "fwa_forward_strided"
-    with _on_device(q.device):
-        rc = fn(*args)
-    if rc != FWA_OK:
-        raise FwaError(rc, what)
+            o = call(q, k, v, int(heads), float(scale), bias, mask, out, _stream_handle(stream, q.device), labels,
+                     float(mask_value))
+    if type(o) is int:
+        raise FwaError(o, _entry("fwa_forward", (q, k, v, out), bias, labels))
+    return o
+
+
+def fwa_forward_qkv(qkv, scale: float, bias=None, mask=None, labels=None, mask_value: float = -100.0):
+    """``fwa_forward`` of the three slices of a contiguous fused [N, L, 3, heads, d] tensor, read in place."""
+    o = (_native_mod or _native()).forward_qkv(qkv, float(scale), bias, mask, labels, float(mask_value))
+    if type(o) is int:
+        raise FwaError(o, _entry("fwa_forward", (qkv[:, :, 0],), bias, labels))
     return o
 
 
@@ -270,64 +247,27 @@ def fwa_backward(q, k, v, d_o, heads: int, scale: float, bias=None, mask=None, w
     q, k, v, d_o may be row-strided views; `out` = (dq, dk, dv) writes the gradients into given
     tensors, e.g. the three views of a fused [N, L, 3, heads, d] gradient buffer.  `labels` and
     `mask_value` give the mask as region labels, as in ``fwa_forward``."""
-    import torch
-    lib = load_library()
-    N, L, C = q.shape
-    with _alloc_on(stream, q.device):
-        if out is None:
-            dq, dk, dv = (torch.empty_like(q, memory_format=torch.contiguous_format) for _ in range(3))
-        else:
-            dq, dk, dv = out
-        dbias = torch.empty((heads, L, L), dtype=torch.float32, device=q.device) if want_dbias else None
-    nW = 0 if mask is None else int(mask.shape[0])
-    bp, bias_code = _bias_ptr(bias, heads, L)
-    if mask is not None and tuple(mask.shape) != (nW, L, L):
-        raise ValueError("mask must be [nW, L, L]")
-    if bias_code == FWA_BF16 and mask is not None:
-        raise ValueError("a bf16 bias goes with a mask given as labels (or with no mask), not with a dense mask")
-    need = fwa_backward_workspace_bytes(N, L, C, heads, _dtype_code(q), want_dbias)
-    # needed for dBias, and above 64 tokens for the fp32 copy the library makes of a bf16 bias
-    if workspace is None and need and (want_dbias or (bias_code == FWA_BF16 and L > 64)):
-        with _alloc_on(stream, q.device):
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    tail = (bp, _dev_ptr(mask, "mask", f32=True), nW, _dtype_code(q),
-            None if workspace is None else workspace.data_ptr(), ws_bytes, _stream_handle(stream, q.device))
-    tensors = (q, k, v, d_o, dq, dk, dv)
-    if labels is not None or bias_code == FWA_BF16:
-        lp, nW = _labels_ptr(labels, mask, L) if labels is not None else (None, 0)
-        rows = [_row_ptr(t, nm, None if nm == "q" else q) for t, nm in zip(tensors, ("q", "k", "v", "d_o", "dq", "dk", "dv"))]
-        if not rows[0][1] == rows[1][1] == rows[2][1]:
-            raise ValueError("q, k and v must share one row stride")
-        if not rows[4][1] == rows[5][1] == rows[6][1]:
-            raise ValueError("dq, dk and dv must share one row stride")
-        args = tuple(r[0] for r in rows) + (None if dbias is None else dbias.data_ptr(), N, L, C, int(heads),
-                                            float(scale), rows[0][1], rows[3][1], rows[4][1],
-                                            bp, bias_code, lp, float(mask_value), nW) + tail[3:]
-        with _on_device(q.device):
-            rc = lib.fwa_backward_labels(*args)
-        if rc != FWA_OK:
-            raise FwaError(rc, "fwa_backward_labels")
-        return dq, dk, dv, dbias
-    if all(t.is_contiguous() for t in tensors):
-        ptrs = (_dev_ptr(q, "q"), _dev_ptr(k, "k", q), _dev_ptr(v, "v", q), _dev_ptr(d_o, "d_o", q),
-                _dev_ptr(dq, "dq", q), _dev_ptr(dk, "dk", q), _dev_ptr(dv, "dv", q))
-        args = ptrs + (None if dbias is None else dbias.data_ptr(), N, L, C, int(heads), float(scale)) + tail
-        fn, what = lib.fwa_backward, "fwa_backward"
+    call = (_native_mod or _native()).backward
+    dq, dk, dv = out if out is not None else (None, None, None)
+    if stream is None:
+        r = call(q, k, v, d_o, int(heads), float(scale), bias, mask, bool(want_dbias), workspace, None, dq, dk, dv, labels,
+                 float(mask_value))
     else:
-        rows = [_row_ptr(t, nm, None if nm == "q" else q) for t, nm in zip(tensors, ("q", "k", "v", "d_o", "dq", "dk", "dv"))]
-        if not rows[0][1] == rows[1][1] == rows[2][1]:
-            raise ValueError("q, k and v must share one row stride")
-        if not rows[4][1] == rows[5][1] == rows[6][1]:
-            raise ValueError("dq, dk and dv must share one row stride")
-        args = tuple(r[0] for r in rows) + (None if dbias is None else dbias.data_ptr(), N, L, C, int(heads),
-                                            float(scale), rows[0][1], rows[3][1], rows[4][1]) + tail
-        fn, what = lib.fwa_backward_strided, "fwa_backward_strided"
-    with _on_device(q.device):
-        rc = fn(*args)
-    if rc != FWA_OK:
-        raise FwaError(rc, what)
-    return dq, dk, dv, dbias
+        with _alloc_on(stream, q.device):
+            r = call(q, k, v, d_o, int(heads), float(scale), bias, mask, bool(want_dbias), workspace,
+                     _stream_handle(stream, q.device), dq, dk, dv, labels, float(mask_value))
+    if type(r) is int:
+        raise FwaError(r, _entry("fwa_backward", (q, k, v, d_o, dq, dk, dv), bias, labels))
+    return r
+
+
+def fwa_backward_qkv(qkv, d_o, scale: float, bias=None, mask=None, want_dbias: bool = False, labels=None,
+                     mask_value: float = -100.0):
+    """(dqkv, dBias) of ``fwa_forward_qkv``: the gradients of the three slices written into one tensor like qkv."""
+    r = (_native_mod or _native()).backward_qkv(qkv, d_o, float(scale), bias, mask, bool(want_dbias), labels, float(mask_value))
+    if type(r) is int:
+        raise FwaError(r, _entry("fwa_backward", (qkv[:, :, 0], d_o), bias, labels))
+    return r
 
 
 def fwa_backward_noalloc(q, k, v, d_o, heads: int, scale: float, out, dbias=None, bias=None, mask=None, stream=None):
@@ -356,35 +296,19 @@ def fwa_backward_noalloc(q, k, v, d_o, heads: int, scale: float, out, dbias=None
     return dq, dk, dv, dbias
 
 
+def _bias_call(fn, t, k: int, stream, what: str):
+    call = getattr(_native_mod or _native(), fn)
+    r = call(t, int(k), None if stream is None else _stream_handle(stream, t.device))
+    if type(r) is int:
+        raise FwaError(r, what)
+    return r
+
+
 def fwa_bias_gather(table, k: int, stream=None):
     """[heads, (2k-1)^2] fp32 table -> [heads, k*k, k*k] fp32 bias, on the GPU."""
-    import torch
-    lib = load_library()
-    heads = int(table.shape[0])
-    if tuple(table.shape) != (heads, (2 * k - 1) ** 2):
-        raise ValueError("table must be [heads, (2k-1)^2]")
-    tp = _dev_ptr(table, "table", f32=True)
-    bias = torch.empty((heads, k * k, k * k), dtype=torch.float32, device=table.device)
-    with _on_device(table.device):
-        rc = lib.fwa_bias_gather(tp, bias.data_ptr(), heads, int(k),
-                                 _stream_handle(stream, table.device))
-    if rc != FWA_OK:
-        raise FwaError(rc, "fwa_bias_gather")
-    return bias
+    return _bias_call("bias_gather", table, k, stream, "fwa_bias_gather")
 
 
 def fwa_bias_scatter(dbias, k: int, stream=None):
     """[heads, k*k, k*k] fp32 bias gradient -> [heads, (2k-1)^2] table gradient."""
-    import torch
-    lib = load_library()
-    heads = int(dbias.shape[0])
-    if tuple(dbias.shape) != (heads, k * k, k * k):
-        raise ValueError("dbias must be [heads, k*k, k*k]")
-    dp = _dev_ptr(dbias, "dbias", f32=True)
-    dtable = torch.empty((heads, (2 * k - 1) ** 2), dtype=torch.float32, device=dbias.device)
-    with _on_device(dbias.device):
-        rc = lib.fwa_bias_scatter(dp, dtable.data_ptr(), heads, int(k),
-                                  _stream_handle(stream, dbias.device))
-    if rc != FWA_OK:
-        raise FwaError(rc, "fwa_bias_scatter")
-    return dtable
+    return _bias_call("bias_scatter", dbias, k, stream, "fwa_bias_scatter")

@@ -1,4 +1,5 @@
-"""Build libfwa.so in-tree with hipcc for gfx950: ``python -m paper_2501_06480_amd.build``."""
+"""Build libfwa.so (hipcc, gfx950) and the torch marshalling module _fwa_torch.so (g++) in-tree:
+``python -m paper_2501_06480_amd.build``."""
 from __future__ import annotations
 
 import os
@@ -9,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libfwa.so")
+TORCH_OUT = os.path.join(HERE, "_fwa_torch.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = ["fwa_api.hip", "fwa_forward.hip", "fwa_forward_staged.hip", "fwa_forward_wide.hip", "fwa_f32_tile.hip", "fwa_backward.hip",
            "fwa_backward_coop.hip", "fwa_backward_large.hip", "fwa_backward_wide.hip", "fwa_bias.hip"]
@@ -24,6 +26,25 @@ def _hipcc() -> str:
         if cand and (os.path.sep not in cand or os.path.exists(cand)):
             return cand
     return "hipcc"
+
+
+def build_torch_binding(verbose: bool = True) -> str:
+    """Host code only: argument marshalling between torch tensors and the C ABI."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(_hipcc()))) if os.path.sep in _hipcc() else "/opt/rocm"
+    includes = [*cpp_extension.include_paths(), os.path.join(rocm, "include"), "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(x for i in includes for x in ("-isystem", i)), os.path.join(CSRC, "torch_binding.cpp"), "-o", TORCH_OUT,
+           "-L" + libs, "-ltorch", "-ltorch_cpu", "-ltorch_python", "-lc10", "-lc10_hip",
+           "-L" + HERE, "-l:libfwa.so", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return TORCH_OUT
 
 
 def build(verbose: bool = True, jobs: int = 6) -> str:
@@ -49,6 +70,7 @@ def build(verbose: bool = True, jobs: int = 6) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_torch_binding(verbose)
     return OUT
 
 
