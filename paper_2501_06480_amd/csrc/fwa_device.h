@@ -105,6 +105,9 @@ __device__ __forceinline__ void load_to_lds(const void* base, uint32_t bytes, ui
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved) : "s"(lds_off), "v"(voffset), "s"(r) : "memory");
 }
+// all but the N youngest global loads and stores of this wave are complete
+template <int N>
+__device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 // every global load and store this wave has issued is complete
 __device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

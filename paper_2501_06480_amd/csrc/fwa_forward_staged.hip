@@ -174,14 +174,19 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock * QS) fwd_bf16_staged_kern
 // (bias[h] + mask[bw % nW]) * log2e ONCE, straight into the registers of the score layout, and
 // the per-window work is that of the bias-free kernel plus one fused multiply-add per score.
 // The slab of the next window is requested before the current one is computed.
-// PW: the mask comes as labels whose period does not divide G; the bias alone stays in registers,
-// the labels of a window travel with its slab and the mask is formed per score (see
-// AddendRegsLabels).
-template <int NB, bool PW>
+// PW: the mask's period does not divide G; the bias alone stays in registers.  PW = 1, labels: those of
+// a window travel with its slab and the mask is formed per score (see AddendRegsLabels).  PW = 2, a
+// dense mask: the tile of the next window is fetched into a second LDS buffer while this one is computed
+// (AddendRegsDense): 1740 windows of 49 tokens, 8 heads, mask of 870 windows, 50 -> 40 us against reading bias and
+// mask per window.
+template <int NB, int PW>
 __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kernel(FwdArgs p, StagedGeom gm, uint32_t G) {
     constexpr int NB2 = (NB + 1) / 2;
     constexpr int ROWS = 16 * NB;
-    extern __shared__ __attribute__((aligned(16))) uint4 lds[];  // [3][ROWS][stride]: K, V, Q (then O); then (PW) [ROWS] labels
+    // (PW == 2) two mask tiles; [3][ROWS][stride]: K, V, Q (then O); then (PW == 1) [ROWS] labels
+    extern __shared__ __attribute__((aligned(16))) uint4 lds_all[];
+    const uint32_t mask_units = PW == 2 ? mask_tile_bytes((uint32_t)p.L) / 16u : 0u;
+    uint4* const lds = lds_all + 2u * mask_units;
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const uint32_t hl = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -220,7 +225,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
             sq[t] = __builtin_amdgcn_raw_buffer_load_b128(rq, goff + 16 * t * row_bytes, 0, 0);
             sv[t] = __builtin_amdgcn_raw_buffer_load_b128(rv, goff + 16 * t * row_bytes, 0, 0);
         }
-        if (PW && hl == 0)  // one wave fetches them
+        if (PW == 1 && hl == 0)  // one wave fetches them
             slab_labels = load_i32x4(make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, (uint32_t)L * 4u), (uint32_t)tid * 16u);
     };
     auto park = [&]() {
@@ -230,8 +235,12 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
             lq[loff + 16 * t * stride] = __builtin_bit_cast(uint4, sq[t]);
             lv[loff + 16 * t * stride] = __builtin_bit_cast(uint4, sv[t]);
         }
-        if (PW && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab)[tid] = slab_labels;
+        if (PW == 1 && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab)[tid] = slab_labels;
     };
+    auto request_mask = [&](uint32_t w, uint32_t buf) {
+        request_mask_tile(p, w, lds_offset(lds_all) + buf * mask_units * 16u, hl, hpb, (uint32_t)lane);
+    };
+    if (PW == 2 && bw < (uint32_t)p.N) request_mask(bw, 0u);
     if (bw < (uint32_t)p.N) request(bw);  // in flight while the additive term is fetched
     // the additive term of this wave's head and this workgroup's mask tile, in score layout
     f32x4 add[NB][NB];
@@ -247,12 +256,13 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
     }
     const float mv = p.mask_value * kLog2e;
 
-    if (bw < (uint32_t)p.N) park();
+    if (bw < (uint32_t)p.N) park();  // waits for the slab, hence also for the mask tile requested before it
 
     // The next slab is parked at the END of an iteration: there the loads it waits for are always
     // older than this iteration's output stores, so the wait counts the stores out.  At the top of
     // the loop the compiler must assume the worse of the two ways in and would wait for the stores.
-    for (uint32_t w = bw; w < (uint32_t)p.N; w += G) {
+    uint32_t mbuf = 0u;
+    for (uint32_t w = bw; w < (uint32_t)p.N; w += G, mbuf ^= 1u) {
         const bool has_next = w + G < (uint32_t)p.N;
         __syncthreads();
         bf16x8 kop[NB], qop[NB];
@@ -274,7 +284,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
             }
         int tq[NB];  // PW: labels of this lane's query rows
 #pragma unroll
-        for (int b = 0; b < NB; ++b) tq[b] = PW ? llab[16 * b + n] : 0;
+        for (int b = 0; b < NB; ++b) tq[b] = PW == 1 ? llab[16 * b + n] : 0;
+        if (PW == 2 && has_next) request_mask(w + G, mbuf ^ 1u);  // in front of the slab: it has landed when that is parked
         if (has_next) request(w + G);  // in flight while this window is computed
 
 #pragma unroll
@@ -286,7 +297,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
                 s[jb] = mfma_bf16(kop[jb], qop[qb], zero);
             }
             float inv;
-            if (PW) {
+            if (PW == 2) {  // rows beyond L stay inside the tile (their results are dropped)
+                const int i = 16 * qb + n < L ? 16 * qb + n : L - 1;
+                const AddendRegsDense<NB> addend = {add[qb], reinterpret_cast<const float*>(lds_all + mbuf * mask_units) + i * L + 4 * g};
+                inv = softmax_block<NB, true>(s, sl2, addend, L, g);
+            } else if (PW == 1) {
                 const AddendRegsLabels<NB> addend = {add[qb], llab, tq[qb], mv, g};
                 inv = softmax_block<NB, true>(s, sl2, addend, L, g);
             } else {
@@ -472,11 +487,12 @@ constexpr int rowpersist_waves(int nb) { return nb <= 12 ? nb : (nb + 1) / 2; }
 // lines when HPB is even or the whole token row when HPB is the head count.  Used with HPB > 1
 // for L <= 64, where W <= 4.
 //
-// PW ("per window"): the mask comes as labels and its period does not divide G, so that a workgroup
-// meets a different mask tile at every window.  Then only the bias stays in registers; the labels
-// of a window travel with its slabs (requested two windows ahead, parked in LDS beside them) and
-// the mask is formed per score.
-template <int NB, int HPB, bool PW>
+// PW ("per window"): the mask's period does not divide G, so that a workgroup meets a different mask
+// tile at every window.  Then only the bias stays in registers.  PW = 1, labels: those of a window
+// travel with its slabs (requested two windows ahead, parked in LDS beside them) and the mask is formed
+// per score.  PW = 2 (HPB > 1), a dense mask: as in the kernel above (2784 windows of 49 tokens, 3 heads, mask of 1392
+// windows: 33.5 -> 25.9 us; 22 as labels).
+template <int NB, int HPB, int PW>
 __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowpersist_kernel(FwdArgs p, RowPersistGeom gm) {
     constexpr int W = rowpersist_waves(NB);
     constexpr int NB2 = (NB + 1) / 2;
@@ -484,7 +500,10 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
     constexpr int PASSES = (ROWS + 16 * W - 1) / (16 * W);  // the workgroup moves 16 W slab rows per pass
     constexpr uint32_t TPR = 4 * HPB;                        // threads per slab row, 16 bytes each
     constexpr uint32_t STRIDE = TPR + 1;                     // LDS row: HPB * 64 bytes of data + 16 of padding
-    extern __shared__ __attribute__((aligned(16))) uint4 lds[];  // [2 buffers][K, V][ROWS][STRIDE], then (PW) [2][ROWS] labels
+    // (PW == 2) two mask tiles; [2 buffers][K, V][ROWS][STRIDE], then (PW == 1) [2][ROWS] labels
+    extern __shared__ __attribute__((aligned(16))) uint4 lds_all[];
+    const uint32_t mask_units = PW == 2 ? mask_tile_bytes((uint32_t)p.L) / 16u : 0u;
+    uint4* const lds = lds_all + 2u * mask_units;
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -532,7 +551,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
         }
         if (active)
             d.q = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.q + tile, tile_bytes), off_row, 0, 0);
-        if (PW && wave == 0)  // one wave fetches them; tokens beyond L lie outside the descriptor: label 0
+        if (PW == 1 && wave == 0)  // one wave fetches them; tokens beyond L lie outside the descriptor: label 0
             d.lab = load_i32x4(make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, (uint32_t)L * 4u), (uint32_t)tid * 16u);
     };
     auto park = [&](const Slab& d, uint32_t b) {
@@ -546,10 +565,14 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
                 dv[row * STRIDE + scol] = __builtin_bit_cast(uint4, d.v[t]);
             }
         }
-        if (PW && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab + b * ROWS)[tid] = d.lab;
+        if (PW == 1 && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab + b * ROWS)[tid] = d.lab;
     };
     // The windows of this workgroup: w0, w0 + step, ... below `end`
     uint32_t w0 = bw, step = gm.G, end = (uint32_t)p.N;
+    auto request_mask = [&](uint32_t w, uint32_t b) {
+        request_mask_tile(p, w, lds_offset(lds_all) + b * mask_units * 16u, wave, (uint32_t)(HPB * W), (uint32_t)lane);
+    };
+    if (PW == 2 && w0 < end) request_mask(w0, 0u);  // in front of the first slab: it has landed when that is parked
     if (w0 < end) request(sa, w0);  // in flight while the additive term is fetched
     if (w0 + step < end) request(sb, w0 + step);
     if (D3 && w0 + 2 * step < end) request(sc, w0 + 2 * step);
@@ -584,6 +607,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
         uint4* const lv = lk + ROWS * STRIDE;
         const bf16x8 qop = as_bf16x8(cur.q);
         __syncthreads();
+        if (PW == 2 && has_next) request_mask(w + step, buf ^ 1u);
         if (w + AHEAD * step < end) request(cur, w + AHEAD * step);
         if (active) {
             const uint4* const lkh = lk + n * STRIDE + 4 * hl + g;  // K[16 jb + n][8g..] of head hl at lkh[16 jb * STRIDE]
@@ -596,7 +620,11 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
                 s[jb] = mfma_bf16(__builtin_bit_cast(bf16x8, lkh[16 * jb * STRIDE]), qop, zero);  // S[16 qb + n][16 jb + 4g + r]
             }
             float mul, sum = 0.f, mb;
-            if (PW) {
+            if constexpr (PW == 2) {  // rows beyond L stay inside the tile (their results are dropped)
+                const int i = 16 * qb + n < L ? 16 * qb + n : L - 1;
+                const AddendRegsDense<NB> addend = {add, reinterpret_cast<const float*>(lds_all + buf * mask_units) + i * L + 4 * g};
+                mb = softmax_scale_max<NB, true>(s, sl2, addend, L, g, mul);
+            } else if (PW == 1) {
                 const int* const lab = llab + buf * ROWS;
                 const AddendRegsLabels<NB> addend = {add, lab, lab[16 * qb + n], mv, g};
                 mb = softmax_scale_max<NB, true>(s, sl2, addend, L, g, mul);
@@ -651,6 +679,13 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
             __builtin_amdgcn_raw_buffer_store_b128(rows, ro, (uint32_t)(16 * qb + (lane >> 2)) * row_out + 16u * (uint32_t)(lane & 3), 0, 0);
             }
         }
+        if (PW == 2 && has_next) {
+            // the next mask tile has landed: of this wave's memory operations only the slab loads requested behind it
+            // and the two output stores are younger
+            static_assert(PW != 2 || HPB > 1, "every wave stores twice");
+            if (w + AHEAD * step < end) wait_vmem<2 * PASSES + 1 + 2>();
+            else wait_vmem<2>();
+        }
         if (has_next) park(nxt, buf ^ 1u);
     };
     if (D3) {
@@ -682,7 +717,7 @@ constexpr size_t rowpersist_lds() {
 }
 
 // Workgroups of the one-head variant a CU holds at once (registers and LDS decide), asked once per kernel.
-template <int NB, bool PW>
+template <int NB, int PW>
 int rowpersist_per_cu() {
     static std::atomic<int> once{0};
     int per_cu = once.load(std::memory_order_relaxed);
@@ -705,7 +740,7 @@ template <int NB>
 long long rowpersist_slots(const FwdArgs& a, bool& pw) {
     const long long parts = NB <= 12 ? 1 : 2;
     const long long nW = mask_period(a);
-    long long most = (long long)cu_count() * rowpersist_per_cu<NB, false>() / ((long long)a.heads * parts);
+    long long most = (long long)cu_count() * rowpersist_per_cu<NB, 0>() / ((long long)a.heads * parts);
     long long G = most / nW * nW;
     if (G > a.N / 2) G = (a.N / 2) / nW * nW;
     pw = false;
@@ -714,12 +749,12 @@ long long rowpersist_slots(const FwdArgs& a, bool& pw) {
     // all the same and form the mask of each window from its labels
     if (a.labels == nullptr) return 0;
     pw = true;
-    most = (long long)cu_count() * rowpersist_per_cu<NB, true>() / ((long long)a.heads * parts);
+    most = (long long)cu_count() * rowpersist_per_cu<NB, 1>() / ((long long)a.heads * parts);
     G = most < a.N / 2 ? most : a.N / 2;
     return G > 0 ? G : 0;
 }
 
-template <int NB, int HPB, bool PW>
+template <int NB, int HPB, int PW>
 hipError_t launch_rowpersist_pw(const FwdArgs& a, long long G, hipStream_t st) {
     RowPersistGeom gm;
     gm.groups = (uint32_t)(a.heads / HPB);
@@ -728,7 +763,7 @@ hipError_t launch_rowpersist_pw(const FwdArgs& a, long long G, hipStream_t st) {
     const unsigned grid = gm.G * gm.groups * gm.parts, block = 64u * (unsigned)(HPB * rowpersist_waves(NB));
     gm.xcd_q = grid / 8u;
     gm.xcd_r = grid % 8u;
-    const size_t lds = rowpersist_lds<NB, HPB>();
+    const size_t lds = rowpersist_lds<NB, HPB>() + (PW == 2 ? 2 * mask_tile_bytes((uint32_t)a.L) : 0);
     {
         const hipError_t e = allow_lds(reinterpret_cast<const void*>(&fwd_bf16_rowpersist_kernel<NB, HPB, PW>), lds);
         if (e != hipSuccess) return e;
@@ -737,10 +772,13 @@ hipError_t launch_rowpersist_pw(const FwdArgs& a, long long G, hipStream_t st) {
     return hipGetLastError();
 }
 
-// pw: the mask comes as labels whose period does not divide G (see the kernel)
+// pw: the mask's period does not divide G (see the kernel)
 template <int NB, int HPB>
 hipError_t launch_rowpersist_hpb(const FwdArgs& a, long long G, hipStream_t st, bool pw = false) {
-    return pw ? launch_rowpersist_pw<NB, HPB, true>(a, G, st) : launch_rowpersist_pw<NB, HPB, false>(a, G, st);
+    if constexpr (HPB > 1) {
+        if (pw && a.mask) return launch_rowpersist_pw<NB, HPB, 2>(a, G, st);
+    }
+    return pw ? launch_rowpersist_pw<NB, HPB, 1>(a, G, st) : launch_rowpersist_pw<NB, HPB, 0>(a, G, st);
 }
 
 template <int NB, bool BM, int QW>
@@ -803,6 +841,9 @@ hipError_t launch_staged_nb(const FwdArgs& a, int hpb, hipStream_t st) {
         // sees the same mask tile, about 4 workgroups per CU (measured best of 2..8), at least 2
         // windows per workgroup, and enough workgroups to cover the chip; else one window each.
         const long long nW = mask_period(a);
+        // A dense mask per window as a tile in LDS: not where its rows fall on the same banks (a row length that is a
+        // multiple of 32 words: 8 x 8 windows, 3 heads, 33 us against 28 with bias and mask read per window)
+        const bool dense_tiles = a.mask != nullptr && a.L % 32 != 0;
         // A small call with an additive term whose workgroups of four waves per head would not all be
         // resident at once (Swin-T stage 4: 24 heads x 128 windows): groups of 3 (or 2) heads in the
         // row-persistent kernel instead, one workgroup per CU walking a few windows with the term in
@@ -825,8 +866,8 @@ hipError_t launch_staged_nb(const FwdArgs& a, int hpb, hipStream_t st) {
             long long G1 = cus / nW * nW;
             if (G1 > a.N / 2) G1 = (a.N / 2) / nW * nW;
             bool pw = false;
-            if (!(G1 >= nW && G1 >= cus / 2) && a.labels != nullptr && a.N >= cus) {
-                // no multiple of the mask period fits: per-window masks from the labels
+            if (!(G1 >= nW && G1 >= cus / 2) && (a.labels || dense_tiles) && a.N >= cus) {
+                // no multiple of the mask period fits: per-window masks
                 G1 = a.N / 2 < cus ? a.N / 2 : cus;
                 pw = true;
             }
@@ -847,15 +888,25 @@ hipError_t launch_staged_nb(const FwdArgs& a, int hpb, hipStream_t st) {
         long long G = most / nW * nW;
         if (G > a.N / 2) G = (a.N / 2) / nW * nW;
         if (!few_tiles && G >= nW && G > 0 && G * groups >= cu_count()) {
-            hipLaunchKernelGGL((fwd_bf16_persistent_kernel<NB, false>), dim3((unsigned)(G * groups)), dim3(block), lds, st,
+            hipLaunchKernelGGL((fwd_bf16_persistent_kernel<NB, 0>), dim3((unsigned)(G * groups)), dim3(block), lds, st,
                                a, gm, (uint32_t)G);
             return hipGetLastError();
         }
         // no multiple of the mask period fits: with the mask as labels, per-window masks from the labels
         G = most < a.N / 2 ? most : a.N / 2;
         if (!few_tiles && a.labels != nullptr && G * groups >= cu_count()) {
-            hipLaunchKernelGGL((fwd_bf16_persistent_kernel<NB, true>), dim3((unsigned)(G * groups)), dim3(block),
+            hipLaunchKernelGGL((fwd_bf16_persistent_kernel<NB, 1>), dim3((unsigned)(G * groups)), dim3(block),
                                lds + (size_t)16 * NB * 4, st, a, gm, (uint32_t)G);
+            return hipGetLastError();
+        }
+        // the same with a dense mask, while the two tiles leave room for two workgroups per CU; four heads share a
+        // tile then (with two, and twice the tiles per CU, it is slower: 6 heads 35 us against 31)
+        const size_t lds_dense = lds + 2 * mask_tile_bytes((uint32_t)a.L);
+        if (!few_tiles && dense_tiles && hpb == 4 && G * groups >= cu_count() && lds_dense <= 80 * 1024) {
+            const hipError_t e = allow_lds(reinterpret_cast<const void*>(&fwd_bf16_persistent_kernel<NB, 2>), lds_dense);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((fwd_bf16_persistent_kernel<NB, 2>), dim3((unsigned)(G * groups)), dim3(block), lds_dense, st, a, gm,
+                               (uint32_t)G);
             return hipGetLastError();
         }
         if (few_tiles)

@@ -69,3 +69,44 @@ SMALL = [
 @pytest.mark.parametrize("name,L,heads,N,nW,use_bias,dbias", SMALL, ids=[c[0] for c in SMALL])
 def test_small_window_backward_long_periods(oracle, name, L, heads, N, nW, use_bias, dbias):
     test_large_window_backward(oracle, name, L, heads, N, nW, use_bias, dbias)
+
+
+# The forward for windows of up to 64 tokens with such a period: the dense tile of every window in a second LDS buffer,
+# with all heads of a window in one workgroup (2, 3 heads) and with groups of 4 heads; beside them the calls next to the
+# rule that read the mask per window (groups of 2 heads, row lengths that are multiples of 32 words, tiles that leave no
+# room for two workgroups).  An odd number of windows per workgroup, and fewer windows than workgroups after the first
+# round, end the walk at every stage of its prefetches.
+# name, L, heads, N, nW, bias
+FORWARD = [
+    ("L16_pairs", 16, 2, 900, 300, True),
+    ("L17", 17, 3, 600, 300, False),
+    ("L33", 33, 3, 300, 300, True),
+    ("L49", 49, 3, 1390, 695, True),
+    ("L64", 64, 3, 600, 300, True),
+    ("L49_groups_of_2", 49, 6, 1050, 350, True),
+    ("L49_groups_of_4", 49, 8, 600, 300, True),
+    ("L32_groups_of_4", 32, 12, 540, 270, False),
+    ("L55_groups_of_4", 55, 8, 600, 300, True),
+    ("L56_groups_of_4", 56, 8, 600, 300, True),
+]
+
+
+@pytest.mark.parametrize("name,L,heads,N,nW,use_bias", FORWARD, ids=[c[0] for c in FORWARD])
+def test_small_window_forward_long_periods(oracle, name, L, heads, N, nW, use_bias):
+    import torch
+    import paper_2501_06480_amd as fwa
+    from gpu_util import check_forward_arithmetic_bound
+    w = synth.Workload("fforms_" + name, N, L, 32 * heads, heads, "bf16", 8500 + L, 0)
+    x = synth.draw(w)
+    bias = synth.normal((heads, L, L), 8600 + L, 0.5) if use_bias else None
+    labels = synth.rng(8700 + L).integers(0, 3, (nW, L)).astype(np.int32)
+    mask = np.where(labels[:, :, None] == labels[:, None, :], 0.0, -3.0).astype(np.float32)
+    want = oracle.forward(x["q"], x["k"], x["v"], heads, w.scale, bias, mask)
+    spread = oracle.forward(x["q"], x["k"], np.abs(x["v"]), heads, w.scale, bias, mask)
+    q, k, v = (to_device(x, w, n) for n in ("q", "k", "v"))
+    for form in ("dense", "labels"):
+        print(f"{name} {form}: L={L} heads={heads} N={N} nW={nW} bias={use_bias}", flush=True)
+        kw = {"mask": f32_device(mask)} if form == "dense" else {"labels": torch.from_numpy(labels).cuda(), "mask_value": -3.0}
+        o = fwa.fwa_forward(q, k, v, heads, w.scale, f32_device(bias), **kw)
+        torch.cuda.synchronize()
+        check_forward_arithmetic_bound(to_f64(o), want, spread, f"{name} {form}")
