@@ -184,9 +184,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
     constexpr int NB2 = (NB + 1) / 2;
     constexpr int ROWS = 16 * NB;
     // (PW == 2) two mask tiles; [3][ROWS][stride]: K, V, Q (then O); then (PW == 1) [ROWS] labels
-    extern __shared__ __attribute__((aligned(16))) uint4 lds_all[];
+    extern __shared__ __attribute__((aligned(16))) uint4 lds[];
     const uint32_t mask_units = PW == 2 ? mask_tile_bytes((uint32_t)p.L) / 16u : 0u;
-    uint4* const lds = lds_all + 2u * mask_units;
+    const uint32_t tiles = 2u * mask_units;  // the slabs lie behind the mask tiles
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const uint32_t hl = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -205,10 +205,10 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
     const uint32_t goff = rip * row_bytes + col * 16u;
     const uint32_t goff_o = rip * row_out + col * 16u;
     const uint32_t loff = rip * stride + col;
-    uint4* const lk = lds;
-    uint4* const lv = lds + ROWS * stride;
-    uint4* const lq = lds + 2 * ROWS * stride;
-    int* const llab = reinterpret_cast<int*>(lds + 3 * ROWS * stride);
+    uint4* const lk = lds + tiles;
+    uint4* const lv = lds + tiles + ROWS * stride;
+    uint4* const lq = lds + tiles + 2 * ROWS * stride;
+    int* const llab = reinterpret_cast<int*>(lds + tiles + 3 * ROWS * stride);
     const uint16_t* const lvh = reinterpret_cast<const uint16_t*>(lv) + 32 * hl +
                                 (4 * g + (n >> 2)) * (stride * 8u) + 4 * (n & 3);
 
@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
         if (PW == 1 && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab)[tid] = slab_labels;
     };
     auto request_mask = [&](uint32_t w, uint32_t buf) {
-        request_mask_tile(p, w, lds_offset(lds_all) + buf * mask_units * 16u, hl, hpb, (uint32_t)lane);
+        request_mask_tile(p, w, lds_offset(lds) + buf * mask_units * 16u, hl, hpb, (uint32_t)lane);
     };
     if (PW == 2 && bw < (uint32_t)p.N) request_mask(bw, 0u);
     if (bw < (uint32_t)p.N) request(bw);  // in flight while the additive term is fetched
@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
 #pragma unroll
         for (int b = 0; b < NB; ++b) rows0[b] = 16u * b;
         // through the slab area, which nothing has been parked in yet
-        fill_rows_staged<NB, NB>(add, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds) + hl * rows_fill_bytes<NB>(), lane);
+        fill_rows_staged<NB, NB>(add, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds + tiles) + hl * rows_fill_bytes<NB>(), lane);
         __syncthreads();
     }
     const float mv = p.mask_value * kLog2e;
@@ -299,7 +299,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
             float inv;
             if (PW == 2) {  // rows beyond L stay inside the tile (their results are dropped)
                 const int i = 16 * qb + n < L ? 16 * qb + n : L - 1;
-                const AddendRegsDense<NB> addend = {add[qb], reinterpret_cast<const float*>(lds_all + mbuf * mask_units) + i * L + 4 * g};
+                const AddendRegsDense<NB> addend = {add[qb], reinterpret_cast<const float*>(lds + mbuf * mask_units) + i * L + 4 * g};
                 inv = softmax_block<NB, true>(s, sl2, addend, L, g);
             } else if (PW == 1) {
                 const AddendRegsLabels<NB> addend = {add[qb], llab, tq[qb], mv, g};
@@ -501,15 +501,15 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
     constexpr uint32_t TPR = 4 * HPB;                        // threads per slab row, 16 bytes each
     constexpr uint32_t STRIDE = TPR + 1;                     // LDS row: HPB * 64 bytes of data + 16 of padding
     // (PW == 2) two mask tiles; [2 buffers][K, V][ROWS][STRIDE], then (PW == 1) [2][ROWS] labels
-    extern __shared__ __attribute__((aligned(16))) uint4 lds_all[];
+    extern __shared__ __attribute__((aligned(16))) uint4 lds[];
     const uint32_t mask_units = PW == 2 ? mask_tile_bytes((uint32_t)p.L) / 16u : 0u;
-    uint4* const lds = lds_all + 2u * mask_units;
+    const uint32_t tiles = 2u * mask_units;  // the slabs lie behind the mask tiles
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t hl = wave / W, wq = wave % W;  // head inside the workgroup, query block inside the part
-    int* const llab = reinterpret_cast<int*>(lds + 2 * (2 * ROWS * STRIDE));
-    uint4* const oscratch = lds + 2 * (2 * ROWS * STRIDE) + (2 * ROWS) / 4;  // behind the labels: 1 KB per wave
+    int* const llab = reinterpret_cast<int*>(lds + tiles + 2 * (2 * ROWS * STRIDE));
+    uint4* const oscratch = lds + tiles + 2 * (2 * ROWS * STRIDE) + (2 * ROWS) / 4;  // behind the labels: 1 KB per wave
     const uint32_t lb = xcd_logical_block(blockIdx.x, gm.xcd_q, gm.xcd_r);
     const uint32_t part = lb % gm.parts, bh = lb / gm.parts;
     const uint32_t grp = bh % gm.groups, bw = bh / gm.groups;
@@ -555,7 +555,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
             d.lab = load_i32x4(make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, (uint32_t)L * 4u), (uint32_t)tid * 16u);
     };
     auto park = [&](const Slab& d, uint32_t b) {
-        uint4* const dk = lds + b * (2 * ROWS * STRIDE);
+        uint4* const dk = lds + tiles + b * (2 * ROWS * STRIDE);
         uint4* const dv = dk + ROWS * STRIDE;
 #pragma unroll
         for (int t = 0; t < PASSES; ++t) {
@@ -570,7 +570,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
     // The windows of this workgroup: w0, w0 + step, ... below `end`
     uint32_t w0 = bw, step = gm.G, end = (uint32_t)p.N;
     auto request_mask = [&](uint32_t w, uint32_t b) {
-        request_mask_tile(p, w, lds_offset(lds_all) + b * mask_units * 16u, wave, (uint32_t)(HPB * W), (uint32_t)lane);
+        request_mask_tile(p, w, lds_offset(lds) + b * mask_units * 16u, wave, (uint32_t)(HPB * W), (uint32_t)lane);
     };
     if (PW == 2 && w0 < end) request_mask(w0, 0u);  // in front of the first slab: it has landed when that is parked
     if (w0 < end) request(sa, w0);  // in flight while the additive term is fetched
@@ -585,7 +585,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
             static_assert(HPB * W * rows_fill_bytes<NB>() <= 2 * 2 * ROWS * STRIDE * 16 + 2 * ROWS * 4, "the slab area holds the waves' stretches");
             f32x4 one[1][NB];
             const uint32_t rows0[1] = {(uint32_t)(16 * qb)};
-            fill_rows_staged<1, NB>(one, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds) + wave * rows_fill_bytes<NB>(), lane);
+            fill_rows_staged<1, NB>(one, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds + tiles) + wave * rows_fill_bytes<NB>(), lane);
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb) add[jb] = one[0][jb];
             __syncthreads();
@@ -603,11 +603,13 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
     // in front of it counts the stores and the younger loads out instead of waiting for them.
     auto window = [&](uint32_t w, Slab& cur, const Slab& nxt, uint32_t buf) {
         const bool has_next = w + step < end;
-        uint4* const lk = lds + buf * (2 * ROWS * STRIDE);
+        uint4* const lk = lds + tiles + buf * (2 * ROWS * STRIDE);
         uint4* const lv = lk + ROWS * STRIDE;
         const bf16x8 qop = as_bf16x8(cur.q);
         __syncthreads();
-        if (PW == 2 && has_next) request_mask(w + step, buf ^ 1u);
+        if constexpr (PW == 2) {
+            if (has_next) request_mask(w + step, buf ^ 1u);
+        }
         if (w + AHEAD * step < end) request(cur, w + AHEAD * step);
         if (active) {
             const uint4* const lkh = lk + n * STRIDE + 4 * hl + g;  // K[16 jb + n][8g..] of head hl at lkh[16 jb * STRIDE]
@@ -622,7 +624,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
             float mul, sum = 0.f, mb;
             if constexpr (PW == 2) {  // rows beyond L stay inside the tile (their results are dropped)
                 const int i = 16 * qb + n < L ? 16 * qb + n : L - 1;
-                const AddendRegsDense<NB> addend = {add, reinterpret_cast<const float*>(lds_all + buf * mask_units) + i * L + 4 * g};
+                const AddendRegsDense<NB> addend = {add, reinterpret_cast<const float*>(lds + buf * mask_units) + i * L + 4 * g};
                 mb = softmax_scale_max<NB, true>(s, sl2, addend, L, g, mul);
             } else if (PW == 1) {
                 const int* const lab = llab + buf * ROWS;
@@ -679,12 +681,12 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
             __builtin_amdgcn_raw_buffer_store_b128(rows, ro, (uint32_t)(16 * qb + (lane >> 2)) * row_out + 16u * (uint32_t)(lane & 3), 0, 0);
             }
         }
-        if (PW == 2 && has_next) {
+        if constexpr (PW == 2) {
             // the next mask tile has landed: of this wave's memory operations only the slab loads requested behind it
             // and the two output stores are younger
-            static_assert(PW != 2 || HPB > 1, "every wave stores twice");
+            static_assert(HPB > 1, "every wave stores twice");
             if (w + AHEAD * step < end) wait_vmem<2 * PASSES + 1 + 2>();
-            else wait_vmem<2>();
+            else if (has_next) wait_vmem<2>();
         }
         if (has_next) park(nxt, buf ^ 1u);
     };
