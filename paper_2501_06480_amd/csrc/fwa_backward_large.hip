@@ -777,6 +777,8 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
 }
 
 // ------------------------------------------------------------------ launches
+}  // namespace
+
 // Workgroups of `fn` one CU holds (LDS and registers decide), asked once per kernel; threads racing
 // through the first call ask twice and store the same figure.
 hipError_t workgroups_per_cu(const void* fn, unsigned block, size_t lds, std::atomic<int>& once, int& per_cu) {
@@ -792,6 +794,8 @@ hipError_t workgroups_per_cu(const void* fn, unsigned block, size_t lds, std::at
     }
     return hipSuccess;
 }
+
+namespace {
 
 LargeGeom large_geom(const BwdArgs& a, int parts, long long G, unsigned& grid) {
     LargeGeom gm;
@@ -857,42 +861,56 @@ hipError_t launch_rows_stream(const BwdArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// dK, dV and, with DB, the dBias partial sums (`slots` receives their number per head) and their reduction
+// window slots of the keys kernel (0: none fits the period)
 template <int NB, int TERM, bool DB>
-hipError_t launch_keys_db(const BwdArgs& a, long long period, hipStream_t st, bool& fits) {
-    const void* fn = reinterpret_cast<const void*>(&bwd_bf16_keys_kernel<NB, TERM, DB>);
-    constexpr unsigned block = 64u * keys_waves(NB);
+hipError_t keys_slots(const BwdArgs& a, long long period, bool dense, long long& G) {
     static std::atomic<int> once{0};
     int per_cu = 1;
-    const hipError_t e = workgroups_per_cu(fn, block, keys_lds<NB>(), once, per_cu);
-    if (e != hipSuccess) return e;
+    const hipError_t e = workgroups_per_cu(reinterpret_cast<const void*>(&bwd_bf16_keys_kernel<NB, TERM, DB>), 64u * keys_waves(NB), keys_lds<NB>(), once, per_cu);
     const long long resident = (long long)cu_count() * per_cu / ((long long)a.heads * keys_parts(NB));
     const long long most = DB ? a.slots : a.N;  // the workspace holds a.slots partial sums per head
-    const long long G = walk_slots(resident, most, a.N, period, a.mask != nullptr);
+    G = walk_slots(resident, most, a.N, period, dense);
+    return e;
+}
+// dK, dV and, with DB, the dBias partial sums and their reduction
+template <int NB, int TERM, bool DB>
+hipError_t launch_keys(const BwdArgs& a, long long period, hipStream_t st, bool& fits) {
+    long long G = 0;
+    const hipError_t e = keys_slots<NB, TERM, DB>(a, period, a.mask != nullptr, G);
     fits = G > 0;
-    if (!fits) return hipSuccess;
+    if (e != hipSuccess || !fits) return e;
     unsigned grid;
     const LargeGeom gm = large_geom(a, keys_parts(NB), G, grid);
-    hipLaunchKernelGGL((bwd_bf16_keys_kernel<NB, TERM, DB>), dim3(grid), dim3(block), keys_lds<NB>(), st, a, gm);
+    hipLaunchKernelGGL((bwd_bf16_keys_kernel<NB, TERM, DB>), dim3(grid), dim3(64u * keys_waves(NB)), keys_lds<NB>(), st, a, gm);
     const hipError_t l = hipGetLastError();
     if (!DB || l != hipSuccess) return l;
     BwdArgs r = a;
     r.slots = (int)G;
     return launch_dbias_reduce(r, st, true);
 }
-template <int NB, int TERM>
-hipError_t launch_keys(const BwdArgs& a, long long period, hipStream_t st, bool& fits) {
-    return a.dbias ? launch_keys_db<NB, TERM, true>(a, period, st, fits) : launch_keys_db<NB, TERM, false>(a, period, st, fits);
-}
 
 // The additive term stays in registers where the number of window positions in flight can be a multiple of the mask
 // period (1 without a mask).  Beyond that labels let the kernels form the mask of each window, and a dense mask is
-// read per window.  The two kernels decide for themselves: they hold different numbers of workgroups.
+// read per window.  The two kernels decide for themselves: they hold different numbers of workgroups.  Calls without
+// dBias go to the fused kernel where it is the faster one; with a dense mask whose period the resident workgroups cannot
+// hold it is (nW = 64, 8 heads, 2048 tiles, pair : fused, us: L = 144 95.7 : 85.6, L = 196 181 : 165, L = 256 214 : 210),
+// but for the smallest windows while launching more than the resident ones will do (L = 81: 35.7 : 39.5).
 template <int NB>
 hipError_t launch_large_nb(const BwdArgs& a, hipStream_t st) {
     if (a.bias && a.bias_bf16) return hipErrorInvalidValue;  // the caller hands over an fp32 copy
     const bool bm = a.bias || has_mask(a);
     const long long period = mask_period(a);
+    if (!a.dbias) {
+        bool forced = !bm, taken = false;
+        if (a.mask) {
+            long long G = 0;
+            const hipError_t q = keys_slots<NB, kTermKept, false>(a, period, NB <= 6, G);
+            if (q != hipSuccess) return q;
+            forced = G == 0;
+        }
+        const hipError_t e = launch_backward_bf16_fused(a, st, forced, taken);
+        if (e != hipSuccess || taken) return e;
+    }
     bool fits = false;
     hipError_t e = bm ? launch_rows<NB, true, false>(a, period, st, fits) : launch_rows<NB, false, false>(a, 1, st, fits);
     if (e == hipSuccess && !fits) {
@@ -900,10 +918,15 @@ hipError_t launch_large_nb(const BwdArgs& a, hipStream_t st) {
         else e = a.bias ? launch_rows_stream<NB, true>(a, st) : launch_rows_stream<NB, false>(a, st);
     }
     if (e != hipSuccess) return e;
-    e = bm ? launch_keys<NB, kTermKept>(a, period, st, fits) : launch_keys<NB, kTermNone>(a, 1, st, fits);
+    if (!a.dbias) {
+        e = launch_keys<NB, kTermKept, false>(a, period, st, fits);
+        if (e == hipSuccess && !fits) e = a.labels ? launch_keys<NB, kTermLabels, false>(a, 1, st, fits) : hipErrorInvalidValue;
+        return e;
+    }
+    e = bm ? launch_keys<NB, kTermKept, true>(a, period, st, fits) : launch_keys<NB, kTermNone, true>(a, 1, st, fits);
     if (e == hipSuccess && !fits) {
-        if (a.labels) e = launch_keys<NB, kTermLabels>(a, 1, st, fits);
-        else e = a.bias ? launch_keys<NB, kTermStream>(a, 1, st, fits) : launch_keys<NB, kTermStreamMask>(a, 1, st, fits);
+        if (a.labels) e = launch_keys<NB, kTermLabels, true>(a, 1, st, fits);
+        else e = a.bias ? launch_keys<NB, kTermStream, true>(a, 1, st, fits) : launch_keys<NB, kTermStreamMask, true>(a, 1, st, fits);
     }
     return e;
 }

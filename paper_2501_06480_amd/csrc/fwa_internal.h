@@ -97,6 +97,9 @@ int backward_max_slots(long long N, int heads);
 int coop_slots(long long N, int heads, int nW);
 hipError_t launch_backward_bf16_coop(const BwdArgs& a, hipStream_t s);
 hipError_t launch_backward_bf16_large(const BwdArgs& a, hipStream_t s);
+hipError_t launch_backward_bf16_fused(const BwdArgs& a, hipStream_t s, bool forced, bool& taken);
+// Workgroups of `fn` one CU holds (LDS and registers decide), asked once per kernel
+hipError_t workgroups_per_cu(const void* fn, unsigned block, size_t lds, std::atomic<int>& once, int& per_cu);
 hipError_t launch_backward_bf16_wide(const BwdArgs& a, hipStream_t s);
 int backward_wide_slots(long long N, int heads);
 hipError_t launch_dbias_reduce(const BwdArgs& a, hipStream_t s, bool key_on_lane = false);
