@@ -108,8 +108,8 @@ int fwa_forward_strided(const void* q, const void* k, const void* v, void* o,
  *                dS; overwritten, not accumulated.  The mask gets no gradient.
  *   workspace  : device scratch of at least fwa_backward_workspace_bytes(...)
  *                bytes, 16-byte aligned.  It holds per-workgroup partial sums
- *                of dbias and, for L > 64, the softmax statistics of every row
- *                and the fp32 copy of a bf16 bias (fwa_backward_labels).  It
+ *                of dbias and, for L > 64, the fp32 copy of a bf16 bias
+ *                (fwa_backward_labels).  It
  *                may be NULL when dbias is NULL, unless L > 64 and the bias is
  *                bf16.  Contents on entry are ignored and undefined on exit.
  * Results are bit-reproducible from run to run for fixed arguments.
@@ -148,8 +148,8 @@ int fwa_backward_strided(const void* q, const void* k, const void* v, const void
  * fwa_forward_strided / fwa_backward_strided, and the results are those of the same call with
  * the dense mask written out from the labels: bit for bit while nW is small enough for a
  * workgroup to keep one mask tile for life (nW <= 256 / heads-per-workgroup, roughly), and to
- * within a rounding of the additive term beyond, where the dense form falls back to slower
- * kernels and this form does not (each window's mask is formed from its labels).
+ * within a rounding of the additive term beyond, where the dense form reads each window's
+ * mask tile and this form makes it from the window's labels.
  */
 int fwa_forward_labels(const void* q, const void* k, const void* v, void* o,
                        int64_t N, int L, int C, int heads, float scale,
@@ -167,7 +167,7 @@ int fwa_backward_labels(const void* q, const void* k, const void* v, const void*
 /*
  * fwa_backward for callers that cannot allocate: code under HIP graph capture, serving loops,
  * harnesses that forbid hipMalloc.  It is fwa_backward without the workspace arguments: the
- * workspace (dBias partial sums; for L > 64 also the row statistics) lives in an array of
+ * workspace (dBias partial sums) lives in an array of
  * FWA_NOALLOC_SCRATCH_BYTES bytes inside the library's code object, of which every device the
  * library runs on holds its own copy until the process ends.  The call itself allocates and frees
  * nothing, and runs the same kernels with the same results, bit for bit, as fwa_backward.
