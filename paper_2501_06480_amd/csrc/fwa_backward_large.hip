@@ -17,11 +17,12 @@
 //       with DB, dS is added to dBias[all queries][the wave's keys], held in registers across windows.
 //
 // Nothing is transposed and no L x L tile is ever stored; the price is a second S / dP / exp.
+// Calls without dBias in which there is little to keep from window to window run in one launch (fwa_backward_fused.hip).
 // P and dS enter the matrix cores as hi + lo bf16 pairs (16 significant bits), as in the
 // kernels for small windows.
 //
 // Both kernels are persistent: a wave keeps its block for life and its workgroup walks the windows bw, bw + G, ...
-// What bounds them is vector instructions (8 to 10 per score besides the exponential, six of them in the keys kernel
+// Most of their work is vector instructions (8 to 10 per score besides the exponential, six of them in the keys kernel
 // for the two hi/lo splits), so everything that does not change from window to window stays out of the loop:
 // (bias + mask[w mod nW]) * log2e of the block's 16 x L scores sits in registers (G is a multiple of the mask
 // period), -delta_i enters as the accumulator the product dO V^T starts from.  Reading the additive term per window
@@ -30,7 +31,8 @@
 // 4 heads, bias + labels + dBias: rows 210 -> 154 us, keys 283 -> 185 us (kernels of their own that read the term per
 // window and parked the slabs out of registers between two barriers), the whole call 465 -> 339 us; N = 315 windows
 // of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 59 us.  Vector instructions issue in
-// 60-64 % of the cycles now, the matrix cores are busy for 25 %, the LDS for 40-48 %.
+// 60-64 % of the cycles now, the matrix cores are busy for 25 %, the LDS for 40-48 %:
+// no unit is full (one instruction less per score gave nothing), two waves per SIMD overlap them only in part.
 //
 // The statistics M_i, -delta_i (8 bytes per query) travel from one kernel to the other inside the outputs that the
 // second one overwrites: the 16 floats of a query block are as long as the 64-byte slice of the head in one token

@@ -342,7 +342,7 @@ hipError_t launch_wide_d(const BwdArgs& a, hipStream_t s) {
 }  // namespace
 
 // Window positions walked in parallel (= dBias slots) when dBias is wanted: two or three resident
-// workgroups per CU; never more than the single-wave kernel's count, which sizes the workspace.
+// workgroups per CU; never more than backward_max_slots, which sizes the workspace.
 int backward_wide_slots(long long N, int heads) {
     long long G = 2 * cu_count() / heads;
     if (G < 1) G = 1;
