@@ -132,7 +132,11 @@ py::object forward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v
     return rc == FWA_OK ? py::cast(o) : py::cast(rc);
 }
 
-// q, k, v as the three slices of a contiguous [N, L, 3, heads, d] tensor
+// q, k, v as the three slices of a contiguous [N, L, 3, heads, d] tensor: slice_of relies on need_qkv
+void need_qkv(const at::Tensor& qkv) {
+    if (qkv.dim() != 5 || qkv.size(2) != 3 || !qkv.is_contiguous()) value_error("qkv must be a contiguous [N, L, 3, heads, d] tensor");
+    need_gpu(qkv, "qkv");
+}
 Rows slice_of(const at::Tensor& qkv, int which) {
     const int64_t C = qkv.size(3) * qkv.size(4);
     return {static_cast<char*>(qkv.data_ptr()) + which * C * qkv.element_size(), 3 * C};
@@ -140,7 +144,7 @@ Rows slice_of(const at::Tensor& qkv, int which) {
 
 py::object forward_qkv(const at::Tensor& qkv, float scale, const OptTensor& bias, const OptTensor& mask, const OptTensor& labels,
                        float mask_value) {
-    need_gpu(qkv, "q");
+    need_qkv(qkv);
     const int64_t N = qkv.size(0), L = qkv.size(1), heads = qkv.size(3), C = heads * qkv.size(4);
     const at::Tensor o = at::empty({N, L, C}, qkv.options());
     const Terms t = terms_of(bias, mask, labels, heads, L);
@@ -200,7 +204,7 @@ py::object backward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& 
 
 py::object backward_qkv(const at::Tensor& qkv, const at::Tensor& d_o, float scale, const OptTensor& bias, const OptTensor& mask,
                         bool want_dbias, const OptTensor& labels, float mask_value) {
-    need_gpu(qkv, "q");
+    need_qkv(qkv);
     const int64_t N = qkv.size(0), L = qkv.size(1), heads = qkv.size(3), C = heads * qkv.size(4);
     need_gpu(d_o, "d_o");
     if (d_o.dim() != 3 || d_o.size(0) != N || d_o.size(1) != L || d_o.size(2) != C || d_o.scalar_type() != qkv.scalar_type() ||
