@@ -95,6 +95,9 @@ __device__ __forceinline__ int load_i32(__amdgpu_buffer_rsrc_t r, uint32_t voffs
 // would wait for the load in front of every later LDS read, whatever that reads: the caller separates the two
 // with lds_loads_done() and a barrier.  `base` is wave-uniform; lanes whose offset lies at or
 // beyond `bytes` fetch nothing, and zeros at most are written for them (callers keep zeros there from the start).
+// The compiler inserts no wait states for what it cannot see: the memory instruction may read m0 one state after its
+// write at the earliest, and a scalar register that a vector instruction wrote (v_readfirstlane, or v_readlane of a
+// spilled descriptor word) five states after it.  The two moves and s_nop 2 are five.
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
@@ -102,7 +105,7 @@ __device__ __forceinline__ void load_to_lds(const void* base, uint32_t bytes, ui
     const uintptr_t a = reinterpret_cast<uintptr_t>(base);
     const u32x4 r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
     uint32_t saved;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 2\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved) : "s"(lds_off), "v"(voffset), "s"(r) : "memory");
 }
 // all but the N youngest global loads and stores of this wave are complete
