@@ -142,7 +142,7 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) add[jb] = one[0][jb];
     }
-    const float mv = p.mask_value * kLog2e;
+    const float mv = 16 * role + n < L ? p.mask_value * kLog2e : 0.f;
     auto request_mask = [&](uint32_t w) { request_mask_tile(p, w, lds_offset(lmask), wv, 4u * hpb, (uint32_t)lane); };
     // this lane's query row of the mask tile; rows beyond L stay inside it (their results are dropped)
     const float* const mask_row = reinterpret_cast<const float*>(lmask) + (16 * role + n < L ? 16 * role + n : L - 1) * L + 4 * g;

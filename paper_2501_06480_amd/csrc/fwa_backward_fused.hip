@@ -250,9 +250,11 @@ __global__ void __launch_bounds__(64 * fused_waves(NB)) bwd_bf16_fused_kernel(Bw
             }
             delta = sum_over_g(delta) * inv;
             if (g == 0) {
-                const float Mi = m + __builtin_amdgcn_logf(sum);  // p_ij = exp2(score_ij - M_i)
-                stM[16 * qb + n] = Mi;
-                stD[16 * qb + n] = delta;
+                // p_ij = exp2(score_ij - M_i).  A row beyond L gets what makes its probabilities zeros in pass 2, whatever its
+                // own scores were: with labels and a mask value of -inf they may be NaN.
+                const bool pad = qb == NB - 1 && 16 * qb + n >= L;
+                stM[16 * qb + n] = pad ? INFINITY : m + __builtin_amdgcn_logf(sum);
+                stD[16 * qb + n] = pad ? 0.f : delta;
             }
             // dQ^T = K^T dS^T over pairs of key blocks; the operands of the next pair are fetched ahead
             f32x4 q0 = zero, q1 = zero;  // dQ[16 qb + n][4g + r], dQ[16 qb + n][16 + 4g + r]

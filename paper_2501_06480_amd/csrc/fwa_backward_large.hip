@@ -68,7 +68,8 @@ constexpr int keys_parts(int nb) { return (nb + 3) / 4; }
 constexpr int keys_waves(int nb) { return (nb + keys_parts(nb) - 1) / keys_parts(nb); }
 
 // M and -delta of query block qb (lane (g, n) holds those of query 16 qb + n, the same for all g) to every part of
-// the keys kernel: lane row g serves part g.
+// the keys kernel: lane row g serves part g.  A row beyond L leaves values that take it out of every sum over the queries
+// (its probabilities are zeros), whatever its own scores were: with labels and a mask value of -inf they may be NaN.
 template <int NB>
 __device__ __forceinline__ void store_stats(const BwdArgs& p, size_t tile_d, uint32_t row_d, int qb, int n, int g, float M,
                                             float neg_delta) {
@@ -76,6 +77,7 @@ __device__ __forceinline__ void store_stats(const BwdArgs& p, size_t tile_d, uin
     // rows 16 part + qb of the head's slice, all below 16 PARTS <= L
     const uint32_t bytes = (16u * PARTS - 1u) * row_d + 64u;
     const uint32_t off = (uint32_t)g < PARTS ? (uint32_t)(16 * g + qb) * row_d + 4u * (uint32_t)n : 0xfffffff0u;
+    if (qb == NB - 1 && 16 * qb + n >= p.L) M = INFINITY, neg_delta = 0.f;
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, M), make_rsrc((char*)p.dv + tile_d, bytes), off, 0, 0);
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, neg_delta), make_rsrc((char*)p.dk + tile_d, bytes), off, 0, 0);
 }

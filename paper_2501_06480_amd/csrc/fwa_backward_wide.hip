@@ -156,7 +156,8 @@ __global__ void __launch_bounds__(256) bwd_bf16_wide_kernel(BwdArgs p, uint32_t 
         float inv;
         if (BM) {
             const BiasSrc rb = bias_of_head(p, h);
-            const AddendGlobal addend = addend_at(rb, mask_of_window(p, w), (uint32_t)(16 * qb + n), 4u * g, (uint32_t)L);
+            const uint32_t i = (uint32_t)(16 * qb + n);
+            const AddendGlobal addend = addend_at(rb, mask_of_row(mask_of_window(p, w), i, (uint32_t)L), i, 4u * g, (uint32_t)L);
             inv = softmax_block<NB, true>(s, sl2, addend, L, g);
         } else {
             inv = softmax_block<NB, false>(s, sl2, AddendNone{}, L, g);

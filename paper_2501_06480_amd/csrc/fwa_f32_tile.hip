@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(256) bwd_f32_tile_kernel(BwdArgs p) {
         MaskSrc msk = {make_rsrc(nullptr, 0), 0.f, false};
         if (BM) {
             rb = bias_of_head(p, h);
-            msk = mask_of_window(p, w);
+            msk = mask_of_row(mask_of_window(p, w), (uint32_t)(16 * qb + n), (uint32_t)L);
         }
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) s[jb] = dp[jb] = zero;

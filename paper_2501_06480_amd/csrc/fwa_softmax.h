@@ -25,6 +25,14 @@ __device__ __forceinline__ MaskSrc mask_of_window(const Args& p, uint32_t w) {
     return MaskSrc{make_rsrc(nullptr, 0), 0.f, false};
 }
 
+// The mask for a lane whose query row is i, in kernels that contract over the queries.  A row beyond L has no label (it
+// reads as 0): it gets no mask.  Masked like label 0 it may lose every key, and with a mask value that removes a pair
+// altogether (-inf) its probabilities are NaN, which the zero rows of Q and dO do not take out of dK and dV.
+__device__ __forceinline__ MaskSrc mask_of_row(MaskSrc m, uint32_t i, uint32_t L) {
+    m.value = i < L ? m.value : 0.f;
+    return m;
+}
+
 // Mask values of 4 consecutive columns of a row from the labels: lq = label of the row,
 // lk = labels of the columns.
 __device__ __forceinline__ f32x4 mask_of_labels(int lq, const i32x4& lk, float value) {
@@ -130,7 +138,7 @@ __device__ __forceinline__ void fill_rows(f32x4 (&add)[NQ][NB], const AddendGlob
         for (int t = 0; t < NQ; ++t)
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb)
-                mk[t][jb] = mask_of_labels(lq[t], __builtin_bit_cast(i32x4, mk[t][jb]), m.value);
+                mk[t][jb] = mask_of_labels(lq[t], __builtin_bit_cast(i32x4, mk[t][jb]), rows[t].m.value);
     }
 #pragma unroll
     for (int t = 0; t < NQ; ++t)
@@ -169,7 +177,7 @@ __device__ __forceinline__ void fill_rows_staged(f32x4 (&add)[NQ][NB], const Bia
     if (b.bf16) {
         AddendGlobal rows[NQ];
 #pragma unroll
-        for (int t = 0; t < NQ; ++t) rows[t] = addend_at(b, m, rows0[t] + n, 4u * g, L);
+        for (int t = 0; t < NQ; ++t) rows[t] = addend_at(b, mask_of_row(m, rows0[t] + n, L), rows0[t] + n, 4u * g, L);
         fill_rows<NQ, NB>(add, rows, mul);
         return;
     }
@@ -215,8 +223,9 @@ __device__ __forceinline__ void fill_rows_staged(f32x4 (&add)[NQ][NB], const Bia
         __builtin_amdgcn_wave_barrier();
         if (m.labels) {
             const int lq = load_i32(m.r, (rows0[t] + n) * 4u);
+            const float value = mask_of_row(m, rows0[t] + n, L).value;
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) add[t][jb] += mask_of_labels(lq, load_i32x4(m.r, (16u * jb + 4u * g) * 4u), m.value);
+            for (int jb = 0; jb < NB; ++jb) add[t][jb] += mask_of_labels(lq, load_i32x4(m.r, (16u * jb + 4u * g) * 4u), value);
         }
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) add[t][jb] *= mul;
@@ -243,7 +252,7 @@ struct AddendRegsLabels {
     const f32x4 (&a)[NB];
     const int* lab;  // LDS: labels of tokens 0 .. 16 NB - 1 of the window
     int tq;          // label of the lane's query row
-    float mv;
+    float mv;        // where the queries are contracted over: 0 for rows beyond L (see mask_of_row)
     int g;
     // the term of key block jb (one block at a time keeps the labels out of the register file)
     __device__ __forceinline__ f32x4 block(int jb) const {
