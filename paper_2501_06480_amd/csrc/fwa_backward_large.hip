@@ -77,7 +77,9 @@ __device__ __forceinline__ void store_stats(const BwdArgs& p, size_t tile_d, uin
     // rows 16 part + qb of the head's slice, all below 16 PARTS <= L
     const uint32_t bytes = (16u * PARTS - 1u) * row_d + 64u;
     const uint32_t off = (uint32_t)g < PARTS ? (uint32_t)(16 * g + qb) * row_d + 4u * (uint32_t)n : 0xfffffff0u;
-    if (qb == NB - 1 && 16 * qb + n >= p.L) M = INFINITY, neg_delta = 0.f;
+    const bool pad = 16 * qb + n >= p.L;
+    M = pad ? INFINITY : M;
+    neg_delta = pad ? 0.f : neg_delta;
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, M), make_rsrc((char*)p.dv + tile_d, bytes), off, 0, 0);
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, neg_delta), make_rsrc((char*)p.dk + tile_d, bytes), off, 0, 0);
 }
