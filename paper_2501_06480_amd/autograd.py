@@ -50,8 +50,11 @@ class _WindowAttentionQKV(torch.autograd.Function):
     def backward(ctx, d_o):
         qkv, bias, mask, labels = ctx.saved_tensors
         want_db = bias is not None and ctx.needs_input_grad[1]
-        # a saved-tensor hook may have handed qkv back in another layout
-        dqkv, db = binding.fwa_backward_qkv(qkv.contiguous(), d_o.contiguous(), ctx.scale, bias, mask, want_db, labels, ctx.mask_value)
+        if not d_o.is_contiguous():
+            d_o = d_o.contiguous()
+        if not qkv.is_contiguous():  # a saved-tensor hook may have handed it back in another layout
+            qkv = qkv.contiguous()
+        dqkv, db = binding.fwa_backward_qkv(qkv, d_o, ctx.scale, bias, mask, want_db, labels, ctx.mask_value)
         return dqkv, db, None, None, None, None
 
 
