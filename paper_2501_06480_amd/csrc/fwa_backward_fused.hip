@@ -250,9 +250,9 @@ __global__ void __launch_bounds__(64 * fused_waves(NB)) bwd_bf16_fused_kernel(Bw
             }
             delta = sum_over_g(delta) * inv;
             if (g == 0) {
-                // p_ij = exp2(score_ij - M_i).  A row beyond L gets what makes its probabilities zeros in pass 2, whatever its
-                // own scores were: with labels and a mask value of -inf they may be NaN.
-                const bool pad = qb == NB - 1 && 16 * qb + n >= L;
+                // p_ij = exp2(score_ij - M_i).  With labels a row beyond L gets what makes its probabilities zeros in pass 2,
+                // whatever its own scores were: a mask value of -inf may have made them NaN.
+                const bool pad = HM == 2 && 16 * qb + n >= L;
                 stM[16 * qb + n] = pad ? INFINITY : m + __builtin_amdgcn_logf(sum);
                 stD[16 * qb + n] = pad ? 0.f : delta;
             }

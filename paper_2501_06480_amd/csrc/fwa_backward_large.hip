@@ -68,8 +68,7 @@ constexpr int keys_parts(int nb) { return (nb + 3) / 4; }
 constexpr int keys_waves(int nb) { return (nb + keys_parts(nb) - 1) / keys_parts(nb); }
 
 // M and -delta of query block qb (lane (g, n) holds those of query 16 qb + n, the same for all g) to every part of
-// the keys kernel: lane row g serves part g.  A row beyond L leaves values that take it out of every sum over the queries
-// (its probabilities are zeros), whatever its own scores were: with labels and a mask value of -inf they may be NaN.
+// the keys kernel: lane row g serves part g.
 template <int NB>
 __device__ __forceinline__ void store_stats(const BwdArgs& p, size_t tile_d, uint32_t row_d, int qb, int n, int g, float M,
                                             float neg_delta) {
@@ -77,9 +76,6 @@ __device__ __forceinline__ void store_stats(const BwdArgs& p, size_t tile_d, uin
     // rows 16 part + qb of the head's slice, all below 16 PARTS <= L
     const uint32_t bytes = (16u * PARTS - 1u) * row_d + 64u;
     const uint32_t off = (uint32_t)g < PARTS ? (uint32_t)(16 * g + qb) * row_d + 4u * (uint32_t)n : 0xfffffff0u;
-    const bool pad = 16 * qb + n >= p.L;
-    M = pad ? INFINITY : M;
-    neg_delta = pad ? 0.f : neg_delta;
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, M), make_rsrc((char*)p.dv + tile_d, bytes), off, 0, 0);
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, neg_delta), make_rsrc((char*)p.dk + tile_d, bytes), off, 0, 0);
 }
@@ -343,7 +339,11 @@ __global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdA
         park_labels(buf ^ 1u);
         if (active) {
             const size_t tile_d = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
-            store_stats<NB>(p, tile_d, row_d, qb, n, g, M, nd);
+            // A row beyond L leaves what takes it out of every sum over the queries (its probabilities are zeros), whatever
+            // its own scores were: with labels and a mask value of -inf they may be NaN.  (Selects, not a branch, which
+            // would cut the window into pieces: 1 % of it.  The kernel below reads dense masks alone, zeros beyond L.)
+            const bool pad = 16 * qb + n >= L;
+            store_stats<NB>(p, tile_d, row_d, qb, n, g, BM && pad ? INFINITY : M, BM && pad ? 0.f : nd);
             store_rows(cell, lo, hi, make_rsrc((char*)p.dq + tile_d, tile_bytes_d), qb, row_d, lane);
         }
         __syncthreads();  // the next window is in place, and every wave is done with this one's buffer
