@@ -133,14 +133,8 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     if (BM && active) {
         const BiasSrc rb = bias_of_head(p, h);
         const MaskSrc msk = PW ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
-        f32x4 one[1][NB];
-        const uint32_t rows0[1] = {(uint32_t)(16 * role)};
-        // through the exchange tiles of the head, which are not in use yet (the barrier that opens the first window
-        // stands between these reads and their first writes)
-        static_assert(kCoopWavesPerTile * rows_fill_bytes<NB>() <= 4 * XT * 2, "the tiles hold the waves' stretches");
-        fill_rows_staged<1, NB>(one, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(ex) + role * rows_fill_bytes<NB>(), lane);
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb) add[jb] = one[0][jb];
+        const uint32_t i = (uint32_t)(16 * role + n);
+        addend_at(rb, mask_of_row(msk, i, (uint32_t)L), i, 4u * g, (uint32_t)L).fill(add, kLog2e);
     }
     const float mv = 16 * role + n < L ? p.mask_value * kLog2e : 0.f;
     auto request_mask = [&](uint32_t w) { request_mask_tile(p, w, lds_offset(lmask), wv, 4u * hpb, (uint32_t)lane); };

@@ -122,6 +122,10 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_kernel(FwdArgs p
 
 #pragma unroll
     for (int qb = 0; qb < NB; ++qb) {
+        // Never taken (NB = ceil(L / 16)): it keeps the compiler from moving the loads and products of one query block
+        // into another's (42 windows of 49 tokens, 7 heads, bias and labels: 6.5 us, 7.1 without it; scheduling barriers
+        // in its place give 7.1 too).
+        if (16 * qb >= L) break;
         f32x4 s[NB];
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) {

@@ -247,12 +247,16 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
     {
         const BiasSrc rb = bias_of_head(p, h);
         const MaskSrc msk = PW ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
-        uint32_t rows0[NB];
+        if (fill_in_lines<NB>(p, PW == 0 && p.mask)) {
+            uint32_t rows0[NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) rows0[b] = 16u * b;
-        // through the slab area, which nothing has been parked in yet
-        fill_rows_staged<NB, NB>(add, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds + tiles) + hl * rows_fill_bytes<NB>(), lane);
-        __syncthreads();
+            for (int b = 0; b < NB; ++b) rows0[b] = 16u * b;
+            // through the slab area, which nothing has been parked in yet
+            fill_rows_staged<NB, NB>(add, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds + tiles) + hl * rows_fill_bytes<NB>(), lane);
+            __syncthreads();
+        } else {
+            fill_rows<NB, NB>(add, rb, msk, (uint32_t)n, 4u * g, (uint32_t)L, kLog2e);
+        }
     }
     const float mv = p.mask_value * kLog2e;
 
@@ -581,17 +585,21 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
         const BiasSrc rb = bias_of_head(p, h);
         // rows beyond L (and the whole block of an idle wave) fall outside the descriptors: zeros
         const MaskSrc msk = PW ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, w0);
-        if constexpr (NB <= 4) {  // every wave has a block; through the slab area, which nothing has been parked in yet
-            static_assert(HPB * W * rows_fill_bytes<NB>() <= 2 * 2 * ROWS * STRIDE * 16 + 2 * ROWS * 4, "the slab area holds the waves' stretches");
-            f32x4 one[1][NB];
-            const uint32_t rows0[1] = {(uint32_t)(16 * qb)};
-            fill_rows_staged<1, NB>(one, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds + tiles) + wave * rows_fill_bytes<NB>(), lane);
+        bool filled = false;
+        if constexpr (NB == 4) {
+            filled = fill_in_lines<NB>(p, false);
+            if (filled) {  // every wave has a block; through the slab area, which nothing has been parked in yet
+                static_assert(HPB * W * rows_fill_bytes<NB>() <= 2 * 2 * ROWS * STRIDE * 16 + 2 * ROWS * 4, "the slab area holds the waves' stretches");
+                f32x4 one[1][NB];
+                const uint32_t rows0[1] = {(uint32_t)(16 * qb)};
+                fill_rows_staged<1, NB>(one, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(lds + tiles) + wave * rows_fill_bytes<NB>(), lane);
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) add[jb] = one[0][jb];
-            __syncthreads();
-        } else {
-            addend_at(rb, msk, active ? (uint32_t)(16 * qb + n) : (uint32_t)L, 4u * g, (uint32_t)L).fill(add, kLog2e);
+                for (int jb = 0; jb < NB; ++jb) add[jb] = one[0][jb];
+                __syncthreads();
+            }
         }
+        if (!filled)
+            addend_at(rb, msk, active ? (uint32_t)(16 * qb + n) : (uint32_t)L, 4u * g, (uint32_t)L).fill(add, kLog2e);
     }
     const float mv = p.mask_value * kLog2e;
     if (w0 < end) park(sa, 0);

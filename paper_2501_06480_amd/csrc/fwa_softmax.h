@@ -162,25 +162,28 @@ __device__ __forceinline__ void AddendGlobal::fill(f32x4 (&add)[NB], float mul) 
 #pragma unroll
     for (int jb = 0; jb < NB; ++jb) add[jb] = one[0][jb];
 }
-// The same term for whole blocks of 16 rows, block t starting at row rows0[t], by a wave that keeps it for life:
-// add[t][jb] = (bias + mask)[rows0[t] + n][16 jb + 4g ..+3] * mul.  fill_rows has every lane fetch the 16-byte pieces of
-// its own row, which the memory pipeline serves a lane at a time; 16 rows are one contiguous stretch of the tile, so here
-// the wave fetches it in whole lines, 1 KB per load, and turns rows into lanes through LDS (`area`: rows_fill_bytes<NB>()
-// bytes of the wave's own).  (Swin-T stage 3 with bias and mask: forward 18.7 -> 18.4 us, backward 38.3 -> 37.0.)  Where L is a multiple of 16 the
-// rows would fall on the same banks: 16 bytes of padding every 256.  A bf16 bias takes fill_rows.
+// The same term for whole blocks of 16 rows, block t starting at row rows0[t], by a wave that keeps it for life, with an
+// fp32 bias: add[t][jb] = (bias + mask)[rows0[t] + n][16 jb + 4g ..+3] * mul.  fill_rows has every lane fetch the 16-byte
+// pieces of its own row, which the memory pipeline serves a lane at a time; 16 rows are one contiguous stretch of the tile,
+// so here the wave fetches it in whole lines, 1 KB per load, and turns rows into lanes through LDS (`area`:
+// rows_fill_bytes<NB>() bytes of the wave's own).  Where L is a multiple of 16 the rows would fall on the same banks: 16
+// bytes of padding every 256.  The turn costs a trip through LDS that fill_rows does not make; fill_in_lines says where it
+// pays.
 template <int NB>
 constexpr uint32_t rows_fill_bytes() { return NB * 1088u; }
+// 256-byte rows (L = 64) fall on the same lines 16 lanes at a time: there the whole lines win, fill_rows against this in us:
+// 630 windows with 2 heads and a dense mask 8.5 : 7.6, 256 with 3 heads 7.4 : 6.7, 952 with 6 heads 22.1 : 20.0.  Rows that
+// are no multiple of 64 bytes spread by themselves: at L = 49 the two are even (-2 .. +5 %), but for two tiles to fetch,
+// bias and dense mask, in the kernel with one wave per head (Swin-T stage 3, shifted: 18.7 : 18.4).  Below 49 tokens
+// fill_rows is 1-9 % faster.
+template <int NB, class Args>
+__device__ __forceinline__ bool fill_in_lines(const Args& p, bool two_tiles) {
+    return NB == 4 && p.bias && !p.bias_bf16 && (p.L % 16 == 0 || two_tiles);
+}
 template <int NQ, int NB>
 __device__ __forceinline__ void fill_rows_staged(f32x4 (&add)[NQ][NB], const BiasSrc& b, const MaskSrc& m, const uint32_t (&rows0)[NQ],
                                                  uint32_t L, float mul, char* area, int lane) {
     const uint32_t n = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4;
-    if (b.bf16) {
-        AddendGlobal rows[NQ];
-#pragma unroll
-        for (int t = 0; t < NQ; ++t) rows[t] = addend_at(b, mask_of_row(m, rows0[t] + n, L), rows0[t] + n, 4u * g, L);
-        fill_rows<NQ, NB>(add, rows, mul);
-        return;
-    }
 #pragma unroll
     for (int t = 0; t < NQ; ++t)
 #pragma unroll
@@ -223,9 +226,8 @@ __device__ __forceinline__ void fill_rows_staged(f32x4 (&add)[NQ][NB], const Bia
         __builtin_amdgcn_wave_barrier();
         if (m.labels) {
             const int lq = load_i32(m.r, (rows0[t] + n) * 4u);
-            const float value = mask_of_row(m, rows0[t] + n, L).value;
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) add[t][jb] += mask_of_labels(lq, load_i32x4(m.r, (16u * jb + 4u * g) * 4u), value);
+            for (int jb = 0; jb < NB; ++jb) add[t][jb] += mask_of_labels(lq, load_i32x4(m.r, (16u * jb + 4u * g) * 4u), m.value);
         }
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) add[t][jb] *= mul;
