@@ -494,7 +494,7 @@ constexpr int rowpersist_waves(int nb) { return nb <= 12 ? nb : (nb + 1) / 2; }
 // PW ("per window"): the mask's period does not divide G, so that a workgroup meets a different mask
 // tile at every window.  Then only the bias stays in registers.  PW = 1, labels: those of a window
 // travel with its slabs (requested two windows ahead, parked in LDS beside them) and the mask is formed
-// per score.  PW = 2 (HPB > 1), a dense mask: as in the kernel above (2784 windows of 49 tokens, 3 heads, mask of 1392
+// per score.  PW = 2 (HPB > 2), a dense mask: as in the kernel above (2784 windows of 49 tokens, 3 heads, mask of 1392
 // windows: 33.5 -> 25.9 us; 22 as labels).
 template <int NB, int HPB, int PW>
 __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowpersist_kernel(FwdArgs p, RowPersistGeom gm) {
@@ -692,7 +692,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
         if constexpr (PW == 2) {
             // the next mask tile has landed: of this wave's memory operations only the slab loads requested behind it
             // and the two output stores are younger
-            static_assert(HPB > 1, "every wave stores twice");
+            static_assert(HPB > 2, "every wave stores twice, straight from its registers");
             if (w + AHEAD * step < end) wait_vmem<2 * PASSES + 1 + 2>();
             else if (has_next) wait_vmem<2>();
         }
@@ -785,7 +785,7 @@ hipError_t launch_rowpersist_pw(const FwdArgs& a, long long G, hipStream_t st) {
 // pw: the mask's period does not divide G (see the kernel)
 template <int NB, int HPB>
 hipError_t launch_rowpersist_hpb(const FwdArgs& a, long long G, hipStream_t st, bool pw = false) {
-    if constexpr (HPB > 1) {
+    if constexpr (HPB > 2 && NB > 1) {
         if (pw && a.mask) return launch_rowpersist_pw<NB, HPB, 2>(a, G, st);
     }
     return pw ? launch_rowpersist_pw<NB, HPB, 1>(a, G, st) : launch_rowpersist_pw<NB, HPB, 0>(a, G, st);
@@ -851,9 +851,12 @@ hipError_t launch_staged_nb(const FwdArgs& a, int hpb, hipStream_t st) {
         // sees the same mask tile, about 4 workgroups per CU (measured best of 2..8), at least 2
         // windows per workgroup, and enough workgroups to cover the chip; else one window each.
         const long long nW = mask_period(a);
-        // A dense mask per window as a tile in LDS: not where its rows fall on the same banks (a row length that is a
-        // multiple of 32 words: 8 x 8 windows, 3 heads, 33 us against 28 with bias and mask read per window)
-        const bool dense_tiles = a.mask != nullptr && a.L % 32 != 0;
+        // A dense mask of a period that does not fit, as a tile per window in LDS: not where its rows fall on the same banks
+        // (a row length that is a multiple of 32 words: 8 x 8 windows, 3 heads, 33 us against 28 with bias and mask read
+        // per window), and only for groups of 3 or 4 heads, which share a tile (per window : tile, us, 2 heads: 4950
+        // windows of 49 tokens 28.3 : 32.2, 5200 of 36 20.2 : 25.8).  Below 49 tokens only in the small calls below (816 windows of 25 tokens, 4 heads 9.4 : 7.3; 1216 of 36, 3 heads 12.2 : 11.4; but 3125 of 25, 3 heads
+        // 13.1 : 15.1, 3040 of 36 18.9 : 21.3), and not for 16, whose tile is a single load (1400, 3 heads 5.0 : 6.4).
+        const bool dense_tiles = a.mask != nullptr && a.L % 32 != 0 && hpb >= 3 && (NB == 4 || (few_tiles && NB > 1));
         // A small call with an additive term whose workgroups of four waves per head would not all be
         // resident at once (Swin-T stage 4: 24 heads x 128 windows): groups of 3 (or 2) heads in the
         // row-persistent kernel instead, one workgroup per CU walking a few windows with the term in
@@ -876,8 +879,9 @@ hipError_t launch_staged_nb(const FwdArgs& a, int hpb, hipStream_t st) {
             long long G1 = cus / nW * nW;
             if (G1 > a.N / 2) G1 = (a.N / 2) / nW * nW;
             bool pw = false;
-            if (!(G1 >= nW && G1 >= cus / 2) && (a.labels || dense_tiles) && a.N >= cus) {
-                // no multiple of the mask period fits: per-window masks
+            // no multiple of the mask period fits: per-window masks.  A dense one needs more windows to pay (3 heads of 49
+            // tokens, per window against tile: 256 windows 5.7 : 7.2 us, 400 7.8 : 7.5, 3072 30.6 : 26.3)
+            if (!(G1 >= nW && G1 >= cus / 2) && ((a.labels && a.N >= cus) || (dense_tiles && 2 * a.N >= 3 * cus))) {
                 G1 = a.N / 2 < cus ? a.N / 2 : cus;
                 pw = true;
             }
@@ -909,15 +913,17 @@ hipError_t launch_staged_nb(const FwdArgs& a, int hpb, hipStream_t st) {
                                lds + (size_t)16 * NB * 4, st, a, gm, (uint32_t)G);
             return hipGetLastError();
         }
-        // the same with a dense mask, while the two tiles leave room for two workgroups per CU; four heads share a
-        // tile then (with two, and twice the tiles per CU, it is slower: 6 heads 35 us against 31)
-        const size_t lds_dense = lds + 2 * mask_tile_bytes((uint32_t)a.L);
-        if (!few_tiles && dense_tiles && hpb == 4 && G * groups >= cu_count() && lds_dense <= 80 * 1024) {
-            const hipError_t e = allow_lds(reinterpret_cast<const void*>(&fwd_bf16_persistent_kernel<NB, 2>), lds_dense);
-            if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((fwd_bf16_persistent_kernel<NB, 2>), dim3((unsigned)(G * groups)), dim3(block), lds_dense, st, a, gm,
-                               (uint32_t)G);
-            return hipGetLastError();
+        // the same with a dense mask, while the two tiles leave room for two workgroups per CU (700 windows of 49
+        // tokens, 16 heads 37.3 : 33.0; no gain below 49 tokens, 720 of 36 with 16 heads 21.4 : 23.6)
+        if constexpr (NB == 4) {
+            const size_t lds_dense = lds + 2 * mask_tile_bytes((uint32_t)a.L);
+            if (!few_tiles && dense_tiles && hpb == 4 && G * groups >= cu_count() && lds_dense <= 80 * 1024) {
+                const hipError_t e = allow_lds(reinterpret_cast<const void*>(&fwd_bf16_persistent_kernel<NB, 2>), lds_dense);
+                if (e != hipSuccess) return e;
+                hipLaunchKernelGGL((fwd_bf16_persistent_kernel<NB, 2>), dim3((unsigned)(G * groups)), dim3(block), lds_dense, st, a,
+                                   gm, (uint32_t)G);
+                return hipGetLastError();
+            }
         }
         if (few_tiles)
             hipLaunchKernelGGL((fwd_bf16_staged_kernel<NB, true, 4>), dim3(grid), dim3(4 * block), lds, st, a, gm);

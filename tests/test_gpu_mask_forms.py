@@ -72,16 +72,21 @@ def test_small_window_backward_long_periods(oracle, name, L, heads, N, nW, use_b
 
 
 # The forward for windows of up to 64 tokens with such a period: the dense tile of every window in a second LDS buffer,
-# with all heads of a window in one workgroup (2, 3 heads) and with groups of 4 heads; beside them the calls next to the
-# rule that read the mask per window (groups of 2 heads, row lengths that are multiples of 32 words, tiles that leave no
-# room for two workgroups).  An odd number of windows per workgroup, and fewer windows than workgroups after the first
-# round, end the walk at every stage of its prefetches.
+# with all heads of a window in one workgroup (3 heads; 4 heads, 16 waves, in the smaller calls) and with groups of 4 heads;
+# beside them the calls next to the rule that read the mask per window (2 heads and groups of 2, row lengths that are
+# multiples of 32 words, the smallest windows, too few windows, tiles that leave no room for two workgroups).  An odd number
+# of windows per workgroup, and fewer windows than workgroups after the first round, end the walk at every stage of its
+# prefetches.
 # name, L, heads, N, nW, bias
 FORWARD = [
     ("L16_pairs", 16, 2, 900, 300, True),
     ("L17", 17, 3, 600, 300, False),
     ("L33", 33, 3, 300, 300, True),
+    ("L33_few_windows_more", 33, 3, 400, 400, True),
+    ("L33_four_heads", 33, 4, 410, 410, False),
     ("L49", 49, 3, 1390, 695, True),
+    ("L49_four_heads", 49, 4, 600, 300, True),
+    ("L55_four_heads", 55, 4, 999, 333, True),
     ("L64", 64, 3, 600, 300, True),
     ("L49_groups_of_2", 49, 6, 1050, 350, True),
     ("L49_groups_of_4", 49, 8, 600, 300, True),
