@@ -343,7 +343,7 @@ int backward_impl(const void* q, const void* k, const void* v, const void* d_o, 
     a.per_window = small && (labels || mask) && !periodic;
     a.slots = C / heads != fwa::kHeadDim ? fwa::backward_wide_slots(N, heads)
               : large                    ? fwa::backward_large_slots(N, heads, L)
-                                         : fwa::backward_slots(N, heads, a.nW);
+                                         : fwa::backward_slots(N, heads, a.nW, L, mask != nullptr, labels != nullptr, dbias != nullptr);
     // workspace: [fp32 copy of a bf16 bias (large windows only)] [partial sums of dBias]; a call needs the
     // parts it uses
     const bool copy_bias = large && bias && bias_dtype == FWA_BF16;

@@ -69,10 +69,11 @@ dbias_reduce_kernel(const f32x4* __restrict__ partial, float* __restrict__ dbias
 
 // Workgroups along the window axis of the cooperative kernel (= dBias slots), N > 0.  Where no multiple of the mask
 // period nW fits the chip the kernel forms or fetches the mask of each window and has no period to keep to.
-int backward_slots(long long N, int heads, int nW) {
-    int c = coop_slots(N, heads, nW);
-    if (c == 0) c = coop_slots(N, heads, 1);
-    return c > 0 ? c : 1;  // more head groups than the chip holds workgroups: each walks all windows
+int backward_slots(long long N, int heads, int nW, int L, bool mask, bool labels, bool dbias) {
+    const int c = coop_slots(N, heads, nW);
+    if (c > 0 || !(mask || labels)) return c > 0 ? c : 1;  // 1: more head groups than the chip holds workgroups
+    const int most = backward_max_slots(N, heads), G = coop_window_slots(N, heads, L, mask, dbias);
+    return G < most ? G : most;
 }
 
 // Upper bound of the above over all periods, as the workspace query has always stated it (it once covered a second

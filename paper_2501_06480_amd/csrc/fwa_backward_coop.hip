@@ -1,5 +1,5 @@
-// Cooperative backward kernel (paper Algorithm 2) for L <= 64: four waves per
-// (window, head) tile, several heads per workgroup, persistent over windows.
+// Cooperative backward kernel (paper Algorithm 2) for L <= 64: one wave per 16-row block of a
+// (window, head) tile (NB = ceil(L / 16) waves), several heads per workgroup, persistent over windows.
 //
 // One wave per tile would need the whole register file and run two waves per SIMD (built first: twice as
 // slow).  Here the tile is split:
@@ -23,11 +23,16 @@
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
 
+#include <algorithm>
+
 namespace fwa {
 namespace {
 
-constexpr int kCoopWavesPerTile = 4;
-constexpr int kCoopMaxHeads = 3;  // heads per workgroup: 12 waves, 3 per SIMD, <= 170 VGPRs each
+constexpr int kCoopMaxHeads = 3;  // heads per workgroup
+// Compiled for 12 waves per CU at every NB, though below 49 tokens a workgroup has fewer
+constexpr int kCoopBoundThreads = 64 * 4 * kCoopMaxHeads;
+// Waves per SIMD the registers leave room for (NB = 1, 2: at most 128)
+constexpr int coop_waves_per_simd(int nb) { return nb <= 2 ? 4 : 3; }
 
 struct CoopGeom {
     FastDiv groups;         // workgroups per window position
@@ -38,25 +43,28 @@ struct CoopGeom {
     uint32_t xcd_remap, xcd_q, xcd_r;
 };
 
+// Mask tiles in LDS of the form that fetches one per window (PW == 2 below): two up to 48 tokens.
+__host__ __device__ constexpr uint32_t coop_mask_tiles(int nb) { return nb <= 3 ? 2u : 1u; }
+
 // KT < 4 promises that only the first KT of a lane's 4 columns in the last key block can be real
 // (L <= 16 (NB - 1) + KT, e.g. KT = 1 for L = 49): the others are zero without any arithmetic.
 // PW ("per window"): G is no multiple of the mask's period.  The registers then hold bias * log2e alone.
 // PW = 1, labels: those of a window travel with its slabs into LDS and phase A forms the mask per score
-// (AddendRegsLabels).  PW = 2, a dense mask: the tile of a window is fetched into LDS during phase B of the window
-// before, straight from memory and in whole lines (AddendRegsDense; every lane loading the values of its own row,
+// (AddendRegsLabels).  PW = 2, a dense mask: the tile of a window is fetched into LDS during the window before (L > 48:
+// during its phase B, there is room for one tile), straight from memory and in whole lines (AddendRegsDense; every lane loading the values of its own row,
 // 16 bytes of a line each, took 93 us instead of 53 below).  Stage 1 of two 800 x 1333 images (2784
 // windows, 3 heads, bias, mask of 1392 windows, dBias): 53 us with the reduction, 52 as labels; a kernel with one
 // wave per tile that such calls took before, 102.
 template <int NB, bool BM, bool DB, int KT, int PW>
-__global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf16_coop_kernel(BwdArgs p, CoopGeom gm) {
+__global__ void __launch_bounds__(kCoopBoundThreads) bwd_bf16_coop_kernel(BwdArgs p, CoopGeom gm) {
     constexpr int NB2 = (NB + 1) / 2;
     constexpr int ROWS = 16 * NB;
     extern __shared__ __attribute__((aligned(16))) uint4 lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t hl = wv >> 2;            // head inside the workgroup
-    const int role = (int)(wv & 3u);        // query block in phase A, key block in phase B
+    const uint32_t hl = wv / (uint32_t)NB;      // head inside the workgroup
+    const int role = (int)(wv % (uint32_t)NB);  // query block in phase A, key block in phase B
     // workgroups that share 128-byte lines (head groups of one window) are neighbours in the logical
     // order; when a group is not made of whole lines the order is mapped so that they share an XCD
     const uint32_t lb = gm.xcd_remap ? xcd_logical_block(blockIdx.x, gm.xcd_q, gm.xcd_r) : blockIdx.x;
@@ -69,11 +77,16 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
     const uint32_t stride = gm.stride;  // slab row stride in 16-byte units
     const float sl2 = p.scale * kLog2e;
-    const bool active = role < NB;
+    // Always true.  Below 49 tokens the branches on it keep the compiler from mixing the phases (NB = 3 with dBias: 142
+    // registers, 168 and 16 spills without them).
+    const bool active = NB == 4 || h < (uint32_t)p.heads;
 
-    // LDS: (PW == 2) the mask tile; slabs [K][V][Q][dO], each [ROWS][stride] uint4; then per head four bf16 tiles.
+    // LDS: (PW == 2) one or two mask tiles; slabs [K][V][Q][dO], each [ROWS][stride] uint4; then per head four bf16 tiles.
+    constexpr bool TWO = coop_mask_tiles(NB) == 2;  // PW == 2: room for the next window's tile beside the current one
+    constexpr bool TURN = KT == 4;  // row lengths that are multiples of 16 are not among those of a smaller KT
+    const uint32_t mask_units = PW == 2 ? mask_tile_bytes((uint32_t)L) / 16u : 0u;
     uint4* const lmask = lds;
-    uint4* const lk = lds + (PW == 2 ? mask_tile_bytes((uint32_t)L) / 16u : 0u);
+    uint4* const lk = lds + coop_mask_tiles(NB) * mask_units;
     uint4* const lv = lk + ROWS * stride;
     uint4* const lq = lk + 2 * ROWS * stride;
     uint4* const lg = lk + 3 * ROWS * stride;
@@ -98,7 +111,9 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
 
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 
-    // slab movement: thread -> (row, 16-byte column); one pass covers 64 rows
+    // slab movement: thread -> (row, 16-byte column); 4 hpb threads per row and 64 NB hpb threads: one pass covers
+    // the slab.  (rip < ROWS holds for every thread; without the branches on it the compiler mixes the stores with what
+    // stands around them: Swin-T stage 1 with bias, mask and dBias 128.4 -> 129.6 us.)
     const uint32_t rip = fastdiv((uint32_t)tid, gm.lanes_per_row);
     const uint32_t col = (uint32_t)tid - rip * gm.lanes_per_row.d;
     const uint32_t slab_bytes = (uint32_t)(L - 1) * row_bytes + hpb * 2u * kHeadDim;
@@ -130,17 +145,35 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     if (bw < (uint32_t)p.N) request(bw);  // in flight while the additive term is fetched
     // additive score term of this wave's query rows, in registers (see the file comment)
     f32x4 add[NB];
-    if (BM && active) {
+    if (BM) {
         const BiasSrc rb = bias_of_head(p, h);
         const MaskSrc msk = PW ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
-        const uint32_t i = (uint32_t)(16 * role + n);
-        addend_at(rb, mask_of_row(msk, i, (uint32_t)L), i, 4u * g, (uint32_t)L).fill(add, kLog2e);
+        bool filled = false;
+        if constexpr (NB == 4) {
+            filled = fill_in_lines<NB>(p, false);
+            if (filled) {
+                f32x4 one[1][NB];
+                const uint32_t rows0[1] = {(uint32_t)(16 * role)};
+                // through the exchange tiles of the head, which are not in use yet (the barrier that opens the first
+                // window stands between these reads and their first writes)
+                static_assert(NB * rows_fill_bytes<NB>() <= 4 * XT * 2, "the tiles hold the waves' stretches");
+                fill_rows_staged<1, NB>(one, rb, msk, rows0, (uint32_t)L, kLog2e, reinterpret_cast<char*>(ex) + role * rows_fill_bytes<NB>(), lane);
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb) add[jb] = one[0][jb];
+            }
+        }
+        if (!filled) {
+            const uint32_t i = (uint32_t)(16 * role + n);
+            addend_at(rb, mask_of_row(msk, i, (uint32_t)L), i, 4u * g, (uint32_t)L).fill(add, kLog2e);
+        }
     }
     const float mv = 16 * role + n < L ? p.mask_value * kLog2e : 0.f;
-    auto request_mask = [&](uint32_t w) { request_mask_tile(p, w, lds_offset(lmask), wv, 4u * hpb, (uint32_t)lane); };
+    auto request_mask = [&](uint32_t w, uint32_t tile) { request_mask_tile<TURN>(p, w, lds_offset(lmask) + tile * mask_units * 16u, wv, NB * hpb, (uint32_t)lane); };
     // this lane's query row of the mask tile; rows beyond L stay inside it (their results are dropped)
-    const float* const mask_row = reinterpret_cast<const float*>(lmask) + (16 * role + n < L ? 16 * role + n : L - 1) * L + 4 * g;
-    if (PW == 2 && bw < (uint32_t)p.N) request_mask(bw);
+    const int mask_i = 16 * role + n < L ? 16 * role + n : L - 1;
+    const float* const mask_row = reinterpret_cast<const float*>(lmask) + mask_i * L;
+    const uint32_t mask_turn = TURN ? mask_tile_turn((uint32_t)mask_i, (uint32_t)L) : 0u;
+    if (PW == 2 && bw < (uint32_t)p.N) request_mask(bw, 0u);
     if (bw < (uint32_t)p.N) park();
     if (PW == 2) lds_loads_done();
 
@@ -155,9 +188,11 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     // loads (the 48 wave-level loads of a workgroup queue at the CU's one address unit) then holds
     // up nobody else (stage 1: 135 -> 128 us, stage 2: 75 -> 70; spreading the four loads of a
     // thread over the stages of phase A adds nothing to that).
+    uint32_t mtile = 0u;  // PW == 2: the mask tile of the window
     for (uint32_t w = bw; w < (uint32_t)p.N; w += gm.G) {
         const bool has_next = w + gm.G < (uint32_t)p.N;
         __syncthreads();
+        if (PW == 2 && TWO && has_next) request_mask(w + gm.G, mtile ^ 1u);
         if (has_next) request(w + gm.G);  // in flight while this window is computed
 
         const size_t tile = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
@@ -177,7 +212,7 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
             // softmax of the block's rows: s <- exp(score - rowmax), inv = 1 / rowsum
             float inv;
             if (BM && PW == 2) {
-                const AddendRegsDense<NB> addend = {add, mask_row};
+                const AddendRegsDense<NB> addend = {add, mask_row + mtile * mask_units * 4u, mask_turn, (uint32_t)g};
                 inv = softmax_block<NB, true, AddendRegsDense<NB>, KT>(s, sl2, addend, L, g);
             } else if (BM && PW == 1) {
                 const AddendRegsLabels<NB> addend = {add, llab, llab[16 * qb + n], mv, g};
@@ -251,7 +286,7 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
                 __builtin_amdgcn_raw_buffer_store_b64(dq_hi, rdq, off_half + 32 + 16 * role * row_d, 0, 0);
             }
         }
-        if (PW == 2 && has_next) request_mask(w + gm.G);  // every wave has left phase A, the tile's only reader
+        if (PW == 2 && !TWO && has_next) request_mask(w + gm.G, 0u);  // every wave has left phase A, the tile's only reader
         if (active) {
             const int jb = role;
             f32x4 v0 = zero, v1 = zero, k0 = zero, k1 = zero;  // dV, dK [16 jb + n][4g + r] and [..][16 + 4g + r]
@@ -302,13 +337,13 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lv[loff]), make_rsrc((char*)p.dv + slab_d, slab_bytes_d), goff_d, 0, 0);
         }
         if (PW == 2) {  // the mask tile has landed; the two stores above are younger and not waited for
-            if (rip < (uint32_t)ROWS) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-            else lds_loads_done();
+            wait_vmem<2>();
+            if (TWO) mtile ^= 1u;
         }
         if (has_next) park();  // each thread overwrites the slab cells it has just read out
     }
 
-    if (DB && active) {
+    if (DB) {
         // partial sums in register order: [slot][head][qb][jb][lane] float4 -- contiguous 16-byte stores
         f32x4* dst = reinterpret_cast<f32x4*>(p.partial) + ((size_t)bw * p.heads + h) * (NB * NB * 64) + lane;
 #pragma unroll
@@ -316,10 +351,19 @@ __global__ void __launch_bounds__(64 * kCoopWavesPerTile * kCoopMaxHeads) bwd_bf
     }
 }
 
+// LDS of a workgroup: slabs, exchange tiles, and the mask tiles or the labels of a window where those come per window
+size_t coop_lds(int nb, int hpb, int L, bool mask_tiles, bool labels, uint32_t& stride) {
+    const size_t rows = (size_t)16 * nb;
+    const size_t tiles = hpb * 4 * rows * 64 * 2 + (mask_tiles ? coop_mask_tiles(nb) * mask_tile_bytes((uint32_t)L) : 0) + (labels ? rows * 4 : 0);
+    // one unit of padding per slab row, but where a dense mask tile per window takes its place: at 3 heads and
+    // L = 56 .. 64 the workgroup then fills the 160 KB of LDS exactly
+    stride = 4 * rows * (4 * hpb + 1) * 16 + tiles <= 160 * 1024 ? 4u * (uint32_t)hpb + 1u : 4u * (uint32_t)hpb;
+    return 4 * rows * stride * 16 + tiles;
+}
+
 template <int NB, bool BM, bool DB, int KT, int PW>
 hipError_t launch_coop_pw(const BwdArgs& a, const CoopGeom& gm, unsigned grid, unsigned block, size_t lds,
                           hipStream_t st) {
-    if (PW == 1) lds += (size_t)16 * NB * 4;  // the window's labels
     {
         const hipError_t e = allow_lds(reinterpret_cast<const void*>(&bwd_bf16_coop_kernel<NB, BM, DB, KT, PW>), lds);
         if (e != hipSuccess) return e;
@@ -355,13 +399,8 @@ hipError_t launch_coop_nb(const BwdArgs& a, int hpb, hipStream_t st) {
     gm.lanes_per_row = make_fastdiv(4u * (uint32_t)hpb);
     gm.heads_per_block = (uint32_t)hpb;
     gm.G = (uint32_t)a.slots;
-    const unsigned grid = gm.G * groups, block = 64u * kCoopWavesPerTile * (unsigned)hpb;
-    // one unit of padding per slab row, but where a dense mask tile per window takes its place: at 3 heads and
-    // L = 56 .. 64 the workgroup then fills the 160 KB of LDS exactly
-    const size_t mask_lds = a.per_window && a.mask ? mask_tile_bytes((uint32_t)a.L) : 0;
-    const size_t tiles = (size_t)hpb * 4 * (16 * NB) * 64 * 2 + mask_lds;
-    gm.stride = (size_t)4 * 16 * NB * (4 * hpb + 1) * 16 + tiles <= 160 * 1024 ? 4u * (uint32_t)hpb + 1u : 4u * (uint32_t)hpb;
-    const size_t lds = (size_t)4 * 16 * NB * gm.stride * 16 + tiles;
+    const unsigned grid = gm.G * groups, block = 64u * NB * (unsigned)hpb;
+    const size_t lds = coop_lds(NB, hpb, a.L, a.per_window && a.mask, a.per_window && a.labels, gm.stride);
     gm.xcd_remap = (hpb % 2 == 1 && groups > 1) ? 1u : 0u;
     gm.xcd_q = grid / 8u;
     gm.xcd_r = grid % 8u;
@@ -405,9 +444,34 @@ int coop_slots(long long N, int heads, int nW) {
     return (int)G;
 }
 
+// Heads per workgroup where the masks come per window: a dense tile at 33 to 48 tokens leaves a CU room for one workgroup of
+// two or three heads, but for three of one (2142 windows of 36 tokens, 4 heads, dBias: pairs 50.7 us, singly 46).
+int coop_window_heads_per_block(int heads, long long N, int nb, bool dense) {
+    return dense && nb == 3 ? 1 : coop_heads_per_block(heads, N);
+}
+
+// Window positions walked in parallel where the masks come per window, which leave no period to keep to.  From 33 tokens
+// on as above, as far as LDS holds the workgroups.  Below, LDS and registers hold more (one workgroup of a pair of heads
+// per CU left most of it idle): 4125 windows of 16 tokens, 8 heads, dense masks 87 us at one per CU, 40 at as many as fit;
+// 2600 of 25, 7 heads, labels, dBias 47.8 : 43.6.  With dBias every workgroup adds to what the reduction reads: more only
+// while each has eight windows, and not for the dense masks of single heads at 17 to 32 tokens (1600 windows, 6 heads
+// 30.8 us at three per CU, 35.0 at five).
+int coop_window_slots(long long N, int heads, int L, bool dense, bool dbias) {
+    const int nb = (L + 15) / 16, hpb = coop_window_heads_per_block(heads, N, nb, dense);
+    uint32_t stride;
+    const long long lds = (long long)coop_lds(nb, hpb, L, dense, !dense, stride);
+    const long long fit = std::max(1LL, std::min(160 * 1024 / lds, (long long)(4 * coop_waves_per_simd(nb) / (nb * hpb))));
+    const int groups = heads / hpb;
+    long long G = cu_count() * std::min(fit, hpb == 1 ? 3LL : 1LL) / groups;
+    if (nb == 1 || (nb == 2 && !(dense && dbias && hpb == 1)))
+        G = std::max(G, std::min(cu_count() * fit / groups, dbias ? N / 8 : N));
+    return (int)std::max(1LL, std::min(G, N));
+}
+
 hipError_t launch_backward_bf16_coop(const BwdArgs& a, hipStream_t s) {
-    const int hpb = coop_heads_per_block(a.heads, a.N);
-    switch ((a.L + 15) / 16) {
+    const int nb = (a.L + 15) / 16;
+    const int hpb = a.per_window ? coop_window_heads_per_block(a.heads, a.N, nb, a.mask != nullptr) : coop_heads_per_block(a.heads, a.N);
+    switch (nb) {
         case 1: return launch_coop_nb<1>(a, hpb, s);
         case 2: return launch_coop_nb<2>(a, hpb, s);
         case 3: return launch_coop_nb<3>(a, hpb, s);

@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
         if (PW == 1 && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab)[tid] = slab_labels;
     };
     auto request_mask = [&](uint32_t w, uint32_t buf) {
-        request_mask_tile(p, w, lds_offset(lds) + buf * mask_units * 16u, hl, hpb, (uint32_t)lane);
+        request_mask_tile<false>(p, w, lds_offset(lds) + buf * mask_units * 16u, hl, hpb, (uint32_t)lane);
     };
     if (PW == 2 && bw < (uint32_t)p.N) request_mask(bw, 0u);
     if (bw < (uint32_t)p.N) request(bw);  // in flight while the additive term is fetched
@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) fwd_bf16_persistent_kerne
             float inv;
             if (PW == 2) {  // rows beyond L stay inside the tile (their results are dropped)
                 const int i = 16 * qb + n < L ? 16 * qb + n : L - 1;
-                const AddendRegsDense<NB> addend = {add[qb], reinterpret_cast<const float*>(lds + mbuf * mask_units) + i * L + 4 * g};
+                const AddendRegsDense<NB> addend = {add[qb], reinterpret_cast<const float*>(lds + mbuf * mask_units) + i * L, 0u, (uint32_t)g};
                 inv = softmax_block<NB, true>(s, sl2, addend, L, g);
             } else if (PW == 1) {
                 const AddendRegsLabels<NB> addend = {add[qb], llab, tq[qb], mv, g};
@@ -574,7 +574,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
     // The windows of this workgroup: w0, w0 + step, ... below `end`
     uint32_t w0 = bw, step = gm.G, end = (uint32_t)p.N;
     auto request_mask = [&](uint32_t w, uint32_t b) {
-        request_mask_tile(p, w, lds_offset(lds) + b * mask_units * 16u, wave, (uint32_t)(HPB * W), (uint32_t)lane);
+        request_mask_tile<false>(p, w, lds_offset(lds) + b * mask_units * 16u, wave, (uint32_t)(HPB * W), (uint32_t)lane);
     };
     if (PW == 2 && w0 < end) request_mask(w0, 0u);  // in front of the first slab: it has landed when that is parked
     if (w0 < end) request(sa, w0);  // in flight while the additive term is fetched
@@ -632,7 +632,7 @@ __global__ void __launch_bounds__(64 * HPB * rowpersist_waves(NB)) fwd_bf16_rowp
             float mul, sum = 0.f, mb;
             if constexpr (PW == 2) {  // rows beyond L stay inside the tile (their results are dropped)
                 const int i = 16 * qb + n < L ? 16 * qb + n : L - 1;
-                const AddendRegsDense<NB> addend = {add, reinterpret_cast<const float*>(lds + buf * mask_units) + i * L + 4 * g};
+                const AddendRegsDense<NB> addend = {add, reinterpret_cast<const float*>(lds + buf * mask_units) + i * L, 0u, (uint32_t)g};
                 mb = softmax_scale_max<NB, true>(s, sl2, addend, L, g, mul);
             } else if (PW == 1) {
                 const int* const lab = llab + buf * ROWS;

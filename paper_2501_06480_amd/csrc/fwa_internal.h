@@ -92,7 +92,8 @@ bool forward_wide_supported(int L, int head_dim);
 hipError_t launch_forward_bf16_wide(const FwdArgs& a, hipStream_t s);
 hipError_t launch_backward_bf16(const BwdArgs& a, hipStream_t s);
 hipError_t launch_backward_f32(const BwdArgs& a, hipStream_t s);
-int backward_slots(long long N, int heads, int nW);
+int backward_slots(long long N, int heads, int nW, int L, bool mask, bool labels, bool dbias);
+int coop_window_slots(long long N, int heads, int L, bool dense, bool dbias);
 int backward_max_slots(long long N, int heads);
 int coop_slots(long long N, int heads, int nW);
 hipError_t launch_backward_bf16_coop(const BwdArgs& a, hipStream_t s);

@@ -274,15 +274,19 @@ struct addend_per_block { static constexpr bool value = false; };
 template <int NB>
 struct addend_per_block<AddendRegsLabels<NB>> { static constexpr bool value = true; };
 // AddendRegsDense: the same with a dense mask, whose tile [L, L] of the current window the kernel has staged in LDS.
-// `row` points at M[i][4g] of the lane's query row; keys beyond L read what follows and are overwritten with -inf.
+// `row` points at M[i][0] of the lane's query row, `turn` is mask_tile_turn of it; keys beyond L read what follows and are
+// overwritten with -inf.
 template <int NB>
 struct AddendRegsDense {
     const f32x4 (&a)[NB];
     const float* row;
+    uint32_t turn;
+    uint32_t g;
     __device__ __forceinline__ f32x4 block(int jb) const {
+        const float* const m = row + 4u * ((4u * (uint32_t)jb + g) ^ turn);
         f32x4 t;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t[r] = fmaf(row[16 * jb + r], kLog2e, a[jb][r]);
+        for (int r = 0; r < 4; ++r) t[r] = fmaf(m[r], kLog2e, a[jb][r]);
         return t;
     }
     __device__ __forceinline__ void fill(f32x4 (&add)[NB], float) const {
@@ -295,13 +299,22 @@ struct addend_per_block<AddendRegsDense<NB>> { static constexpr bool value = tru
 // LDS bytes of a staged mask tile: it is fetched in pieces of 1 KB per wave, and its last row is read up to column
 // 16 ceil(L / 16) - 1
 __host__ __device__ constexpr uint32_t mask_tile_bytes(uint32_t L) { return (L * L * 4u + 1023u) / 1024u * 1024u; }
+// Rows of 64, 128 and 256 bytes fall on the same banks 4, 8 and 16 at a time.  TURN: unit u (16 bytes) of such a row then
+// holds unit u ^ mask_tile_turn(row) of the mask; 0 for every other row length.
+__host__ __device__ constexpr uint32_t mask_tile_turn(uint32_t row, uint32_t L) {
+    return L == 64 ? row & 15u : L == 32 ? (row >> 1) & 7u : L == 16 ? (row >> 2) & 3u : 0u;
+}
 // Requests the dense mask tile of a window into LDS byte `to` (see load_to_lds): 1 KB pieces in turns over the
 // workgroup's `waves` waves, of which this is number `wave`.
-template <class Args>
+template <bool TURN, class Args>
 __device__ __forceinline__ void request_mask_tile(const Args& p, uint32_t w, uint32_t to, uint32_t wave, uint32_t waves, uint32_t lane) {
-    const uint32_t bytes = (uint32_t)p.L * (uint32_t)p.L * 4u;
+    const uint32_t L = (uint32_t)p.L, bytes = L * L * 4u;
     const char* const src = reinterpret_cast<const char*>(p.mask) + (size_t)(w % (uint32_t)p.nW) * bytes;
-    for (uint32_t c = wave * 1024u; c < bytes; c += waves * 1024u) load_to_lds(src + c, bytes - c, lane * 16u, to + c);
+    for (uint32_t c = wave * 1024u; c < bytes; c += waves * 1024u) {
+        uint32_t unit = lane;
+        if (TURN && (L == 64 || L == 32 || L == 16)) unit ^= mask_tile_turn((c / 16u + lane) / (L / 4u), L);  // stays inside its row
+        load_to_lds(src + c, bytes - c, unit * 16u, to + c);
+    }
 }
 
 struct AddendNone {

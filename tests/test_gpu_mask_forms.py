@@ -49,13 +49,21 @@ def test_large_window_backward(oracle, name, L, heads, N, nW, use_bias, dbias):
 
 # The backward for windows of up to 64 tokens with a mask period that no slot count is a multiple of: labels parked in
 # LDS, or a dense tile fetched into LDS per window.  Tiles of less than, exactly and more than a 1 KB piece; 3 heads at
-# L = 55 and 56 (with and without room for the padding of the slab rows) and 64; 1, 2 and 3 heads per workgroup; idle
-# waves (L <= 48); the trimmed last key block (L = 17, 33, 49).
+# L = 55 and 56 (with and without room for the padding of the slab rows) and 64; 1, 2 and 3 heads per workgroup (1 for
+# dense tiles of L = 33 .. 48); row lengths whose tiles are stored turned (L = 16, 32, 64); several workgroups per CU
+# (L <= 32), with one window and with many per workgroup; the trimmed last key block (L = 17, 33, 49).
 # name, L, heads, N, nW, bias, dbias
 SMALL = [
     ("L16", 16, 3, 600, 300, True, True),
     ("L17_pairs", 17, 4, 280, 140, True, False),
+    ("L16_pairs", 16, 8, 1200, 600, True, True),
+    ("L16_more_windows_than_workgroups", 16, 4, 1750, 875, False, False),
+    ("L25_single_heads", 25, 7, 900, 450, True, True),
+    ("L32_pairs", 32, 4, 560, 280, True, True),
+    ("L32", 32, 3, 410, 410, True, False),
     ("L33_single_heads", 33, 24, 80, 40, True, True),
+    ("L36", 36, 3, 520, 520, False, False),
+    ("L48_pairs", 48, 2, 300, 300, True, True),
     ("L49", 49, 3, 600, 300, True, True),
     ("L49_mask_alone", 49, 2, 300, 300, False, True),
     ("L55", 55, 3, 300, 300, True, True),
