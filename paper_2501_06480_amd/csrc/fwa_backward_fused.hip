@@ -458,23 +458,25 @@ __global__ void __launch_bounds__(64 * fused_waves(NB)) bwd_bf16_fused_kernel(Bw
 //                                              44.2 : 42.8 (2048), 60.3 : 67.7 (3072)
 //   NB = 11                                    up to four rounds.  L = 169: 21.8 : 15.4 (256), 49.8 : 49.0 (1024), 67.7 : 69.8 (1536)
 //   the others (9, 10: three blocks for one wave; from 12 on the second block of most waves): only in the first two
-//                                              rounds and where the last one is nearly full, since a round takes its time
-//                                              whatever it holds.  L = 144: 12.7 : 14.3 (64), 24.5 : 21.6 (512), 32.1 : 36.4 (768),
-//                                              39.0 : 37.1 (1024); L = 256: 18.6 : 22.6 (64), 30.8 : 24.7 (256), 39.2 : 44.2 (384),
-//                                              48.6 : 44.7 (512), 82.2 : 85.7 (1024)
-bool fused_pays(int nb, bool term, long long tiles, long long resident) {
+//                                              rounds, and where the pair's keys kernel walks two windows in the first, four
+//                                              (NB = 9, 10: six) in the second: both sides go up in steps.  (tiles; windows)
+//                                              L = 144: 12.7 : 14.3 (64; 1), 24.5 : 21.6 (512; 4), 32.1 : 36.4 (768; 5),
+//                                              39.0 : 37.1 (1024; 7); with 16 heads and labels 44.5 : 42.2 (864; 6);
+//                                              L = 225, 3 heads 31.4 : 24.2 (144; 2), 8 heads and labels 53.9 : 48.4 (432; 4);
+//                                              L = 256: 18.6 : 22.6 (64; 1), 30.8 : 24.7 (256; 2), 39.2 : 44.2 (384; 3),
+//                                              48.6 : 44.7 (512; 4), 82.2 : 85.7 (1024)
+bool fused_pays(int nb, bool term, long long tiles, long long resident, long long windows) {
     if (!term) return true;
     if (nb <= 6) return tiles <= 3 * resident;
     if (nb <= 8) return tiles <= 4 * resident;
     if (nb == 11) return tiles <= 4 * resident;
     const long long before = (tiles - 1) / resident * resident;  // tiles of the full rounds
     if (before > resident) return false;
-    const long long last = 8 * (tiles - before);
-    return last >= (before ? 7 : nb <= 10 ? 3 : 5) * resident;
+    return before > 0 ? windows >= (nb <= 10 ? 6 : 4) : windows >= 2;
 }
 
 template <int NB, int HB, int HM>
-hipError_t launch_fused_one(const BwdArgs& a, hipStream_t st, bool forced, bool& taken) {
+hipError_t launch_fused_one(const BwdArgs& a, hipStream_t st, bool forced, long long windows, bool& taken) {
     constexpr int W = fused_waves(NB);
     const void* fn = reinterpret_cast<const void*>(&bwd_bf16_fused_kernel<NB, HB, HM>);
     const unsigned block = 64u * W;
@@ -484,7 +486,7 @@ hipError_t launch_fused_one(const BwdArgs& a, hipStream_t st, bool forced, bool&
     const hipError_t e = workgroups_per_cu(fn, block, lds, once, per_cu);
     if (e != hipSuccess) return e;
     const long long resident = (long long)cu_count() * per_cu;
-    taken = forced || fused_pays(NB, HB != 0 || HM != 0, a.N * (long long)a.heads, resident);
+    taken = forced || fused_pays(NB, HB != 0 || HM != 0, a.N * (long long)a.heads, resident, windows);
     if (!taken) return hipSuccess;
     FusedGeom gm;
     gm.heads = (uint32_t)a.heads;
@@ -500,35 +502,36 @@ hipError_t launch_fused_one(const BwdArgs& a, hipStream_t st, bool forced, bool&
 }
 
 template <int NB>
-hipError_t launch_fused_nb(const BwdArgs& a, hipStream_t st, bool forced, bool& taken) {
+hipError_t launch_fused_nb(const BwdArgs& a, hipStream_t st, bool forced, long long windows, bool& taken) {
     if (a.bias) {
-        if (a.labels) return launch_fused_one<NB, 1, 2>(a, st, forced, taken);
-        return a.mask ? launch_fused_one<NB, 1, 1>(a, st, forced, taken) : launch_fused_one<NB, 1, 0>(a, st, forced, taken);
+        if (a.labels) return launch_fused_one<NB, 1, 2>(a, st, forced, windows, taken);
+        return a.mask ? launch_fused_one<NB, 1, 1>(a, st, forced, windows, taken) : launch_fused_one<NB, 1, 0>(a, st, forced, windows, taken);
     }
-    if (a.labels) return launch_fused_one<NB, 0, 2>(a, st, forced, taken);
-    return a.mask ? launch_fused_one<NB, 0, 1>(a, st, forced, taken) : launch_fused_one<NB, 0, 0>(a, st, forced, taken);
+    if (a.labels) return launch_fused_one<NB, 0, 2>(a, st, forced, windows, taken);
+    return a.mask ? launch_fused_one<NB, 0, 1>(a, st, forced, windows, taken) : launch_fused_one<NB, 0, 0>(a, st, forced, windows, taken);
 }
 
 }  // namespace
 
-// `taken` tells whether the call was launched: always with `forced`, else where this kernel is the faster one
-hipError_t launch_backward_bf16_fused(const BwdArgs& a, hipStream_t st, bool forced, bool& taken) {
+// `taken` tells whether the call was launched: always with `forced`, else where this kernel is the faster one; `windows`: per
+// workgroup of the keys kernel, were the pair to run
+hipError_t launch_backward_bf16_fused(const BwdArgs& a, hipStream_t st, bool forced, long long windows, bool& taken) {
     taken = false;
     if (a.dbias) return hipSuccess;  // the keys kernel sums it up
     if (a.bias && a.bias_bf16) return hipErrorInvalidValue;  // the caller hands over an fp32 copy
     switch ((a.L + 15) / 16) {
-        case 5: return launch_fused_nb<5>(a, st, forced, taken);
-        case 6: return launch_fused_nb<6>(a, st, forced, taken);
-        case 7: return launch_fused_nb<7>(a, st, forced, taken);
-        case 8: return launch_fused_nb<8>(a, st, forced, taken);
-        case 9: return launch_fused_nb<9>(a, st, forced, taken);
-        case 10: return launch_fused_nb<10>(a, st, forced, taken);
-        case 11: return launch_fused_nb<11>(a, st, forced, taken);
-        case 12: return launch_fused_nb<12>(a, st, forced, taken);
-        case 13: return launch_fused_nb<13>(a, st, forced, taken);
-        case 14: return launch_fused_nb<14>(a, st, forced, taken);
-        case 15: return launch_fused_nb<15>(a, st, forced, taken);
-        case 16: return launch_fused_nb<16>(a, st, forced, taken);
+        case 5: return launch_fused_nb<5>(a, st, forced, windows, taken);
+        case 6: return launch_fused_nb<6>(a, st, forced, windows, taken);
+        case 7: return launch_fused_nb<7>(a, st, forced, windows, taken);
+        case 8: return launch_fused_nb<8>(a, st, forced, windows, taken);
+        case 9: return launch_fused_nb<9>(a, st, forced, windows, taken);
+        case 10: return launch_fused_nb<10>(a, st, forced, windows, taken);
+        case 11: return launch_fused_nb<11>(a, st, forced, windows, taken);
+        case 12: return launch_fused_nb<12>(a, st, forced, windows, taken);
+        case 13: return launch_fused_nb<13>(a, st, forced, windows, taken);
+        case 14: return launch_fused_nb<14>(a, st, forced, windows, taken);
+        case 15: return launch_fused_nb<15>(a, st, forced, windows, taken);
+        case 16: return launch_fused_nb<16>(a, st, forced, windows, taken);
         default: return hipErrorInvalidValue;
     }
 }

@@ -816,17 +816,26 @@ LargeGeom large_geom(const BwdArgs& a, int parts, long long G, unsigned& grid) {
 
 // Window positions walked in parallel, `resident` = as many as the chip holds at once.  Without a mask period: those,
 // at most one per window.  With one, a workgroup that keeps its additive term needs a multiple of it: the largest
-// that is resident, or, for a dense mask (`dense`), more than are resident at once, in several rounds, as long as
-// the cost in windows -- rounds times (windows per workgroup + about one and a half for fetching the term) -- stays
-// below that of the kernels that read the mask per window, 1.35 times as long per window (L = 256: 210 against 154 us
-// and 283 against 185).  0: those, or for labels the per-window form.  `most`: an upper limit (the dBias slots).
-long long walk_slots(long long resident, long long most, long long N, long long period, bool dense) {
+// that is resident, unless what the rounding leaves idle costs more than the form that takes the mask per window and has
+// no period to keep to (0 is returned for that one): per window it takes 1.08 times as long with labels, 1.35 times with
+// a dense mask (kept : per window, us, labels: 125 windows of 256 tokens, 3 heads, period 25 53.9 : 42.8; 270 of 196, 9
+// heads, period 9 219 : 172; 1440 of 81, 1 head, period 144, dBias 46.4 : 39.8; where nothing is rounded away, 1448 of 225,
+// 2 heads, period 4, dBias 218 : 238; 1512 of 256, 1 head, period 12 137 : 150).  For a dense mask with a longer period
+// (`rounds`) more than are resident at once, in several rounds, as long as the cost in windows -- rounds times (windows per workgroup + about one and a half for fetching the term) -- stays
+// below that of the kernels that read the mask per window (L = 256: 210 against 154 us
+// and 283 against 185).  `most`: an upper limit (the dBias slots).
+long long walk_slots(long long resident, long long most, long long N, long long period, bool dense, bool rounds) {
     if (resident < 1) resident = 1;
     long long G = resident < most ? resident : most;
     if (G > N) G = N;
     const long long fit = G / period * period;
-    if (fit > 0 || !dense) return fit;
-    const double stream = 1.35 * (double)((N + G - 1) / G);
+    const double whole = (double)((N + G - 1) / G);  // windows per workgroup with nothing rounded away
+    if (fit > 0) {
+        const double kept = (double)((N + fit - 1) / fit);
+        return kept > (dense ? 1.35 * whole + 1.0 : 1.08 * whole + 0.5) ? 0 : fit;
+    }
+    if (!rounds) return 0;
+    const double stream = 1.35 * whole;
     long long best = 0;
     double best_cost = stream;
     for (long long c = period; c <= N && c <= most && c <= 16 * resident; c += period) {
@@ -844,7 +853,7 @@ hipError_t launch_rows(const BwdArgs& a, long long period, hipStream_t st, bool&
     int per_cu = 1;
     const hipError_t e = workgroups_per_cu(fn, block, rows_lds<NB>(), once, per_cu);
     if (e != hipSuccess) return e;
-    const long long G = walk_slots((long long)cu_count() * per_cu / ((long long)a.heads * rows_parts(NB)), a.N, a.N, period, a.mask != nullptr);
+    const long long G = walk_slots((long long)cu_count() * per_cu / ((long long)a.heads * rows_parts(NB)), a.N, a.N, period, a.mask != nullptr, a.mask != nullptr);
     fits = G > 0;
     if (!fits) return hipSuccess;
     unsigned grid;
@@ -862,20 +871,20 @@ hipError_t launch_rows_stream(const BwdArgs& a, hipStream_t st) {
     const hipError_t e = workgroups_per_cu(fn, block, stream_lds<NB>(), once, per_cu);
     if (e != hipSuccess) return e;
     unsigned grid;
-    const LargeGeom gm = large_geom(a, 1, walk_slots((long long)cu_count() * per_cu / a.heads, a.N, a.N, 1, false), grid);
+    const LargeGeom gm = large_geom(a, 1, walk_slots((long long)cu_count() * per_cu / a.heads, a.N, a.N, 1, false, false), grid);
     hipLaunchKernelGGL((bwd_bf16_rows_stream_kernel<NB, HB>), dim3(grid), dim3(block), stream_lds<NB>(), st, a, gm);
     return hipGetLastError();
 }
 
 // window slots of the keys kernel (0: none fits the period)
 template <int NB, int TERM, bool DB>
-hipError_t keys_slots(const BwdArgs& a, long long period, bool dense, long long& G) {
+hipError_t keys_slots(const BwdArgs& a, long long period, bool rounds, long long& G) {
     static std::atomic<int> once{0};
     int per_cu = 1;
     const hipError_t e = workgroups_per_cu(reinterpret_cast<const void*>(&bwd_bf16_keys_kernel<NB, TERM, DB>), 64u * keys_waves(NB), keys_lds<NB>(), once, per_cu);
     const long long resident = (long long)cu_count() * per_cu / ((long long)a.heads * keys_parts(NB));
     const long long most = DB ? a.slots : a.N;  // the workspace holds a.slots partial sums per head
-    G = walk_slots(resident, most, a.N, period, dense);
+    G = walk_slots(resident, most, a.N, period, a.mask != nullptr, rounds);
     return e;
 }
 // dK, dV and, with DB, the dBias partial sums and their reduction
@@ -908,13 +917,14 @@ hipError_t launch_large_nb(const BwdArgs& a, hipStream_t st) {
     const long long period = mask_period(a);
     if (!a.dbias) {
         bool forced = !bm, taken = false;
-        if (a.mask) {
-            long long G = 0;
-            const hipError_t q = keys_slots<NB, kTermKept, false>(a, period, NB <= 6, G);
+        long long G = 1;  // of the keys kernel as it would run
+        if (bm) {
+            hipError_t q = keys_slots<NB, kTermKept, false>(a, period, a.mask && NB <= 6, G);
+            forced = a.mask && G == 0;
+            if (q == hipSuccess && G == 0) q = keys_slots<NB, kTermKept, false>(a, 1, false, G);
             if (q != hipSuccess) return q;
-            forced = G == 0;
         }
-        const hipError_t e = launch_backward_bf16_fused(a, st, forced, taken);
+        const hipError_t e = launch_backward_bf16_fused(a, st, forced, (a.N + G - 1) / G, taken);
         if (e != hipSuccess || taken) return e;
     }
     bool fits = false;

@@ -98,7 +98,7 @@ int backward_max_slots(long long N, int heads);
 int coop_slots(long long N, int heads, int nW);
 hipError_t launch_backward_bf16_coop(const BwdArgs& a, hipStream_t s);
 hipError_t launch_backward_bf16_large(const BwdArgs& a, hipStream_t s);
-hipError_t launch_backward_bf16_fused(const BwdArgs& a, hipStream_t s, bool forced, bool& taken);
+hipError_t launch_backward_bf16_fused(const BwdArgs& a, hipStream_t s, bool forced, long long windows, bool& taken);
 // Workgroups of `fn` one CU holds (LDS and registers decide), asked once per kernel
 hipError_t workgroups_per_cu(const void* fn, unsigned block, size_t lds, std::atomic<int>& once, int& per_cu);
 hipError_t launch_backward_bf16_wide(const BwdArgs& a, hipStream_t s);

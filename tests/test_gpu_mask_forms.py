@@ -1,7 +1,8 @@
 """The forms in which the backward for windows of more than 64 tokens takes its additive term, each at the sizes
 where the choice between them falls, against the fp64 oracle: kept in registers (the number of workgroups in flight
 is a multiple of the mask period, or more workgroups than are resident are launched), the mask formed per window from
-labels, and a dense mask read per window.  The block counts cover odd ones, whose last workgroup has idle waves."""
+labels, and a dense mask read per window, both also where a multiple of the period would fit but leave much of the
+device idle.  The block counts cover odd ones, whose last workgroup has idle waves."""
 import numpy as np
 import pytest
 
@@ -16,6 +17,11 @@ CASES = [
     ("kept_idle_waves", 129, 3, 96, 8, True, True),
     ("kept_last_part_one_block", 193, 2, 64, 4, True, False),
     ("more_workgroups_than_resident", 65, 24, 960, 40, True, True),
+    ("more_workgroups_than_resident_no_dbias", 65, 24, 960, 40, True, False),
+    ("rounding_loses_labels", 256, 3, 100, 25, True, True),
+    ("rounding_loses_labels_no_dbias", 241, 3, 150, 25, True, False),
+    ("rounding_loses_dense", 193, 2, 288, 36, True, True),
+    ("rounding_loses_dense_no_dbias", 193, 2, 288, 36, True, False),
     ("beyond_L65", 65, 24, 100, 50, True, True),
     ("beyond_L65_no_bias", 65, 24, 100, 50, False, True),
     ("beyond_L81_no_dbias", 81, 24, 100, 50, True, False),

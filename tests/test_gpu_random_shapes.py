@@ -22,7 +22,7 @@ ELEMENTS = 2_000_000          # cap on N*L*C per tensor: the oracle stays within
 def draw_case(i, long_period=False):
     """The i-th combination (a pure function of i).  long_period: mask periods of 16 to 512 windows, which
     decide how many windows a persistent workgroup may walk; beyond the slot counts, labels make the
-    kernels form each window's mask themselves and dense masks go to the kernels without a walk."""
+    kernels form each window's mask themselves, and dense masks are fetched or read per window."""
     r = synth.rng(424200 + i)
     dtype = "f32" if r.random() < 0.25 else "bf16"
     wide = r.random() < 0.3

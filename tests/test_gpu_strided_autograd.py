@@ -79,6 +79,35 @@ def test_strided_dbias_and_stride_checks():
     assert lib.fwa_forward_strided(*args, w.C + 4, w.C, *tail) == binding.FWA_ERR_ALIGN      # rows not 16-byte aligned
 
 
+# rows and keys kernels: the row statistics between them travel inside the dV and dK rows, wherever those lie
+@pytest.mark.parametrize("L,heads,N,nW", [(65, 3, 40, 4), (100, 5, 24, 8), (144, 3, 18, 9), (196, 4, 12, 4), (241, 1, 70, 70)])
+@pytest.mark.parametrize("as_labels", [False, True])
+def test_strided_large_windows_with_dbias(oracle, L, heads, N, nW, as_labels):
+    import torch
+    import paper_2501_06480_amd as fwa
+    w = synth.Workload(f"strided_db_L{L}_h{heads}", N, L, heads * 32, heads, "bf16", 9300 + L + heads, 0, backward=True)
+    x = synth.draw(w)
+    bias_np = synth.normal((heads, L, L), 71 + L, 0.5)
+    labels = synth.rng(73 + L).integers(0, 3, (nW, L)).astype(np.int32)
+    mask = np.where(labels[:, :, None] == labels[:, None, :], 0.0, -3.0).astype(np.float32)
+    kw = {"labels": torch.from_numpy(labels).cuda(), "mask_value": -3.0} if as_labels else {"mask": f32_device(mask)}
+    q, k, v, g = (to_device(x, w, n) for n in ("q", "k", "v", "d_o"))
+    _, (qs, ks, vs) = fused_views(x, w, ("q", "k", "v"), torch)
+    gbuf = torch.full((N, L, 2, heads * 32), 5.0, dtype=torch.bfloat16, device="cuda")
+    gbuf[:, :, 1] = g
+    dbuf, dviews = fused_views(x, w, (None, None, None), torch)
+    dbuf.fill_(3.0)
+    ref = fwa.fwa_backward(q, k, v, g, heads, w.scale, f32_device(bias_np), want_dbias=True, **kw)
+    got = fwa.fwa_backward(qs, ks, vs, gbuf[:, :, 1], heads, w.scale, f32_device(bias_np), want_dbias=True, out=tuple(dviews), **kw)
+    torch.cuda.synchronize()
+    for a, b, nme in zip(ref, got, ("dq", "dk", "dv", "dbias")):
+        assert torch.equal(a, b), nme
+    want = oracle.backward(x["q"], x["k"], x["v"], x["d_o"], heads, w.scale, bias_np, mask)
+    for a, b, nme in zip(got, want, ("dq", "dk", "dv")):
+        check_bf16_output(to_f64(a), b, nme)
+    assert max_abs(to_f64(got[3]), want[3]) <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("fused", [False, True])
 @pytest.mark.parametrize("as_labels", [False, True])
 def test_autograd_wrappers_against_the_oracle(oracle, fused, as_labels):
