@@ -375,8 +375,6 @@ int backward_impl(const void* q, const void* k, const void* v, const void* d_o, 
     a.partial = dbias ? reinterpret_cast<float*>(ws) : nullptr;
     a.bias = bias; a.bias_bf16 = bias && bias_dtype == FWA_BF16;
     a.ldq = (int)ld_qkv; a.ldg = (int)ld_do; a.ldd = (int)ld_dqkv; a.f16 = dtype == FWA_F16;
-    // more head groups than the chip holds workgroups: fp32 biases only, as ever
-    if (a.bias_bf16 && small && !periodic && fwa::coop_slots(N, heads, 1) == 0) return FWA_ERR_UNSUPPORTED;
     const hipError_t e = dtype != FWA_F32 ? fwa::launch_backward_bf16(a, st) : fwa::launch_backward_f32(a, st);
     return e == hipSuccess ? FWA_OK : FWA_ERR_LAUNCH;
 }

@@ -129,3 +129,37 @@ def test_small_window_forward_long_periods(oracle, name, L, heads, N, nW, use_bi
         o = fwa.fwa_forward(q, k, v, heads, w.scale, f32_device(bias), **kw)
         torch.cuda.synchronize()
         check_forward_arithmetic_bound(to_f64(o), want, spread, f"{name} {form}")
+
+
+# The backward for windows of up to 64 tokens with more groups of heads than the chip holds workgroups: one workgroup per
+# group walks all windows.  The mask periods leave no other choice than a mask per window.
+# heads, L, N, nW (0: no mask), bias type, dbias
+MANY_HEADS = [(771, 9, 2, 0, "f32", True), (771, 9, 2, 0, "bf16", True), (1026, 5, 3, 3, "f32", True),
+              (1026, 17, 2, 2, "f32", False), (773, 4, 4, 4, "bf16", True), (775, 33, 1, 1, "bf16", True)]
+
+
+@pytest.mark.parametrize("heads,L,N,nW,bias_type,dbias", MANY_HEADS)
+def test_more_head_groups_than_workgroups(oracle, heads, L, N, nW, bias_type, dbias):
+    import torch
+    import paper_2501_06480_amd as fwa
+    w = synth.Workload(f"many_heads_{heads}_{L}", N, L, 32 * heads, heads, "bf16", 8900 + heads + L, 0, backward=True)
+    x = synth.draw(w)
+    bias = synth.normal((heads, L, L), 8950 + L, 0.5)
+    if bias_type == "bf16":
+        bias = synth.bf16_round(bias.astype(np.float32))[0]
+    bias_d = f32_device(bias) if bias_type == "f32" else f32_device(bias).bfloat16()
+    labels = synth.rng(8960 + L).integers(0, 3, (max(nW, 1), L)).astype(np.int32)
+    mask = np.where(labels[:, :, None] == labels[:, None, :], 0.0, -3.0).astype(np.float32) if nW else None
+    ref = oracle.backward(x["q"], x["k"], x["v"], x["d_o"], heads, w.scale, bias, mask)
+    q, k, v, g = (to_device(x, w, n) for n in ("q", "k", "v", "d_o"))
+    forms = [{}] if not nW else [{"labels": torch.from_numpy(labels).cuda(), "mask_value": -3.0}]
+    if nW and bias_type == "f32":
+        forms.append({"mask": f32_device(mask)})
+    for kw in forms:
+        print(f"heads={heads} L={L} N={N} nW={nW} bias={bias_type} dbias={dbias} {list(kw)}", flush=True)
+        got = fwa.fwa_backward(q, k, v, g, heads, w.scale, bias_d, want_dbias=dbias, **kw)
+        torch.cuda.synchronize()
+        for what, a, b in zip(("dq", "dk", "dv"), got, ref):
+            check_bf16_output(to_f64(a), b, f"{heads} heads {list(kw)} {what}")
+        if dbias:
+            assert max_abs(to_f64(got[3]), ref[3]) <= TOL["bf16"], list(kw)
