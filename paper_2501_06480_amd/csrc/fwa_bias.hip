@@ -27,23 +27,24 @@ __global__ void bias_gather_kernel(const float* __restrict__ table, float* __res
 constexpr int kScatterLanes = 16;
 __global__ void bias_scatter_kernel(const float* __restrict__ dbias, float* __restrict__ dtable, int heads, int k) {
     const int L = k * k, W = 2 * k - 1, T = W * W;
-    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int e = (int)(t / kScatterLanes), lane = (int)(t % kScatterLanes);
-    if (e >= heads * T) return;  // all lanes of an entry
-    const int h = e / T;
-    const int dy = (e % T) / W - (k - 1);
-    const int dx = (e % T) % W - (k - 1);
-    const int y0 = max(0, dy), x0 = max(0, dx), nx = k - abs(dx), count = (k - abs(dy)) * nx;
-    const float* src = dbias + (size_t)h * L * L;
-    float acc = 0.f;
+    const int lane = (int)(threadIdx.x % kScatterLanes);
+    // total below 2^31, a step of at most 2^27; the lanes of an entry leave together
+    const uint32_t total = (uint32_t)heads * (uint32_t)T, step = gridDim.x * (blockDim.x / kScatterLanes);
+    for (uint32_t e = blockIdx.x * (blockDim.x / kScatterLanes) + threadIdx.x / kScatterLanes; e < total; e += step) {
+        const int h = (int)e / T, at = (int)e % T;
+        const int dy = at / W - (k - 1), dx = at % W - (k - 1);
+        const int y0 = max(0, dy), x0 = max(0, dx), nx = k - abs(dx), count = (k - abs(dy)) * nx;
+        const float* src = dbias + (size_t)h * L * L;
+        float acc = 0.f;
 #pragma unroll 4
-    for (int c = lane; c < count; c += kScatterLanes) {
-        const int yi = y0 + c / nx, xi = x0 + c % nx;
-        acc += src[(size_t)(yi * k + xi) * L + (yi - dy) * k + (xi - dx)];
-    }
+        for (int c = lane; c < count; c += kScatterLanes) {
+            const int yi = y0 + c / nx, xi = x0 + c % nx;
+            acc += src[(size_t)(yi * k + xi) * L + (yi - dy) * k + (xi - dx)];
+        }
 #pragma unroll
-    for (int d = kScatterLanes / 2; d > 0; d /= 2) acc += __shfl_xor(acc, d, kScatterLanes);
-    if (lane == 0) dtable[e] = acc;
+        for (int d = kScatterLanes / 2; d > 0; d /= 2) acc += __shfl_xor(acc, d, kScatterLanes);
+        if (lane == 0) dtable[e] = acc;
+    }
 }
 
 __global__ void zero_f32_kernel(float* __restrict__ dst, size_t count) {
@@ -81,8 +82,12 @@ hipError_t launch_bias_gather(const float* table, float* bias, int heads, int k,
 }
 
 hipError_t launch_bias_scatter(const float* dbias, float* dtable, int heads, int k, hipStream_t s) {
-    const long long threads = (long long)heads * (2 * k - 1) * (2 * k - 1) * kScatterLanes;
-    hipLaunchKernelGGL(bias_scatter_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, dbias, dtable, heads, k);
+    // a launch holds fewer than 2^32 threads: beyond 2^27 entries the workgroups take several each
+    const long long total = (long long)heads * (2 * k - 1) * (2 * k - 1);
+    if (total > 0x7fffffffLL) return hipErrorInvalidValue;
+    const long long per_block = 256 / kScatterLanes, blocks = (total + per_block - 1) / per_block;
+    const unsigned grid = (unsigned)(blocks < (1LL << 23) ? blocks : (1LL << 23));
+    hipLaunchKernelGGL(bias_scatter_kernel, dim3(grid), dim3(256), 0, s, dbias, dtable, heads, k);
     return hipGetLastError();
 }
 

@@ -23,3 +23,12 @@ def test_scatter(heads, k):
     # at most 16 additions in a row and four levels of the tree, each rounding once by 2^-24 of a partial sum
     assert (np.abs(got[0] - want) <= 20 * 2.0 ** -24 * bound).all()
     assert np.array_equal(got[0], got[1])
+
+
+def test_more_entries_than_a_launch_has_room_for():
+    """16 lanes per entry of 2^28 + 5 entries are more threads than one launch holds."""
+    import torch
+    import paper_2501_06480_amd as fwa
+    heads = 2 ** 28 + 5
+    db = torch.arange(heads, dtype=torch.float32, device="cuda").view(heads, 1, 1)
+    assert torch.equal(fwa.fwa_bias_scatter(db, 1).view(-1), db.view(-1))
