@@ -147,7 +147,9 @@ int fwa_backward_strided(const void* q, const void* k, const void* v, const void
  * Everything else (shapes, strides, dtype, workspace, error codes, supported ranges) is as in
  * fwa_forward_strided / fwa_backward_strided, and the results are those of the same call with
  * the dense mask written out from the labels: bit for bit while nW is small enough for a
- * workgroup to keep one mask tile for life (nW <= 256 / heads-per-workgroup, roughly), and to
+ * workgroup to keep one mask tile for life (nW <= 256 / heads-per-workgroup, roughly, and
+ * for the backward above 64 tokens as long as a number of workgroups that is a multiple of nW
+ * leaves less than about a quarter of the device idle), and to
  * within a rounding of the additive term beyond, where the dense form reads each window's
  * mask tile and this form makes it from the window's labels.
  */

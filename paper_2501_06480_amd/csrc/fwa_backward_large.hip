@@ -816,14 +816,15 @@ LargeGeom large_geom(const BwdArgs& a, int parts, long long G, unsigned& grid) {
 
 // Window positions walked in parallel, `resident` = as many as the chip holds at once.  Without a mask period: those,
 // at most one per window.  With one, a workgroup that keeps its additive term needs a multiple of it: the largest
-// that is resident, unless what the rounding leaves idle costs more than the form that takes the mask per window and has
-// no period to keep to (0 is returned for that one): per window it takes 1.08 times as long with labels, 1.35 times with
-// a dense mask (kept : per window, us, labels: 125 windows of 256 tokens, 3 heads, period 25 53.9 : 42.8; 270 of 196, 9
-// heads, period 9 219 : 172; 1440 of 81, 1 head, period 144, dBias 46.4 : 39.8; where nothing is rounded away, 1448 of 225,
-// 2 heads, period 4, dBias 218 : 238; 1512 of 256, 1 head, period 12 137 : 150).  For a dense mask with a longer period
-// (`rounds`) more than are resident at once, in several rounds, as long as the cost in windows -- rounds times (windows per workgroup + about one and a half for fetching the term) -- stays
-// below that of the kernels that read the mask per window (L = 256: 210 against 154 us
-// and 283 against 185).  `most`: an upper limit (the dBias slots).
+// that is resident, unless the rounding leaves so much idle that the form that takes the mask per window, and has no
+// period to keep to, is faster (0 is returned for that one).  Per window it takes 1.35 times as long with a dense mask.
+// With labels only 1.08 times, but while a call keeps its term its results are those of the dense mask bit for bit, which
+// is not given up for less than a quarter of the time (kept : per window, us, labels: 125 windows of 256 tokens, 3 heads,
+// period 25 53.9 : 42.8; 270 of 196, 9 heads, period 9 219 : 172; where nothing is rounded away, 1448 of 225, 2 heads,
+// period 4, dBias 218 : 238; 1512 of 256, 1 head, period 12 137 : 150).  For a dense mask with a longer period (`rounds`)
+// more than are resident at once, in several rounds, as long as the cost in windows -- rounds times (windows per workgroup
+// + about one and a half for fetching the term) -- stays below that of the kernels that read the mask per window (L = 256:
+// 210 against 154 us and 283 against 185).  `most`: an upper limit (the dBias slots).
 long long walk_slots(long long resident, long long most, long long N, long long period, bool dense, bool rounds) {
     if (resident < 1) resident = 1;
     long long G = resident < most ? resident : most;
@@ -832,7 +833,7 @@ long long walk_slots(long long resident, long long most, long long N, long long 
     const double whole = (double)((N + G - 1) / G);  // windows per workgroup with nothing rounded away
     if (fit > 0) {
         const double kept = (double)((N + fit - 1) / fit);
-        return kept > (dense ? 1.35 * whole + 1.0 : 1.08 * whole + 0.5) ? 0 : fit;
+        return kept > (dense ? 1.35 * whole + 1.0 : 1.3 * whole + 0.5) ? 0 : fit;
     }
     if (!rounds) return 0;
     const double stream = 1.35 * whole;
