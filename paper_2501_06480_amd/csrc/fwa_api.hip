@@ -89,14 +89,6 @@ int check_backward_support(int L, int dtype, bool want_dbias) {
     return FWA_OK;
 }
 
-// Part of the published workspace size of a large-window call with dBias that the kernels no longer use (two floats
-// per padded query and head; the row statistics now travel inside dV and dK, see fwa_backward_large.hip).  Sizes
-// that callers have stored, and the set of calls that fit fwa_backward_noalloc's scratch, stay what they were.
-size_t large_reserved_bytes(int64_t N, int L, int heads) {
-    const size_t nb = (size_t)(L + 15) / 16;
-    return (size_t)N * heads * 2 * 16 * nb * sizeof(float);
-}
-
 // fp32 copy of a bf16 bias for the large-window backward, which reads the bias once per window and
 // query block (a copy made once per call costs less than widening it at every use): [heads, L, L]
 // floats, rounded up to 256 bytes
@@ -231,8 +223,7 @@ size_t fwa_backward_workspace_bytes(int64_t N, int L, int C, int heads, int dtyp
         // room for the fp32 copy of a bf16 bias whether or not the call will pass one
         const size_t copy = large_bias_copy_bytes(L, heads);
         if (!want_dbias) return copy;
-        return copy + large_reserved_bytes(N, L, heads) +
-               (size_t)fwa::backward_large_slots(N, heads, L) * heads * nb * nb * 256 * sizeof(float);
+        return copy + (size_t)fwa::backward_large_slots(N, heads, L) * heads * nb * nb * 256 * sizeof(float);
     }
     if (!want_dbias) return 0;
     return (size_t)fwa::backward_max_slots(N, heads) * heads * nb * nb * 256 * sizeof(float);
@@ -351,7 +342,7 @@ int backward_impl(const void* q, const void* k, const void* v, const void* d_o, 
     if (static_scratch) {
         // the parts at their exact sizes for this call, out of the library's own array
         const size_t nb = (size_t)(L + 15) / 16;
-        const size_t exact = (copy_bias ? copy_room : 0) + (dbias && large ? large_reserved_bytes(N, L, heads) : 0) +
+        const size_t exact = (copy_bias ? copy_room : 0) +
                              (dbias ? (size_t)a.slots * heads * nb * nb * 256 * sizeof(float) : 0);
         if (exact > FWA_NOALLOC_SCRATCH_BYTES) return FWA_ERR_WORKSPACE;
         workspace = nullptr;

@@ -76,8 +76,8 @@ int backward_slots(long long N, int heads, int nW, int L, bool mask, bool labels
     return G < most ? G : most;
 }
 
-// Upper bound of the above over all periods, as the workspace query has always stated it (it once covered a second
-// kernel with about eight waves per CU; stored sizes stay valid).
+// Upper bound of the above over all periods and forms, which the workspace query states: eight waves per CU in groups of
+// four heads, or the largest count with a period, and for every call at least what any kernel needs.
 int backward_max_slots(long long N, int heads) {
     const int hpb = heads < kWavesPerBlock ? heads : kWavesPerBlock;
     const int groups = (heads + hpb - 1) / hpb;
@@ -88,7 +88,7 @@ int backward_max_slots(long long N, int heads) {
     return a > (int)slots ? a : (int)slots;
 }
 
-// dbias[h][i][j] = sum over the slots of partial[slot][h][i][j]
+// The kernels for wide heads and for large windows add their partial sums up themselves.
 hipError_t launch_backward_bf16(const BwdArgs& a, hipStream_t s) {
     if (a.C / a.heads != kHeadDim) return launch_backward_bf16_wide(a, s);
     if (a.L > kMaxBackwardL) return launch_backward_bf16_large(a, s);

@@ -220,6 +220,19 @@ def test_noalloc_backward_checks_its_arguments_and_its_limit(lib):
     assert call(N=64, L=144, C=128, heads=4, dbias=P + 0x7000000) == b.FWA_ERR_WORKSPACE
 
 
+def test_large_window_workspace_is_the_partial_sums_and_the_bias_copy(lib):
+    """Nothing else: 16 x 16 sums per pair of blocks, head and slot, and room for the fp32 copy of a bf16 bias."""
+    from paper_2501_06480_amd import binding as b
+    for N, L, heads, slots in ((1024, 256, 4, 64), (6000, 65, 1, 512), (7, 144, 3, 7)):
+        nb, copy = (L + 15) // 16, (heads * L * L * 4 + 255) // 256 * 256
+        assert lib.fwa_backward_workspace_bytes(N, L, 32 * heads, heads, 1, 1) == copy + slots * heads * nb * nb * 1024
+        # without a bf16 bias the copy's room is not asked for
+        short = lambda ws: lib.fwa_backward(P, P + 0x10000000, P + 0x20000000, P + 0x30000000, P + 0x40000000, P + 0x50000000,
+                                            P + 0x60000000, P + 0x70000000, N, L, 32 * heads, heads, 0.1, None, None, 0, 1,
+                                            P + 0x80000000, ws, None)
+        assert short(slots * heads * nb * nb * 1024 - 1) == b.FWA_ERR_WORKSPACE
+
+
 def test_header_and_binding_agree_on_the_scratch_limit():
     from paper_2501_06480_amd import binding as b
     text = open(os.path.join(ROOT, "include", "fwa.h")).read()

@@ -79,3 +79,19 @@ def test_without_dbias_no_scratch_is_touched(oracle):
     torch.cuda.synchronize()
     for got, ref in zip((dq, dk, dv), want[:3]):
         assert torch.equal(got.view(torch.int16), ref.view(torch.int16))
+
+
+def test_large_windows_whose_partial_sums_fit():
+    """13.1 MB of partial sums: the array holds them, however many windows are added up."""
+    import torch
+    import paper_2501_06480_amd as fwa
+    w = synth.Workload("noalloc_L65", 6000, 65, 32, 1, "bf16", 7302, 0, backward=True)
+    x = synth.draw(w)
+    q, k, v, g = (to_device(x, w, n) for n in ("q", "k", "v", "d_o"))
+    want = fwa.fwa_backward(q, k, v, g, 1, w.scale, want_dbias=True)
+    out = tuple(torch.full_like(q, 7.0) for _ in range(3))
+    db = torch.full((1, 65, 65), 7.0, dtype=torch.float32, device="cuda")
+    got = fwa.fwa_backward_noalloc(q, k, v, g, 1, w.scale, out, dbias=db)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("dq", "dk", "dv", "dbias"), got, want):
+        assert torch.equal(a, b), name
