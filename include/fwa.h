@@ -174,8 +174,8 @@ int fwa_backward_labels(const void* q, const void* k, const void* v, const void*
  * library runs on holds its own copy until the process ends.  The call itself allocates and frees
  * nothing, and runs the same kernels with the same results, bit for bit, as fwa_backward.
  *   - A call whose workspace would exceed the array returns FWA_ERR_WORKSPACE.  Every bf16 call
- *     with L <= 64 and head width 32 fits (at most 3 x compute-units tiles of 16 KB = 12 MiB);
- *     large windows with dbias mostly do not.  Without dbias no scratch is used at all.
+ *     with L <= 64, head width 32 and at most 1024 heads fits (at most 3 x compute-units tiles of
+ *     16 KB = 12 MiB); large windows with dbias mostly do not.  Without dbias no scratch is used at all.
  *   - All calls on one device share that device's array, which keeps the previous call's contents;
  *     the kernels overwrite every element they later read, so nothing needs clearing.  Calls that
  *     overlap in time on one device (two streams, two threads) race on it: serialise them.
