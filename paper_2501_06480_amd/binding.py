@@ -204,11 +204,9 @@ def _native():
     return _native_mod
 
 
-def _entry(what: str, tensors, bias, labels) -> str:
+def _entry(what: str, bias, labels) -> str:
     """Name of the C entry a call went through, for the message of an error."""
-    if labels is not None or (bias is not None and bias.dtype == _torch().bfloat16):
-        return what + "_labels"
-    return what if all(t is None or t.is_contiguous() for t in tensors) else what + "_strided"
+    return what + ("_labels" if labels is not None or (bias is not None and bias.dtype == _torch().bfloat16) else "_strided")
 
 
 def fwa_forward(q, k, v, heads: int, scale: float, bias=None, mask=None, out=None, stream=None, labels=None,
@@ -225,7 +223,7 @@ def fwa_forward(q, k, v, heads: int, scale: float, bias=None, mask=None, out=Non
             o = call(q, k, v, int(heads), float(scale), bias, mask, out, _stream_handle(stream, q.device), labels,
                      float(mask_value))
     if type(o) is int:
-        raise FwaError(o, _entry("fwa_forward", (q, k, v, out), bias, labels))
+        raise FwaError(o, _entry("fwa_forward", bias, labels))
     return o
 
 
@@ -233,7 +231,7 @@ def fwa_forward_qkv(qkv, scale: float, bias=None, mask=None, labels=None, mask_v
     """``fwa_forward`` of the three slices of a contiguous fused [N, L, 3, heads, d] tensor, read in place."""
     o = (_native_mod or _native()).forward_qkv(qkv, float(scale), bias, mask, labels, float(mask_value))
     if type(o) is int:
-        raise FwaError(o, _entry("fwa_forward", (qkv[:, :, 0],), bias, labels))
+        raise FwaError(o, _entry("fwa_forward", bias, labels))
     return o
 
 
@@ -257,7 +255,7 @@ def fwa_backward(q, k, v, d_o, heads: int, scale: float, bias=None, mask=None, w
             r = call(q, k, v, d_o, int(heads), float(scale), bias, mask, bool(want_dbias), workspace,
                      _stream_handle(stream, q.device), dq, dk, dv, labels, float(mask_value))
     if type(r) is int:
-        raise FwaError(r, _entry("fwa_backward", (q, k, v, d_o, dq, dk, dv), bias, labels))
+        raise FwaError(r, _entry("fwa_backward", bias, labels))
     return r
 
 
@@ -266,7 +264,7 @@ def fwa_backward_qkv(qkv, d_o, scale: float, bias=None, mask=None, want_dbias: b
     """(dqkv, dBias) of ``fwa_forward_qkv``: the gradients of the three slices written into one tensor like qkv."""
     r = (_native_mod or _native()).backward_qkv(qkv, d_o, float(scale), bias, mask, bool(want_dbias), labels, float(mask_value))
     if type(r) is int:
-        raise FwaError(r, _entry("fwa_backward", (qkv[:, :, 0], d_o), bias, labels))
+        raise FwaError(r, _entry("fwa_backward", bias, labels))
     return r
 
 

@@ -31,7 +31,7 @@
 // 4 heads, bias + labels + dBias: rows 210 -> 154 us, keys 283 -> 185 us (kernels of their own that read the term per
 // window and parked the slabs out of registers between two barriers), the whole call 465 -> 339 us; N = 315 windows
 // of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 59 us.  Vector instructions issue in
-// 60-64 % of the cycles now, the matrix cores are busy for 25 %, the LDS for 40-48 %:
+// 60-64 % of the cycles now, the matrix cores are busy for 25 %, the LDS for 27-38 %:
 // no unit is full (one instruction less per score gave nothing), two waves per SIMD overlap them only in part.
 //
 // The statistics M_i, -delta_i (8 bytes per query) travel from one kernel to the other inside the outputs that the
@@ -522,7 +522,7 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
     constexpr bool KEEP = TERM == kTermKept || TERM == kTermLabels;
     constexpr bool STREAM = TERM == kTermStream || TERM == kTermStreamMask;
     constexpr bool PW = TERM == kTermLabels;
-    constexpr bool KEEPB = TERM == kTermStream && (!DB || NB <= 12);  // the bias in registers all the same
+    constexpr bool KEEPB = TERM == kTermStream && NB <= 12;  // the bias in registers all the same
     constexpr bool HB = TERM == kTermStream && !KEEPB;
     constexpr uint32_t PARTS = (uint32_t)keys_parts(NB);
     constexpr int W = keys_waves(NB);
