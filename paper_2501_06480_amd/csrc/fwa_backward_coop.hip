@@ -51,8 +51,8 @@ __host__ __device__ constexpr uint32_t coop_mask_tiles(int nb) { return nb <= 3 
 // PW ("per window"): G is no multiple of the mask's period.  The registers then hold bias * log2e alone.
 // PW = 1, labels: those of a window travel with its slabs into LDS and phase A forms the mask per score
 // (AddendRegsLabels).  PW = 2, a dense mask: the tile of a window is fetched into LDS during the window before (L > 48:
-// during its phase B, there is room for one tile), straight from memory and in whole lines (AddendRegsDense; every lane loading the values of its own row,
-// 16 bytes of a line each, took 93 us instead of 53 below).  Stage 1 of two 800 x 1333 images (2784
+// during its phase B, there is room for one tile), straight from memory and in whole lines (AddendRegsDense; every lane
+// loading the values of its own row, 16 bytes of a line each, took 93 us instead of 53 below).  Stage 1 of two 800 x 1333 images (2784
 // windows, 3 heads, bias, mask of 1392 windows, dBias): 53 us with the reduction, 52 as labels; a kernel with one
 // wave per tile that such calls took before, 102.
 template <int NB, bool BM, bool DB, int KT, int PW>
