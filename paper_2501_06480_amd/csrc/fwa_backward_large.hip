@@ -56,6 +56,12 @@ struct LargeGeom {
 constexpr uint32_t kLargeStride = 4;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
+// A scalar whose sums with lane values are formed where they are used, not kept in registers over the loop.
+__device__ __forceinline__ uint32_t here(uint32_t s) {
+    asm volatile("" : "+s"(s));
+    return s;
+}
+
 __device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
     const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
     return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
@@ -249,42 +255,49 @@ __global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdA
     i32x4 nlab = {0, 0, 0, 0};
     // No branches in here (they would cut the window into pieces): without a next window `on` is false, the
     // descriptors are empty and nothing is fetched.
-    auto request_slab = [&](uint32_t w, uint32_t buf, int t, bool on) {  // 16 rows of K and V: block W t + wave
-        const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
+    // One descriptor per tensor and window (`ask`); the 16 rows of a pass are an offset on top of the lane's own.
+    size_t next_q = ((size_t)bw * L * p.ldq + (size_t)h * kHeadDim) * 2u, next_g = ((size_t)bw * L * p.ldg + (size_t)h * kHeadDim) * 2u;
+    const size_t step_q = (size_t)gm.G * L * p.ldq * 2u, step_g = (size_t)gm.G * L * p.ldg * 2u;
+    u32x4 from_k, from_v;
+    auto ask = [&](bool on) {
+        from_k = lds_source((const char*)p.k + next_q, on ? tile_bytes : 0u);
+        from_v = lds_source((const char*)p.v + next_q, on ? tile_bytes : 0u);
+    };
+    auto request_slab = [&](uint32_t buf, int t) {  // 16 rows of K and V: block W t + wave
         // a wave beyond the last block moves that one too
         const uint32_t blk = NB % W == 0 || wave + t * W < (uint32_t)NB ? wave + t * W : (uint32_t)NB - 1u;
         const uint32_t to = lds_offset(lds) + buf * (2 * SLAB * 16) + blk * 1024u;
-        const uint32_t skip = 16u * blk * row_bytes;  // of the rows in front, fewer than L
-        load_to_lds((const char*)p.k + tile + skip, on ? tile_bytes - skip : 0u, off_slab, to);
-        load_to_lds((const char*)p.v + tile + skip, on ? tile_bytes - skip : 0u, off_slab, to + SLAB * 16);
+        const uint32_t off = off_slab + here(16u * blk * row_bytes);
+        load_to_lds(from_k, off, to);
+        load_to_lds(from_v, off, to + SLAB * 16);
     };
     auto request_rest = [&](uint32_t w, bool on) {
-        const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
-        const size_t tile_g = ((size_t)w * L * p.ldg + (size_t)h * kHeadDim) * 2u;
-        nq = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.q + tile, on ? tile_bytes : 0u), off_q, 0, 0);
-        ng = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.d_o + tile_g, on ? tile_bytes_g : 0u), off_g, 0, 0);
+        nq = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.q + next_q, on ? tile_bytes : 0u), off_q, 0, 0);
+        ng = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.d_o + next_g, on ? tile_bytes_g : 0u), off_g, 0, 0);
         if (PW)  // wave 0's are parked; tokens beyond L lie outside the descriptor: label 0
             nlab = load_i32x4(make_rsrc(p.labels + (size_t)(w % (uint32_t)p.nW) * L, on && wave == 0 ? (uint32_t)L * 4u : 0u), (uint32_t)tid * 16u);
     };
     auto park_labels = [&](uint32_t buf) {
         if (PW && tid < ROWS / 4) reinterpret_cast<i32x4*>(llab + buf * ROWS)[tid] = nlab;
     };
-    for (uint32_t i = (uint32_t)(4 * L + tid); i < SLAB; i += 64u * W) {  // rows L .. ROWS - 1 of the four slabs
-        const uint4 z = {0u, 0u, 0u, 0u};
-        lds[i] = lds[SLAB + i] = lds[2 * SLAB + i] = lds[3 * SLAB + i] = z;
-    }
     const uint32_t end = (uint32_t)p.N, step = gm.G;
     if (bw < end) {  // in flight while the additive term is fetched
+        ask(true);
 #pragma unroll
-        for (int t = 0; t < PASSES; ++t) request_slab(bw, 0u, t, true);
+        for (int t = 0; t < PASSES; ++t) request_slab(0u, t);
         request_rest(bw, true);
     }
+    next_q += step_q, next_g += step_g;
     f32x4 add[NB];
     if (BM) {
         const BiasSrc rb = bias_of_head(p, h);
         // rows beyond L (and the whole block of an idle wave) fall outside the descriptors: zeros
         const MaskSrc msk = PW ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
         addend_at(rb, msk, active ? (uint32_t)(16 * qb + n) : (uint32_t)L, 4u * g, (uint32_t)L).template fill<NB, false>(add, kLog2e);
+    }
+    for (uint32_t i = (uint32_t)(4 * L + tid); i < SLAB; i += 64u * W) {  // rows L .. ROWS - 1 of the four slabs
+        const uint4 z = {0u, 0u, 0u, 0u};
+        lds[i] = lds[SLAB + i] = lds[2 * SLAB + i] = lds[3 * SLAB + i] = z;
     }
     const float mv = p.mask_value * kLog2e;
     park_labels(0u);
@@ -297,6 +310,7 @@ __global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdA
         const uint4* const lv = lk + SLAB;
         const bf16x8 qop = as_bf16x8(nq), gop = as_bf16x8(ng);
         const bool has_next = w + step < end;
+        ask(has_next);
         float M, nd;
         u32x2 lo, hi;
         if (active) {
@@ -326,15 +340,16 @@ __global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdA
                 // and hold the wave up
 #pragma unroll
                 for (int t = 0; t < PASSES; ++t)
-                    if (i == 2 * t) request_slab(w + step, buf ^ 1u, t, has_next);
+                    if (i == 2 * t) request_slab(buf ^ 1u, t);
                 if (i == 3) request_rest(w + step, has_next);
             });
         } else {  // an idle wave moves its share all the same
 #pragma unroll
-            for (int t = 0; t < PASSES; ++t) request_slab(w + step, buf ^ 1u, t, has_next);
+            for (int t = 0; t < PASSES; ++t) request_slab(buf ^ 1u, t);
         }
         // The next window's slabs are in LDS before this wave passes the barrier; the
         // wait stands in front of the stores, so that it does not wait for those.
+        next_q += step_q, next_g += step_g;
         lds_loads_done();
         park_labels(buf ^ 1u);
         if (active) {
@@ -573,22 +588,26 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
     // No branches in here (they would cut the block loop into pieces): without a next window `on` is false, the
     // descriptors are empty and nothing is fetched.
     const uint32_t off_st = wave < 2 ? (16u * part + ((uint32_t)lane >> 2)) * row_d + 16u * ((uint32_t)lane & 3u) : 16u * (uint32_t)lane;
-    auto request_slab = [&](uint32_t w, uint32_t buf, int t, bool on) {  // 16 rows of Q and dO: block W t + wave
-        const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
-        const size_t tile_g = ((size_t)w * L * p.ldg + (size_t)h * kHeadDim) * 2u;
+    // One descriptor per tensor and window (`ask`); the 16 rows of a pass are an offset on top of the lane's own.
+    size_t next_q = ((size_t)bw * L * p.ldq + (size_t)h * kHeadDim) * 2u, next_g = ((size_t)bw * L * p.ldg + (size_t)h * kHeadDim) * 2u;
+    size_t next_d = ((size_t)bw * L * p.ldd + (size_t)h * kHeadDim) * 2u;
+    const size_t step_q = (size_t)gm.G * L * p.ldq * 2u, step_g = (size_t)gm.G * L * p.ldg * 2u, step_d = (size_t)gm.G * L * p.ldd * 2u;
+    u32x4 from_q, from_g;
+    auto ask = [&](bool on) {
+        from_q = lds_source((const char*)p.q + next_q, on ? tile_bytes : 0u);
+        from_g = lds_source((const char*)p.d_o + next_g, on ? tile_bytes_g : 0u);
+    };
+    auto request_slab = [&](uint32_t buf, int t) {  // 16 rows of Q and dO: block W t + wave
         // a wave beyond the last block moves that one too
         const uint32_t blk = NB % W == 0 || wave + t * W < (uint32_t)NB ? wave + t * W : (uint32_t)NB - 1u;
         const uint32_t to = lds_offset(lds) + buf * (2 * SLAB * 16) + blk * 1024u;
-        const uint32_t skip = 16u * blk;  // rows, below L
-        load_to_lds((const char*)p.q + tile + skip * row_bytes, on ? tile_bytes - skip * row_bytes : 0u, off_q, to);
-        load_to_lds((const char*)p.d_o + tile_g + skip * row_g, on ? tile_bytes_g - skip * row_g : 0u, off_g, to + SLAB * 16);
+        load_to_lds(from_q, off_q + here(16u * blk * row_bytes), to);
+        load_to_lds(from_g, off_g + here(16u * blk * row_g), to + SLAB * 16);
     };
     auto request_rest = [&](uint32_t w, bool on) {
-        const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u;
-        const size_t tile_d = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
         // waves 0, 1: floats 4 lane .. 4 lane + 3 of M resp. -delta, i.e. row 16 part + lane / 4 of the head's slice
         // of dV resp. dK; wave 2 with PW: labels 4 lane .. 4 lane + 3 (0 beyond L)
-        const char* src = (wave == 0 ? static_cast<const char*>(p.dv) : static_cast<const char*>(p.dk)) + tile_d;
+        const char* src = (wave == 0 ? static_cast<const char*>(p.dv) : static_cast<const char*>(p.dk)) + next_d;
         uint32_t bytes = wave < 2 ? (16u * PARTS - 1u) * row_d + 64u : 0u;
         if (PW) {
             const char* const lab = reinterpret_cast<const char*>(p.labels + (size_t)(w % (uint32_t)p.nW) * L);
@@ -598,36 +617,38 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
         pst = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(src, on ? bytes : 0u), off_st, 0, 0);
         // the wave's own K and V rows as operands: row 16 jb + n, channels 8g .. 8g + 7
         const uint32_t off = (uint32_t)(16 * jb + n) * row_bytes + 16u * g, own = on ? tile_bytes : 0u;
-        pk = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.k + tile, own), off, 0, 0);
-        pv = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.v + tile, own), off, 0, 0);
+        pk = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.k + next_q, own), off, 0, 0);
+        pv = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.v + next_q, own), off, 0, 0);
     };
     auto park = [&](uint32_t buf) {
         // M, -delta and labels lie one behind the other: ROWS / 4 = 4 NB <= 64 units of 16 bytes each
         if (wave < (PW ? 3u : 2u) && lane < ROWS / 4) reinterpret_cast<u32x4*>(stats + buf * ST + wave * ROWS)[lane] = pst;
     };
-    for (uint32_t i = (uint32_t)(4 * L + tid); i < SLAB; i += 64u * W) {  // rows L .. ROWS - 1 of the four slabs
-        const uint4 z = {0u, 0u, 0u, 0u};
-        lds[i] = lds[SLAB + i] = lds[2 * SLAB + i] = lds[3 * SLAB + i] = z;
-    }
     if (bw < (uint32_t)p.N) {  // in flight while the additive term is fetched
+        ask(true);
 #pragma unroll
-        for (int t = 0; t < PASSES; ++t) request_slab(bw, 0u, t, true);
+        for (int t = 0; t < PASSES; ++t) request_slab(0u, t);
         request_rest(bw, true);
     }
+    next_q += step_q, next_g += step_g, next_d += step_d;
     f32x4 add[NB];  // (bias + mask) * log2e, resp. bias * log2e, in the layout of dbacc
     if (KEEP || KEEPB) {
         const MaskSrc msk = PW || KEEPB ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
-        const __amdgpu_buffer_rsrc_t rb = p.bias ? make_rsrc(bias32 + (size_t)h * L * L, ll) : make_rsrc(nullptr, 0);
         // rows beyond L lie outside the descriptors: zeros.  A key beyond L reads into the next row: what it makes
         // of that stays in its own column of every product, i.e. in rows of dV, dK and columns of dBias beyond L,
         // which the stores and the reduce kernel drop.
+        const BiasSrc rb = bias_of_head(p, h);
 #pragma unroll
         for (int qb = 0; qb < NB; ++qb) {
             const uint32_t off = ((uint32_t)(16 * qb + 4 * g) * L + 16u * jb + n) * 4u;
             const f32x4 mk = mask_rows4(msk, (uint32_t)(16 * qb + 4 * g), 16u * jb + n, (uint32_t)L);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) add[qb][r] = (load_f32(rb, off + 4u * L * r) + mk[r]) * kLog2e;
+            for (int r = 0; r < 4; ++r) add[qb][r] = (load_f32(rb.r, off + 4u * L * r) + mk[r]) * kLog2e;
         }
+    }
+    for (uint32_t i = (uint32_t)(4 * L + tid); i < SLAB; i += 64u * W) {  // rows L .. ROWS - 1 of the four slabs
+        const uint4 z = {0u, 0u, 0u, 0u};
+        lds[i] = lds[SLAB + i] = lds[2 * SLAB + i] = lds[3 * SLAB + i] = z;
     }
     uint32_t aoff[4];  // STREAM: additive term of query 4g + r (of a query block) and this lane's key
 #pragma unroll
@@ -638,7 +659,9 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
     __syncthreads();
 
     uint32_t buf = 0u;
-    for (uint32_t w = bw; w < (uint32_t)p.N; w += gm.G, buf ^= 1u) {
+    uint32_t left = ((uint32_t)p.N - bw + gm.G - 1u) / gm.G;
+    for (uint32_t w = bw; w < (uint32_t)p.N; w += gm.G, buf ^= 1u, --left) {
+        take_turns(left);
         const uint4* const lq = lds + buf * (2 * SLAB);
         const uint4* const lg = lq + SLAB;
         const float* const stM = stats + buf * ST;
@@ -646,9 +669,10 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
         const int* const llab = reinterpret_cast<const int*>(stD + ROWS);
         const uint16_t* const lg16 = reinterpret_cast<const uint16_t*>(lg) + trs;
         const uint16_t* const lq16 = reinterpret_cast<const uint16_t*>(lq) + trs;
-        const size_t tile_d = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
+        const size_t tile_d = next_d - step_d;
         const bf16x8 kop = as_bf16x8(pk), vop = as_bf16x8(pv);
         const bool has_next = w + gm.G < (uint32_t)p.N;
+        ask(has_next);
         u32x2 va = {0u, 0u}, vb = {0u, 0u}, ka = {0u, 0u}, kb = {0u, 0u};  // the wave's 16 rows of dV and dK, packed
 
         if (active) {
@@ -719,7 +743,7 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
                 // CU's address unit and hold the wave up
 #pragma unroll
                 for (int t = 0; t < PASSES; ++t)
-                    if (qb == t * (NB / 2) / PASSES) request_slab(w + gm.G, buf ^ 1u, t, has_next);
+                    if (qb == t * (NB / 2) / PASSES) request_slab(buf ^ 1u, t);
                 if (qb == NB / 2) request_rest(w + gm.G, has_next);
                 if (qb + 1 < NB) products(qb + 1);
                 if (u == 0 && qb > 0) accumulate();
@@ -759,11 +783,12 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
             kb = u32x2{pack_bf16(k1[0] * p.scale, k1[1] * p.scale), pack_bf16(k1[2] * p.scale, k1[3] * p.scale)};
         } else {  // an idle wave moves its share all the same
 #pragma unroll
-            for (int t = 0; t < PASSES; ++t) request_slab(w + gm.G, buf ^ 1u, t, has_next);
+            for (int t = 0; t < PASSES; ++t) request_slab(buf ^ 1u, t);
             request_rest(w + gm.G, has_next);
         }
         // The next window's slabs are in LDS before this wave passes the barrier; the wait stands in front of the
         // stores, so that it does not wait for those.
+        next_q += step_q, next_g += step_g, next_d += step_d;
         lds_loads_done();
         park(buf ^ 1u);
         if (active) {

@@ -101,18 +101,39 @@ __device__ __forceinline__ int load_i32(__amdgpu_buffer_rsrc_t r, uint32_t voffs
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t bytes, uint32_t voffset, uint32_t lds_off) {
+// The descriptor words of such loads: one source per tensor and window serves all of them.
+__device__ __forceinline__ u32x4 lds_source(const void* base, uint32_t bytes) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(base);
-    const u32x4 r = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
+}
+__device__ __forceinline__ void load_to_lds(const u32x4& r, uint32_t voffset, uint32_t lds_off) {
     uint32_t saved;
     asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 2\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved) : "s"(lds_off), "v"(voffset), "s"(r) : "memory");
+}
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t bytes, uint32_t voffset, uint32_t lds_off) {
+    load_to_lds(lds_source(base, bytes), voffset, lds_off);
 }
 // all but the N youngest global loads and stores of this wave are complete
 template <int N>
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 // every global load and store this wave has issued is complete
 __device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Of several workgroups on a CU the scheduler serves the oldest first: the others get what it leaves, and when it has
+// finished they run alone.  The priority of a wave with `left` windows to go is left mod 4, so that of two workgroups
+// less than four windows apart the one behind is served first.  Keys kernel of the large-window backward, two workgroups
+// per CU with 32 windows of 16 x 16 tokens each: the first ended at 129 us and the second at 173, half of it alone on
+// the CU (whole call 340 -> 332 us; 14 x 14, 315 windows, 5 heads 101.6 -> 97.8).  No gain where the memory system or a
+// workgroup's own barriers set the pace: three single heads per CU in the cooperative backward, the forward.
+__device__ __forceinline__ void take_turns(uint32_t left) {
+    switch (left & 3u) {
+        case 3: __builtin_amdgcn_s_setprio(3); break;
+        case 2: __builtin_amdgcn_s_setprio(2); break;
+        case 1: __builtin_amdgcn_s_setprio(1); break;
+        default: __builtin_amdgcn_s_setprio(0);
+    }
+}
 
 // Unsigned division by a runtime constant with a host-made multiplier
 // (round-up method): n / d == (mulhi(n, mul) + n) >> shift for n < 2^31.
