@@ -175,8 +175,8 @@ __device__ __forceinline__ void rows_block(f32x4 (&s)[NB], float m, const bf16x8
         tk1 = operand_tr(lk16 + (32 * kp) * SROW + 16, 16 * SROW, two);
         bf16x4 hi[2], lo[2];
         hi[1] = lo[1] = as_bf16x4(uint2{0u, 0u});
-        split_hi_lo(s[2 * kp] * da[cur], hi[0], lo[0]);  // dS, times the row sum
-        if (two) split_hi_lo(s[two ? 2 * kp + 1 : 0] * db[cur], hi[1], lo[1]);
+        split_hi_lo_dot(s[2 * kp] * da[cur], hi[0], lo[0]);  // dS, times the row sum
+        if (two) split_hi_lo_dot(s[two ? 2 * kp + 1 : 0] * db[cur], hi[1], lo[1]);
         dh = pair_operand(hi[0], hi[1]), dl = pair_operand(lo[0], lo[1]);
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -766,8 +766,8 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
                     ds[r] = pr[r] * dp[u][r];
                 }
                 if (DB) dbacc[qb] += ds;
-                split_hi_lo(pr, ph[u], pl[u]);
-                split_hi_lo(ds, sh[u], sl[u]);
+                split_hi_lo_dot(pr, ph[u], pl[u]);
+                split_hi_lo_dot(ds, sh[u], sl[u]);
                 if (STREAM && qb + 2 < NB) fetch_term(qb + 2);
                 if (u == 1 || qb == NB - 1) {
                     if (u == 0) ph[1] = pl[1] = sh[1] = sl[1] = as_bf16x4(uint2{0u, 0u});

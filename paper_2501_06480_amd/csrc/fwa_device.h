@@ -232,6 +232,29 @@ __device__ __forceinline__ void split_hi_lo(const f32x4& x, bf16x4& hi, bf16x4& 
     lo = as_bf16x4(l);
 }
 
+// The same split with the remainder from the two-term dot product, x - hi = x + (hi, other) . (-1, 0), which is exact:
+// two instructions fewer per pair.  It shares no issue slot with the other wave of a SIMD, which the masks and subtractions
+// above do, so it is for kernels with two waves per SIMD, where a wave's own issue counts (backward of 16 x 16 windows
+// 336 -> 328 us, of 14 x 14 97.4 -> 95.3; kernels with three waves per SIMD and more -1 .. +1 %).  The factors come out of
+// registers: as a literal the compiler takes the pair (-1, 0) for the inline constant -1.0f, which the instruction reads as (0, -1).
+__device__ __forceinline__ void split_hi_lo_dot(const f32x4& x, bf16x4& hi, bf16x4& lo) {
+    uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;  // (-1, 0), (0, -1)
+    asm("" : "+s"(c0));
+    asm("" : "+s"(c1));
+    const bf16x2 first = __builtin_bit_cast(bf16x2, c0), second = __builtin_bit_cast(bf16x2, c1);
+    const float x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
+    uint2 h, l;
+    h.x = upper_halves(__builtin_bit_cast(uint32_t, x0), __builtin_bit_cast(uint32_t, x1));
+    h.y = upper_halves(__builtin_bit_cast(uint32_t, x2), __builtin_bit_cast(uint32_t, x3));
+    const bf16x2 a = __builtin_bit_cast(bf16x2, h.x), b = __builtin_bit_cast(bf16x2, h.y);
+    const float r0 = __builtin_amdgcn_fdot2_f32_bf16(a, first, x0, false), r1 = __builtin_amdgcn_fdot2_f32_bf16(a, second, x1, false);
+    const float r2 = __builtin_amdgcn_fdot2_f32_bf16(b, first, x2, false), r3 = __builtin_amdgcn_fdot2_f32_bf16(b, second, x3, false);
+    l.x = pack_bf16(r0, r1);
+    l.y = pack_bf16(r2, r3);
+    hi = as_bf16x4(h);
+    lo = as_bf16x4(l);
+}
+
 // A operand of the K=32 matrix op that is all ones: times the probability operand of a pair of key blocks it
 // returns, in every component of every lane (g, n), the sum over the pair's 32 keys of the (rounded)
 // probabilities of query n.  Accumulated over the pairs this is the row sum the output is divided by -- the sum of
