@@ -289,11 +289,14 @@ __global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdA
     }
     next_q += step_q, next_g += step_g;
     f32x4 add[NB];
-    if (BM) {
+    if (BM) {  // through the second buffer, which nothing has been requested into yet
+        static_assert(W * kFillPatch <= 2 * SLAB * 16, "the buffer holds the waves' patches");
         const BiasSrc rb = bias_of_head(p, h);
         // rows beyond L (and the whole block of an idle wave) fall outside the descriptors: zeros
         const MaskSrc msk = PW ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
-        addend_at(rb, msk, active ? (uint32_t)(16 * qb + n) : (uint32_t)L, 4u * g, (uint32_t)L).template fill<NB, false>(add, kLog2e);
+        fill_rows_patch<NB>(add, rb, msk, active ? (uint32_t)(16 * qb) : (uint32_t)L, (uint32_t)L, kLog2e,
+                            reinterpret_cast<char*>(lds + 2 * SLAB) + wave * kFillPatch, lane);
+        __syncthreads();
     }
     for (uint32_t i = (uint32_t)(4 * L + tid); i < SLAB; i += 64u * W) {  // rows L .. ROWS - 1 of the four slabs
         const uint4 z = {0u, 0u, 0u, 0u};

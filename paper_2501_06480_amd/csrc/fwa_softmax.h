@@ -234,6 +234,54 @@ __device__ __forceinline__ void fill_rows_staged(f32x4 (&add)[NQ][NB], const Bia
     }
 }
 
+// fill_rows for one block of 16 rows of a longer window (64 < L <= 256) by a wave that keeps it for life, with an fp32
+// bias: 32 columns of the 16 rows at a time go through 2 KB of LDS of the wave's own (`patch`).  They are fetched 128
+// bytes of a row per 8 lanes and written with unit u (16 bytes) of row r at u ^ (r & 7), so that neither the writes nor the
+// reads (a unit of 8 rows) meet on a bank.  (fill_rows took 8 us of the rows kernel's 150 at L = 256, whose rows of 1 KB fall on
+// the same channels; the call 312 -> 309 us, 100 windows with 6 heads 53.7 -> 51.7; other lengths 0 .. 1 %.)
+constexpr uint32_t kFillPatch = 2048;
+template <int NB>
+__device__ __forceinline__ void fill_rows_patch(f32x4 (&add)[NB], const BiasSrc& b, const MaskSrc& m, uint32_t row0, uint32_t L,
+                                                float mul, char* patch, int lane) {
+    const uint32_t n = (uint32_t)lane & 15u, g = (uint32_t)lane >> 4, r = (uint32_t)lane >> 3, u = (uint32_t)lane & 7u;
+    const uint32_t off = ((row0 + r) * L + 4u * u) * 4u;
+    f32x4 raw[NB + 1];  // rows r and r + 8 of columns 32 c + 4u .. + 3
+#pragma unroll
+    for (int c = 0; c < (NB + 1) / 2; ++c) {
+        raw[2 * c] = load_f32x4(b.r, off + 128u * c);
+        raw[2 * c + 1] = load_f32x4(b.r, off + 32u * L + 128u * c);
+    }
+    if (!m.labels) {
+        f32x4 mk[NB + 1];
+#pragma unroll
+        for (int c = 0; c < (NB + 1) / 2; ++c) {
+            mk[2 * c] = load_f32x4(m.r, off + 128u * c);
+            mk[2 * c + 1] = load_f32x4(m.r, off + 32u * L + 128u * c);
+        }
+#pragma unroll
+        for (int c = 0; c < NB + NB % 2; ++c) raw[c] += mk[c];
+    }
+    char* const to = patch + r * 128u + ((u ^ r) * 16u);
+#pragma unroll
+    for (int c = 0; c < (NB + 1) / 2; ++c) {
+        *reinterpret_cast<f32x4*>(to) = raw[2 * c];
+        *reinterpret_cast<f32x4*>(to + 1024) = raw[2 * c + 1];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int b2 = 0; b2 < 2; ++b2)
+            if (2 * c + b2 < NB) add[2 * c + b2] = *reinterpret_cast<const f32x4*>(patch + n * 128u + (((4u * b2 + g) ^ (n & 7u)) * 16u));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (m.labels) {
+        const int lq = load_i32(m.r, (row0 + n) * 4u);
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) add[jb] += mask_of_labels(lq, load_i32x4(m.r, (16u * jb + 4u * g) * 4u), m.value);
+    }
+#pragma unroll
+    for (int jb = 0; jb < NB; ++jb) add[jb] *= mul;
+}
 // AddendRegs: the term is already in registers (one f32x4 per key block), times log2e.
 template <int NB>
 struct AddendRegs {
