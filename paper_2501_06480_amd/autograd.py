@@ -15,6 +15,16 @@ import torch
 from . import binding
 
 
+def _native_node(t) -> bool:
+    """Whether a call goes through the native autograd node: GPU tensors of the plain kind, outside functorch's transforms
+    and dispatch modes.  Everything else takes the Python functions below, which do the same."""
+    return (t.is_cuda and type(t) in _PLAIN and not torch._C._are_functorch_transforms_active()
+            and not torch._C._len_torch_dispatch_stack())
+
+
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
 def _check_dbias_supported(q, N, L, C, heads, bias):
     if bias is not None and bias.requires_grad:
         if binding.fwa_backward_workspace_bytes(max(N, 1), L, C, heads, binding._dtype_code(q), True) == 0 and N > 0:
@@ -60,6 +70,8 @@ class _WindowAttentionQKV(torch.autograd.Function):
 
 def window_attention(q, k, v, heads: int, scale: float, bias=None, mask=None, labels=None, mask_value: float = -100.0):
     """softmax(scale * Q K^T + bias + mask) V per window and head, differentiable in q, k, v and bias."""
+    if _native_node(q):
+        return binding._native().attention(q, k, v, int(heads), float(scale), bias, mask, labels, float(mask_value))
     N, L, C = q.shape
     _check_dbias_supported(q, N, L, C, heads, bias)
     return _WindowAttention.apply(q, k, v, bias, mask, heads, scale, labels, float(mask_value))
@@ -67,6 +79,8 @@ def window_attention(q, k, v, heads: int, scale: float, bias=None, mask=None, la
 
 def window_attention_qkv(qkv, scale: float, bias=None, mask=None, labels=None, mask_value: float = -100.0):
     """The same on a fused, contiguous [N, L, 3, heads, d] tensor; returns [N, L, heads * d]."""
+    if _native_node(qkv):
+        return binding._native().attention_qkv(qkv, float(scale), bias, mask, labels, float(mask_value))
     if qkv.dim() != 5 or qkv.shape[2] != 3 or not qkv.is_contiguous():
         raise ValueError("qkv must be a contiguous [N, L, 3, heads, d] tensor")
     N, L, _, heads, d = qkv.shape

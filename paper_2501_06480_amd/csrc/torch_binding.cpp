@@ -1,12 +1,17 @@
 // Marshalling between torch tensors and the C ABI of libfwa: argument checks, output allocation, the current stream,
 // one call.  Nothing is computed here and nothing is kept from call to call.  The same steps in Python took 9 us for a
 // forward and 45 us for the forward and backward of a fused qkv tensor (nine views, two dozen attribute reads, two
-// calls through ctypes), more than the kernels of the smaller calls run.
+// calls through ctypes), more than the kernels of the smaller calls run.  The autograd nodes below are native for the
+// same reason: a Python function's bookkeeping, and the interpreter that its backward has to enter from the engine's
+// thread, left a training step of the smaller calls waiting for the host (stage 3 of Swin-T at batch 128: 92 us a step, 74
+// as native nodes, 66 of them kernels).
 //
 // Each function returns the outputs, or the library's error code as an int for the Python layer to raise.
 #include <ATen/ATen.h>
 #include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/utils/pybind.h>
 
 #include <optional>
@@ -99,6 +104,12 @@ Terms terms_of(const OptTensor& bias, const OptTensor& mask, const OptTensor& la
     return t;
 }
 
+// Lets other Python threads run during a launch; the autograd engine's threads do not hold the interpreter to begin with.
+struct Nogil {
+    std::optional<py::gil_scoped_release> released;
+    Nogil() { if (PyGILState_Check()) released.emplace(); }
+};
+
 void* stream_of(std::optional<uintptr_t> handle, const at::Tensor& t) {
     return handle ? reinterpret_cast<void*>(*handle) : static_cast<void*>(c10::hip::getCurrentHIPStream(t.device().index()).stream());
 }
@@ -112,7 +123,7 @@ int call_forward(Rows q, Rows k, Rows v, Rows o, const at::Tensor& like, int64_t
     if (!(q.ld == k.ld && q.ld == v.ld)) value_error("q, k and v must share one row stride");
     const int dtype = dtype_code(like);
     const c10::DeviceGuard guard(like.device());
-    const py::gil_scoped_release nogil;
+    const Nogil nogil;
     if (t.labels_entry())
         return fwa_forward_labels(q.p, k.p, v.p, o.p, N, (int)L, (int)C, heads, scale, q.ld, o.ld, t.bias, t.bias_dtype,
                                   t.labels, mask_value, t.nW, dtype, stream);
@@ -120,15 +131,20 @@ int call_forward(Rows q, Rows k, Rows v, Rows o, const at::Tensor& like, int64_t
                                static_cast<const float*>(t.bias), t.mask, t.nW, dtype, stream);
 }
 
-py::object forward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, int heads, float scale, const OptTensor& bias,
-                   const OptTensor& mask, const OptTensor& out, std::optional<uintptr_t> stream, const OptTensor& labels, float mask_value) {
+int run_forward(at::Tensor& o, const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, int heads, float scale, const OptTensor& bias,
+                const OptTensor& mask, const OptTensor& out, std::optional<uintptr_t> stream, const OptTensor& labels, float mask_value) {
     need_3d(q);
     const int64_t N = q.size(0), L = q.size(1), C = q.size(2);
     need_gpu(q, "q");
-    const at::Tensor o = out ? *out : at::empty(q.sizes(), q.options());
+    o = out ? *out : at::empty(q.sizes(), q.options());
     const Terms t = terms_of(bias, mask, labels, heads, L);
-    const int rc = call_forward(rows_of(q, "q", nullptr), rows_of(k, "k", &q), rows_of(v, "v", &q), rows_of(o, "out", &q), q, N,
-                                L, C, heads, scale, t, mask_value, stream_of(stream, q));
+    return call_forward(rows_of(q, "q", nullptr), rows_of(k, "k", &q), rows_of(v, "v", &q), rows_of(o, "out", &q), q, N, L, C, heads,
+                        scale, t, mask_value, stream_of(stream, q));
+}
+py::object forward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, int heads, float scale, const OptTensor& bias,
+                   const OptTensor& mask, const OptTensor& out, std::optional<uintptr_t> stream, const OptTensor& labels, float mask_value) {
+    at::Tensor o;
+    const int rc = run_forward(o, q, k, v, heads, scale, bias, mask, out, stream, labels, mask_value);
     return rc == FWA_OK ? py::cast(o) : py::cast(rc);
 }
 
@@ -142,14 +158,20 @@ Rows slice_of(const at::Tensor& qkv, int which) {
     return {static_cast<char*>(qkv.data_ptr()) + which * C * qkv.element_size(), 3 * C};
 }
 
-py::object forward_qkv(const at::Tensor& qkv, float scale, const OptTensor& bias, const OptTensor& mask, const OptTensor& labels,
-                       float mask_value) {
+// The library's code, and the output where that is FWA_OK
+int run_forward_qkv(at::Tensor& o, const at::Tensor& qkv, float scale, const OptTensor& bias, const OptTensor& mask, const OptTensor& labels,
+                    float mask_value) {
     need_qkv(qkv);
     const int64_t N = qkv.size(0), L = qkv.size(1), heads = qkv.size(3), C = heads * qkv.size(4);
-    const at::Tensor o = at::empty({N, L, C}, qkv.options());
+    o = at::empty({N, L, C}, qkv.options());
     const Terms t = terms_of(bias, mask, labels, heads, L);
-    const int rc = call_forward(slice_of(qkv, 0), slice_of(qkv, 1), slice_of(qkv, 2), {o.data_ptr(), C}, qkv, N, L, C, (int)heads,
-                                scale, t, mask_value, stream_of(std::nullopt, qkv));
+    return call_forward(slice_of(qkv, 0), slice_of(qkv, 1), slice_of(qkv, 2), {o.data_ptr(), C}, qkv, N, L, C, (int)heads, scale, t,
+                        mask_value, stream_of(std::nullopt, qkv));
+}
+py::object forward_qkv(const at::Tensor& qkv, float scale, const OptTensor& bias, const OptTensor& mask, const OptTensor& labels,
+                       float mask_value) {
+    at::Tensor o;
+    const int rc = run_forward_qkv(o, qkv, scale, bias, mask, labels, mask_value);
     return rc == FWA_OK ? py::cast(o) : py::cast(rc);
 }
 
@@ -169,7 +191,7 @@ int call_backward(const Rows (&r)[7], const at::Tensor& like, const at::Tensor& 
     void* const wp = ws.defined() ? ws.data_ptr() : nullptr;
     const size_t wb = ws.defined() ? (size_t)ws.nbytes() : 0;
     const c10::DeviceGuard guard(like.device());
-    const py::gil_scoped_release nogil;
+    const Nogil nogil;
     if (t.labels_entry())
         return fwa_backward_labels(r[0].p, r[1].p, r[2].p, r[3].p, r[4].p, r[5].p, r[6].p, db, N, (int)L, (int)C, heads, scale,
                                    r[0].ld, r[3].ld, r[4].ld, t.bias, t.bias_dtype, t.labels, mask_value, t.nW, dtype, wp, wb, stream);
@@ -182,43 +204,59 @@ at::Tensor dbias_like(const at::Tensor& q, int64_t heads, int64_t L, bool want) 
 }
 py::object or_none(const at::Tensor& t) { return t.defined() ? py::cast(t) : py::none(); }
 
+struct Grads {
+    at::Tensor q, k, v, bias;  // of the fused tensor: q alone
+};
+
+int run_backward(Grads& d, const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const at::Tensor& d_o, int heads, float scale,
+                 const OptTensor& bias, const OptTensor& mask, bool want_dbias, const OptTensor& workspace,
+                 std::optional<uintptr_t> stream, const OptTensor& dq_out, const OptTensor& dk_out, const OptTensor& dv_out,
+                 const OptTensor& labels, float mask_value) {
+    need_3d(q);
+    const int64_t N = q.size(0), L = q.size(1), C = q.size(2);
+    need_gpu(q, "q");
+    d.q = dq_out ? *dq_out : at::empty(q.sizes(), q.options());
+    d.k = dk_out ? *dk_out : at::empty(q.sizes(), q.options());
+    d.v = dv_out ? *dv_out : at::empty(q.sizes(), q.options());
+    d.bias = dbias_like(q, heads, L, want_dbias);
+    const Terms t = terms_of(bias, mask, labels, heads, L);
+    const at::Tensor ws = workspace ? *workspace : workspace_for(q, N, L, C, heads, want_dbias, t);
+    const Rows r[7] = {rows_of(q, "q", nullptr), rows_of(k, "k", &q), rows_of(v, "v", &q), rows_of(d_o, "d_o", &q),
+                       rows_of(d.q, "dq", &q), rows_of(d.k, "dk", &q), rows_of(d.v, "dv", &q)};
+    return call_backward(r, q, d.bias, N, L, C, heads, scale, t, mask_value, ws, stream_of(stream, q));
+}
 py::object backward(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const at::Tensor& d_o, int heads, float scale,
                     const OptTensor& bias, const OptTensor& mask, bool want_dbias, const OptTensor& workspace,
                     std::optional<uintptr_t> stream, const OptTensor& dq_out, const OptTensor& dk_out, const OptTensor& dv_out,
                     const OptTensor& labels, float mask_value) {
-    need_3d(q);
-    const int64_t N = q.size(0), L = q.size(1), C = q.size(2);
-    need_gpu(q, "q");
-    const at::Tensor dq = dq_out ? *dq_out : at::empty(q.sizes(), q.options());
-    const at::Tensor dk = dk_out ? *dk_out : at::empty(q.sizes(), q.options());
-    const at::Tensor dv = dv_out ? *dv_out : at::empty(q.sizes(), q.options());
-    const at::Tensor db = dbias_like(q, heads, L, want_dbias);
-    const Terms t = terms_of(bias, mask, labels, heads, L);
-    const at::Tensor ws = workspace ? *workspace : workspace_for(q, N, L, C, heads, want_dbias, t);
-    const Rows r[7] = {rows_of(q, "q", nullptr), rows_of(k, "k", &q), rows_of(v, "v", &q), rows_of(d_o, "d_o", &q),
-                       rows_of(dq, "dq", &q), rows_of(dk, "dk", &q), rows_of(dv, "dv", &q)};
-    const int rc = call_backward(r, q, db, N, L, C, heads, scale, t, mask_value, ws, stream_of(stream, q));
+    Grads d;
+    const int rc = run_backward(d, q, k, v, d_o, heads, scale, bias, mask, want_dbias, workspace, stream, dq_out, dk_out, dv_out, labels, mask_value);
     if (rc != FWA_OK) return py::cast(rc);
-    return py::make_tuple(dq, dk, dv, or_none(db));
+    return py::make_tuple(d.q, d.k, d.v, or_none(d.bias));
 }
 
-py::object backward_qkv(const at::Tensor& qkv, const at::Tensor& d_o, float scale, const OptTensor& bias, const OptTensor& mask,
-                        bool want_dbias, const OptTensor& labels, float mask_value) {
+int run_backward_qkv(Grads& d, const at::Tensor& qkv, const at::Tensor& d_o, float scale, const OptTensor& bias, const OptTensor& mask,
+                     bool want_dbias, const OptTensor& labels, float mask_value) {
     need_qkv(qkv);
     const int64_t N = qkv.size(0), L = qkv.size(1), heads = qkv.size(3), C = heads * qkv.size(4);
     need_gpu(d_o, "d_o");
     if (d_o.dim() != 3 || d_o.size(0) != N || d_o.size(1) != L || d_o.size(2) != C || d_o.scalar_type() != qkv.scalar_type() ||
         d_o.device() != qkv.device())
         value_error("d_o must match q in shape, dtype and device");
-    const at::Tensor dqkv = at::empty(qkv.sizes(), qkv.options());
-    const at::Tensor db = dbias_like(qkv, heads, L, want_dbias);
+    d.q = at::empty(qkv.sizes(), qkv.options());
+    d.bias = dbias_like(qkv, heads, L, want_dbias);
     const Terms t = terms_of(bias, mask, labels, heads, L);
     const at::Tensor ws = workspace_for(qkv, N, L, C, (int)heads, want_dbias, t);
     const Rows r[7] = {slice_of(qkv, 0), slice_of(qkv, 1), slice_of(qkv, 2), rows_of(d_o, "d_o", nullptr),
-                       slice_of(dqkv, 0), slice_of(dqkv, 1), slice_of(dqkv, 2)};
-    const int rc = call_backward(r, qkv, db, N, L, C, (int)heads, scale, t, mask_value, ws, stream_of(std::nullopt, qkv));
+                       slice_of(d.q, 0), slice_of(d.q, 1), slice_of(d.q, 2)};
+    return call_backward(r, qkv, d.bias, N, L, C, (int)heads, scale, t, mask_value, ws, stream_of(std::nullopt, qkv));
+}
+py::object backward_qkv(const at::Tensor& qkv, const at::Tensor& d_o, float scale, const OptTensor& bias, const OptTensor& mask,
+                        bool want_dbias, const OptTensor& labels, float mask_value) {
+    Grads d;
+    const int rc = run_backward_qkv(d, qkv, d_o, scale, bias, mask, want_dbias, labels, mask_value);
     if (rc != FWA_OK) return py::cast(rc);
-    return py::make_tuple(dqkv, or_none(db));
+    return py::make_tuple(d.q, or_none(d.bias));
 }
 
 py::object bias_gather(const at::Tensor& table, int k, std::optional<uintptr_t> stream) {
@@ -252,6 +290,110 @@ py::object bias_scatter(const at::Tensor& dbias, int k, std::optional<uintptr_t>
     return rc == FWA_OK ? py::cast(dtable) : py::cast(rc);
 }
 
+// ------------------------------------------------------------------ autograd
+// The two differentiable calls as native nodes.  What they save goes through the engine's saved variables (version counters,
+// saved-tensor hooks); an error in the backward reaches Python as the exception that the direct call raises.
+using torch::autograd::AutogradContext;
+using torch::autograd::variable_list;
+
+OptTensor opt(const at::Tensor& t) { return t.defined() ? OptTensor(t) : OptTensor(); }
+at::Tensor or_undefined(const OptTensor& t) { return t ? *t : at::Tensor(); }
+
+std::string entry_name(const char* what, const OptTensor& bias, const OptTensor& labels) {
+    return std::string(what) + (labels || (bias && bias->scalar_type() == at::kBFloat16) ? "_labels" : "_strided");
+}
+
+// `body`, with whatever it raises left as a Python error that may cross the engine's threads
+template <class Body>
+variable_list with_python_errors(Body body) {
+    try {
+        return body();
+    } catch (py::builtin_exception& e) {
+        const py::gil_scoped_acquire gil;
+        e.set_error();
+        python_error err;
+        err.persist();
+        throw err;
+    }
+}
+[[noreturn]] void raise_status(int rc, const std::string& entry) {
+    const py::gil_scoped_acquire gil;
+    const py::object type = py::module_::import("paper_2501_06480_amd.binding").attr("FwaError");
+    PyErr_SetObject(type.ptr(), type(rc, entry).ptr());
+    python_error err;
+    err.persist();
+    throw err;
+}
+
+// a gradient of the bias that this shape and type do not have is refused in front of the forward
+void need_dbias(const at::Tensor& q, int64_t N, int64_t L, int64_t C, int64_t heads, const OptTensor& bias) {
+    if (!bias || !bias->requires_grad() || N == 0) return;
+    if (fwa_backward_workspace_bytes(N, (int)L, (int)C, (int)heads, dtype_code(q), 1) != 0) return;
+    PyErr_SetString(PyExc_NotImplementedError, "the gradient of the bias is not available for this shape and dtype");
+    throw py::error_already_set();
+}
+
+struct Attention : torch::autograd::Function<Attention> {
+    static at::Tensor forward(AutogradContext* ctx, const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, const OptTensor& bias,
+                              const OptTensor& mask, const OptTensor& labels, int64_t heads, double scale, double mask_value) {
+        ctx->save_for_backward({q, k, v, or_undefined(bias), or_undefined(mask), or_undefined(labels)});
+        ctx->saved_data["heads"] = heads;
+        ctx->saved_data["scale"] = scale;
+        ctx->saved_data["mask_value"] = mask_value;
+        at::Tensor o;
+        const int rc = run_forward(o, q, k, v, (int)heads, (float)scale, bias, mask, std::nullopt, std::nullopt, labels, (float)mask_value);
+        if (rc != FWA_OK) raise_status(rc, entry_name("fwa_forward", bias, labels));
+        return o;
+    }
+    static variable_list backward(AutogradContext* ctx, const variable_list& grads) {
+        return with_python_errors([&]() -> variable_list {
+            const variable_list s = ctx->get_saved_variables();
+            Grads d;
+            const int rc = run_backward(d, s[0], s[1], s[2], grads[0].contiguous(), (int)ctx->saved_data["heads"].toInt(),
+                                        (float)ctx->saved_data["scale"].toDouble(), opt(s[3]), opt(s[4]), s[3].defined() && ctx->needs_input_grad(3),
+                                        std::nullopt, std::nullopt, std::nullopt, std::nullopt, std::nullopt, opt(s[5]),
+                                        (float)ctx->saved_data["mask_value"].toDouble());
+            if (rc != FWA_OK) raise_status(rc, entry_name("fwa_backward", opt(s[3]), opt(s[5])));
+            return {d.q, d.k, d.v, d.bias, at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor()};
+        });
+    }
+};
+struct AttentionQKV : torch::autograd::Function<AttentionQKV> {
+    static at::Tensor forward(AutogradContext* ctx, const at::Tensor& qkv, const OptTensor& bias, const OptTensor& mask,
+                              const OptTensor& labels, double scale, double mask_value) {
+        ctx->save_for_backward({qkv, or_undefined(bias), or_undefined(mask), or_undefined(labels)});
+        ctx->saved_data["scale"] = scale;
+        ctx->saved_data["mask_value"] = mask_value;
+        at::Tensor o;
+        const int rc = run_forward_qkv(o, qkv, (float)scale, bias, mask, labels, (float)mask_value);
+        if (rc != FWA_OK) raise_status(rc, entry_name("fwa_forward", bias, labels));
+        return o;
+    }
+    static variable_list backward(AutogradContext* ctx, const variable_list& grads) {
+        return with_python_errors([&]() -> variable_list {
+            const variable_list s = ctx->get_saved_variables();
+            Grads d;
+            // a saved-tensor hook may have handed the fused tensor back in another layout
+            const int rc = run_backward_qkv(d, s[0].contiguous(), grads[0].contiguous(), (float)ctx->saved_data["scale"].toDouble(), opt(s[1]), opt(s[2]),
+                                            s[1].defined() && ctx->needs_input_grad(1), opt(s[3]), (float)ctx->saved_data["mask_value"].toDouble());
+            if (rc != FWA_OK) raise_status(rc, entry_name("fwa_backward", opt(s[1]), opt(s[3])));
+            return {d.q, d.bias, at::Tensor(), at::Tensor(), at::Tensor(), at::Tensor()};
+        });
+    }
+};
+
+at::Tensor attention(const at::Tensor& q, const at::Tensor& k, const at::Tensor& v, int heads, double scale, const OptTensor& bias,
+                     const OptTensor& mask, const OptTensor& labels, double mask_value) {
+    need_3d(q);
+    need_dbias(q, q.size(0), q.size(1), q.size(2), heads, bias);
+    return Attention::apply(q, k, v, bias, mask, labels, (int64_t)heads, scale, mask_value);
+}
+at::Tensor attention_qkv(const at::Tensor& qkv, double scale, const OptTensor& bias, const OptTensor& mask, const OptTensor& labels, double mask_value) {
+    need_qkv(qkv);
+    need_dbias(qkv, qkv.size(0), qkv.size(1), qkv.size(3) * qkv.size(4), qkv.size(3), bias);
+    return AttentionQKV::apply(qkv, bias, mask, labels, scale, mask_value);
+}
+
 }  // namespace
 
 PYBIND11_MODULE(_fwa_torch, m) {
@@ -259,6 +401,8 @@ PYBIND11_MODULE(_fwa_torch, m) {
     m.def("forward_qkv", &forward_qkv);
     m.def("backward", &backward);
     m.def("backward_qkv", &backward_qkv);
+    m.def("attention", torch::wrap_pybind_function(&attention));
+    m.def("attention_qkv", torch::wrap_pybind_function(&attention_qkv));
     m.def("bias_gather", &bias_gather);
     m.def("bias_scatter", &bias_scatter);
 }
