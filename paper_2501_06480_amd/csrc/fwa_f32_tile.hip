@@ -1,5 +1,5 @@
 // fp32 kernels: windows of up to 64 tokens and head widths 32, 64, 128, 256, forward and
-// backward, and the forward for longer windows of width 32.
+// backward.  (The forward for longer windows is in fwa_f32_rows.hip.)
 // True fp32 arithmetic throughout: v_mfma_f32_16x16x4_f32 products, v_exp_f32, IEEE division.
 // These are the shapes and the precision of the paper's kernel benchmark (section 3.1).
 //
@@ -181,139 +181,6 @@ __global__ void __launch_bounds__(256) fwd_f32_tile_kernel(FwdArgs p) {
     }
 }
 
-// ------------------------------------------- forward, 64 < L <= 256, width 32
-// One workgroup per (window, head): K and V of the head in two LDS slabs, W waves walk the query blocks wave,
-// wave + W, ... with the 16 x L scores of a block in registers.  What bounds it is the fp32 matrix instruction (16
-// per 16 x 16 block of scores, 32 cycles each); so the operands must come from LDS (fetching V element by element
-// from memory for every query block, as the first kernel did, took 278 us at N = 256 windows of 256 tokens, 4 heads,
-// bias, against 98 now; 62 us is the matrix instruction's own time) and a CU needs a second workgroup
-// to load while the first computes: W is the number of waves that leaves the fewest idle turns
-// (NB / (W ceil(NB / W))) among those that let two or more workgroups share a CU.
-constexpr int rows_f32_waves(int nb) {
-    return nb <= 7 ? nb : (nb == 9 || nb == 10 ? 5 : (nb == 13 || nb == 14 ? 7 : 4));
-}
-
-template <int NB, bool BM>
-__global__ void __launch_bounds__(64 * rows_f32_waves(NB), 2) fwd_f32_rows_kernel(FwdArgs p, int parts) {
-    using T = F32Tile<32>;
-    constexpr int W = rows_f32_waves(NB);
-    constexpr int ROWS = 16 * NB;
-    constexpr int PASSES = (ROWS + 8 * W - 1) / (8 * W);  // the workgroup moves 8 W slab rows per pass
-    extern __shared__ __attribute__((aligned(16))) float ldsf[];  // slabs [K][V], each [ROWS][RS]
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int n = lane & 15, g = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t bh = blockIdx.x / (uint32_t)parts, part = blockIdx.x % (uint32_t)parts;
-    const uint32_t w = bh / (uint32_t)p.heads, h = bh % (uint32_t)p.heads;
-    const int first = (int)part * W + wave, step = parts * W;  // this wave's query blocks
-    const int L = p.L;
-    const uint32_t row_bytes = (uint32_t)p.ldq * 4u, row_out = (uint32_t)p.ldo * 4u;
-    const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 4u;
-    const uint32_t tile_bytes = (uint32_t)(L - 1) * row_bytes + 4u * kHeadDim;
-    const __amdgpu_buffer_rsrc_t rq = make_rsrc((const char*)p.q + tile, tile_bytes);
-    float* const sk = ldsf;
-    float* const sv = ldsf + ROWS * T::RS;
-    {
-        const __amdgpu_buffer_rsrc_t rk = make_rsrc((const char*)p.k + tile, tile_bytes);
-        const __amdgpu_buffer_rsrc_t rv = make_rsrc((const char*)p.v + tile, tile_bytes);
-        const uint32_t srow = (uint32_t)tid >> 3, scol = (uint32_t)tid & 7u;
-        f32x4 k[PASSES], v[PASSES];
-#pragma unroll
-        for (int t = 0; t < PASSES; ++t) k[t] = load_f32x4(rk, (8 * W * t + srow) * row_bytes + scol * 16u);
-#pragma unroll
-        for (int t = 0; t < PASSES; ++t) v[t] = load_f32x4(rv, (8 * W * t + srow) * row_bytes + scol * 16u);
-#pragma unroll
-        for (int t = 0; t < PASSES; ++t) {  // rows beyond L arrive as zeros
-            const uint32_t row = 8 * W * t + srow;
-            if (row < (uint32_t)ROWS) {
-                *reinterpret_cast<f32x4*>(sk + row * T::RS + 4 * scol) = k[t];
-                *reinterpret_cast<f32x4*>(sv + row * T::RS + 4 * scol) = v[t];
-            }
-        }
-    }
-    BiasSrc rb = no_bias();
-    MaskSrc msk = {make_rsrc(nullptr, 0), 0.f, false};
-    if (BM) {
-        rb = bias_of_head(p, h);
-        msk = mask_of_window(p, w);
-    }
-    const __amdgpu_buffer_rsrc_t ro =
-        make_rsrc((char*)p.o + ((size_t)w * L * p.ldo + (size_t)h * kHeadDim) * 4u, (uint32_t)(L - 1) * row_out + 4u * kHeadDim);
-    f32x4 qv[T::CH];
-    load_own_rows<32>(qv, rq, row_bytes, first, n, g);
-    __syncthreads();
-
-    for (int qb = first; qb < NB; qb += step) {
-        // Four key blocks at a time: their additive term is requested in front of their score products, which outlast
-        // its way from L2.  The scheduling barriers keep the compiler from hoisting the operand reads of all blocks
-        // (it spills then).
-        const AddendGlobal at = addend_at(rb, msk, (uint32_t)(16 * qb + n), 4u * g, (uint32_t)L);
-        f32x4 s[NB];
-        float m = -INFINITY;
-#pragma unroll
-        for (int j0 = 0; j0 < NB; j0 += 4) {
-            __builtin_amdgcn_sched_barrier(0);
-            f32x4 add[4];
-            if (BM) AddendGlobal{rb, msk, at.off + 64u * j0, at.i4, at.j4 + 64u * j0}.fill(add, 1.0f);
-#pragma unroll
-            for (int jb = j0; jb < (j0 + 4 < NB ? j0 + 4 : NB); ++jb) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = 0; c < T::CH; ++c) {
-                    const f32x4 x = *reinterpret_cast<const f32x4*>(sk + (16 * jb + n) * T::RS + 16 * c + 4 * g);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const float a = x[t], b = qv[c][t];
-                        acc = mfma_f32(a, b, acc);
-                    }
-                }
-                s[jb] = acc;  // S[16 qb + n][16 jb + 4g + r]
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int jb = j0; jb < (j0 + 4 < NB ? j0 + 4 : NB); ++jb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float x = BM ? s[jb][r] * p.scale + add[jb - j0][r] : s[jb][r] * p.scale;
-                    if (jb == NB - 1 && 16 * jb + 4 * g + r >= L) x = -INFINITY;
-                    s[jb][r] = x;
-                    m = fmaxf(m, x);
-                }
-        }
-        if (qb + step < NB) load_own_rows<32>(qv, rq, row_bytes, qb + step, n, g);
-        m = max_over_g(m);
-        float sum = 0.f;
-        f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = {0.f, 0.f, 0.f, 0.f};
-        f32x4 v0[2], v1[2];  // the V values of a key block, fetched one block ahead
-        auto fetch = [&](int jb) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float* const v = sv + (16 * jb + 4 * g + r) * T::RS + n;
-                v0[jb & 1][r] = v[0];
-                v1[jb & 1][r] = v[16];
-            }
-        };
-        fetch(0);
-#pragma unroll
-        for (int jb = 0; jb < NB; ++jb) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (jb + 1 < NB) fetch(jb + 1);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float e = __builtin_amdgcn_exp2f((s[jb][r] - m) * kLog2e);
-                sum += e;
-                const float a = v0[jb & 1][r], b = v1[jb & 1][r];
-                o0 = mfma_f32(a, e, o0);  // o0[r'] = O[16 qb + n][4g + r']
-                o1 = mfma_f32(b, e, o1);  // o1[r'] = O[16 qb + n][16 + 4g + r']
-            }
-        }
-        sum = sum_over_g(sum);
-        const uint32_t off_o = (uint32_t)(16 * qb + n) * row_out + 16u * g;
-        store_f32x4(o0 / sum, ro, off_o);
-        store_f32x4(o1 / sum, ro, off_o + 64);
-    }
-}
-
 // ----------------------------------------------------------------- backward
 // Pass 1 ("query on the lane", K and V parked in the two slabs): S, softmax, dP, delta, dS, dQ.
 // P and dS are not made a second time for dV and dK: the fp32 matrix instruction takes single
@@ -467,31 +334,6 @@ hipError_t launch_fwd_nb(const FwdArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int NB>
-hipError_t launch_fwd_rows(const FwdArgs& a, hipStream_t st) {
-    constexpr int W = rows_f32_waves(NB);
-    // fewer tiles than half the CUs: the query blocks of a tile over several workgroups, each with its own copy of K
-    // and V (2 tiles of 256 tokens: 28 -> 12 us; with 192 tiles on 256 CUs it is a loss, 22 -> 25 us at 196 tokens)
-    const long long tiles = a.N * a.heads;
-    long long parts = cu_count() / tiles;
-    if (parts > (NB + W - 1) / W) parts = (NB + W - 1) / W;
-    if (parts < 1) parts = 1;
-    const unsigned grid = (unsigned)(tiles * parts), block = 64u * W;
-    const size_t lds = f32_slab_bytes<NB, 32>();
-    const bool bm = a.bias || has_mask(a);
-    const void* fn = bm ? reinterpret_cast<const void*>(&fwd_f32_rows_kernel<NB, true>)
-                        : reinterpret_cast<const void*>(&fwd_f32_rows_kernel<NB, false>);
-    {
-        const hipError_t e = allow_lds(fn, lds);
-        if (e != hipSuccess) return e;
-    }
-    if (bm)
-        hipLaunchKernelGGL((fwd_f32_rows_kernel<NB, true>), dim3(grid), dim3(block), lds, st, a, (int)parts);
-    else
-        hipLaunchKernelGGL((fwd_f32_rows_kernel<NB, false>), dim3(grid), dim3(block), lds, st, a, (int)parts);
-    return hipGetLastError();
-}
-
 template <int NB, int D>
 hipError_t launch_bwd_nb(const BwdArgs& a, hipStream_t st) {
     const unsigned grid = (unsigned)(a.N * a.heads);
@@ -528,23 +370,7 @@ hipError_t bwd_d(const BwdArgs& a, hipStream_t s) { FWA_F32_NB_SWITCH(launch_bwd
 }  // namespace
 
 hipError_t launch_forward_f32(const FwdArgs& a, hipStream_t s) {
-    if (a.L > kMaxWideL) {  // width 32
-        switch ((a.L + 15) / 16) {
-            case 5: return launch_fwd_rows<5>(a, s);
-            case 6: return launch_fwd_rows<6>(a, s);
-            case 7: return launch_fwd_rows<7>(a, s);
-            case 8: return launch_fwd_rows<8>(a, s);
-            case 9: return launch_fwd_rows<9>(a, s);
-            case 10: return launch_fwd_rows<10>(a, s);
-            case 11: return launch_fwd_rows<11>(a, s);
-            case 12: return launch_fwd_rows<12>(a, s);
-            case 13: return launch_fwd_rows<13>(a, s);
-            case 14: return launch_fwd_rows<14>(a, s);
-            case 15: return launch_fwd_rows<15>(a, s);
-            case 16: return launch_fwd_rows<16>(a, s);
-            default: return hipErrorInvalidValue;
-        }
-    }
+    if (a.L > kMaxWideL) return launch_forward_f32_rows(a, s);  // width 32
     switch (a.C / a.heads) {
         case 32: return fwd_d<32>(a, s);
         case 64: return fwd_d<64>(a, s);

@@ -1,0 +1,64 @@
+"""The fp32 forward for more than 64 tokens multiplies in bf16 thirds: values over the whole range of fp32, tiles that its
+workgroups walk, and an error no larger than fp32 arithmetic has."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def tensors(N, L, heads, seed):
+    g = torch.Generator().manual_seed(seed)
+    return [torch.randn((N, L, 32 * heads), generator=g) for _ in range(3)]
+
+
+def reference(q, k, v, heads, scale):
+    N, L, C = q.shape
+    Q, K, V = (t.double().view(N, L, heads, 32).transpose(1, 2) for t in (q, k, v))
+    P = torch.softmax(scale * Q @ K.transpose(2, 3).contiguous(), -1)
+    return (P @ V).transpose(1, 2).reshape(N, L, C)
+
+
+def forward(q, k, v, heads, scale):
+    import paper_2501_06480_amd as fwa
+    o = fwa.fwa_forward(q.cuda(), k.cuda(), v.cuda(), heads, scale).cpu().double()
+    torch.cuda.synchronize()
+    return o
+
+
+# more tiles than workgroups are resident, for every count of waves; a sum of L products of 24-bit values, each rounded to
+# 2^-24 of the largest partial sum, and the exponential: 2^-22 of the result's root mean square covers both
+@pytest.mark.parametrize("L", [65, 96, 100, 128, 144, 160, 169, 196, 209, 225, 256])
+def test_walked_tiles_and_error(L):
+    heads, N = 3, 700 if L < 100 else 400
+    q, k, v = tensors(N, L, heads, L)
+    o, want = forward(q, k, v, heads, 32 ** -0.5), reference(q, k, v, heads, 32 ** -0.5)
+    err = (o - want).norm() / want.norm()
+    print(f"L={L} error {err:.2e}", flush=True)
+    assert err < 2 ** -22
+
+
+@pytest.mark.parametrize("L", [81, 144, 256])
+def test_the_whole_range(L):
+    heads, N = 2, 6
+    q, k, v = tensors(N, L, heads, 7 + L)
+    v[0] *= 1e-30                   # tiny values
+    v[5] *= 1e-37
+    v[1, :, :32] *= 1e32            # large ones, one of which rounds to infinity in bf16
+    v[1, 3, 0] = 3.395e38
+    q[1] *= 1e-3                    # (weights of 1 / L: nothing overflows)
+    k[1, 3] = 0
+    q[2, 5] *= 3e37                 # a query block beyond the split, with keys that bring its scores back
+    k[2] *= 1e-37
+    k[3, 2, 4] = float("inf")       # the key's scores are +-inf: rows that see +inf are NaN, the others drop the key
+    v[4, 1, 9] = float("nan")       # one channel of one head
+    q[4, 2, 40] = float("nan")      # one row of the other
+    o, want = forward(q, k, v, heads, 0.2), reference(q, k, v, heads, 0.2)
+    assert torch.equal(torch.isnan(o), torch.isnan(want)) and torch.equal(torch.isinf(o), torch.isinf(want))
+    assert torch.isnan(want[3]).any() and not torch.isnan(want[3, :, 32:]).any() and not torch.isnan(want[3, :, :32]).all()
+    for w in range(N):
+        for h in range(heads):
+            a, b = o[w, :, 32 * h:32 * h + 32], want[w, :, 32 * h:32 * h + 32]
+            ok = torch.isfinite(b)
+            # fp32 scores of up to 60 in the exponent: 2^-24 of them times log2(e) each way, and the sums
+            assert (a - b)[ok].norm() <= 2 ** -18 * b[ok].norm(), (w, h)
