@@ -25,52 +25,13 @@
 #include "fwa_device.h"
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
+#include "fwa_split3.h"
 
 #include <algorithm>
 
 namespace fwa {
 namespace {
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-struct Planes {
-    u32x2 h, m, l;  // four values as 3 x 4 bf16
-};
-// two values -> their packed upper parts; what remains of them is left in a, b (exact)
-__device__ __forceinline__ uint32_t take_upper(float& a, float& b, bf16x2 first, bf16x2 second) {
-    const uint32_t u = pack_bf16(a, b);
-    const bf16x2 h = __builtin_bit_cast(bf16x2, u);
-    a = __builtin_amdgcn_fdot2_f32_bf16(h, first, a, false);
-    b = __builtin_amdgcn_fdot2_f32_bf16(h, second, b, false);
-    return u;
-}
-__device__ __forceinline__ Planes split3(const f32x4& x) {
-    uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;  // (-1, 0), (0, -1), see split_hi_lo_dot
-    asm("" : "+s"(c0));
-    asm("" : "+s"(c1));
-    const bf16x2 first = __builtin_bit_cast(bf16x2, c0), second = __builtin_bit_cast(bf16x2, c1);
-    float a = x[0], b = x[1], c = x[2], d = x[3];
-    const uint32_t h0 = take_upper(a, b, first, second), h1 = take_upper(c, d, first, second);
-    const uint32_t m0 = take_upper(a, b, first, second), m1 = take_upper(c, d, first, second);
-    return Planes{u32x2{h0, h1}, u32x2{m0, m1}, u32x2{pack_bf16(a, b), pack_bf16(c, d)}};
-}
-struct Operand3 {
-    bf16x8 h, m, l;
-};
-__device__ __forceinline__ Operand3 operand3(const Planes& a, const Planes& b) {
-    return Operand3{as_bf16x8(u32x4{a.h.x, a.h.y, b.h.x, b.h.y}), as_bf16x8(u32x4{a.m.x, a.m.y, b.m.x, b.m.y}),
-                    as_bf16x8(u32x4{a.l.x, a.l.y, b.l.x, b.l.y})};
-}
-// the largest magnitude of four values; NaN if one is
-__device__ __forceinline__ float largest(float m, const f32x4& x) {
-    const float a = x[0], b = x[1], c = x[2], d = x[3];
-    asm("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(a), "v"(b));
-    asm("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(c), "v"(d));
-    return m;
-}
-// Values of which the largest is `top` have thirds that the products take: below what rounds to infinity in bf16, no NaN (it
-// would spread to the value it shares a register with), and large enough that what a product drops -- the matrix instruction
-// takes a bf16 below 2^-126 as zero -- is beyond fp32 next to the largest.
-__device__ __forceinline__ bool fits_split(float top) { return top == 0.f || (top > 0x1p-70f && top < 0x1p127f); }
 // keeps the offsets of the rare path out of the registers of the other
 __device__ __forceinline__ uint32_t here(uint32_t s) {
     asm volatile("" : "+s"(s));

@@ -1,6 +1,7 @@
 // fp32 kernels: windows of up to 64 tokens and head widths 32, 64, 128, 256, forward and
 // backward.  (The forward for longer windows is in fwa_f32_rows.hip.)
-// True fp32 arithmetic throughout: v_mfma_f32_16x16x4_f32 products, v_exp_f32, IEEE division.
+// fp32 arithmetic throughout: v_mfma_f32_16x16x4_f32 products (from 33 tokens on the backward takes the same 24 bits in three
+// bf16 parts, below), v_exp_f32, IEEE division.
 // These are the shapes and the precision of the paper's kernel benchmark (section 3.1).
 //
 // One workgroup per (window, head), one wave per block of 16 rows.  The fp32 matrix instruction
@@ -15,6 +16,7 @@
 #include "fwa_device.h"
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
+#include "fwa_split3.h"
 
 namespace fwa {
 namespace {
@@ -193,12 +195,12 @@ __global__ void __launch_bounds__(256) fwd_f32_tile_kernel(FwdArgs p) {
 // the second orientation, as the large-window bf16 kernel must, costs 14 and was 15-30 % slower).
 constexpr int kTileStrideF32 = 68;  // floats per tile row: rows 4 apart fall 16 banks apart
 template <int NB, int D, bool BM>
-__global__ void __launch_bounds__(256) bwd_f32_tile_kernel(BwdArgs p) {
+__device__ __forceinline__ void bwd_f32_products(const BwdArgs& p, float* ldsf) {
     using T = F32Tile<D>;
     constexpr int ROWS = 16 * NB;
     constexpr int TS = kTileStrideF32;
     static_assert(TS <= T::RS || D == 32, "a tile must fit into a slab");
-    extern __shared__ __attribute__((aligned(16))) float ldsf[];  // two slabs [ROWS][max(RS, TS)]
+    // LDS: two slabs [ROWS][max(RS, TS)]
     constexpr int SLAB = ROWS * (T::RS > TS ? T::RS : TS);
     const int tid = threadIdx.x, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
@@ -311,6 +313,241 @@ __global__ void __launch_bounds__(256) bwd_f32_tile_kernel(BwdArgs p) {
     if (active) contract_and_store(make_rsrc((char*)p.dk + tile_d, tile_bytes_d), p.scale);  // dK^T = Q^T dS
 }
 
+template <int NB, int D, bool BM>
+__global__ void __launch_bounds__(256) bwd_f32_plain_kernel(BwdArgs p) {
+    extern __shared__ __attribute__((aligned(16))) float ldsf[];
+    bwd_f32_products<NB, D, BM>(p, ldsf);
+}
+
+// ---------------------------------------------------------------------------
+// The same on the bf16 matrix instruction, with every value as three bf16 parts (fwa_split3.h): 6 products at 8 times the
+// rate.  One LDS slab of three planes holds V, K, dO and Q in turn -- dP needs V alone, and the scores, dS and dQ
+// need K -- and a tile of three planes the probabilities, then dS, for the contractions over the queries, whose operands
+// come out of both through the transposing read.  Unit u (16 bytes) of slab row i lies at u ^ (i & 7) from 128-byte rows on,
+// the tile's 8-byte units as in the bf16 backward: no two lanes of a read or write meet on a bank.  Tiles with values
+// that do not fit the split are done over by bwd_f32_products.
+// Measured against it, us: 2048 windows of 64 tokens, 4 heads of width 64 228 -> 195 (HBM alone 173), 488 windows, width 128
+// 142 -> 109, 244 of width 256 170 -> 144, 1700 of 49 tokens, 6 heads of width 32 144 -> 130; the error against 64 bits halves
+// (3.0e-7 -> 1.4e-7).  The spills of a few registers at NB = 4 buy the third (width 64) workgroup per CU.
+template <int NB, int D>
+struct Split {
+    static constexpr int ROWS = 16 * NB, CH = D / 32, ROW = 2 * D;  // rows, 32-channel chunks, bytes of a plane's row
+    static constexpr uint32_t PS = ROWS * ROW, PT = ROWS * 128;     // bytes of a slab plane and of a tile plane
+    static constexpr size_t bytes = 3 * (PS + PT) + 16;
+    static __device__ __forceinline__ uint32_t at(uint32_t row, uint32_t unit) { return row * ROW + ((D >= 64 ? unit ^ (row & 7u) : unit) << 4); }
+};
+
+template <int NB, int D, bool BM>
+__global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 2 : 1))) bwd_f32_tile_kernel(BwdArgs p) {
+    using S = Split<NB, D>;
+    constexpr int NB2 = (NB + 1) / 2;
+    extern __shared__ __attribute__((aligned(16))) float ldsf[];
+    char* const slab = reinterpret_cast<char*>(ldsf);
+    char* const cells = slab + 3 * S::PS;
+    int* const flag = reinterpret_cast<int*>(cells + 3 * S::PT);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4;
+    const int role = __builtin_amdgcn_readfirstlane(tid >> 6);  // query block in pass 1, key block afterwards
+    const bool active = role < NB;
+    const uint32_t w = blockIdx.x / (uint32_t)p.heads, h = blockIdx.x % (uint32_t)p.heads;
+    const int L = p.L;
+    const uint32_t row_bytes = (uint32_t)p.ldq * 4u, row_g = (uint32_t)p.ldg * 4u, row_d = (uint32_t)p.ldd * 4u;
+    const size_t tile = ((size_t)w * L * p.ldq + (size_t)h * D) * 4u;
+    const size_t tile_g = ((size_t)w * L * p.ldg + (size_t)h * D) * 4u;
+    const size_t tile_d = ((size_t)w * L * p.ldd + (size_t)h * D) * 4u;
+    const uint32_t tile_bytes = (uint32_t)(L - 1) * row_bytes + 4u * D;
+    const uint32_t tile_bytes_d = (uint32_t)(L - 1) * row_d + 4u * D;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+
+    SlabInFlight<D, S::ROWS> kv;
+    kv.request(make_rsrc((const char*)p.v + tile, tile_bytes), row_bytes, tid);
+    f32x4 q[2 * S::CH], dO[2 * S::CH];  // own rows: channels 32 c + 8g .. + 7 (rows beyond L arrive as zeros)
+    {
+        const __amdgpu_buffer_rsrc_t rq = make_rsrc((const char*)p.q + tile, tile_bytes);
+        const __amdgpu_buffer_rsrc_t rg = make_rsrc((const char*)p.d_o + tile_g, (uint32_t)(L - 1) * row_g + 4u * D);
+        const uint32_t row = (uint32_t)(16 * role + n);
+#pragma unroll
+        for (int c = 0; c < 2 * S::CH; ++c) {
+            const uint32_t off = 128u * (c >> 1) + 32u * g + 16u * (c & 1);
+            dO[c] = load_f32x4(rg, row * row_g + off);
+            q[c] = load_f32x4(rq, row * row_bytes + off);
+        }
+    }
+    if (tid == 0) *flag = 0;
+    __syncthreads();
+    bool fits = true;
+    auto park = [&]() {  // three planes of the requested slab
+        const uint32_t srow = (uint32_t)tid / F32Tile<D>::TPR, scol = (uint32_t)tid % F32Tile<D>::TPR;
+        float top = 0.f;
+#pragma unroll
+        for (int t = 0; t < SlabInFlight<D, S::ROWS>::PASSES; ++t) {
+            const uint32_t row = F32Tile<D>::RPP * t + srow;
+            top = largest(top, kv.v[t]);
+            if (row < (uint32_t)S::ROWS) {
+                const Planes x = split3(kv.v[t]);
+                char* const to = slab + S::at(row, scol >> 1) + 8u * (scol & 1u);
+                *reinterpret_cast<u32x2*>(to) = x.h;
+                *reinterpret_cast<u32x2*>(to + S::PS) = x.m;
+                *reinterpret_cast<u32x2*>(to + 2 * S::PS) = x.l;
+            }
+        }
+        fits = fits && fits_split(top);
+    };
+    auto own = [&](const f32x4 (&x)[2 * S::CH], int c) { return operand3(split3(x[2 * c]), split3(x[2 * c + 1])); };
+    auto own_top = [&](const f32x4 (&x)[2 * S::CH]) {
+        float top = 0.f;
+#pragma unroll
+        for (int c = 0; c < 2 * S::CH; ++c) top = largest(top, x[c]);
+        return top;
+    };
+    auto place_rows = [&](const f32x4 (&x)[2 * S::CH]) {
+#pragma unroll
+        for (int c = 0; c < S::CH; ++c) {
+            const Operand3 o = own(x, c);
+            char* const to = slab + S::at((uint32_t)(16 * role + n), (uint32_t)(4 * c + g));
+            *reinterpret_cast<bf16x8*>(to) = o.h;
+            *reinterpret_cast<bf16x8*>(to + S::PS) = o.m;
+            *reinterpret_cast<bf16x8*>(to + 2 * S::PS) = o.l;
+        }
+    };
+    auto three = [&](const char* from, uint32_t plane) {
+        return Operand3{*reinterpret_cast<const bf16x8*>(from), *reinterpret_cast<const bf16x8*>(from + plane), *reinterpret_cast<const bf16x8*>(from + 2 * plane)};
+    };
+    // <slab rows, own rows>: out[jb][r] = X[16 jb + 4g + r] . own[n]
+    auto rows_times = [&](f32x4 (&out)[NB], const f32x4 (&x)[2 * S::CH]) {
+        f32x4 small[NB];
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) out[jb] = small[jb] = zero;
+#pragma unroll
+        for (int c = 0; c < S::CH; ++c) {
+            const Operand3 b = own(x, c);
+#pragma unroll
+            for (int jb = 0; jb < NB; ++jb) {
+                const Operand3 a = three(slab + S::at((uint32_t)(16 * jb + n), (uint32_t)(4 * c + g)), S::PS);
+                small[jb] = small_products(a, b, small[jb]);
+                out[jb] = mfma_bf16(a.h, b.h, out[jb]);
+            }
+        }
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) out[jb] += small[jb];
+    };
+    // channel block cb of the slab's rows 32 rp .. + 31 with the rows on the k-slots
+    auto turned = [&](int rp, int cb) {
+        const bool two = 2 * rp + 1 < NB;
+        const uint16_t* const from =
+            reinterpret_cast<const uint16_t*>(slab + S::at((uint32_t)(32 * rp + 4 * g + (n >> 2)), (uint32_t)(2 * cb + ((n & 3) >> 1))) + 8 * (n & 1));
+        constexpr uint32_t P16 = S::PS / 2, R16 = 16 * D;
+        return Operand3{operand_tr(from, R16, two), operand_tr(from + P16, R16, two), operand_tr(from + 2 * P16, R16, two)};
+    };
+    // out[16 role + n][16 cb + 4g + r] = mul * sum over the slab's rows of X[row][16 cb + 4g + r] b[row]
+    auto contract_and_store = [&](const Operand3 (&b)[NB2], void* out, float mul) {
+        const __amdgpu_buffer_rsrc_t dst = make_rsrc((char*)out + tile_d, tile_bytes_d);
+        const uint32_t off = (uint32_t)(16 * role + n) * row_d + 16u * g;
+#pragma unroll
+        for (int cb = 0; cb < D / 16; ++cb) {
+            f32x4 acc = zero, small = zero;
+#pragma unroll
+            for (int rp = 0; rp < NB2; ++rp) {
+                const Operand3 a = turned(rp, cb);
+                small = small_products(a, b[rp], small);
+                acc = mfma_bf16(a.h, b[rp].h, acc);
+            }
+            store_f32x4((acc + small) * mul, dst, off + 64u * cb);
+        }
+    };
+    const Planes none = {u32x2{0u, 0u}, u32x2{0u, 0u}, u32x2{0u, 0u}};
+
+    park();
+    kv.request(make_rsrc((const char*)p.k + tile, tile_bytes), row_bytes, tid);
+    __syncthreads();
+    f32x4 s[NB], dp[NB];
+    if (active) {
+        fits = fits && fits_split(own_top(q)) && fits_split(own_top(dO));
+        rows_times(dp, dO);  // <v_j, do_i>: query i = 16 role + n, key j = 16 jb + 4g + r
+    }
+    __syncthreads();
+    park();
+    __syncthreads();
+    // cell of the tile's row 16 role + n, key block jb
+    auto cell = [&](int jb) { return cells + (16 * role + n) * 128 + ((jb ^ (n & 3)) << 5) + ((g ^ ((n >> 2) & 3)) << 3); };
+    auto place_tile = [&](const Planes& x, int jb) {
+        *reinterpret_cast<u32x2*>(cell(jb)) = x.h;
+        *reinterpret_cast<u32x2*>(cell(jb) + S::PT) = x.m;
+        *reinterpret_cast<u32x2*>(cell(jb) + 2 * S::PT) = x.l;
+    };
+    Planes ds[NB];
+    if (active) {
+        BiasSrc rb = no_bias();
+        MaskSrc msk = {make_rsrc(nullptr, 0), 0.f, false};
+        if (BM) {
+            rb = bias_of_head(p, h);
+            msk = mask_of_row(mask_of_window(p, w), (uint32_t)(16 * role + n), (uint32_t)L);
+        }
+        rows_times(s, q);  // <k_j, q_i>
+        float m, sum;
+        softmax_f32<NB, BM>(s, p.scale, addend_at(rb, msk, (uint32_t)(16 * role + n), 4u * g, (uint32_t)L), L, g, m, sum);
+        const float inv = 1.0f / sum;
+        float delta = 0.f, top = 0.f;
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[jb][r] *= inv;  // P
+                delta = fmaf(s[jb][r], dp[jb][r], delta);
+            }
+        delta = sum_over_g(delta);
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) {
+            place_tile(split3(s[jb]), jb);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dp[jb][r] = s[jb][r] * (dp[jb][r] - delta);  // dS
+            top = largest(top, dp[jb]);
+            ds[jb] = split3(dp[jb]);
+        }
+        fits = fits && top < 0x1p127f;
+        Operand3 b[NB2];
+#pragma unroll
+        for (int kp = 0; kp < NB2; ++kp) b[kp] = operand3(ds[2 * kp], 2 * kp + 1 < NB ? ds[2 * kp + 1 < NB ? 2 * kp + 1 : 0] : none);
+        contract_and_store(b, p.dq, p.scale);  // dQ^T = K^T dS^T
+    }
+    if (__any(!fits)) *flag = 1;
+    __syncthreads();  // P rows are in the tile; K no longer needed
+    if (__builtin_amdgcn_readfirstlane(*flag) != 0) {  // uniform
+        __syncthreads();
+        bwd_f32_products<NB, D, BM>(p, ldsf);
+        return;
+    }
+    // the tile with the query on the k-slots and key 16 role + n on the lane
+    const uint16_t* const column = reinterpret_cast<const uint16_t*>(cells) + (4 * g + (n >> 2)) * 64 + ((role ^ (n >> 2)) << 4) + (((n & 3) ^ g) << 2);
+    auto tile_columns = [&](Operand3 (&b)[NB2]) {
+        constexpr uint32_t P16 = S::PT / 2;
+#pragma unroll
+        for (int qp = 0; qp < NB2; ++qp) {
+            const bool two = 2 * qp + 1 < NB;
+            const uint16_t* const from = column + 32 * qp * 64;
+            b[qp] = Operand3{operand_tr(from, 16 * 64, two), operand_tr(from + P16, 16 * 64, two), operand_tr(from + 2 * P16, 16 * 64, two)};
+        }
+    };
+    if (active) place_rows(dO);
+    __syncthreads();
+    Operand3 b[NB2];
+    if (active) {
+        tile_columns(b);
+        contract_and_store(b, p.dv, 1.0f);  // dV^T = dO^T P
+    }
+    __syncthreads();  // dO and P no longer needed
+    if (active) {
+        place_rows(q);
+#pragma unroll
+        for (int jb = 0; jb < NB; ++jb) place_tile(ds[jb], jb);
+    }
+    __syncthreads();
+    if (active) {
+        tile_columns(b);
+        contract_and_store(b, p.dk, p.scale);  // dK^T = Q^T dS
+    }
+}
+
 template <int NB, int D>
 size_t f32_slab_bytes() {
     return (size_t)2 * 16 * NB * (D + 4) * 4;
@@ -334,23 +571,29 @@ hipError_t launch_fwd_nb(const FwdArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
+// From 33 tokens on the split products, below that the fp32 ones: with one or two of four waves at work the split of the slabs
+// is most of the kernel (split : fp32, us: 3333 windows of 25 tokens, width 32 113 : 101, 625 of width 256 167 : 138, 1953 of
+// 16 tokens, width 128 109 : 91; 2314 of 36 tokens, width 32 even, 1736 of width 64 114 : 122).
+template <int NB, int D, bool BM>
+hipError_t launch_bwd_bm(const BwdArgs& a, hipStream_t st) {
+    const unsigned grid = (unsigned)(a.N * a.heads);
+    constexpr size_t rs = (D + 4) > kTileStrideF32 ? (D + 4) : kTileStrideF32;  // of bwd_f32_products, where a slab also holds a tile
+    constexpr size_t plain = (size_t)2 * 16 * NB * rs * 4;
+    if constexpr (NB <= 2) {
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(&bwd_f32_plain_kernel<NB, D, BM>), plain);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_f32_plain_kernel<NB, D, BM>), dim3(grid), dim3(256), plain, st, a);
+    } else {
+        constexpr size_t lds = plain > Split<NB, D>::bytes ? plain : Split<NB, D>::bytes;
+        const hipError_t e = allow_lds(reinterpret_cast<const void*>(&bwd_f32_tile_kernel<NB, D, BM>), lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_f32_tile_kernel<NB, D, BM>), dim3(grid), dim3(256), lds, st, a);
+    }
+    return hipGetLastError();
+}
 template <int NB, int D>
 hipError_t launch_bwd_nb(const BwdArgs& a, hipStream_t st) {
-    const unsigned grid = (unsigned)(a.N * a.heads);
-    const bool bm = a.bias || has_mask(a);
-    constexpr size_t rs = (D + 4) > kTileStrideF32 ? (D + 4) : kTileStrideF32;  // a slab also holds a tile
-    const size_t lds = (size_t)2 * 16 * NB * rs * 4;
-    const void* fn = bm ? reinterpret_cast<const void*>(&bwd_f32_tile_kernel<NB, D, true>)
-                        : reinterpret_cast<const void*>(&bwd_f32_tile_kernel<NB, D, false>);
-    {
-        const hipError_t e = allow_lds(fn, lds);
-        if (e != hipSuccess) return e;
-    }
-    if (bm)
-        hipLaunchKernelGGL((bwd_f32_tile_kernel<NB, D, true>), dim3(grid), dim3(256), lds, st, a);
-    else
-        hipLaunchKernelGGL((bwd_f32_tile_kernel<NB, D, false>), dim3(grid), dim3(256), lds, st, a);
-    return hipGetLastError();
+    return a.bias || has_mask(a) ? launch_bwd_bm<NB, D, true>(a, st) : launch_bwd_bm<NB, D, false>(a, st);
 }
 
 #define FWA_F32_NB_SWITCH(FN, D, a, s)            \

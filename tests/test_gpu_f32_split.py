@@ -1,5 +1,5 @@
-"""The fp32 forward for more than 64 tokens multiplies in bf16 thirds: values over the whole range of fp32, tiles that its
-workgroups walk, and an error no larger than fp32 arithmetic has."""
+"""The fp32 forward for more than 64 tokens and the fp32 backward from 33 tokens on multiply in bf16 thirds: values over the
+whole range of fp32, tiles that workgroups walk, and an error no larger than fp32 arithmetic has."""
 import numpy as np
 import pytest
 import torch
@@ -62,3 +62,43 @@ def test_the_whole_range(L):
             ok = torch.isfinite(b)
             # fp32 scores of up to 60 in the exponent: 2^-24 of them times log2(e) each way, and the sums
             assert (a - b)[ok].norm() <= 2 ** -18 * b[ok].norm(), (w, h)
+
+
+def gradients(q, k, v, d_o, heads, scale):
+    N, L, C = q.shape
+    Q, K, V, G = (t.double().view(N, L, heads, C // heads).transpose(1, 2) for t in (q, k, v, d_o))
+    P = torch.softmax(scale * Q @ K.transpose(2, 3).contiguous(), -1)
+    S = G @ V.transpose(2, 3).contiguous()
+    S = P * (S - (P * S).sum(-1, keepdim=True))
+    out = scale * S @ K, scale * S.transpose(2, 3).contiguous() @ Q, P.transpose(2, 3).contiguous() @ G
+    return [t.transpose(1, 2).reshape(N, L, C) for t in out]
+
+
+# either side of the line between the two kernels, and the remainders above it
+@pytest.mark.parametrize("L", [17, 32, 33, 48, 49, 63, 64])
+@pytest.mark.parametrize("d", [32, 64, 128, 256])
+def test_backward(L, d):
+    import paper_2501_06480_amd as fwa
+    heads, N = 2, 9
+    g = torch.Generator().manual_seed(L + d)
+    q, k, v, d_o = (torch.randn((N, L, d * heads), generator=g) for _ in range(4))
+    d_o[0] *= 1e-30                 # tiny gradients
+    v[1, :, :d] *= 1e-37
+    d_o[1, :, :d] *= 1e30
+    q[2, 5] *= 1e33                 # a row that fits the split in part, with keys that bring its scores back
+    k[2] *= 1e-33
+    d_o[3, 2, 4] = float("nan")     # one head of a window
+    k[4, 3, d + 1] = float("inf")
+    v[5, 1, 2] = 3.395e38           # rounds to infinity in bf16
+    d_o[5, :, 2] = 0
+    got = fwa.fwa_backward(q.cuda(), k.cuda(), v.cuda(), d_o.cuda(), heads, d ** -0.5)[:3]
+    torch.cuda.synchronize()
+    for a, b, name in zip(got, gradients(q, k, v, d_o, heads, d ** -0.5), ("dq", "dk", "dv")):
+        a = a.cpu().double()
+        for w in range(N):
+            for h in range(heads):
+                x, y = a[w, :, d * h:d * h + d], b[w, :, d * h:d * h + d]
+                assert torch.equal(torch.isnan(x), torch.isnan(y)), (name, w, h)
+                ok = torch.isfinite(y) & (y.abs() < 3e38)
+                # sums of L and of d products in 2^-24 each, twice, and dP - delta cancels part of it
+                assert (x - y)[ok].norm() <= 2 ** -19 * y[ok].norm(), (name, w, h)
