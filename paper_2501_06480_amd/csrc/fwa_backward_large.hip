@@ -22,17 +22,17 @@
 // kernels for small windows.
 //
 // Both kernels are persistent: a wave keeps its block for life and its workgroup walks the windows bw, bw + G, ...
-// Most of their work is vector instructions (8 to 10 per score besides the exponential, six of them in the keys kernel
+// Most of their work is vector instructions (7 to 8 per score besides the exponential, four of them in the keys kernel
 // for the two hi/lo splits), so everything that does not change from window to window stays out of the loop:
 // (bias + mask[w mod nW]) * log2e of the block's 16 x L scores sits in registers (G is a multiple of the mask
 // period), -delta_i enters as the accumulator the product dO V^T starts from.  Reading the additive term per window
 // instead (the form for dense masks whose period no G is a multiple of) costs its loads, the LDS patch that turns
 // rows into lanes, and three to four more instructions per score.  Measured, N = 1024 windows of 16 x 16 tokens,
-// 4 heads, bias + labels + dBias: rows 210 -> 154 us, keys 283 -> 185 us (kernels of their own that read the term per
-// window and parked the slabs out of registers between two barriers), the whole call 465 -> 339 us; N = 315 windows
-// of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 59 us.  Vector instructions issue in
-// 60-64 % of the cycles now, the matrix cores are busy for 25 %, the LDS for 27-38 %:
-// no unit is full (one instruction less per score gave nothing), two waves per SIMD overlap them only in part.
+// 4 heads, bias + labels + dBias: rows 210 -> 148 us, keys 283 -> 167 us (kernels of their own that read the term per
+// window and parked the slabs out of registers between two barriers), the whole call 465 -> 325 us; N = 315 windows
+// of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 55 us.  Vector instructions issue in
+// 57-61 % of the cycles, the matrix cores are busy for 26-28 %, the LDS for 29-42 %: no unit is full, two waves per SIMD
+// overlap them only in part, and the card runs at 1.9 to 2.0 GHz of 2.4 meanwhile.
 //
 // The statistics M_i, -delta_i (8 bytes per query) travel from one kernel to the other inside the outputs that the
 // second one overwrites: the 16 floats of a query block are as long as the 64-byte slice of the head in one token

@@ -1,9 +1,9 @@
 // fp32 forward for windows of more than 64 tokens, head width 32.
 //
-// The fp32 matrix instruction does 64 products a cycle and SIMD, the bf16 one 512.  An fp32 value is the sum of three bf16
+// The fp32 matrix instruction does 32 products a cycle and SIMD, the bf16 one 512.  An fp32 value is the sum of three bf16
 // values (8 + 8 + 8 significant bits), and a product of two such sums is, but for terms below 2^-26 of it, six bf16
 // products, each exact and summed in fp32: x y = h h' + (h m' + m h') + (h l' + m m' + l h').  So the same result to the
-// last bits of fp32 costs 6 of the 8 times as fast products (the kernel before this one waited for the fp32 instruction in half
+// last bits of fp32 costs 6 products of the 16 times as fast kind (the kernel before this one waited for the fp32 instruction in half
 // of its cycles).  What that needs: every K, V and Q value is split once per tile, every probability once, 3.5 vector
 // instructions each.  The error against 64 bits is smaller than that of the fp32 instruction, whose sums are rounded after
 // every four products instead of 32: 1.2e-7 .. 1.7e-7 (2-norm) against 2.4e-7 .. 3.7e-7 over 81 to 256 tokens.

@@ -320,7 +320,7 @@ __global__ void __launch_bounds__(256) bwd_f32_plain_kernel(BwdArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// The same on the bf16 matrix instruction, with every value as three bf16 parts (fwa_split3.h): 6 products at 8 times the
+// The same on the bf16 matrix instruction, with every value as three bf16 parts (fwa_split3.h): 6 products at 16 times the
 // rate.  One LDS slab of three planes holds V, K, dO and Q in turn -- dP needs V alone, and the scores, dS and dQ
 // need K -- and a tile of three planes the probabilities, then dS, for the contractions over the queries, whose operands
 // come out of both through the transposing read.  Unit u (16 bytes) of slab row i lies at u ^ (i & 7) from 128-byte rows on,
