@@ -227,7 +227,16 @@ __global__ void __launch_bounds__(64 * f32_rows_waves(NB, BM), NB <= 7 || (NB ==
                 qc = load_f32x4(rq, off_q + 16u);
             }
             m = max_over_g(m);
+            // One fma and exponential per score, with the rounding of mb a factor that the division takes out again -- as long
+            // as it is small against 1 (2^-4 at 2^20).  Beyond that the largest score comes off first, which is exact next to it:
+            // scores of 1e10, or a row masked out by the type's lowest value, whose mb is infinite.  (Always subtracting:
+            // 0.7 % more time over 50 calls.)
             float mb = m * kLog2e;
+            if (__any(!(fabsf(m) < 0x1p20f))) {
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb) s[jb] -= m;
+                mb = 0.f;
+            }
             float sum = 0.f;
             auto exponentials = [&](int jb) {
 #pragma unroll
