@@ -16,10 +16,11 @@ from . import binding
 
 
 def _native_node(t) -> bool:
-    """Whether a call goes through the native autograd node: GPU tensors of the plain kind, outside functorch's transforms
-    and dispatch modes.  Everything else takes the Python functions below, which do the same."""
+    """Whether a call goes through the native autograd node: GPU tensors of the plain kind, outside functorch's transforms,
+    dispatch modes and the tracer (which would record of the node the allocation of its output alone).  Everything else
+    takes the Python functions below, which do the same."""
     return (t.is_cuda and type(t) in _PLAIN and not torch._C._are_functorch_transforms_active()
-            and not torch._C._len_torch_dispatch_stack())
+            and not torch._C._len_torch_dispatch_stack() and torch._C._get_tracing_state() is None)
 
 
 _PLAIN = (torch.Tensor, torch.nn.Parameter)

@@ -1,0 +1,30 @@
+"""What cannot go through the native autograd nodes goes through the Python functions: calls that are being traced."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+N, L, HEADS, D = 4, 49, 3, 32
+
+
+def fused(seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn((N, L, 3, HEADS, D), device="cuda", generator=g).bfloat16()
+
+
+@pytest.mark.parametrize("grad", [False, True])
+def test_traced(grad):
+    """A traced call computes: its replay on other inputs is the call on those inputs."""
+    from paper_2501_06480_amd import autograd
+    bias = torch.randn((HEADS, L, L), device="cuda")
+
+    def qkv_call(x):
+        return autograd.window_attention_qkv(x, 0.2, bias)
+
+    def three(q, k, v):
+        return autograd.window_attention(q, k, v, HEADS, 0.2)
+
+    a, b = (fused(s).requires_grad_(grad) for s in (1, 2))
+    rows = [[t[:, :, i].reshape(N, L, -1).contiguous() for i in range(3)] for t in (a.detach(), b.detach())]
+    assert torch.equal(torch.jit.trace(qkv_call, (a,), check_trace=False)(b), qkv_call(b))
+    assert torch.equal(torch.jit.trace(three, tuple(rows[0]), check_trace=False)(*rows[1]), three(*rows[1]))
