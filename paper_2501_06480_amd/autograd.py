@@ -15,12 +15,17 @@ import torch
 from . import binding
 
 
-def _native_node(t) -> bool:
-    """Whether a call goes through the native autograd node: GPU tensors of the plain kind, outside functorch's transforms,
-    dispatch modes and the tracer (which would record of the node the allocation of its output alone).  Everything else
-    takes the Python functions below, which do the same."""
-    return (t.is_cuda and type(t) in _PLAIN and not torch._C._are_functorch_transforms_active()
-            and not torch._C._len_torch_dispatch_stack() and torch._C._get_tracing_state() is None)
+def _native_node(q, *others) -> bool:
+    """Whether a call goes through the native autograd node: GPU tensors of the plain kind in every place, outside functorch's
+    transforms, dispatch modes and the tracer (which would record of the node the allocation of its output alone).
+    Everything else takes the Python functions below, which do the same."""
+    if not (q.is_cuda and type(q) in _PLAIN):
+        return False
+    for t in others:
+        if t is not None and type(t) not in _PLAIN:
+            return False
+    return not (torch._C._are_functorch_transforms_active() or torch._C._len_torch_dispatch_stack()
+                or torch._C._get_tracing_state() is not None)
 
 
 _PLAIN = (torch.Tensor, torch.nn.Parameter)
@@ -71,7 +76,7 @@ class _WindowAttentionQKV(torch.autograd.Function):
 
 def window_attention(q, k, v, heads: int, scale: float, bias=None, mask=None, labels=None, mask_value: float = -100.0):
     """softmax(scale * Q K^T + bias + mask) V per window and head, differentiable in q, k, v and bias."""
-    if _native_node(q):
+    if _native_node(q, k, v, bias, mask, labels):
         return binding._native().attention(q, k, v, int(heads), float(scale), bias, mask, labels, float(mask_value))
     N, L, C = q.shape
     _check_dbias_supported(q, N, L, C, heads, bias)
@@ -80,7 +85,7 @@ def window_attention(q, k, v, heads: int, scale: float, bias=None, mask=None, la
 
 def window_attention_qkv(qkv, scale: float, bias=None, mask=None, labels=None, mask_value: float = -100.0):
     """The same on a fused, contiguous [N, L, 3, heads, d] tensor; returns [N, L, heads * d]."""
-    if _native_node(qkv):
+    if _native_node(qkv, bias, mask, labels):
         return binding._native().attention_qkv(qkv, float(scale), bias, mask, labels, float(mask_value))
     if qkv.dim() != 5 or qkv.shape[2] != 3 or not qkv.is_contiguous():
         raise ValueError("qkv must be a contiguous [N, L, 3, heads, d] tensor")

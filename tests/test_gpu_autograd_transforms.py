@@ -1,4 +1,5 @@
-"""What cannot go through the native autograd nodes goes through the Python functions: calls that are being traced."""
+"""What cannot go through the native autograd nodes goes through the Python functions: calls that are being traced, tensor
+subclasses in any place."""
 import pytest
 import torch
 
@@ -28,3 +29,22 @@ def test_traced(grad):
     rows = [[t[:, :, i].reshape(N, L, -1).contiguous() for i in range(3)] for t in (a.detach(), b.detach())]
     assert torch.equal(torch.jit.trace(qkv_call, (a,), check_trace=False)(b), qkv_call(b))
     assert torch.equal(torch.jit.trace(three, tuple(rows[0]), check_trace=False)(*rows[1]), three(*rows[1]))
+
+
+class Tagged(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("which", ["q", "k", "v", "bias", "mask", "labels"])
+def test_subclasses(which):
+    from paper_2501_06480_amd import autograd
+    q, k, v = (fused(3)[:, :, i].reshape(N, L, -1).contiguous() for i in range(3))
+    bias = torch.randn((HEADS, L, L), device="cuda")
+    mask = torch.zeros((2, L, L), device="cuda")
+    labels = torch.zeros((2, L), dtype=torch.int32, device="cuda")
+    mask, labels = (None, labels) if which == "labels" else (mask, None)
+    args = {"q": q, "k": k, "v": v, "bias": bias, "mask": mask, "labels": labels}
+    args[which] = args[which].as_subclass(Tagged)
+    q = args.pop("q").requires_grad_()
+    o = autograd.window_attention(q, args.pop("k"), args.pop("v"), HEADS, 0.2, **args)
+    assert "autograd" in type(o.grad_fn).__module__  # the Python function's
