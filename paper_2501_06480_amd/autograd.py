@@ -11,21 +11,23 @@ Both take the mask either as a dense fp32 ``mask`` [nW, L, L] or as int32 region
 from __future__ import annotations
 
 import torch
+from torch.autograd import forward_ad
 
 from . import binding
 
 
 def _native_node(q, *others) -> bool:
     """Whether a call goes through the native autograd node: GPU tensors of the plain kind in every place, outside functorch's
-    transforms, dispatch modes and the tracer (which would record of the node the allocation of its output alone).
-    Everything else takes the Python functions below, which do the same."""
+    transforms, dispatch modes, forward-mode differentiation (which the Python functions refuse with an error of its own) and
+    the tracer (which would record of the node the allocation of its output alone).  Everything else takes the Python
+    functions below, which do the same."""
     if not (q.is_cuda and type(q) in _PLAIN):
         return False
     for t in others:
         if t is not None and type(t) not in _PLAIN:
             return False
     return not (torch._C._are_functorch_transforms_active() or torch._C._len_torch_dispatch_stack()
-                or torch._C._get_tracing_state() is not None)
+                or torch._C._get_tracing_state() is not None or forward_ad._current_level >= 0)
 
 
 _PLAIN = (torch.Tensor, torch.nn.Parameter)

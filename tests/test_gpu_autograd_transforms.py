@@ -1,5 +1,5 @@
 """What cannot go through the native autograd nodes goes through the Python functions: calls that are being traced, tensor
-subclasses in any place."""
+subclasses in any place, forward mode."""
 import pytest
 import torch
 
@@ -48,3 +48,16 @@ def test_subclasses(which):
     q = args.pop("q").requires_grad_()
     o = autograd.window_attention(q, args.pop("k"), args.pop("v"), HEADS, 0.2, **args)
     assert "autograd" in type(o.grad_fn).__module__  # the Python function's
+
+
+def test_forward_mode_is_refused_as_before():
+    from paper_2501_06480_amd import autograd
+    import torch.autograd.forward_ad as fwd
+    x = fused(4)
+    with fwd.dual_level():
+        dual = fwd.make_dual(x, torch.ones_like(x))
+        with pytest.raises(NotImplementedError):
+            autograd.window_attention_qkv(dual, 0.2)
+        rows = [dual[:, :, i].reshape(N, L, -1) for i in range(3)]
+        with pytest.raises(NotImplementedError):
+            autograd.window_attention(*rows, HEADS, 0.2)
