@@ -324,8 +324,9 @@ __global__ void __launch_bounds__(256) bwd_f32_plain_kernel(BwdArgs p) {
 // rate.  One LDS slab of three planes holds V, K, dO and Q in turn -- dP needs V alone, and the scores, dS and dQ
 // need K -- and a tile of three planes the probabilities, then dS, for the contractions over the queries, whose operands
 // come out of both through the transposing read.  Unit u (16 bytes) of slab row i lies at u ^ (i & 7) from 128-byte rows on,
-// the tile's 8-byte units as in the bf16 backward: no two lanes of a read or write meet on a bank.  Tiles with values
-// that do not fit the split are done over by bwd_f32_products.
+// the tile's 8-byte units as in the bf16 backward: no two lanes of a read or write meet on a bank.  Inputs, P and dS are lifted
+// (kLift) in front of the split: dS in particular is the product of three factors of any size.  Tiles with values
+// that do not fit are done over by bwd_f32_products.
 // Measured against it, us: 2048 windows of 64 tokens, 4 heads of width 64 228 -> 195 (HBM alone 173), 488 windows, width 128
 // 142 -> 109, 244 of width 256 170 -> 144, 1700 of 49 tokens, 6 heads of width 32 144 -> 130; the error against 64 bits halves
 // (3.0e-7 -> 1.4e-7).  The spills of a few registers at NB = 4 buy the third (width 64) workgroup per CU.
@@ -376,22 +377,23 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
     if (tid == 0) *flag = 0;
     __syncthreads();
     bool fits = true;
-    auto park = [&]() {  // three planes of the requested slab
+    auto park = [&]() {  // three planes of the requested slab, lifted
         const uint32_t srow = (uint32_t)tid / F32Tile<D>::TPR, scol = (uint32_t)tid % F32Tile<D>::TPR;
         float top = 0.f;
 #pragma unroll
         for (int t = 0; t < SlabInFlight<D, S::ROWS>::PASSES; ++t) {
             const uint32_t row = F32Tile<D>::RPP * t + srow;
-            top = largest(top, kv.v[t]);
+            const f32x4 lifted = kv.v[t] * kLift;
+            top = largest(top, lifted);
             if (row < (uint32_t)S::ROWS) {
-                const Planes x = split3(kv.v[t]);
+                const Planes x = split3(lifted);
                 char* const to = slab + S::at(row, scol >> 1) + 8u * (scol & 1u);
                 *reinterpret_cast<u32x2*>(to) = x.h;
                 *reinterpret_cast<u32x2*>(to + S::PS) = x.m;
                 *reinterpret_cast<u32x2*>(to + 2 * S::PS) = x.l;
             }
         }
-        fits = fits && fits_split(top);
+        fits = fits && fits_lifted(top);
     };
     auto own = [&](const f32x4 (&x)[2 * S::CH], int c) { return operand3(split3(x[2 * c]), split3(x[2 * c + 1])); };
     auto own_top = [&](const f32x4 (&x)[2 * S::CH]) {
@@ -413,7 +415,7 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
     auto three = [&](const char* from, uint32_t plane) {
         return Operand3{*reinterpret_cast<const bf16x8*>(from), *reinterpret_cast<const bf16x8*>(from + plane), *reinterpret_cast<const bf16x8*>(from + 2 * plane)};
     };
-    // <slab rows, own rows>: out[jb][r] = X[16 jb + 4g + r] . own[n]
+    // <slab rows, own rows>: out[jb][r] = X[16 jb + 4g + r] . own[n], both lifted
     auto rows_times = [&](f32x4 (&out)[NB], const f32x4 (&x)[2 * S::CH]) {
         f32x4 small[NB];
 #pragma unroll
@@ -429,7 +431,7 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
             }
         }
 #pragma unroll
-        for (int jb = 0; jb < NB; ++jb) out[jb] += small[jb];
+        for (int jb = 0; jb < NB; ++jb) out[jb] = (out[jb] + small[jb]) * kDrop;
     };
     // channel block cb of the slab's rows 32 rp .. + 31 with the rows on the k-slots
     auto turned = [&](int rp, int cb) {
@@ -439,7 +441,7 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
         constexpr uint32_t P16 = S::PS / 2, R16 = 16 * D;
         return Operand3{operand_tr(from, R16, two), operand_tr(from + P16, R16, two), operand_tr(from + 2 * P16, R16, two)};
     };
-    // out[16 role + n][16 cb + 4g + r] = mul * sum over the slab's rows of X[row][16 cb + 4g + r] b[row]
+    // out[16 role + n][16 cb + 4g + r] = mul * sum over the slab's rows of X[row][16 cb + 4g + r] b[row], X and b lifted
     auto contract_and_store = [&](const Operand3 (&b)[NB2], void* out, float mul) {
         const __amdgpu_buffer_rsrc_t dst = make_rsrc((char*)out + tile_d, tile_bytes_d);
         const uint32_t off = (uint32_t)(16 * role + n) * row_d + 16u * g;
@@ -452,7 +454,7 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
                 small = small_products(a, b[rp], small);
                 acc = mfma_bf16(a.h, b[rp].h, acc);
             }
-            store_f32x4((acc + small) * mul, dst, off + 64u * cb);
+            store_f32x4((acc + small) * kDrop * mul, dst, off + 64u * cb);
         }
     };
     const Planes none = {u32x2{0u, 0u}, u32x2{0u, 0u}, u32x2{0u, 0u}};
@@ -462,7 +464,9 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
     __syncthreads();
     f32x4 s[NB], dp[NB];
     if (active) {
-        fits = fits && fits_split(own_top(q)) && fits_split(own_top(dO));
+#pragma unroll
+        for (int c = 0; c < 2 * S::CH; ++c) q[c] *= kLift, dO[c] *= kLift;
+        fits = fits && fits_lifted(own_top(q)) && fits_lifted(own_top(dO));
         rows_times(dp, dO);  // <v_j, do_i>: query i = 16 role + n, key j = 16 jb + 4g + r
     }
     __syncthreads();
@@ -498,13 +502,14 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
         delta = sum_over_g(delta);
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) {
+            s[jb] *= kLift;
             place_tile(split3(s[jb]), jb);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dp[jb][r] = s[jb][r] * (dp[jb][r] - delta);  // dS
+            for (int r = 0; r < 4; ++r) dp[jb][r] = s[jb][r] * (dp[jb][r] - delta);  // dS, lifted
             top = largest(top, dp[jb]);
             ds[jb] = split3(dp[jb]);
         }
-        fits = fits && top < 0x1p127f;
+        fits = fits && fits_lifted(top);
         Operand3 b[NB2];
 #pragma unroll
         for (int kp = 0; kp < NB2; ++kp) b[kp] = operand3(ds[2 * kp], 2 * kp + 1 < NB ? ds[2 * kp + 1 < NB ? 2 * kp + 1 : 0] : none);
