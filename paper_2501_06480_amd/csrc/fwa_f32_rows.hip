@@ -15,8 +15,8 @@
 // four ahead of the products that it is added to (in front of the same four: 95 us instead of 75 below; through LDS in whole lines:
 // 84).
 //
-// Values that do not fit the split (see fits_split) are looked for on the way, and the tiles (K, V) or query blocks (Q)
-// that have some go through the fp32 matrix instruction, with K and V straight from memory.
+// Values that do not fit the split (see fits_split: from 2^43 on, infinite, NaN) are looked for on the way, and the tiles (K, V)
+// or query blocks (Q) that have some go through the fp32 matrix instruction, with K and V straight from memory.
 //
 // Measured, 256 windows of 16 x 16 tokens, 4 heads, bias: 99 -> 75 us (62: the fp32 instruction's own time); 264 tiles of 14 x 14
 // 41 -> 25; 64 windows of 12 x 12, 3 heads 12.5 -> 10.  A wave spends its time in thirds on scores, on probabilities and their
@@ -105,18 +105,19 @@ __global__ void __launch_bounds__(64 * f32_rows_waves(NB, BM), NB <= 7 || (NB ==
 
     uint32_t turn = 0u;
     for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x, turn ^= 1u) {
-        float top_k = 0.f, top_v = 0.f;
+        float top = 0.f;
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) {
             const uint32_t row = 8 * W * i + srow;
-            top_k = largest(top_k, nk[i]);
-            top_v = largest(top_v, nv[i]);
+            top = largest(largest(top, nk[i]), nv[i]);
             if (ROWS % (8 * W) == 0 || row < (uint32_t)ROWS) {
                 put(lk, row, nk[i]);
-                put(lv, row, nv[i]);
+                put(lv, row, nv[i] * kLift);
             }
         }
-        if (__any(!fits_split(top_k) || !fits_split(top_v))) flag[turn] = 1;
+        // K and Q go without the lift: what they lose, 2^-134 of a value below 2^-110, is nothing to a score, whatever Q and K
+        // that fit it is multiplied by, unless the scale makes it something.
+        if (__any(!fits_split(top)) || !(fabsf(p.scale) < 0x1p40f)) flag[turn] = 1;
         __syncthreads();
         const bool wide = __builtin_amdgcn_readfirstlane(flag[turn]) != 0;
         if (tid == 0) flag[turn ^ 1u] = 0;  // read by all before the barrier that ended the last tile
@@ -238,10 +239,11 @@ __global__ void __launch_bounds__(64 * f32_rows_waves(NB, BM), NB <= 7 || (NB ==
                 mb = 0.f;
             }
             float sum = 0.f;
-            auto exponentials = [&](int jb) {
+            // Split, the weights are lifted like V (2.5 % of the time; as a multiplication it took registers that spilled)
+            auto exponentials = [&](int jb, int lift) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float e = __builtin_amdgcn_exp2f(fmaf(s[jb][r], kLog2e, -mb));
+                    const float e = ldexpf(__builtin_amdgcn_exp2f(fmaf(s[jb][r], kLog2e, -mb)), lift);
                     sum += e;
                     s[jb][r] = e;
                 }
@@ -258,8 +260,8 @@ __global__ void __launch_bounds__(64 * f32_rows_waves(NB, BM), NB <= 7 || (NB ==
                     const bf16x8 h0 = operand_tr(v, 512, two), h1 = operand_tr(v + 16, 512, two);
                     const bf16x8 m0 = operand_tr(v + P16, 512, two), m1 = operand_tr(v + P16 + 16, 512, two);
                     const bf16x8 l0 = operand_tr(v + 2 * P16, 512, two), l1 = operand_tr(v + 2 * P16 + 16, 512, two);
-                    exponentials(2 * kp);
-                    if (two) exponentials(2 * kp + 1);
+                    exponentials(2 * kp, kLiftBits);
+                    if (two) exponentials(2 * kp + 1, kLiftBits);
                     Planes second = {u32x2{0u, 0u}, u32x2{0u, 0u}, u32x2{0u, 0u}};
                     if (two) second = split3(s[two ? 2 * kp + 1 : 0]);
                     const Operand3 e = operand3(split3(s[2 * kp]), second);
@@ -277,14 +279,14 @@ __global__ void __launch_bounds__(64 * f32_rows_waves(NB, BM), NB <= 7 || (NB ==
                     t1 = mfma_bf16(h1, e.l, t1);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                o0 += t0;
-                o1 += t1;
+                o0 = (o0 + t0) * (1.0f / kLift);  // the lift of the weights leaves with their sum
+                o1 = (o1 + t1) * (1.0f / kLift);
             } else {
                 const __amdgpu_buffer_rsrc_t rv = make_rsrc((const char*)p.v + tile, tile_bytes);
                 asm volatile("" : "+v"(mb));  // or the exponentials of both paths are taken in front of the branch
 #pragma unroll
                 for (int jb = 0; jb < NB; ++jb) {
-                    exponentials(jb);
+                    exponentials(jb, 0);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const uint32_t off = (uint32_t)(16 * jb + 4 * g + r) * here(row_bytes) + 4u * n;

@@ -42,17 +42,15 @@ __device__ __forceinline__ float largest(float m, const f32x4& x) {
     asm("v_maximum3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(c), "v"(d));
     return m;
 }
-// Values of which the largest is `top` have thirds that the products take: below what rounds to infinity in bf16, no NaN (it
-// would spread to the value it shares a register with), and large enough that what a product drops -- the matrix instruction
-// takes a bf16 below 2^-126 as zero -- is beyond fp32 next to the largest.
-__device__ __forceinline__ bool fits_split(float top) { return top == 0.f || (top > 0x1p-70f && top < 0x1p127f); }
-
 // The smallest step of a bf16 is 2^-133 (subnormal ones count: the conversion, the dot product and the matrix instruction take
-// and give them), so a value below 2^-110 has no third of its own any more.  Times kLift every fp32 value has, subnormal ones
-// too, and the results of two lifted operands come back with kDrop: exact, both.
+// and give them), so the thirds of a value below 2^-110 lose bits, 2^-134 at most.  Times kLift every fp32 value has exact
+// thirds, subnormal ones too.  Multiplying by it and by its inverse (kDrop: for a product of two) is exact.
+constexpr int kLiftBits = 16;
 constexpr float kLift = 0x1p16f, kDrop = 0x1p-32f;
-// Lifted values of which the largest is `top` have products that stay finite in sums of up to 256, parts included: a product of
-// fp32 values overflows as a whole, to one infinity, its parts to infinities of both signs.  No NaN, as above.
+// Values of which the largest is `top` (fits_lifted: lifted ones) have products whose sums of up to 256 stay finite in every
+// part.  Beyond that a product of fp32 values overflows as a whole, to one infinity, but its parts to infinities of both signs.  A
+// NaN does not fit either: it would spread to the value it shares a register with.
+__device__ __forceinline__ bool fits_split(float top) { return top < 0x1p43f; }
 __device__ __forceinline__ bool fits_lifted(float top) { return top < 0x1p59f; }
 // The five small ones of the six products (the largest, h h', is the caller's), smallest first.
 __device__ __forceinline__ f32x4 small_products(const Operand3& a, const Operand3& b, f32x4 acc) {
