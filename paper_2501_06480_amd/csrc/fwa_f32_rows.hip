@@ -50,9 +50,8 @@ constexpr int f32_rows_waves(int nb, bool bm) {
 template <int NB>
 constexpr size_t f32_rows_lds() { return (size_t)6 * 16 * NB * 64 + 16; }
 
-template <int NB, bool BM>
-__global__ void __launch_bounds__(64 * f32_rows_waves(NB, BM), NB <= 7 || (NB == 8 && !BM) ? 3 : 2) fwd_f32_rows_kernel(FwdArgs p, uint32_t parts, uint32_t tiles) {
-    constexpr int W = f32_rows_waves(NB, BM);
+template <int NB, bool BM, int W>
+__global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)) ? 3 : 2) fwd_f32_rows_kernel(FwdArgs p, uint32_t parts, uint32_t tiles) {
     constexpr int ROWS = 16 * NB;
     constexpr int PASSES = (ROWS + 8 * W - 1) / (8 * W);  // the workgroup moves 8 W slab rows per pass
     constexpr uint32_t SLAB = ROWS * 64;                  // bytes of a plane; rows of 32 bf16
@@ -307,21 +306,32 @@ __global__ void __launch_bounds__(64 * f32_rows_waves(NB, BM), NB <= 7 || (NB ==
     }
 }
 
-template <int NB, bool BM>
-hipError_t launch_rows_bm(const FwdArgs& a, hipStream_t st) {
-    constexpr int W = f32_rows_waves(NB, BM);
+template <int NB, bool BM, int W>
+hipError_t launch_rows_w(const FwdArgs& a, hipStream_t st) {
     static std::atomic<int> once{0};
     int per_cu = 1;
-    const hipError_t e = workgroups_per_cu(reinterpret_cast<const void*>(&fwd_f32_rows_kernel<NB, BM>), 64u * W, f32_rows_lds<NB>(), once, per_cu);
+    const hipError_t e = workgroups_per_cu(reinterpret_cast<const void*>(&fwd_f32_rows_kernel<NB, BM, W>), 64u * W, f32_rows_lds<NB>(), once, per_cu);
     if (e != hipSuccess) return e;
     // While the chip holds several workgroups per tile: the query blocks of a tile over them, each with its own copy of K and V
     // (150 tiles of 196 tokens 15.4 -> 13.9 us), down to one block per SIMD (with two for half of them 8.7 -> 11.1).
     const long long pairs = a.N * a.heads, resident = (long long)cu_count() * per_cu;
-    const long long parts = std::max(1LL, std::min(resident / pairs, (long long)(NB + 3) / 4));
+    const long long parts = W > f32_rows_waves(NB, BM) ? 1LL : std::max(1LL, std::min(resident / pairs, (long long)(NB + 3) / 4));
     const long long tiles = pairs * parts;
     const unsigned grid = (unsigned)std::min(tiles, resident);
-    hipLaunchKernelGGL((fwd_f32_rows_kernel<NB, BM>), dim3(grid), dim3(64u * W), f32_rows_lds<NB>(), st, a, (uint32_t)parts, (uint32_t)tiles);
+    hipLaunchKernelGGL((fwd_f32_rows_kernel<NB, BM, W>), dim3(grid), dim3(64u * W), f32_rows_lds<NB>(), st, a, (uint32_t)parts, (uint32_t)tiles);
     return hipGetLastError();
+}
+template <int NB, bool BM>
+hipError_t launch_rows_bm(const FwdArgs& a, hipStream_t st) {
+    if constexpr (NB == 7) {
+        // More tiles than half the CUs but not more than those: a wave per block.  Of two workgroups of four waves per tile some
+        // CUs get both, and split K and V twice (200 tiles of 100 tokens, bias 9.0 -> 7.1 us, without 6.7 -> 6.2).  Up to half
+        // the CUs each of the two has one to itself; beyond one tile per CU seven waves leave no room for a second workgroup.
+        // (At 5, 6 and 8 blocks the two workgroups were no slower than the fp32 instruction; here they were, 7.9 us.)
+        const long long pairs = a.N * a.heads;
+        if (2 * pairs > cu_count() && pairs <= cu_count()) return launch_rows_w<NB, BM, NB>(a, st);
+    }
+    return launch_rows_w<NB, BM, f32_rows_waves(NB, BM)>(a, st);
 }
 template <int NB>
 hipError_t launch_rows(const FwdArgs& a, hipStream_t st) {

@@ -34,3 +34,19 @@ def test_forward(oracle, L, N, heads, form):
     torch.cuda.synchronize()
     want = oracle.forward(x["q"], x["k"], x["v"], heads, w.scale, bias, mask)
     assert max_abs(to_f64(o), want) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("L", [97, 100, 112])
+@pytest.mark.parametrize("tiles", [128, 129, 256, 257])
+@pytest.mark.parametrize("form", ["none", "bias"])
+def test_about_one_tile_per_cu(oracle, L, tiles, form):
+    """7 blocks: a wave per block from over half the 256 CUs to all of them, four waves per workgroup on either side."""
+    import torch
+    import paper_2501_06480_amd as fwa
+    w = synth.Workload(f"f32_rows_tiles_L{L}", tiles, L, 32, 1, "f32", 9400 + L, 0)
+    x = synth.draw(w)
+    bias = None if form == "none" else synth.normal((1, L, L), 9500 + L, 0.5)
+    q, k, v = (to_device(x, w, n) for n in ("q", "k", "v"))
+    o = fwa.fwa_forward(q, k, v, 1, w.scale, f32_device(bias))
+    torch.cuda.synchronize()
+    assert max_abs(to_f64(o), oracle.forward(x["q"], x["k"], x["v"], 1, w.scale, bias, None)) <= TOL["f32"]
