@@ -15,8 +15,10 @@
 // four ahead of the products that it is added to (in front of the same four: 95 us instead of 75 below; through LDS in whole lines:
 // 84).
 //
-// Values that do not fit the split (see fits_split: from 2^43 on, infinite, NaN) are looked for on the way, and the tiles (K, V)
-// or query blocks (Q) that have some go through the fp32 matrix instruction, with K and V straight from memory.
+// Values that do not fit (Q and K from 2^60 on, V from 2^86, infinities, NaN) are looked for on the way, and the tiles (K, V) or
+// query blocks (Q) that have some go through the fp32 matrix instruction, with K from memory and V in LDS as it is: 146 us
+// where all tiles do in the first case below (96 the kernel before this one), 60 at 256 tiles of 12 x 12, 4 heads (47), 41 at 864 of
+// 9 x 9, 2 heads (37).
 //
 // Measured, 256 windows of 16 x 16 tokens, 4 heads, bias: 99 -> 75 us (62: the fp32 instruction's own time); 264 tiles of 14 x 14
 // 41 -> 25; 64 windows of 12 x 12, 3 heads 12.5 -> 10.  A wave spends its time in thirds on scores, on probabilities and their
@@ -47,6 +49,10 @@ __device__ __forceinline__ uint32_t here(uint32_t s) {
 constexpr int f32_rows_waves(int nb, bool bm) {
     return nb <= 6 ? 3 : (nb == 9 ? (bm ? 5 : 9) : (nb <= 13 ? 4 : (nb <= 14 ? 7 : 8)));
 }
+// Magnitudes below which the sums of 32 score products, resp. of 256 products of weights and V, both lifted, stay finite in every
+// part (see fits_lifted)
+constexpr float kMostQK = 0x1p60f, kMostV = 0x1p86f;
+constexpr uint32_t kRowV = 144;  // bytes from row to row of a V that is not split (32 floats and room between the banks)
 template <int NB>
 constexpr size_t f32_rows_lds() { return (size_t)6 * 16 * NB * 64 + 16; }
 
@@ -104,11 +110,12 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
 
     uint32_t turn = 0u;
     for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x, turn ^= 1u) {
-        float top = 0.f;
+        float top = 0.f, top_v = 0.f;
 #pragma unroll
         for (int i = 0; i < PASSES; ++i) {
             const uint32_t row = 8 * W * i + srow;
-            top = largest(largest(top, nk[i]), nv[i]);
+            top = largest(top, nk[i]);
+            top_v = largest(top_v, nv[i]);
             if (ROWS % (8 * W) == 0 || row < (uint32_t)ROWS) {
                 put(lk, row, nk[i]);
                 put(lv, row, nv[i] * kLift);
@@ -116,9 +123,18 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
         }
         // K and Q go without the lift: what they lose, 2^-134 of a value below 2^-110, is nothing to a score, whatever Q and K
         // that fit it is multiplied by, unless the scale makes it something.
-        if (__any(!fits_split(top)) || !(fabsf(p.scale) < 0x1p40f)) flag[turn] = 1;
+        if (__any(!(top < kMostQK) || !(top_v < kMostV)) || !(fabsf(p.scale) < 0x1p40f)) flag[turn] = 1;
         __syncthreads();
         const bool wide = __builtin_amdgcn_readfirstlane(flag[turn]) != 0;
+        if (wide) {  // V as it is, over its planes
+            uint32_t w, h;
+            tile_of(t, w, h);
+            const __amdgpu_buffer_rsrc_t rv = make_rsrc((const char*)p.v + ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 4u, tile_bytes);
+#pragma unroll 1
+            for (uint32_t row = srow; row < (uint32_t)ROWS; row += 8 * W)
+                *reinterpret_cast<f32x4*>(lv + row * kRowV + scol * 16u) = load_f32x4(rv, row * row_bytes + scol * 16u);
+            __syncthreads();
+        }
         if (tid == 0) flag[turn ^ 1u] = 0;  // read by all before the barrier that ended the last tile
         f32x4 qa = nqa, qc = nqc;
         if (t + gridDim.x < tiles) request(t + gridDim.x);
@@ -137,7 +153,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
             msk = mask_of_window(p, w);
         }
         for (int qb = (int)(t % parts + parts * wave); qb < NB; qb += (int)parts * W) {
-            const bool fp32 = wide || __any(!fits_split(largest(largest(0.f, qa), qc)));
+            const bool fp32 = wide || __any(!(largest(largest(0.f, qa), qc) < kMostQK));
             const Operand3 q = operand3(split3(qa), split3(qc));
             const __amdgpu_buffer_rsrc_t rk = make_rsrc((const char*)p.k + tile, tile_bytes);
             // Four key blocks at a time: their additive term is requested in front of their score products, which outlast its
@@ -281,15 +297,16 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
                 o0 = (o0 + t0) * (1.0f / kLift);  // the lift of the weights leaves with their sum
                 o1 = (o1 + t1) * (1.0f / kLift);
             } else {
-                const __amdgpu_buffer_rsrc_t rv = make_rsrc((const char*)p.v + tile, tile_bytes);
+                int at = lane;
+                asm volatile("" : "+v"(at));  // or the address is kept in a register over the loop
+                const float* const v = reinterpret_cast<const float*>(lv + (at >> 4) * (4 * kRowV)) + (at & 15);
                 asm volatile("" : "+v"(mb));  // or the exponentials of both paths are taken in front of the branch
 #pragma unroll
                 for (int jb = 0; jb < NB; ++jb) {
                     exponentials(jb, 0);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const uint32_t off = (uint32_t)(16 * jb + 4 * g + r) * here(row_bytes) + 4u * n;
-                        const float a = load_f32(rv, off), b = load_f32(rv, off + 64u), e = s[jb][r];
+                        const float a = v[(16 * jb + r) * (kRowV / 4)], b = v[(16 * jb + r) * (kRowV / 4) + 16], e = s[jb][r];
                         o0 = mfma_f32(a, e, o0);
                         o1 = mfma_f32(b, e, o1);
                     }

@@ -47,10 +47,9 @@ __device__ __forceinline__ float largest(float m, const f32x4& x) {
 // thirds, subnormal ones too.  Multiplying by it and by its inverse (kDrop: for a product of two) is exact.
 constexpr int kLiftBits = 16;
 constexpr float kLift = 0x1p16f, kDrop = 0x1p-32f;
-// Values of which the largest is `top` (fits_lifted: lifted ones) have products whose sums of up to 256 stay finite in every
+// Lifted values of which the largest is `top` (below 2^43 as they were) have products whose sums of up to 256 stay finite in every
 // part.  Beyond that a product of fp32 values overflows as a whole, to one infinity, but its parts to infinities of both signs.  A
 // NaN does not fit either: it would spread to the value it shares a register with.
-__device__ __forceinline__ bool fits_split(float top) { return top < 0x1p43f; }
 __device__ __forceinline__ bool fits_lifted(float top) { return top < 0x1p59f; }
 // The five small ones of the six products (the largest, h h', is the caller's), smallest first.
 __device__ __forceinline__ f32x4 small_products(const Operand3& a, const Operand3& b, f32x4 acc) {
