@@ -56,12 +56,6 @@ struct LargeGeom {
 constexpr uint32_t kLargeStride = 4;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// A scalar whose sums with lane values are formed where they are used, not kept in registers over the loop.
-__device__ __forceinline__ uint32_t here(uint32_t s) {
-    asm volatile("" : "+s"(s));
-    return s;
-}
-
 __device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
     const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
     return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});

@@ -114,6 +114,11 @@ __device__ __forceinline__ void load_to_lds(const u32x4& r, uint32_t voffset, ui
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t bytes, uint32_t voffset, uint32_t lds_off) {
     load_to_lds(lds_source(base, bytes), voffset, lds_off);
 }
+// A scalar whose sums and products with lane values are formed where they are used, not kept in registers over a loop.
+__device__ __forceinline__ uint32_t here(uint32_t s) {
+    asm volatile("" : "+s"(s));
+    return s;
+}
 // all but the N youngest global loads and stores of this wave are complete
 template <int N>
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
@@ -121,9 +126,11 @@ __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)"
 __device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Of several workgroups on a CU the scheduler serves the oldest first: the others get what it leaves, and when it has
-// finished they run alone.  The priority of a wave with `left` windows to go is left mod 4, so that of two workgroups
-// less than four windows apart the one behind is served first.  Keys kernel of the large-window backward, two workgroups
-// per CU with 32 windows of 16 x 16 tokens each: the first ended at 129 us and the second at 173, half of it alone on
+// finished they run alone.  The priority of a wave with `left` windows to go is left mod 4: of two workgroups that are g < 4
+// windows apart the one behind is served first at 4 - g of every 4 positions, the one ahead at the other g (across a multiple
+// of four its remainder is the larger one).  So a distance of one window shrinks, one of two stays, and the two no longer
+// drift apart by dozens.  Keys kernel of the large-window backward, two workgroups
+// per CU with 32 windows of 16 x 16 tokens each: without it the first ended at 129 us and the second at 173, half of it alone on
 // the CU (whole call 340 -> 332 us; 14 x 14, 315 windows, 5 heads 101.6 -> 97.8).  No gain where the memory system or a
 // workgroup's own barriers set the pace: three single heads per CU in the cooperative backward, the forward.
 __device__ __forceinline__ void take_turns(uint32_t left) {

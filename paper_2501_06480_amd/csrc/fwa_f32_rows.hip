@@ -22,8 +22,8 @@
 //
 // Measured, 256 windows of 16 x 16 tokens, 4 heads, bias: 99 -> 75 us (62: the fp32 instruction's own time); 264 tiles of 14 x 14
 // 41 -> 25; 64 windows of 12 x 12, 3 heads 12.5 -> 10.  A wave spends its time in thirds on scores, on probabilities and their
-// products, and on stores, splits and barriers; with two or three waves per SIMD the matrix cores (25 % busy) and
-// the vector ALU (50 %) overlap in part.
+// products, and on stores, splits and barriers, which two or three waves per SIMD overlap in part: in the first case the
+// vector ALU is busy for 35 % of the cycles, the matrix cores for 25 %, the LDS for 23 %.
 #include "fwa_device.h"
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
@@ -33,12 +33,6 @@
 
 namespace fwa {
 namespace {
-
-// keeps the offsets of the rare path out of the registers of the other
-__device__ __forceinline__ uint32_t here(uint32_t s) {
-    asm volatile("" : "+s"(s));
-    return s;
-}
 
 // Waves per workgroup.  LDS and registers leave a CU room for 8 waves (12 while the kernel fits 168 registers: up to 7 blocks,
 // 8 without an additive term), and what counts is that they come as two workgroups or more, one loading and splitting while the
@@ -189,17 +183,12 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
                     for (int jb = j0; jb < j1; ++jb) {
                         const Operand3 c = k;
                         if (jb + 1 < j1) k = k_rows(jb + 1);
-                        f32x4 a = mfma_bf16(c.l, q.h, zero);  // the small terms first
-                        a = mfma_bf16(c.h, q.l, a);
-                        a = mfma_bf16(c.m, q.m, a);
-                        a = mfma_bf16(c.m, q.h, a);
-                        a = mfma_bf16(c.h, q.m, a);
-                        s[jb] = mfma_bf16(c.h, q.h, a);  // S[16 qb + n][16 jb + 4g + r]
+                        s[jb] = mfma_bf16(c.h, q.h, small_products(c, q, zero));  // S[16 qb + n][16 jb + 4g + r]
                     }
                 } else {
 #pragma unroll
                     for (int jb = j0; jb < j1; ++jb) {
-                        const uint32_t off = (uint32_t)(16 * jb + n) * here(row_bytes) + 32u * g;
+                        const uint32_t off = (uint32_t)(16 * jb + n) * here(row_bytes) + 32u * g;  // not kept beside the split path
                         const f32x4 ka = load_f32x4(rk, off), kc = load_f32x4(rk, off + 16u);
                         f32x4 a = zero;
 #pragma unroll
@@ -280,6 +269,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
                     Planes second = {u32x2{0u, 0u}, u32x2{0u, 0u}, u32x2{0u, 0u}};
                     if (two) second = split3(s[two ? 2 * kp + 1 : 0]);
                     const Operand3 e = operand3(split3(s[2 * kp]), second);
+                    // (in the order of small_products, each half on its own: even to 5 % slower, at 12 x 12 with a bias)
                     t0 = mfma_bf16(l0, e.h, t0);
                     t1 = mfma_bf16(l1, e.h, t1);
                     o0 = mfma_bf16(h0, e.h, o0);
