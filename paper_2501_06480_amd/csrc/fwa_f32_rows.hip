@@ -238,8 +238,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
             // 0.7 % more time over 50 calls.)
             float mb = m * kLog2e;
             if (__any(!(fabsf(m) < 0x1p20f))) {
-#pragma unroll
-                for (int jb = 0; jb < NB; ++jb) s[jb] -= m;
+                subtract_rounded(s, m);
                 mb = 0.f;
             }
             float sum = 0.f;

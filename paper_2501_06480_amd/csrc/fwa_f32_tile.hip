@@ -95,23 +95,34 @@ __device__ __forceinline__ void softmax_f32(f32x4 (&s)[NB], float scale, const A
     m = -INFINITY;
     f32x4 add[NB];
     if (BM) addend.fill(add, 1.0f);
+    // Without an additive term (and but for the last block, whose padding is -inf) the scale is applied once more by the fma that
+    // subtracts the maximum: the rounding of a score stays out of its exponential.  That of the maximum is then a factor, which the
+    // division takes out again as long as it is small against 1 (2^-4 at 2^20).  Beyond that the rounded scores are subtracted.
+    float mul = scale, top;
 #pragma unroll
     for (int jb = 0; jb < NB; ++jb) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float x = BM ? s[jb][r] * scale + add[jb][r] : s[jb][r] * scale;
+            float x = BM ? fmaf(s[jb][r], scale, add[jb][r]) : s[jb][r] * scale;
             if (jb == NB - 1 && 16 * jb + 4 * g + r >= L) x = -INFINITY;
-            s[jb][r] = x;
+            if (BM || jb == NB - 1) s[jb][r] = x;
             m = fmaxf(m, x);
         }
     }
-    m = max_over_g(m);
+    top = m = max_over_g(m);
+    if (!BM && NB > 1 && __builtin_expect(__any(!(fabsf(m) < 0x1p20f)), 0)) {
+#pragma unroll
+        for (int jb = 0; jb + 1 < NB; ++jb) s[jb] *= scale;
+        subtract_rounded(s, m);
+        mul = 1.0f;
+        top = 0.f;
+    }
     sum = 0.f;
 #pragma unroll
     for (int jb = 0; jb < NB; ++jb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float e = __builtin_amdgcn_exp2f((s[jb][r] - m) * kLog2e);
+            const float e = __builtin_amdgcn_exp2f((BM || jb == NB - 1 ? s[jb][r] - top : fmaf(s[jb][r], mul, -top)) * kLog2e);
             s[jb][r] = e;
             sum += e;
         }

@@ -282,6 +282,19 @@ __device__ __forceinline__ void fill_rows_patch(f32x4 (&add)[NB], const BiasSrc&
 #pragma unroll
     for (int jb = 0; jb < NB; ++jb) add[jb] *= mul;
 }
+// s - m of scores that have been rounded like m, their largest: exact next to it.  Opaque, so that no product that a score may be
+// is made anew inside an fma with the subtraction: the rounding of a score of 1e10 is hundreds.
+template <int NB>
+__device__ __forceinline__ void subtract_rounded(f32x4 (&s)[NB], float m) {
+#pragma unroll
+    for (int jb = 0; jb < NB; ++jb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float x = s[jb][r];
+            asm("" : "+v"(x));
+            s[jb][r] = x - m;
+        }
+}
 // AddendRegs: the term is already in registers (one f32x4 per key block), times log2e.
 template <int NB>
 struct AddendRegs {

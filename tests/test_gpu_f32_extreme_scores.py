@@ -52,3 +52,41 @@ def test_forward(L, form, split):
     for c in range(32 * heads):  # per channel: one is far larger than the others
         # the scores' own rounding (2^-24 of up to 100 in the exponent) and the sums
         assert (o[:, :, c] - want[:, :, c]).norm() <= 2 ** -18 * want[:, :, c].norm(), c
+
+
+# without an additive term the score is a bare product, whose rounding must not come back when the largest one is subtracted
+@pytest.mark.parametrize("L", [49, 64, 65, 81, 112, 144, 256])
+@pytest.mark.parametrize("size", [1e9, 1.3e15, 1e29, 1e36])
+def test_forward_without_a_term(L, size):
+    import paper_2501_06480_amd as fwa
+    g = torch.Generator().manual_seed(L)
+    q, k, v = (torch.randn((6, L, 64), generator=g) for _ in range(3))
+    k[1::2] *= size  # every score of the window, one row's, one column's
+    q[0, 5] *= size
+    k[2, 7] *= size
+    o = fwa.fwa_forward(q.cuda(), k.cuda(), v.cuda(), 2, 32 ** -0.5).cpu().double()
+    # the two largest scores of a row lie far apart for some rows only: ties within fp32's rounding weigh what they like
+    Q, K, V = (t.double().view(6, L, 2, 32).transpose(1, 2) for t in (q, k, v))
+    S = 32 ** -0.5 * Q @ K.transpose(2, 3).contiguous()
+    top = S.topk(2, -1).values
+    sure = ((top[..., 0] - top[..., 1]) > 2 ** -20 * top.abs().amax(-1) + 30) | (S.abs().amax(-1) < 1e3)
+    want = (torch.softmax(S, -1) @ V).transpose(1, 2).reshape(6, L, 2, 32)
+    sure = sure.transpose(1, 2)
+    assert torch.isfinite(o).all() and sure.float().mean() > 0.9
+    assert (o.view(6, L, 2, 32) - want)[sure].norm() <= 2 ** -18 * want[sure].norm()
+
+
+@pytest.mark.parametrize("L,d", [(25, 32), (49, 32), (64, 64), (49, 256)])
+@pytest.mark.parametrize("size", [1e9, 1e12, 1e29])
+def test_backward_without_a_term(L, d, size):
+    import paper_2501_06480_amd as fwa
+    g = torch.Generator().manual_seed(L)
+    q, k, v, d_o = (torch.randn((4, L, 2 * d), generator=g) for _ in range(4))
+    q[1::2] *= size
+    got = [t.cpu().double() for t in fwa.fwa_backward(q.cuda(), k.cuda(), v.cuda(), d_o.cuda(), 2, d ** -0.5)[:3]]
+    assert all(torch.isfinite(t).all() for t in got)
+    # weights of 0 and 1: dV gathers rows of dO
+    Q, K, V, G = (t.double().view(4, L, 2, d).transpose(1, 2) for t in (q, k, v, d_o))
+    P = torch.softmax(d ** -0.5 * Q @ K.transpose(2, 3).contiguous(), -1)
+    want = (P.transpose(2, 3).contiguous() @ G).transpose(1, 2).reshape(4, L, 2 * d)
+    assert (got[2] - want).norm() <= 2 ** -18 * want.norm()
