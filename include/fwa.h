@@ -23,7 +23,10 @@
  *    1 <= L <= 64 (the feature-dimension loop of paper eq. 5-6; the shapes of
  *    its Section 3.1 benchmark), in fp32 and bf16 (half: the wider heads only,
  *    see dtype).  N >= 0 (N == 0 is a no-op).
- *  - dtype is FWA_F32 (fp32 data, fp32 arithmetic), FWA_BF16 (bf16 data,
+ *  - dtype is FWA_F32 (fp32 data, sums and softmax; products with 24
+ *    significant bits of every value, subnormal ones included, by the fp32
+ *    matrix instruction or by bf16 ones on exact three-part splits; infinities,
+ *    NaN and overflow as in fp32 arithmetic), FWA_BF16 (bf16 data,
  *    bf16 matrix-core products with fp32 accumulation, fp32 softmax, one final
  *    round-to-nearest-even to bf16) or FWA_F16 (IEEE half data, handled like
  *    bf16 with half products; head widths 64, 128 and 256 only, i.e. the

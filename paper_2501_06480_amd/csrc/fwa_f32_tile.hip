@@ -1,7 +1,7 @@
 // fp32 kernels: windows of up to 64 tokens and head widths 32, 64, 128, 256, forward and
 // backward.  (The forward for longer windows is in fwa_f32_rows.hip.)
 // fp32 arithmetic throughout: v_mfma_f32_16x16x4_f32 products (from 33 tokens on the backward takes the same 24 bits in three
-// bf16 parts, below), v_exp_f32, IEEE division.
+// bf16 parts, below), v_exp_f32, division by the row sum (the backward from 33 tokens on multiplies by its reciprocal).
 // These are the shapes and the precision of the paper's kernel benchmark (section 3.1).
 //
 // One workgroup per (window, head), one wave per block of 16 rows.  The fp32 matrix instruction
@@ -339,9 +339,10 @@ __global__ void __launch_bounds__(256) bwd_f32_plain_kernel(BwdArgs p) {
 // (kLift) in front of the split: dS in particular is the product of three factors of any size.  Tiles with values
 // that do not fit (from 2^43 on, infinities, NaN) are done over by bwd_f32_products, at the price of both: 1.5 to 1.8 times the
 // fp32 instruction's time where all tiles are (leaving as early as V, dO, Q or K show it cost the others 4 % in spilled registers).
-// Measured against it, us: 2048 windows of 64 tokens, 4 heads of width 64 228 -> 195 (HBM alone 173), 488 windows, width 128
-// 142 -> 109, 244 of width 256 170 -> 144, 1700 of 49 tokens, 6 heads of width 32 144 -> 130; the error against 64 bits halves
-// (3.0e-7 -> 1.4e-7).  The spills of a few registers at NB = 4 buy the third (width 64) workgroup per CU.
+// Measured against it, us: 2048 windows of 64 tokens, 4 heads of width 64 232 -> 202 (HBM alone 173), 488 windows, width 128
+// 135 -> 105, 244 of width 256 170 -> 147, 1700 of 49 tokens, 6 heads of width 32 138 -> 125; the error against 64 bits halves
+// (3.0e-7 -> 1.4e-7).  1 % of that is the lift.  Up to 256 tiles of 33 to 48 tokens and width 32 are 0.1 to 0.2 us (2 to 4 %)
+// slower than by the fp32 instruction.  The spills of a few registers at NB = 4 buy the third (width 64) workgroup per CU.
 template <int NB, int D>
 struct Split {
     static constexpr int ROWS = 16 * NB, CH = D / 32, ROW = 2 * D;  // rows, 32-channel chunks, bytes of a plane's row

@@ -234,8 +234,8 @@ __device__ __forceinline__ void fill_rows_staged(f32x4 (&add)[NQ][NB], const Bia
     }
 }
 
-// fill_rows for one block of 16 rows of a longer window (64 < L <= 256) by a wave that keeps it for life, with an fp32
-// bias: 32 columns of the 16 rows at a time go through 2 KB of LDS of the wave's own (`patch`).  They are fetched 128
+// fill_rows for one block of 16 rows of a longer window by a wave that keeps it for life (the backward's rows kernel, 64 < L <= 256,
+// and the forward above 224 tokens), with an fp32 bias: 32 columns of the 16 rows at a time go through 2 KB of LDS of the wave's own (`patch`).  They are fetched 128
 // bytes of a row per 8 lanes and written with unit u (16 bytes) of row r at u ^ (r & 7), so that neither the writes nor the
 // reads (a unit of 8 rows) meet on a bank.  (fill_rows took 8 us of the rows kernel's 150 at L = 256, whose rows of 1 KB fall on
 // the same channels; the call 312 -> 309 us, 100 windows with 6 heads 53.7 -> 51.7; other lengths 0 .. 1 %.)
