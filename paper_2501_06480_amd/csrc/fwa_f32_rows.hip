@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
                 mb = 0.f;
             }
             float sum = 0.f;
-            // Split, the weights are lifted like V (2.5 % of the time; as a multiplication it took registers that spilled)
+            // Split, the weights are lifted like V (1.4 % of the time; as a multiplication it took registers that spilled)
             auto exponentials = [&](int jb, int lift) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
