@@ -22,17 +22,20 @@
 // kernels for small windows.
 //
 // Both kernels are persistent: a wave keeps its block for life and its workgroup walks the windows bw, bw + G, ...
-// Most of their work is vector instructions (7 to 8 per score besides the exponential, four of them in the keys kernel
-// for the two hi/lo splits), so everything that does not change from window to window stays out of the loop:
+// Most of their work is vector instructions (5 to 6 per score besides the exponential), so everything that does not change from window to window stays out of the loop:
 // (bias + mask[w mod nW]) * log2e of the block's 16 x L scores sits in registers (G is a multiple of the mask
-// period), -delta_i enters as the accumulator the product dO V^T starts from.  Reading the additive term per window
+// period), -M_i / scale and -delta_i enter as the
+// accumulators that the products Q K^T and dO V^T start from.  Reading the additive term per window
 // instead (the form for dense masks whose period no G is a multiple of) costs its loads, the LDS patch that turns
 // rows into lanes, and three to four more instructions per score.  Measured, N = 1024 windows of 16 x 16 tokens,
 // 4 heads, bias + labels + dBias: rows 210 -> 148 us, keys 283 -> 167 us (kernels of their own that read the term per
 // window and parked the slabs out of registers between two barriers), the whole call 465 -> 325 us; N = 315 windows
-// of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 55 us.  Vector instructions issue in
-// 57-61 % of the cycles, the matrix cores are busy for 26-28 %, the LDS for 29-42 %: no unit is full, two waves per SIMD
-// overlap them only in part, and the card runs at 1.9 to 2.0 GHz of 2.4 meanwhile.
+// of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 55 us.  What bounds them is the instruction
+// stream of a SIMD: a matrix instruction takes 8 to 11 cycles from the vector instructions beside it, and some vector instructions
+// (the two-term dot product, which made the remainder of the hi/lo split before) wait for the matrix core to be idle.  Cycles of a
+// wave per block of 16 x 16 scores, two waves per SIMD, 16 x 16 windows: keys 515 -> 466 with the remainder from the matrix core
+// and M in the products, rows 427 -> 386 with that and without a row maximum; the clock falls from 1.9 to 1.83 GHz of 2.4
+// meanwhile (power).  The call 320 -> 302 us, 14 x 14 windows without dBias 95 -> 90.
 //
 // The statistics M_i, -delta_i (8 bytes per query) travel from one kernel to the other inside the outputs that the
 // second one overwrites: the 16 floats of a query block are as long as the 64-byte slice of the head in one token
@@ -42,6 +45,8 @@
 #include "fwa_device.h"
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
+
+#include <cfloat>
 
 namespace fwa {
 namespace {
@@ -55,11 +60,6 @@ struct LargeGeom {
 // reads run at the same rate as with 16 bytes of padding (measured).
 constexpr uint32_t kLargeStride = 4;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
-    const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
-    return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
-}
 
 // The key blocks of a head are spread over the workgroups ("parts") of the keys kernel in turns: wave v of part
 // `part` owns key block part + parts * v.  The first block of a part is then always one of the first four, i.e. a
@@ -97,14 +97,106 @@ __device__ __forceinline__ void store_rows(char* cell, const u32x2 lo, const u32
     __builtin_amdgcn_raw_buffer_store_b128(rows, dst, (uint32_t)(16 * blk + r) * row_d + 16u * c, 0, 0);
 }
 
-// What follows the scores in the query orientation, shared by the two rows kernels: s holds the scaled scores (with
-// the additive term, -inf beyond L), m their maximum over the lane's keys; on return the block's dQ rows are packed in
-// lo2, hi2, and M, neg_delta are its statistics.  lk, lv: the K and V slabs; opd / trs: the lane's offsets for row
-// operands / transposing reads.  Matrix products are issued one step ahead of the vector work that needs them, and
-// the scheduling barriers keep the compiler from collecting them at one end of a loop (2-3 % at L = 196).
+// The second half of a query block's work, from the exponentials in s (not normalised: P = s / sum) and their reduced sums over
+// the row, sum and delta: dQ^T = K^T dS^T over pairs of key blocks, packed into lo2, hi2, and the statistics M (m = the largest
+// score, 0 where it was not subtracted) and neg_delta.  lk, lv: the K and V slabs; opd / trs: the lane's offsets for row
+// operands / transposing reads.  dP is made anew, from -delta; products are issued one step ahead of the vector work that
+// needs them, what remains of dS after its upper parts comes from the matrix core and is packed a step later, and the scheduling
+// barriers keep the compiler from collecting them at one end of the loop (2-3 % at L = 196).
+template <int NB>
+__device__ __forceinline__ void rows_gradient(const f32x4 (&s)[NB], float m, float sum, float delta, const bf16x8 gop, const uint4* lk,
+                                              const uint4* lv, uint32_t opd, uint32_t trs, const bf16x4 minus_one, float scale,
+                                              float& M, float& neg_delta, f32x4& q0, f32x4& q1) {
+    constexpr int NB2 = (NB + 1) / 2;
+    constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    auto v_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]); };
+    bf16x8 o0 = v_rows(0), o1 = v_rows(1);
+    sum = sum_over_g(sum);
+    const float inv = __builtin_amdgcn_rcpf(sum);
+    delta = sum_over_g(delta) * inv;
+    M = m + __builtin_amdgcn_logf(sum);  // p_ij = exp2(score_ij - M_i)
+    neg_delta = -delta;
+    const f32x4 nd = {neg_delta, neg_delta, neg_delta, neg_delta};
+    q0 = zero, q1 = zero;  // dQ[16 qb + n][4g + r], dQ[16 qb + n][16 + 4g + r]
+    const uint16_t* lk16 = reinterpret_cast<const uint16_t*>(lk) + trs;
+    f32x4 da, db;  // dP - delta of the two blocks of a pair
+    da = mfma_bf16(o0, gop, nd);
+    db = mfma_bf16(o1, gop, nd);
+    if (NB > 2) o0 = v_rows(2);
+    if (NB > 3) o1 = v_rows(3);
+    bf16x8 tk0, tk1;
+    u32x4 dh = {0u, 0u, 0u, 0u};
+    f32x4 ra = zero, rb = zero;  // what remains of dS of the last pair
+    auto accumulate = [&]() {
+        q0 = mfma_bf16(tk0, as_bf16x8(dh), q0);
+        q1 = mfma_bf16(tk1, as_bf16x8(dh), q1);
+        const bf16x8 dl = as_bf16x8(u32x4{pack_bf16(ra[0], ra[1]), pack_bf16(ra[2], ra[3]), pack_bf16(rb[0], rb[1]), pack_bf16(rb[2], rb[3])});
+        q0 = mfma_bf16(tk0, dl, q0);
+        q1 = mfma_bf16(tk1, dl, q1);
+    };
+#pragma unroll
+    for (int kp = 0; kp < NB2; ++kp) {
+        const bool two = 2 * kp + 1 < NB;
+        __builtin_amdgcn_sched_barrier(0);
+        if (kp > 0) accumulate();
+        tk0 = operand_tr(lk16 + (32 * kp) * SROW, 16 * SROW, two);
+        tk1 = operand_tr(lk16 + (32 * kp) * SROW + 16, 16 * SROW, two);
+        const f32x4 a = s[2 * kp] * da, b = two ? s[two ? 2 * kp + 1 : 0] * db : zero;  // dS, times the row sum
+        if (2 * kp + 2 < NB) da = mfma_bf16(o0, gop, nd);
+        if (2 * kp + 3 < NB) db = mfma_bf16(o1, gop, nd);
+        if (2 * kp + 4 < NB) o0 = v_rows(2 * kp + 4);
+        if (2 * kp + 5 < NB) o1 = v_rows(2 * kp + 5);
+        dh = u32x4{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), two ? pack_bf16(b[0], b[1]) : 0u, two ? pack_bf16(b[2], b[3]) : 0u};
+        ra = remainder(minus_one, uint2{dh.x, dh.y}, a);
+        rb = two ? remainder(minus_one, uint2{dh.z, dh.w}, b) : zero;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    accumulate();
+    const float qs = scale * inv;  // the lane's query row: dQ_i = scale / sum_i * (the products above)
+    q0 *= qs;
+    q1 *= qs;
+}
+// The same from the scores: s holds them (scaled, with the additive term, -inf beyond L) and m their maximum over the lane's keys.
 // `between(i)` is called in between, i = 0, 1, ..., NB - 1 (a place for the next window's loads).
 template <int NB, class Between>
 __device__ __forceinline__ void rows_block(f32x4 (&s)[NB], float m, const bf16x8 gop, const uint4* lk, const uint4* lv,
+                                           uint32_t opd, uint32_t trs, const bf16x4 minus_one, float scale, float& M, float& neg_delta,
+                                           f32x4& q0, f32x4& q1, Between between) {
+    constexpr uint32_t STRIDE = kLargeStride;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    auto v_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]); };
+    m = max_over_g(m);
+    float sum = 0.f, delta = 0.f;
+    f32x4 dp[2];
+    dp[0] = mfma_bf16(v_rows(0), gop, zero);
+    bf16x8 ov = v_rows(1);
+#pragma unroll
+    for (int jb = 0; jb < NB; ++jb) {
+        __builtin_amdgcn_sched_barrier(0);
+        between(jb);
+        if (jb + 1 < NB) dp[(jb + 1) & 1] = mfma_bf16(ov, gop, zero);
+        if (jb + 2 < NB) ov = v_rows(jb + 2);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float e = __builtin_amdgcn_exp2f(s[jb][r] - m);
+            s[jb][r] = e;
+            sum += e;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) delta = fmaf(s[jb][r], dp[jb & 1][r], delta);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    rows_gradient<NB>(s, m, sum, delta, gop, lk, lv, opd, trs, minus_one, scale, M, neg_delta, q0, q1);
+}
+__device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
+    const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
+    return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
+}
+// The same in fewer registers, for the kernels whose waves per SIMD leave no room for the pipeline above: both parts of dS in one step,
+// the remainder by the dot product.
+template <int NB, class Between>
+__device__ __forceinline__ void rows_block_tight(f32x4 (&s)[NB], float m, const bf16x8 gop, const uint4* lk, const uint4* lv,
                                            uint32_t opd, uint32_t trs, float scale, float& M, float& neg_delta,
                                            u32x2& lo2, u32x2& hi2, Between between) {
     constexpr int NB2 = (NB + 1) / 2;
@@ -182,6 +274,7 @@ __device__ __forceinline__ void rows_block(f32x4 (&s)[NB], float m, const bf16x8
     lo2 = u32x2{pack_bf16(q0[0] * qs, q0[1] * qs), pack_bf16(q0[2] * qs, q0[3] * qs)};
     hi2 = u32x2{pack_bf16(q1[0] * qs, q1[1] * qs), pack_bf16(q1[2] * qs, q1[3] * qs)};
 }
+__device__ __forceinline__ u32x2 packed_row(const f32x4& q) { return u32x2{pack_bf16(q[0], q[1]), pack_bf16(q[2], q[3])}; }
 // -inf for the keys of the last block beyond L; the running maximum m takes a block's scores in
 template <int NB>
 __device__ __forceinline__ void pad_and_max(f32x4& x, int jb, int L, int g, float& m) {
@@ -208,10 +301,19 @@ constexpr size_t rows_lds() {
     return (size_t)2 * 2 * 16 * NB * kLargeStride * 16 + (size_t)2 * 16 * NB * 4 + (size_t)rows_waves(NB) * 16 * 80;
 }
 
+// Waves per SIMD that the registers leave room for: said where the compiler would take a few more and lose one (81 tokens, labels
+// per window, 1656 windows, 3 heads: 46 us with four, 52 with three).
+constexpr int rows_per_simd(int nb, bool bm, bool pw) { return nb <= 6 ? (bm ? 4 : 5) : nb == 7 ? (pw ? 3 : 4) : nb <= 12 ? (bm || nb == 12 ? 3 : 4) : (bm ? 2 : 3); }
+
+// Kernels whose waves per SIMD leave no registers for the longer pipeline (11 to 40 of them spilled): they take every row around its
+// maximum and split dS where it is made.
+constexpr bool rows_tight(int nb, bool bm, bool pw) { return pw ? nb <= 6 || nb == 11 || nb == 12 : bm && nb == 12; }
+
 template <int NB, bool BM, bool PW>
-__global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdArgs p, LargeGeom gm) {
+__global__ void __launch_bounds__(64 * rows_waves(NB), rows_per_simd(NB, BM, PW)) bwd_bf16_rows_kernel(BwdArgs p, LargeGeom gm) {
     constexpr int W = rows_waves(NB);
     constexpr int ROWS = 16 * NB;
+    constexpr bool TIGHT = rows_tight(NB, BM, PW);
     constexpr int PASSES = (ROWS + 16 * W - 1) / (16 * W);  // the workgroup moves 16 W slab rows per pass
     constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
     constexpr uint32_t SLAB = ROWS * STRIDE;                // in uint4
@@ -230,6 +332,7 @@ __global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdA
     const int L = p.L;
     const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
     const float sl2 = p.scale * kLog2e;
+    const bf16x4 minus_one = minus_identity(g, n);
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 
     const uint32_t tile_bytes = (uint32_t)(L - 1) * row_bytes + 2u * kHeadDim;
@@ -312,34 +415,100 @@ __global__ void __launch_bounds__(64 * rows_waves(NB)) bwd_bf16_rows_kernel(BwdA
         u32x2 lo, hi;
         if (active) {
             f32x4 s[NB];
-            float m = -INFINITY;
             const int* const lab = llab + buf * ROWS;
             const AddendRegsLabels<NB> with_labels = {add, lab, PW ? lab[16 * qb + n] : 0, mv, g};
-            // all K operands are asked for at once (they are as large as the scores that replace them), and the
-            // products run two blocks ahead of the vector work on them
-            bf16x8 ok[NB];
+            auto k_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lk[opd + 16 * jb * STRIDE]); };
+            auto v_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]); };
+            auto scaled = [&](int jb) {
+                const f32x4 t = PW ? with_labels.block(jb) : (BM ? add[jb] : zero);
+                f32x4 x;
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) ok[jb] = __builtin_bit_cast(bf16x8, lk[opd + 16 * jb * STRIDE]);
-#pragma unroll
-            for (int jb = 0; jb < NB + 2; ++jb) {
-                if (jb < NB) s[jb] = mfma_bf16(ok[jb], qop, zero);
-                if (jb >= 2) {
-                    const int c = jb - 2;
-                    const f32x4 t = PW ? with_labels.block(c) : (BM ? add[c] : zero);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) s[c][r] = BM ? fmaf(s[c][r], sl2, t[r]) : s[c][r] * sl2;
-                    pad_and_max<NB>(s[c], c, L, g, m);
+                for (int r = 0; r < 4; ++r) {
+                    x[r] = BM ? fmaf(s[jb][r], sl2, t[r]) : s[jb][r] * sl2;
+                    if (jb == NB - 1 && 16 * jb + 4 * g + r >= L) x[r] = -INFINITY;
                 }
-                if (jb & 1) __builtin_amdgcn_sched_barrier(0);
-            }
-            rows_block<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, [&](int i) {
+                return x;
+            };
+            auto next_loads = [&](int i) {
                 // the next window's loads one pair at a time: issued in one go they queue at the CU's address unit
                 // and hold the wave up
 #pragma unroll
                 for (int t = 0; t < PASSES; ++t)
                     if (i == 2 * t) request_slab(buf ^ 1u, t);
                 if (i == 3) request_rest(w + step, has_next);
-            });
+            };
+            if constexpr (!TIGHT) {
+                f32x4 q0, q1;
+                // The exponentials are taken of the scores as they are: what the row maximum would keep in range is in range for any
+                // scores but the largest, and a maximum has to wait for the last product of the row.  The row is
+                // made again around its maximum where that does not hold (see below).
+                float sum = 0.f, delta = 0.f;
+                f32x4 dp[2];
+                bf16x8 ok = k_rows(2), ov = v_rows(1);
+                s[0] = mfma_bf16(k_rows(0), qop, zero);
+                dp[0] = mfma_bf16(v_rows(0), gop, zero);
+                s[1] = mfma_bf16(k_rows(1), qop, zero);
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    next_loads(jb);
+                    if (jb + 2 < NB) s[jb + 2] = mfma_bf16(ok, qop, zero);
+                    if (jb + 1 < NB) dp[(jb + 1) & 1] = mfma_bf16(ov, gop, zero);
+                    if (jb + 3 < NB) ok = k_rows(jb + 3);
+                    if (jb + 2 < NB) ov = v_rows(jb + 2);
+                    const f32x4 x = scaled(jb);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float e = __builtin_amdgcn_exp2f(x[r]);
+                        s[jb][r] = e;
+                        sum += e;
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) delta = fmaf(s[jb][r], dp[jb & 1][r], delta);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                rows_gradient<NB>(s, 0.f, sum, delta, gop, lk, lv, opd, trs, minus_one, p.scale, M, nd, q0, q1);
+                // In range: a sum of at least 2^-10 (so that no probability that counts was lost below 2^-126) and at most 2^40, and
+                // nothing in dQ that is not finite (a product with an exponential of up to 2^40 may overflow where one with a
+                // probability does not).
+                float rest = 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) rest = fmaf(q0[r], 0.f, rest), rest = fmaf(q1[r], 0.f, rest);
+                const bool good = fabsf(M + rest - 15.f) <= 25.f;
+                if (__builtin_expect(__any(!good && 16 * qb + n < L), 0)) {
+                    float m = -INFINITY;
+#pragma unroll
+                    for (int jb = 0; jb < NB; ++jb) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        s[jb] = mfma_bf16(k_rows(jb), qop, zero);
+                        s[jb] = scaled(jb);
+                        m = fmaxf(fmaxf(m, s[jb][0]), s[jb][1]);
+                        m = fmaxf(fmaxf(m, s[jb][2]), s[jb][3]);
+                    }
+                    rows_block<NB>(s, m, gop, lk, lv, opd, trs, minus_one, p.scale, M, nd, q0, q1, [](int) {});
+                }
+                lo = packed_row(q0), hi = packed_row(q1);
+            } else {
+                float m = -INFINITY;
+                // all K operands are asked for at once (they are as large as the scores that replace them), and the
+                // products run two blocks ahead of the vector work on them
+                bf16x8 ok[NB];
+#pragma unroll
+                for (int jb = 0; jb < NB; ++jb) ok[jb] = k_rows(jb);
+#pragma unroll
+                for (int jb = 0; jb < NB + 2; ++jb) {
+                    if (jb < NB) s[jb] = mfma_bf16(ok[jb], qop, zero);
+                    if (jb >= 2) {
+                        const int c = jb - 2;
+                        const f32x4 t = PW ? with_labels.block(c) : (BM ? add[c] : zero);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) s[c][r] = BM ? fmaf(s[c][r], sl2, t[r]) : s[c][r] * sl2;
+                        pad_and_max<NB>(s[c], c, L, g, m);
+                    }
+                    if (jb & 1) __builtin_amdgcn_sched_barrier(0);
+                }
+                rows_block_tight<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, next_loads);
+            }
         } else {  // an idle wave moves its share all the same
 #pragma unroll
             for (int t = 0; t < PASSES; ++t) request_slab(buf ^ 1u, t);
@@ -498,11 +667,11 @@ __global__ void __launch_bounds__(64 * stream_waves(NB)) bwd_bf16_rows_stream_ke
                 __builtin_amdgcn_sched_barrier(0);
             }
             float M, nd;
-            u32x2 lo, hi;
             float m = -INFINITY;
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb) pad_and_max<NB>(s[jb], jb, L, g, m);
-            rows_block<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, [](int) {});
+            u32x2 lo, hi;
+            rows_block_tight<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, [](int) {});
             if (has_next && qb + W >= NB) request(w + gm.G);  // the wave's last block of this window
             store_stats<NB>(p, tile_d, row_d, qb, n, g, M, nd);
             store_rows(reinterpret_cast<char*>(patch), lo, hi, make_rsrc((char*)p.dq + tile_d, tile_bytes_d), qb, row_d, lane);
@@ -524,18 +693,38 @@ enum { kTermNone = 0,    // no additive term
        kTermStream = 3,  // a dense mask read for every window, and the bias too where the registers are needed for dBias
        kTermStreamMask = 4 };  // a dense mask alone, read for every window
 
+// What the score products of a row start from, -M / sl2, so that exp2(sl2 * score + term) is the probability: one fma per
+// score instead of an fma and a subtraction.  The roundings of M, the quotient and the sums are 2^-21 of M at most.  Where that is
+// more than a probability can bear (M beyond 2^20, rows that lost every key to a large finite mask) M is raised by as much, or it
+// would be a power of two of any size; and a negative M makes no infinity.  M = +infinity (rows beyond L) makes all of them zero.
+__device__ __forceinline__ float start_of_scores(float m, float sl2) {
+    const float a = fabsf(m);
+    const float c = (a > 0x1p20f && a < INFINITY ? fmaf(a, 0x1p-21f, m) : m) / -sl2;
+    return m < 0.f ? fminf(fmaxf(c, -FLT_MAX), FLT_MAX) : c;
+}
+
 template <int NB>
 constexpr size_t keys_lds() {  // two buffers of: Q, dO slabs; then two of: M, -delta, labels; the waves' output cells
     return (size_t)2 * 2 * 16 * NB * kLargeStride * 16 + (size_t)2 * 3 * 16 * NB * 4 + (size_t)keys_waves(NB) * 16 * 80;
 }
 
+// Waves per SIMD: two at least, more where the registers and the LDS have room for them.
+constexpr int keys_per_simd(int nb, int term, bool db) {
+    return (nb == 9 && term == kTermLabels && !db) || (nb == 7 && term == kTermStreamMask) ? 3 : 2;
+}
+
 template <int NB, int TERM, bool DB>
-__global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(BwdArgs p, LargeGeom gm) {
+__global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, DB)) bwd_bf16_keys_kernel(BwdArgs p, LargeGeom gm) {
     constexpr bool KEEP = TERM == kTermKept || TERM == kTermLabels;
     constexpr bool STREAM = TERM == kTermStream || TERM == kTermStreamMask;
     constexpr bool PW = TERM == kTermLabels;
     constexpr bool KEEPB = TERM == kTermStream && NB <= 12;  // the bias in registers all the same
     constexpr bool HB = TERM == kTermStream && !KEEPB;
+    // the block during which the next window's rows and statistics are requested: late, while they wait they take registers,
+    // but ahead of the loads of a term that is read for every window
+    constexpr int REST_AT = STREAM ? NB / 2 : NB == 5 || (NB >= 15 && PW) ? NB - 1 : NB - 3;
+    // the products of the lower parts with those of the upper ones, not a block later: fewer registers
+    constexpr bool EARLY = NB == 5 || STREAM;
     constexpr uint32_t PARTS = (uint32_t)keys_parts(NB);
     constexpr int W = keys_waves(NB);
     constexpr int ROWS = 16 * NB;
@@ -552,8 +741,12 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
     const bool active = jb < NB;                // wave-uniform
     const int L = p.L;
     const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
-    const float sl2 = p.scale * kLog2e;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    // The score products start from -M_i / sl2, so that one fma makes the exponent.  Without a scale to divide by the scores
+    // are zeros: the K operand is, and the divisor is one.
+    const bool flat = fabsf(p.scale) < 0x1p-100f;
+    const float sl2 = flat ? 1.0f : p.scale * kLog2e;
+    const bf16x4 minus_one = minus_identity(g, n);
 
     // two buffers: window w is computed out of one while the slabs of w + G are on their way into the other
     constexpr uint32_t SLAB = ROWS * STRIDE;                              // in uint4
@@ -584,10 +777,13 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
     u32x4 pst = {0u, 0u, 0u, 0u}, pk = pst, pv = pst;
     // No branches in here (they would cut the block loop into pieces): without a next window `on` is false, the
     // descriptors are empty and nothing is fetched.
-    const uint32_t off_st = wave < 2 ? (16u * part + ((uint32_t)lane >> 2)) * row_d + 16u * ((uint32_t)lane & 3u) : 16u * (uint32_t)lane;
     // One descriptor per tensor and window (`ask`); the 16 rows of a pass are an offset on top of the lane's own.
-    size_t next_q = ((size_t)bw * L * p.ldq + (size_t)h * kHeadDim) * 2u, next_g = ((size_t)bw * L * p.ldg + (size_t)h * kHeadDim) * 2u;
-    size_t next_d = ((size_t)bw * L * p.ldd + (size_t)h * kHeadDim) * 2u;
+    // The windows are walked from the last to the first: what the rows kernel has touched last is in the 256 MB cache (16 x 16
+    // windows 321.2 -> 317.4 us, 14 x 14 93.5 -> 92.5).
+    uint32_t left = bw < (uint32_t)p.N ? ((uint32_t)p.N - bw + gm.G - 1u) / gm.G : 0u;
+    uint32_t w = bw + (left - 1u) * gm.G;
+    size_t next_q = ((size_t)w * L * p.ldq + (size_t)h * kHeadDim) * 2u, next_g = ((size_t)w * L * p.ldg + (size_t)h * kHeadDim) * 2u;
+    size_t next_d = ((size_t)w * L * p.ldd + (size_t)h * kHeadDim) * 2u;
     const size_t step_q = (size_t)gm.G * L * p.ldq * 2u, step_g = (size_t)gm.G * L * p.ldg * 2u, step_d = (size_t)gm.G * L * p.ldd * 2u;
     u32x4 from_q, from_g;
     auto ask = [&](bool on) {
@@ -611,23 +807,35 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
             src = wave == 2 ? lab : src;
             bytes = wave == 2 ? (uint32_t)L * 4u : bytes;
         }
+        const uint32_t l = (uint32_t)lane;
+        const uint32_t off_st = wave < 2 ? (16u * part + (l >> 2)) * row_d + 16u * (l & 3u) : 16u * l;
         pst = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(src, on ? bytes : 0u), off_st, 0, 0);
         // the wave's own K and V rows as operands: row 16 jb + n, channels 8g .. 8g + 7
-        const uint32_t off = (uint32_t)(16 * jb + n) * row_bytes + 16u * g, own = on ? tile_bytes : 0u;
-        pk = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.k + next_q, own), off, 0, 0);
+        const uint32_t off = (16u * jb + (l & 15u)) * row_bytes + 16u * (l >> 4), own = on ? tile_bytes : 0u;
+        pk = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.k + next_q, flat ? 0u : own), off, 0, 0);
         pv = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.v + next_q, own), off, 0, 0);
     };
     auto park = [&](uint32_t buf) {
         // M, -delta and labels lie one behind the other: ROWS / 4 = 4 NB <= 64 units of 16 bytes each
-        if (wave < (PW ? 3u : 2u) && lane < ROWS / 4) reinterpret_cast<u32x4*>(stats + buf * ST + wave * ROWS)[lane] = pst;
+        u32x4 st = pst;
+        if (wave == 0) {  // what the products start from instead of M
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t b = pst[c];
+                const float m = __builtin_bit_cast(float, b);
+                const float x = start_of_scores(m, sl2);
+                st[c] = __builtin_bit_cast(uint32_t, x);
+            }
+        }
+        if (wave < (PW ? 3u : 2u) && lane < ROWS / 4) reinterpret_cast<u32x4*>(stats + buf * ST + wave * ROWS)[lane] = st;
     };
-    if (bw < (uint32_t)p.N) {  // in flight while the additive term is fetched
+    if (left > 0) {  // in flight while the additive term is fetched
         ask(true);
 #pragma unroll
         for (int t = 0; t < PASSES; ++t) request_slab(0u, t);
-        request_rest(bw, true);
+        request_rest(w, true);
     }
-    next_q += step_q, next_g += step_g, next_d += step_d;
+    next_q -= step_q, next_g -= step_g, next_d -= step_d;
     f32x4 add[NB];  // (bias + mask) * log2e, resp. bias * log2e, in the layout of dbacc
     if (KEEP || KEEPB) {
         const MaskSrc msk = PW || KEEPB ? MaskSrc{make_rsrc(nullptr, 0), 0.f, false} : mask_of_window(p, bw);
@@ -651,13 +859,12 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
 #pragma unroll
     for (int r = 0; r < 4; ++r) aoff[r] = ((uint32_t)(4 * g + r) * L + 16u * jb + n) * 4u;
     const float mv = p.mask_value * kLog2e;
-    if (bw < (uint32_t)p.N) park(0u);
+    if (left > 0) park(0u);
     lds_loads_done();
     __syncthreads();
 
     uint32_t buf = 0u;
-    uint32_t left = ((uint32_t)p.N - bw + gm.G - 1u) / gm.G;
-    for (uint32_t w = bw; w < (uint32_t)p.N; w += gm.G, buf ^= 1u, --left) {
+    for (; left > 0; w -= gm.G, buf ^= 1u, --left) {
         take_turns(left);
         const uint4* const lq = lds + buf * (2 * SLAB);
         const uint4* const lg = lq + SLAB;
@@ -666,9 +873,9 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
         const int* const llab = reinterpret_cast<const int*>(stD + ROWS);
         const uint16_t* const lg16 = reinterpret_cast<const uint16_t*>(lg) + trs;
         const uint16_t* const lq16 = reinterpret_cast<const uint16_t*>(lq) + trs;
-        const size_t tile_d = next_d - step_d;
+        const size_t tile_d = next_d + step_d;
         const bf16x8 kop = as_bf16x8(pk), vop = as_bf16x8(pv);
-        const bool has_next = w + gm.G < (uint32_t)p.N;
+        const bool has_next = left > 1;
         ask(has_next);
         u32x2 va = {0u, 0u}, vb = {0u, 0u}, ka = {0u, 0u}, kb = {0u, 0u};  // the wave's 16 rows of dV and dK, packed
 
@@ -676,18 +883,20 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
             const int lkey = PW ? llab[16 * jb + n] : 0;
             f32x4 v0 = zero, v1 = zero, k0 = zero, k1 = zero;  // dV, dK [16 jb + n][4g + r] and [..][16 + 4g + r]
             // The products S, dP of a query block are issued one block ahead of the block's vector work, from operands
-            // fetched two blocks ahead, and the dV, dK products of a pair of blocks during the next block's: so every
+            // fetched two blocks ahead; what remains of P and dS after their upper parts is made by the matrix core and packed during
+            // the next block, and the dV, dK products of a pair of blocks follow in the next two: so every
             // stretch of vector instructions has matrix instructions beside it that do not depend on it.
-            bf16x8 oq, og, tg0, tg1, tx0, tx1, PH, PL, SH, SL;
-            f32x4 oM[2], oD, sc[2], dp[2], ab[2], am[2];
+            bf16x8 oq, og, tg0, tg1, tx0, tx1;
+            u32x4 PH = {0u, 0u, 0u, 0u}, SH = PH, PL = PH, SL = PH;  // operands of a pair: upper and lower parts of P and dS
+            f32x4 oM, oD, sc, dp, rp = zero, rs = zero, ab[2], am[2];
             i32x4 al[2];
             auto fetch_q = [&](int qb) {
                 oq = __builtin_bit_cast(bf16x8, lq[opd + 16 * qb * STRIDE]);
                 og = __builtin_bit_cast(bf16x8, lg[opd + 16 * qb * STRIDE]);
+                oM = *reinterpret_cast<const f32x4*>(stM + 16 * qb + 4 * g);
                 oD = *reinterpret_cast<const f32x4*>(stD + 16 * qb + 4 * g);
             };
-            auto fetch_m = [&](int qb) {
-                oM[qb & 1] = *reinterpret_cast<const f32x4*>(stM + 16 * qb + 4 * g);
+            auto fetch_l = [&](int qb) {
                 if (PW) al[qb & 1] = *reinterpret_cast<const i32x4*>(llab + 16 * qb + 4 * g);
             };
             auto fetch_term = [&](int qb) {
@@ -704,9 +913,9 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
                     am[qb & 1][r] = load_f32(rmq, aoff[r]);
                 }
             };
-            auto products = [&](int qb) {
-                sc[qb & 1] = mfma_bf16(oq, kop, zero);  // <q_i, k_j>, i = 16 qb + 4g + r, j = 16 jb + n
-                dp[qb & 1] = mfma_bf16(og, vop, oD);    // dP - delta
+            auto products = [&]() {
+                sc = mfma_bf16(oq, kop, oM);  // <q_i, k_j> - M_i / sl2, i = 16 qb + 4g + r, j = 16 jb + n
+                dp = mfma_bf16(og, vop, oD);  // dP - delta
             };
             auto fetch_t = [&](int qp) {  // dO^T and Q^T of the 32 queries (channel on the lane)
                 const bool two = 2 * qp + 1 < NB;
@@ -715,23 +924,22 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
                 tx0 = operand_tr(lq16 + (32 * qp) * SROW, 16 * SROW, two);
                 tx1 = operand_tr(lq16 + (32 * qp) * SROW + 16, 16 * SROW, two);
             };
-            auto accumulate = [&]() {
-                v0 = mfma_bf16(tg0, PH, v0);
-                v1 = mfma_bf16(tg1, PH, v1);
-                k0 = mfma_bf16(tx0, SH, k0);
-                k1 = mfma_bf16(tx1, SH, k1);
-                v0 = mfma_bf16(tg0, PL, v0);
-                v1 = mfma_bf16(tg1, PL, v1);
-                k0 = mfma_bf16(tx0, SL, k0);
-                k1 = mfma_bf16(tx1, SL, k1);
+            auto accumulate = [&](const u32x4& pp, const u32x4& ss) {
+                v0 = mfma_bf16(tg0, as_bf16x8(pp), v0);
+                v1 = mfma_bf16(tg1, as_bf16x8(pp), v1);
+                k0 = mfma_bf16(tx0, as_bf16x8(ss), k0);
+                k1 = mfma_bf16(tx1, as_bf16x8(ss), k1);
+            };
+            auto lower = [&](int u) {  // of block u of a pair
+                PL[2 * u] = pack_bf16(rp[0], rp[1]), PL[2 * u + 1] = pack_bf16(rp[2], rp[3]);
+                SL[2 * u] = pack_bf16(rs[0], rs[1]), SL[2 * u + 1] = pack_bf16(rs[2], rs[3]);
             };
             fetch_q(0);
-            fetch_m(0);
             if (STREAM) fetch_term(0);
-            products(0);
+            products();
             fetch_q(1);
+            fetch_l(0);
             if (STREAM) fetch_term(1);
-            bf16x4 ph[2], pl[2], sh[2], sl[2];
 #pragma unroll
             for (int qb = 0; qb < NB; ++qb) {
                 const int u = qb & 1;
@@ -741,39 +949,46 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
 #pragma unroll
                 for (int t = 0; t < PASSES; ++t)
                     if (qb == t * (NB / 2) / PASSES) request_slab(buf ^ 1u, t);
-                if (qb == NB / 2) request_rest(w + gm.G, has_next);
-                if (qb + 1 < NB) products(qb + 1);
-                if (u == 0 && qb > 0) accumulate();
-                if (u == 1 || qb == NB - 1) fetch_t(qb / 2);
-                if (qb + 1 < NB) fetch_m(qb + 1);
-                if (qb + 2 < NB) fetch_q(qb + 2);
+                if (qb == REST_AT) request_rest(w - gm.G, has_next);
+                if (EARLY && u == 0 && qb > 0) lower(1);
+                if (u == 0 && qb > 0) accumulate(PH, SH);
+                if (EARLY ? u == 0 && qb > 0 : u == 1 && qb > 1) accumulate(PL, SL);
+                if (u == 1) fetch_t(qb / 2);
+                if (qb + 1 < NB) fetch_l(qb + 1);
+                if (qb > 0 && !(EARLY && u == 0)) lower(u ^ 1);
                 f32x4 pr, ds;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     float x;
                     if (TERM == kTermNone) {
-                        x = fmaf(sc[u][r], sl2, -oM[u][r]);
+                        x = sc[r] * sl2;
                     } else {
                         float t;
                         if (STREAM) t = KEEPB ? fmaf(am[u][r], kLog2e, add[qb][r]) : (HB ? ab[u][r] + am[u][r] : am[u][r]) * kLog2e;
                         else t = PW ? add[qb][r] + (al[u][r] == lkey ? 0.f : mv) : add[qb][r];
-                        x = fmaf(sc[u][r], sl2, t) - oM[u][r];
+                        x = fmaf(sc[r], sl2, t);
                     }
                     pr[r] = __builtin_amdgcn_exp2f(x);
-                    ds[r] = pr[r] * dp[u][r];
+                    ds[r] = pr[r] * dp[r];
                 }
                 if (DB) dbacc[qb] += ds;
-                split_hi_lo_dot(pr, ph[u], pl[u]);
-                split_hi_lo_dot(ds, sh[u], sl[u]);
                 if (STREAM && qb + 2 < NB) fetch_term(qb + 2);
-                if (u == 1 || qb == NB - 1) {
-                    if (u == 0) ph[1] = pl[1] = sh[1] = sl[1] = as_bf16x4(uint2{0u, 0u});
-                    PH = pair_operand(ph[0], ph[1]), PL = pair_operand(pl[0], pl[1]);
-                    SH = pair_operand(sh[0], sh[1]), SL = pair_operand(sl[0], sl[1]);
-                }
+                PH[2 * u] = pack_bf16(pr[0], pr[1]), PH[2 * u + 1] = pack_bf16(pr[2], pr[3]);
+                rp = remainder(minus_one, uint2{PH[2 * u], PH[2 * u + 1]}, pr);
+                SH[2 * u] = pack_bf16(ds[0], ds[1]), SH[2 * u + 1] = pack_bf16(ds[2], ds[3]);
+                rs = remainder(minus_one, uint2{SH[2 * u], SH[2 * u + 1]}, ds);
+                if (qb + 1 < NB) products();
+                if (qb + 2 < NB) fetch_q(qb + 2);
             }
             __builtin_amdgcn_sched_barrier(0);
-            accumulate();
+            if (NB % 2 == 1) {
+                if (!EARLY) accumulate(PL, SL);  // of the last whole pair
+                fetch_t(NB / 2);
+                PH[2] = PH[3] = SH[2] = SH[3] = PL[2] = PL[3] = SL[2] = SL[3] = 0u;
+            }
+            lower((NB - 1) & 1);
+            accumulate(PH, SH);
+            accumulate(PL, SL);
             va = u32x2{pack_bf16(v0[0], v0[1]), pack_bf16(v0[2], v0[3])};
             vb = u32x2{pack_bf16(v1[0], v1[1]), pack_bf16(v1[2], v1[3])};
             ka = u32x2{pack_bf16(k0[0] * p.scale, k0[1] * p.scale), pack_bf16(k0[2] * p.scale, k0[3] * p.scale)};
@@ -781,11 +996,11 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), 2) bwd_bf16_keys_kernel(B
         } else {  // an idle wave moves its share all the same
 #pragma unroll
             for (int t = 0; t < PASSES; ++t) request_slab(buf ^ 1u, t);
-            request_rest(w + gm.G, has_next);
+            request_rest(w - gm.G, has_next);
         }
         // The next window's slabs are in LDS before this wave passes the barrier; the wait stands in front of the
         // stores, so that it does not wait for those.
-        next_q += step_q, next_g += step_g, next_d += step_d;
+        next_q -= step_q, next_g -= step_g, next_d -= step_d;
         lds_loads_done();
         park(buf ^ 1u);
         if (active) {

@@ -17,6 +17,7 @@ namespace fwa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef short bf16x4 __attribute__((ext_vector_type(4)));  // raw bf16 bits
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -202,7 +203,6 @@ __device__ __forceinline__ float sum_over_g(float x) {
 __device__ __forceinline__ uint32_t lower_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
 __device__ __forceinline__ uint32_t upper_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));  // raw bf16 bits
 __device__ __forceinline__ bf16x4 as_bf16x4(uint2 u) { return __builtin_bit_cast(bf16x4, u); }
 
 // fp32 values that are exactly bf16 (results of a product with a 0/1 matrix) -> packed bf16
@@ -260,6 +260,20 @@ __device__ __forceinline__ void split_hi_lo_dot(const f32x4& x, bf16x4& hi, bf16
     l.y = pack_bf16(r2, r3);
     hi = as_bf16x4(h);
     lo = as_bf16x4(l);
+}
+
+// The remainder x - hi of four values per lane from the matrix core, exact: minus_identity(g, n) times the packed upper parts
+// returns -hi to the lane that supplied it, whatever the values stand for, and x is the accumulator the product starts from.
+// (A NaN or an infinity makes the remainders of the four lanes with the same n NaN.)  It takes 8 to 11 cycles from the other
+// instructions of a SIMD, where masks and subtractions take 20 and the two-term dot product v_dot2c_f32_bf16 takes 17 and waits for the
+// matrix core to be idle besides: a block of 16 x 16 scores of the large-window backward's keys kernel as straight code,
+// two waves per SIMD, cycles with the dot product / masks / this: 272 / 258 / 198.
+__device__ __forceinline__ bf16x4 minus_identity(int g, int n) {
+    const uint32_t d = (uint32_t)(n - 4 * g);
+    return __builtin_bit_cast(bf16x4, uint2{d == 0u ? 0x0000bf80u : d == 1u ? 0xbf800000u : 0u, d == 2u ? 0x0000bf80u : d == 3u ? 0xbf800000u : 0u});
+}
+__device__ __forceinline__ f32x4 remainder(bf16x4 minus_one, uint2 hi, const f32x4& x) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(minus_one, __builtin_bit_cast(bf16x4, hi), x, 0, 0, 0);
 }
 
 // A operand of the K=32 matrix op that is all ones: times the probability operand of a pair of key blocks it

@@ -19,7 +19,7 @@ __device__ __forceinline__ uint32_t take_upper(float& a, float& b, bf16x2 first,
     return u;
 }
 __device__ __forceinline__ Planes split3(const f32x4& x) {
-    uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;  // (-1, 0), (0, -1), see split_hi_lo_dot
+    uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;  // (-1, 0), (0, -1): out of registers, as a literal the compiler takes the first for the inline constant -1.0f, which the instruction reads as (0, -1)
     asm("" : "+s"(c0));
     asm("" : "+s"(c1));
     const bf16x2 first = __builtin_bit_cast(bf16x2, c0), second = __builtin_bit_cast(bf16x2, c1);
