@@ -23,6 +23,13 @@ dbias_reduce_kernel(const f32x4* __restrict__ partial, float* __restrict__ dbias
     const size_t padded = (size_t)heads * nb * nb * 64;  // float4 per slot
     const size_t f = (size_t)blockIdx.x * 16 + x;        // < padded: the grid is padded / 16
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    // Lanes and quads of lanes beyond L hold nothing (the kernels may leave them unwritten): at L = 49, where they are 38 % of the
+    // array, they are neither written nor read.
+    const int lane = (int)(f & 63), blk = (int)(f >> 6);
+    const int b1 = blk % nb, b0 = (blk / nb) % nb, h = blk / (nb * nb);
+    if (16 * b1 + 4 * (lane >> 4) >= L) return;  // the whole workgroup: its 16 lanes share the quad
+    const bool live = 16 * b0 + (lane & 15) < L;
+    if (!live) slots = 0;
     // 8 loads in flight per thread (one at a time leaves the kernel waiting on L2 latency); the
     // additions keep the index order
     for (int s = y; s < slots; s += 8 * kReduceRows) {
@@ -42,8 +49,6 @@ dbias_reduce_kernel(const f32x4* __restrict__ partial, float* __restrict__ dbias
         f32x4 total = part[0][x];
 #pragma unroll
         for (int r = 1; r < kReduceRows; ++r) total += part[r][x];
-        const int lane = (int)(f & 63), blk = (int)(f >> 6);
-        const int b1 = blk % nb, b0 = (blk / nb) % nb, h = blk / (nb * nb);
         if (!key_on_lane) {
             // blocks [qb][jb]; lane (g, n) holds query 16 qb + n, keys 16 jb + 4g + r
             const int i = 16 * b0 + (lane & 15), j = 16 * b1 + 4 * (lane >> 4);

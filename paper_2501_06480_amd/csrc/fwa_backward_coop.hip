@@ -347,7 +347,8 @@ __global__ void __launch_bounds__(kCoopBoundThreads) bwd_bf16_coop_kernel(BwdArg
         // partial sums in register order: [slot][head][qb][jb][lane] float4 -- contiguous 16-byte stores
         f32x4* dst = reinterpret_cast<f32x4*>(p.partial) + ((size_t)bw * p.heads + h) * (NB * NB * 64) + lane;
 #pragma unroll
-        for (int jb = 0; jb < NB; ++jb) dst[(role * NB + jb) * 64] = dbacc[jb];
+        for (int jb = 0; jb < NB; ++jb)
+            if (16 * role + n < L && (jb < NB - 1 || 16 * jb + 4 * g < L)) dst[(role * NB + jb) * 64] = dbacc[jb];  // the rest is never read
     }
 }
 

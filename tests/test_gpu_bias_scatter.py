@@ -25,6 +25,15 @@ def test_scatter(heads, k):
     assert np.array_equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("heads,k", [(1, 1), (3, 2), (5, 7), (12, 8), (33, 9), (40, 16)])
+def test_gather(oracle, heads, k):
+    """One row per workgroup and several (more than 8192 rows), rows shorter and longer than a workgroup."""
+    import torch
+    import paper_2501_06480_amd as fwa
+    table = np.random.default_rng(200 * heads + k).standard_normal((heads, (2 * k - 1) ** 2)).astype(np.float32)
+    assert np.array_equal(fwa.fwa_bias_gather(torch.from_numpy(table).cuda(), k).cpu().numpy(), oracle.bias_gather(table, k).astype(np.float32))
+
+
 def test_more_entries_than_a_launch_has_room_for():
     """16 lanes per entry of 2^28 + 5 entries are more threads than one launch holds."""
     import torch
