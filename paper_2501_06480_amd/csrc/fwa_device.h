@@ -272,9 +272,12 @@ __device__ __forceinline__ bf16x4 minus_identity(int g, int n) {
     const uint32_t d = (uint32_t)(n - 4 * g);
     return __builtin_bit_cast(bf16x4, uint2{d == 0u ? 0x0000bf80u : d == 1u ? 0xbf800000u : 0u, d == 2u ? 0x0000bf80u : d == 3u ? 0xbf800000u : 0u});
 }
-__device__ __forceinline__ f32x4 remainder(bf16x4 minus_one, uint2 hi, const f32x4& x) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(minus_one, __builtin_bit_cast(bf16x4, hi), x, 0, 0, 0);
+__device__ __forceinline__ f32x4 remainder(bf16x4 minus_one, bf16x4 hi, const f32x4& x) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(minus_one, hi, x, 0, 0, 0);
 }
+__device__ __forceinline__ f32x4 remainder(bf16x4 minus_one, uint2 hi, const f32x4& x) { return remainder(minus_one, as_bf16x4(hi), x); }
+// four fp32 -> bf16, round to nearest even
+__device__ __forceinline__ bf16x4 packed4(const f32x4& x) { return as_bf16x4(uint2{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])}); }
 
 // A operand of the K=32 matrix op that is all ones: times the probability operand of a pair of key blocks it
 // returns, in every component of every lane (g, n), the sum over the pair's 32 keys of the (rounded)
