@@ -5,7 +5,7 @@
 // products, each exact and summed in fp32: x y = h h' + (h m' + m h') + (h l' + m m' + l h').  So the same result to the
 // last bits of fp32 costs 6 products of the 16 times as fast kind (the kernel before this one waited for the fp32 instruction in half
 // of its cycles).  What that needs: every K, V and Q value is split once per tile, every probability once, 3.5 vector
-// instructions each.  The error against 64 bits is smaller than that of the fp32 instruction, whose sums are rounded after
+// instructions each, or 1.5 and half a matrix instruction (split3).  The error against 64 bits is smaller than that of the fp32 instruction, whose sums are rounded after
 // every four products instead of 32: 1.2e-7 .. 1.7e-7 (2-norm) against 2.4e-7 .. 3.7e-7 over 81 to 256 tokens.
 //
 // A workgroup holds K and V of a (window, head) tile in LDS as three bf16 slabs each and walks the tiles t, t + grid, ...;
@@ -20,8 +20,9 @@
 // where all tiles do in the first case below (96 the kernel before this one), 60 at 256 tiles of 12 x 12, 4 heads (47), 41 at 864 of
 // 9 x 9, 2 heads (37).
 //
-// Measured, 256 windows of 16 x 16 tokens, 4 heads, bias: 99 -> 75 us (62: the fp32 instruction's own time); 264 tiles of 14 x 14
-// 41 -> 25; 64 windows of 12 x 12, 3 heads 12.5 -> 10.  A wave spends its time in thirds on scores, on probabilities and their
+// Measured, 256 windows of 16 x 16 tokens, 4 heads, bias: 99 -> 76 us (62: the fp32 instruction's own time), 73.5 since
+// the remainders of the splits come from the matrix core (1056 tiles of 14 x 14 68.6 -> 65.8, 4096 of 12 x 12 without a term
+// 87.4 -> 82.2); 264 tiles of 14 x 14 41 -> 25; 64 windows of 12 x 12, 3 heads 12.5 -> 10.  A wave spends its time in thirds on scores, on probabilities and their
 // products, and on stores, splits and barriers, which two or three waves per SIMD overlap in part: in the first case the
 // vector ALU is busy for 35 % of the cycles, the matrix cores for 25 %, the LDS for 23 %.
 #include "fwa_device.h"
@@ -68,6 +69,15 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
     int* const flag = reinterpret_cast<int*>(ldsb + 6 * SLAB);
     const uint32_t srow = (uint32_t)tid >> 3, scol = (uint32_t)tid & 7u;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    // Splits with the remainders from the matrix core, those of the next pair's weights beside the products of this one -- but not
+    // with an additive term at up to 7 blocks, where 168 registers would spill more (2304 tiles of 10 x 10 tokens 45.0 -> 46.8 us; of
+    // 9 x 9 3456 tiles 48.5 -> 47.2 but 48 tiles 5.38 -> 5.63), and at 9 (2048 tiles of 12 x 12 even, 48 tiles 7.03 -> 7.20).
+    constexpr bool MATRIX = !(BM && W < NB && (NB <= 7 || NB == 9));
+    const bf16x4 minus_one = minus_identity(g, n);
+    auto split = [&](const f32x4& x) {
+        if constexpr (MATRIX) return split3(minus_one, x);
+        else return split3(x);
+    };
 
     auto tile_of = [&](uint32_t t, uint32_t& w, uint32_t& h) {
         const uint32_t bh = t / parts;
@@ -92,7 +102,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
         nqc = load_f32x4(rq, off_q + 16u);
     };
     auto put = [&](char* slab, uint32_t row, const f32x4& x) {
-        const Planes s = split3(x);
+        const Planes s = split(x);
         char* const to = slab + row * 64u + scol * 8u;
         *reinterpret_cast<u32x2*>(to) = s.h;
         *reinterpret_cast<u32x2*>(to + SLAB) = s.m;
@@ -148,7 +158,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
         }
         for (int qb = (int)(t % parts + parts * wave); qb < NB; qb += (int)parts * W) {
             const bool fp32 = wide || __any(!(largest(largest(0.f, qa), qc) < kMostQK));
-            const Operand3 q = operand3(split3(qa), split3(qc));
+            const Operand3 q = operand3(split(qa), split(qc));
             const __amdgpu_buffer_rsrc_t rk = make_rsrc((const char*)p.k + tile, tile_bytes);
             // Four key blocks at a time: their additive term is requested in front of their score products, which outlast its
             // way from L2.
@@ -256,6 +266,16 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
                 f32x4 t0 = zero, t1 = zero;  // the small terms of both
                 const uint16_t* const lv16 = reinterpret_cast<const uint16_t*>(lv) + (4 * g + (n >> 2)) * 32 + 4 * (n & 3);
                 constexpr uint32_t P16 = SLAB / 2;
+                auto weights = [&](int kp) {  // of a pair of key blocks, in parts
+                    const bool two = 2 * kp + 1 < NB;
+                    exponentials(2 * kp, kLiftBits);
+                    if (two) exponentials(2 * kp + 1, kLiftBits);
+                    Planes second = {u32x2{0u, 0u}, u32x2{0u, 0u}, u32x2{0u, 0u}};
+                    if (two) second = split(s[two ? 2 * kp + 1 : 0]);
+                    return operand3(split(s[2 * kp]), second);
+                };
+                Operand3 e, next;
+                if (MATRIX) e = weights(0);
 #pragma unroll
                 for (int kp = 0; kp < NB2; ++kp) {
                     const bool two = 2 * kp + 1 < NB;
@@ -263,11 +283,8 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
                     const bf16x8 h0 = operand_tr(v, 512, two), h1 = operand_tr(v + 16, 512, two);
                     const bf16x8 m0 = operand_tr(v + P16, 512, two), m1 = operand_tr(v + P16 + 16, 512, two);
                     const bf16x8 l0 = operand_tr(v + 2 * P16, 512, two), l1 = operand_tr(v + 2 * P16 + 16, 512, two);
-                    exponentials(2 * kp, kLiftBits);
-                    if (two) exponentials(2 * kp + 1, kLiftBits);
-                    Planes second = {u32x2{0u, 0u}, u32x2{0u, 0u}, u32x2{0u, 0u}};
-                    if (two) second = split3(s[two ? 2 * kp + 1 : 0]);
-                    const Operand3 e = operand3(split3(s[2 * kp]), second);
+                    if (!MATRIX) e = weights(kp);
+                    else if (kp + 1 < NB2) next = weights(kp + 1);
                     // (in the order of small_products, each half on its own: even to 5 % slower, at 12 x 12 with a bias)
                     t0 = mfma_bf16(l0, e.h, t0);
                     t1 = mfma_bf16(l1, e.h, t1);
@@ -281,6 +298,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
                     t1 = mfma_bf16(h1, e.m, t1);
                     t0 = mfma_bf16(h0, e.l, t0);
                     t1 = mfma_bf16(h1, e.l, t1);
+                    if (MATRIX && kp + 1 < NB2) e = next;
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 o0 = (o0 + t0) * (1.0f / kLift);  // the lift of the weights leaves with their sum

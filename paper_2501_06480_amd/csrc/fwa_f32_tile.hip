@@ -341,7 +341,8 @@ __global__ void __launch_bounds__(256) bwd_f32_plain_kernel(BwdArgs p) {
 // fp32 instruction's time where all tiles are (leaving as early as V, dO, Q or K show it cost the others 4 % in spilled registers).
 // Measured against it, us: 2048 windows of 64 tokens, 4 heads of width 64 232 -> 202 (HBM alone 173), 488 windows, width 128
 // 135 -> 105, 244 of width 256 170 -> 147, 1700 of 49 tokens, 6 heads of width 32 138 -> 125; the error against 64 bits halves
-// (3.0e-7 -> 1.4e-7).  1 % of that is the lift.  Up to 256 tiles of 33 to 48 tokens and width 32 are 0.1 to 0.2 us (2 to 4 %)
+// (3.0e-7 -> 1.4e-7).  1 % of that is the lift.  Since the remainders of the splits come from the matrix core (split3) these take 200,
+// 104, 147 and 123; 128 windows of 49 tokens, 3 heads 10.5 -> 10.0.  Up to 256 tiles of 33 to 48 tokens and width 32 are 0.1 to 0.2 us (2 to 4 %)
 // slower than by the fp32 instruction.  The spills of a few registers at NB = 4 buy the third (width 64) workgroup per CU.
 template <int NB, int D>
 struct Split {
@@ -372,6 +373,7 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
     const uint32_t tile_bytes = (uint32_t)(L - 1) * row_bytes + 4u * D;
     const uint32_t tile_bytes_d = (uint32_t)(L - 1) * row_d + 4u * D;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    const bf16x4 minus_one = minus_identity(g, n);
 
     SlabInFlight<D, S::ROWS> kv;
     kv.request(make_rsrc((const char*)p.v + tile, tile_bytes), row_bytes, tid);
@@ -399,7 +401,7 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
             const f32x4 lifted = kv.v[t] * kLift;
             top = largest(top, lifted);
             if (row < (uint32_t)S::ROWS) {
-                const Planes x = split3(lifted);
+                const Planes x = split3(minus_one, lifted);
                 char* const to = slab + S::at(row, scol >> 1) + 8u * (scol & 1u);
                 *reinterpret_cast<u32x2*>(to) = x.h;
                 *reinterpret_cast<u32x2*>(to + S::PS) = x.m;
@@ -408,7 +410,7 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
         }
         fits = fits && fits_lifted(top);
     };
-    auto own = [&](const f32x4 (&x)[2 * S::CH], int c) { return operand3(split3(x[2 * c]), split3(x[2 * c + 1])); };
+    auto own = [&](const f32x4 (&x)[2 * S::CH], int c) { return operand3(split3(minus_one, x[2 * c]), split3(minus_one, x[2 * c + 1])); };
     auto own_top = [&](const f32x4 (&x)[2 * S::CH]) {
         float top = 0.f;
 #pragma unroll
@@ -516,11 +518,11 @@ __global__ void __launch_bounds__(256, D == 32 ? 4 : (D == 64 ? 3 : (D == 128 ? 
 #pragma unroll
         for (int jb = 0; jb < NB; ++jb) {
             s[jb] *= kLift;
-            place_tile(split3(s[jb]), jb);
+            place_tile(split3(minus_one, s[jb]), jb);
 #pragma unroll
             for (int r = 0; r < 4; ++r) dp[jb][r] = s[jb][r] * (dp[jb][r] - delta);  // dS, lifted
             top = largest(top, dp[jb]);
-            ds[jb] = split3(dp[jb]);
+            ds[jb] = split3(minus_one, dp[jb]);
         }
         fits = fits && fits_lifted(top);
         Operand3 b[NB2];

@@ -28,6 +28,16 @@ __device__ __forceinline__ Planes split3(const f32x4& x) {
     const uint32_t m0 = take_upper(a, b, first, second), m1 = take_upper(c, d, first, second);
     return Planes{u32x2{h0, h1}, u32x2{m0, m1}, u32x2{pack_bf16(a, b), pack_bf16(c, d)}};
 }
+// The same bits with the remainders from the matrix core (minus_identity, fwa_device.h): six conversions and two matrix instructions
+// for four values a lane instead of six and eight dot products, which wait for the matrix core to be idle.  Takes two registers
+// more, and an infinity or a NaN spreads to the lanes with the same n: for callers whose tiles with such values go another way.
+__device__ __forceinline__ Planes split3(bf16x4 minus_one, const f32x4& x) {
+    const bf16x4 h = packed4(x);
+    const f32x4 y = remainder(minus_one, h, x);
+    const bf16x4 m = packed4(y);
+    const bf16x4 l = packed4(remainder(minus_one, m, y));
+    return Planes{__builtin_bit_cast(u32x2, h), __builtin_bit_cast(u32x2, m), __builtin_bit_cast(u32x2, l)};
+}
 struct Operand3 {
     bf16x8 h, m, l;
 };
