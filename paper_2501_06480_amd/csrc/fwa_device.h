@@ -241,8 +241,8 @@ __device__ __forceinline__ void split_hi_lo(const f32x4& x, bf16x4& hi, bf16x4& 
 
 // The same split with the remainder from the two-term dot product, x - hi = x + (hi, other) . (-1, 0), which is exact:
 // two instructions fewer per pair.  It shares no issue slot with the other wave of a SIMD, which the masks and subtractions
-// above do, so it is for kernels with two waves per SIMD, where a wave's own issue counts (backward of 16 x 16 windows
-// 336 -> 328 us, of 14 x 14 97.4 -> 95.3; kernels with three waves per SIMD and more -1 .. +1 %).  The factors come out of
+// above do, so it is for kernels with two waves per SIMD, where a wave's own issue counts, that have no registers for remainder() below
+// (against the masks: backward of 16 x 16 windows 336 -> 328 us; kernels with three waves per SIMD and more -1 .. +1 %).  The factors come out of
 // registers: as a literal the compiler takes the pair (-1, 0) for the inline constant -1.0f, which the instruction reads as (0, -1).
 __device__ __forceinline__ void split_hi_lo_dot(const f32x4& x, bf16x4& hi, bf16x4& lo) {
     uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;  // (-1, 0), (0, -1)
