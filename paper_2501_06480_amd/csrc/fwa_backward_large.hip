@@ -24,8 +24,9 @@
 // Both kernels are persistent: a wave keeps its block for life and its workgroup walks the windows bw, bw + G, ...
 // Most of their work is vector instructions (5 to 6 per score besides the exponential), so everything that does not change from window to window stays out of the loop:
 // (bias + mask[w mod nW]) * log2e of the block's 16 x L scores sits in registers (G is a multiple of the mask
-// period), -M_i / scale and -delta_i enter as the
-// accumulators that the products Q K^T and dO V^T start from.  Reading the additive term per window
+// period), -delta_i enters as the accumulator that the product dO V^T starts from.  (-M_i / scale as that of Q K^T saves a subtraction
+// per score, 0 to 4 % of a call, but rounds every score at the size of M: the probability of a key that holds its row
+// alone was off by 1 % at scores of 1e5 and by any factor beyond 1e6.)  Reading the additive term per window
 // instead (the form for dense masks whose period no G is a multiple of) costs its loads, the LDS patch that turns
 // rows into lanes, and three to four more instructions per score.  Measured, N = 1024 windows of 16 x 16 tokens,
 // 4 heads, bias + labels + dBias: rows 210 -> 148 us, keys 283 -> 167 us (kernels of their own that read the term per
@@ -45,8 +46,6 @@
 #include "fwa_device.h"
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
-
-#include <cfloat>
 
 namespace fwa {
 namespace {
@@ -693,16 +692,6 @@ enum { kTermNone = 0,    // no additive term
        kTermStream = 3,  // a dense mask read for every window, and the bias too where the registers are needed for dBias
        kTermStreamMask = 4 };  // a dense mask alone, read for every window
 
-// What the score products of a row start from, -M / sl2, so that exp2(sl2 * score + term) is the probability: one fma per
-// score instead of an fma and a subtraction.  The roundings of M, the quotient and the sums are 2^-21 of M at most.  Where that is
-// more than a probability can bear (M beyond 2^20, rows that lost every key to a large finite mask) M is raised by as much, or it
-// would be a power of two of any size; and a negative M makes no infinity.  M = +infinity (rows beyond L) makes all of them zero.
-__device__ __forceinline__ float start_of_scores(float m, float sl2) {
-    const float a = fabsf(m);
-    const float c = (a > 0x1p20f && a < INFINITY ? fmaf(a, 0x1p-21f, m) : m) / -sl2;
-    return m < 0.f ? fminf(fmaxf(c, -FLT_MAX), FLT_MAX) : c;
-}
-
 template <int NB>
 constexpr size_t keys_lds() {  // two buffers of: Q, dO slabs; then two of: M, -delta, labels; the waves' output cells
     return (size_t)2 * 2 * 16 * NB * kLargeStride * 16 + (size_t)2 * 3 * 16 * NB * 4 + (size_t)keys_waves(NB) * 16 * 80;
@@ -742,10 +731,7 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
     const int L = p.L;
     const uint32_t row_bytes = (uint32_t)p.ldq * 2u, row_g = (uint32_t)p.ldg * 2u, row_d = (uint32_t)p.ldd * 2u;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    // The score products start from -M_i / sl2, so that one fma makes the exponent.  Without a scale to divide by the scores
-    // are zeros: the K operand is, and the divisor is one.
-    const bool flat = fabsf(p.scale) < 0x1p-100f;
-    const float sl2 = flat ? 1.0f : p.scale * kLog2e;
+    const float sl2 = p.scale * kLog2e;
     const bf16x4 minus_one = minus_identity(g, n);
 
     // two buffers: window w is computed out of one while the slabs of w + G are on their way into the other
@@ -812,22 +798,12 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
         pst = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc(src, on ? bytes : 0u), off_st, 0, 0);
         // the wave's own K and V rows as operands: row 16 jb + n, channels 8g .. 8g + 7
         const uint32_t off = (16u * jb + (l & 15u)) * row_bytes + 16u * (l >> 4), own = on ? tile_bytes : 0u;
-        pk = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.k + next_q, flat ? 0u : own), off, 0, 0);
+        pk = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.k + next_q, own), off, 0, 0);
         pv = __builtin_amdgcn_raw_buffer_load_b128(make_rsrc((const char*)p.v + next_q, own), off, 0, 0);
     };
     auto park = [&](uint32_t buf) {
         // M, -delta and labels lie one behind the other: ROWS / 4 = 4 NB <= 64 units of 16 bytes each
-        u32x4 st = pst;
-        if (wave == 0) {  // what the products start from instead of M
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t b = pst[c];
-                const float m = __builtin_bit_cast(float, b);
-                const float x = start_of_scores(m, sl2);
-                st[c] = __builtin_bit_cast(uint32_t, x);
-            }
-        }
-        if (wave < (PW ? 3u : 2u) && lane < ROWS / 4) reinterpret_cast<u32x4*>(stats + buf * ST + wave * ROWS)[lane] = st;
+        if (wave < (PW ? 3u : 2u) && lane < ROWS / 4) reinterpret_cast<u32x4*>(stats + buf * ST + wave * ROWS)[lane] = pst;
     };
     if (left > 0) {  // in flight while the additive term is fetched
         ask(true);
@@ -888,15 +864,15 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
             // stretch of vector instructions has matrix instructions beside it that do not depend on it.
             bf16x8 oq, og, tg0, tg1, tx0, tx1;
             u32x4 PH = {0u, 0u, 0u, 0u}, SH = PH, PL = PH, SL = PH;  // operands of a pair: upper and lower parts of P and dS
-            f32x4 oM, oD, sc, dp, rp = zero, rs = zero, ab[2], am[2];
+            f32x4 oM[2], oD, sc, dp, rp = zero, rs = zero, ab[2], am[2];
             i32x4 al[2];
             auto fetch_q = [&](int qb) {
                 oq = __builtin_bit_cast(bf16x8, lq[opd + 16 * qb * STRIDE]);
                 og = __builtin_bit_cast(bf16x8, lg[opd + 16 * qb * STRIDE]);
-                oM = *reinterpret_cast<const f32x4*>(stM + 16 * qb + 4 * g);
                 oD = *reinterpret_cast<const f32x4*>(stD + 16 * qb + 4 * g);
             };
-            auto fetch_l = [&](int qb) {
+            auto fetch_m = [&](int qb) {
+                oM[qb & 1] = *reinterpret_cast<const f32x4*>(stM + 16 * qb + 4 * g);
                 if (PW) al[qb & 1] = *reinterpret_cast<const i32x4*>(llab + 16 * qb + 4 * g);
             };
             auto fetch_term = [&](int qb) {
@@ -914,7 +890,7 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
                 }
             };
             auto products = [&]() {
-                sc = mfma_bf16(oq, kop, oM);  // <q_i, k_j> - M_i / sl2, i = 16 qb + 4g + r, j = 16 jb + n
+                sc = mfma_bf16(oq, kop, zero);  // <q_i, k_j>, i = 16 qb + 4g + r, j = 16 jb + n
                 dp = mfma_bf16(og, vop, oD);  // dP - delta
             };
             auto fetch_t = [&](int qp) {  // dO^T and Q^T of the 32 queries (channel on the lane)
@@ -938,7 +914,7 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
             if (STREAM) fetch_term(0);
             products();
             fetch_q(1);
-            fetch_l(0);
+            fetch_m(0);
             if (STREAM) fetch_term(1);
 #pragma unroll
             for (int qb = 0; qb < NB; ++qb) {
@@ -954,20 +930,17 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
                 if (u == 0 && qb > 0) accumulate(PH, SH);
                 if (EARLY ? u == 0 && qb > 0 : u == 1 && qb > 1) accumulate(PL, SL);
                 if (u == 1) fetch_t(qb / 2);
-                if (qb + 1 < NB) fetch_l(qb + 1);
+                if (qb + 1 < NB) fetch_m(qb + 1);
                 if (qb > 0 && !(EARLY && u == 0)) lower(u ^ 1);
                 f32x4 pr, ds;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    float x;
-                    if (TERM == kTermNone) {
-                        x = sc[r] * sl2;
-                    } else {
-                        float t;
-                        if (STREAM) t = KEEPB ? fmaf(am[u][r], kLog2e, add[qb][r]) : (HB ? ab[u][r] + am[u][r] : am[u][r]) * kLog2e;
-                        else t = PW ? add[qb][r] + (al[u][r] == lkey ? 0.f : mv) : add[qb][r];
-                        x = fmaf(sc[r], sl2, t);
-                    }
+                    // The score is rounded as in the rows kernel before M leaves it (without a term too, where one fma would make the
+                    // exponent): so the probabilities are those that its sums were made of, whatever the size of the scores.
+                    float t = 0.f;
+                    if (STREAM) t = KEEPB ? fmaf(am[u][r], kLog2e, add[qb][r]) : (HB ? ab[u][r] + am[u][r] : am[u][r]) * kLog2e;
+                    else if (TERM != kTermNone) t = PW ? add[qb][r] + (al[u][r] == lkey ? 0.f : mv) : add[qb][r];
+                    const float x = fmaf(sc[r], sl2, t) - oM[u][r];
                     pr[r] = __builtin_amdgcn_exp2f(x);
                     ds[r] = pr[r] * dp[r];
                 }
