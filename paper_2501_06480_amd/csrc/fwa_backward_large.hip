@@ -22,7 +22,8 @@
 // kernels for small windows.
 //
 // Both kernels are persistent: a wave keeps its block for life and its workgroup walks the windows bw, bw + G, ...
-// Most of their work is vector instructions (5 to 6 per score besides the exponential), so everything that does not change from window to window stays out of the loop:
+// Most of their work is vector instructions (6 to 7 per score besides the exponential), so everything that does not
+// change from window to window stays out of the loop:
 // (bias + mask[w mod nW]) * log2e of the block's 16 x L scores sits in registers (G is a multiple of the mask
 // period), -delta_i enters as the accumulator that the product dO V^T starts from.  (-M_i / scale as that of Q K^T saves a subtraction
 // per score, 0 to 4 % of a call, but rounds every score at the size of M: the probability of a key that holds its row
@@ -33,10 +34,10 @@
 // window and parked the slabs out of registers between two barriers), the whole call 465 -> 325 us; N = 315 windows
 // of 14 x 14, 5 heads, bias, no dBias: 133 (one kernel with both passes) -> 51 + 55 us.  What bounds them is the instruction
 // stream of a SIMD: a matrix instruction takes 8 to 11 cycles from the vector instructions beside it, and some vector instructions
-// (the two-term dot product, which made the remainder of the hi/lo split before) wait for the matrix core to be idle.  Cycles of a
-// wave per block of 16 x 16 scores, two waves per SIMD, 16 x 16 windows: keys 515 -> 466 with the remainder from the matrix core
-// and M in the products, rows 427 -> 386 with that and without a row maximum; the clock falls from 1.9 to 1.83 GHz of 2.4
-// meanwhile (power).  The call 320 -> 302 us, 14 x 14 windows without dBias 95 -> 90.
+// (the two-term dot product, which made the remainder of the hi/lo split before) wait for the matrix core to be idle.  With the
+// remainder from the matrix core the call takes 298 us instead of 314, 14 x 14 windows without dBias 89 instead of 94; the clock falls from
+// 1.9 to 1.83 GHz of 2.4 meanwhile (power).  (Exponentials of the scores without their maximum save another 2 to 3 %, but rows whose sum
+// they lose have to be made twice: 28 to 38 % of the call at scores of standard deviation 10.)
 //
 // The statistics M_i, -delta_i (8 bytes per query) travel from one kernel to the other inside the outputs that the
 // second one overwrites: the 16 floats of a query block are as long as the 64-byte slice of the head in one token
@@ -96,108 +97,22 @@ __device__ __forceinline__ void store_rows(char* cell, const u32x2 lo, const u32
     __builtin_amdgcn_raw_buffer_store_b128(rows, dst, (uint32_t)(16 * blk + r) * row_d + 16u * c, 0, 0);
 }
 
-// The second half of a query block's work, from the exponentials in s (not normalised: P = s / sum) and their reduced sums over
-// the row, sum and delta: dQ^T = K^T dS^T over pairs of key blocks, packed into lo2, hi2, and the statistics M (m = the largest
-// score, 0 where it was not subtracted) and neg_delta.  lk, lv: the K and V slabs; opd / trs: the lane's offsets for row
-// operands / transposing reads.  dP is made anew, from -delta; products are issued one step ahead of the vector work that
-// needs them, what remains of dS after its upper parts comes from the matrix core and is packed a step later, and the scheduling
-// barriers keep the compiler from collecting them at one end of the loop (2-3 % at L = 196).
-template <int NB>
-__device__ __forceinline__ void rows_gradient(const f32x4 (&s)[NB], float m, float sum, float delta, const bf16x8 gop, const uint4* lk,
-                                              const uint4* lv, uint32_t opd, uint32_t trs, const bf16x4 minus_one, float scale,
-                                              float& M, float& neg_delta, f32x4& q0, f32x4& q1) {
-    constexpr int NB2 = (NB + 1) / 2;
-    constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    auto v_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]); };
-    bf16x8 o0 = v_rows(0), o1 = v_rows(1);
-    sum = sum_over_g(sum);
-    const float inv = __builtin_amdgcn_rcpf(sum);
-    delta = sum_over_g(delta) * inv;
-    M = m + __builtin_amdgcn_logf(sum);  // p_ij = exp2(score_ij - M_i)
-    neg_delta = -delta;
-    const f32x4 nd = {neg_delta, neg_delta, neg_delta, neg_delta};
-    q0 = zero, q1 = zero;  // dQ[16 qb + n][4g + r], dQ[16 qb + n][16 + 4g + r]
-    const uint16_t* lk16 = reinterpret_cast<const uint16_t*>(lk) + trs;
-    f32x4 da, db;  // dP - delta of the two blocks of a pair
-    da = mfma_bf16(o0, gop, nd);
-    db = mfma_bf16(o1, gop, nd);
-    if (NB > 2) o0 = v_rows(2);
-    if (NB > 3) o1 = v_rows(3);
-    bf16x8 tk0, tk1;
-    u32x4 dh = {0u, 0u, 0u, 0u};
-    f32x4 ra = zero, rb = zero;  // what remains of dS of the last pair
-    auto accumulate = [&]() {
-        q0 = mfma_bf16(tk0, as_bf16x8(dh), q0);
-        q1 = mfma_bf16(tk1, as_bf16x8(dh), q1);
-        const bf16x8 dl = as_bf16x8(u32x4{pack_bf16(ra[0], ra[1]), pack_bf16(ra[2], ra[3]), pack_bf16(rb[0], rb[1]), pack_bf16(rb[2], rb[3])});
-        q0 = mfma_bf16(tk0, dl, q0);
-        q1 = mfma_bf16(tk1, dl, q1);
-    };
-#pragma unroll
-    for (int kp = 0; kp < NB2; ++kp) {
-        const bool two = 2 * kp + 1 < NB;
-        __builtin_amdgcn_sched_barrier(0);
-        if (kp > 0) accumulate();
-        tk0 = operand_tr(lk16 + (32 * kp) * SROW, 16 * SROW, two);
-        tk1 = operand_tr(lk16 + (32 * kp) * SROW + 16, 16 * SROW, two);
-        const f32x4 a = s[2 * kp] * da, b = two ? s[two ? 2 * kp + 1 : 0] * db : zero;  // dS, times the row sum
-        if (2 * kp + 2 < NB) da = mfma_bf16(o0, gop, nd);
-        if (2 * kp + 3 < NB) db = mfma_bf16(o1, gop, nd);
-        if (2 * kp + 4 < NB) o0 = v_rows(2 * kp + 4);
-        if (2 * kp + 5 < NB) o1 = v_rows(2 * kp + 5);
-        dh = u32x4{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), two ? pack_bf16(b[0], b[1]) : 0u, two ? pack_bf16(b[2], b[3]) : 0u};
-        ra = remainder(minus_one, uint2{dh.x, dh.y}, a);
-        rb = two ? remainder(minus_one, uint2{dh.z, dh.w}, b) : zero;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    accumulate();
-    const float qs = scale * inv;  // the lane's query row: dQ_i = scale / sum_i * (the products above)
-    q0 *= qs;
-    q1 *= qs;
-}
-// The same from the scores: s holds them (scaled, with the additive term, -inf beyond L) and m their maximum over the lane's keys.
-// `between(i)` is called in between, i = 0, 1, ..., NB - 1 (a place for the next window's loads).
-template <int NB, class Between>
-__device__ __forceinline__ void rows_block(f32x4 (&s)[NB], float m, const bf16x8 gop, const uint4* lk, const uint4* lv,
-                                           uint32_t opd, uint32_t trs, const bf16x4 minus_one, float scale, float& M, float& neg_delta,
-                                           f32x4& q0, f32x4& q1, Between between) {
-    constexpr uint32_t STRIDE = kLargeStride;
-    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    auto v_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]); };
-    m = max_over_g(m);
-    float sum = 0.f, delta = 0.f;
-    f32x4 dp[2];
-    dp[0] = mfma_bf16(v_rows(0), gop, zero);
-    bf16x8 ov = v_rows(1);
-#pragma unroll
-    for (int jb = 0; jb < NB; ++jb) {
-        __builtin_amdgcn_sched_barrier(0);
-        between(jb);
-        if (jb + 1 < NB) dp[(jb + 1) & 1] = mfma_bf16(ov, gop, zero);
-        if (jb + 2 < NB) ov = v_rows(jb + 2);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float e = __builtin_amdgcn_exp2f(s[jb][r] - m);
-            s[jb][r] = e;
-            sum += e;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) delta = fmaf(s[jb][r], dp[jb & 1][r], delta);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    rows_gradient<NB>(s, m, sum, delta, gop, lk, lv, opd, trs, minus_one, scale, M, neg_delta, q0, q1);
-}
 __device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
     const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
     return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
 }
-// The same in fewer registers, for the kernels whose waves per SIMD leave no room for the pipeline above: both parts of dS in one step,
-// the remainder by the dot product.
-template <int NB, class Between>
-__device__ __forceinline__ void rows_block_tight(f32x4 (&s)[NB], float m, const bf16x8 gop, const uint4* lk, const uint4* lv,
-                                           uint32_t opd, uint32_t trs, float scale, float& M, float& neg_delta,
-                                           u32x2& lo2, u32x2& hi2, Between between) {
+// What follows the scores in the query orientation, shared by the two rows kernels: s holds the scaled scores (with
+// the additive term, -inf beyond L), m their maximum over the lane's keys; on return the block's dQ rows are packed in
+// lo2, hi2, and M, neg_delta are its statistics.  lk, lv: the K and V slabs; opd / trs: the lane's offsets for row
+// operands / transposing reads.  Matrix products are issued one step ahead of the vector work that needs them, and
+// the scheduling barriers keep the compiler from collecting them at one end of a loop (2-3 % at L = 196).
+// `between(i)` is called in between, i = 0, 1, ..., NB - 1 (a place for the next window's loads).
+// What remains of dS after its upper parts comes from the matrix core and is packed a step later; TIGHT: both parts in one step, the
+// remainder by the dot product, in fewer registers.
+template <int NB, bool TIGHT, class Between>
+__device__ __forceinline__ void rows_block(f32x4 (&s)[NB], float m, const bf16x8 gop, const uint4* lk, const uint4* lv,
+                                           uint32_t opd, uint32_t trs, [[maybe_unused]] const bf16x4 minus_one, float scale, float& M,
+                                           float& neg_delta, u32x2& lo2, u32x2& hi2, Between between) {
     constexpr int NB2 = (NB + 1) / 2;
     constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -232,48 +147,64 @@ __device__ __forceinline__ void rows_block_tight(f32x4 (&s)[NB], float m, const 
     M = m + __builtin_amdgcn_logf(sum);  // p_ij = exp2(score_ij - M_i)
     neg_delta = -delta;
     const f32x4 nd = {neg_delta, neg_delta, neg_delta, neg_delta};
-    // dQ^T = K^T dS^T over pairs of key blocks
+    // dQ^T = K^T dS^T over pairs of key blocks; dP is made anew, from -delta
     f32x4 q0 = zero, q1 = zero;  // dQ[16 qb + n][4g + r], dQ[16 qb + n][16 + 4g + r]
     const uint16_t* lk16 = reinterpret_cast<const uint16_t*>(lk) + trs;
-    f32x4 da[2], db[2];  // dP - delta of the two blocks of a pair
+    f32x4 da[2], db[2];  // dP - delta of the two blocks of a pair (TIGHT: of two pairs in turns)
     da[0] = mfma_bf16(o0, gop, nd);
     db[0] = mfma_bf16(o1, gop, nd);
     if (NB > 2) o0 = v_rows(2);
     if (NB > 3) o1 = v_rows(3);
-    bf16x8 tk0, tk1, dh, dl;
+    bf16x8 tk0, tk1;
+    u32x4 dh = {0u, 0u, 0u, 0u}, dl = dh;
+    [[maybe_unused]] f32x4 ra = zero, rb = zero;  // what remains of dS of the last pair
+    auto accumulate = [&]() {
+        q0 = mfma_bf16(tk0, as_bf16x8(dh), q0);
+        q1 = mfma_bf16(tk1, as_bf16x8(dh), q1);
+        if constexpr (!TIGHT)
+            dl = u32x4{pack_bf16(ra[0], ra[1]), pack_bf16(ra[2], ra[3]), pack_bf16(rb[0], rb[1]), pack_bf16(rb[2], rb[3])};
+        q0 = mfma_bf16(tk0, as_bf16x8(dl), q0);
+        q1 = mfma_bf16(tk1, as_bf16x8(dl), q1);
+    };
 #pragma unroll
     for (int kp = 0; kp < NB2; ++kp) {
         const bool two = 2 * kp + 1 < NB;
-        const int cur = kp & 1;
+        const int cur = TIGHT ? kp & 1 : 0, nxt = TIGHT ? cur ^ 1 : 0;
         __builtin_amdgcn_sched_barrier(0);
-        if (2 * kp + 2 < NB) da[cur ^ 1] = mfma_bf16(o0, gop, nd);
-        if (2 * kp + 3 < NB) db[cur ^ 1] = mfma_bf16(o1, gop, nd);
-        if (kp > 0) {
-            q0 = mfma_bf16(tk0, dh, q0);
-            q1 = mfma_bf16(tk1, dh, q1);
-            q0 = mfma_bf16(tk0, dl, q0);
-            q1 = mfma_bf16(tk1, dl, q1);
+        if constexpr (TIGHT) {
+            if (2 * kp + 2 < NB) da[nxt] = mfma_bf16(o0, gop, nd);
+            if (2 * kp + 3 < NB) db[nxt] = mfma_bf16(o1, gop, nd);
+            if (kp > 0) accumulate();
+            if (2 * kp + 4 < NB) o0 = v_rows(2 * kp + 4);
+            if (2 * kp + 5 < NB) o1 = v_rows(2 * kp + 5);
+        } else if (kp > 0) {
+            accumulate();
         }
-        if (2 * kp + 4 < NB) o0 = v_rows(2 * kp + 4);
-        if (2 * kp + 5 < NB) o1 = v_rows(2 * kp + 5);
         tk0 = operand_tr(lk16 + (32 * kp) * SROW, 16 * SROW, two);
         tk1 = operand_tr(lk16 + (32 * kp) * SROW + 16, 16 * SROW, two);
-        bf16x4 hi[2], lo[2];
-        hi[1] = lo[1] = as_bf16x4(uint2{0u, 0u});
-        split_hi_lo_dot(s[2 * kp] * da[cur], hi[0], lo[0]);  // dS, times the row sum
-        if (two) split_hi_lo_dot(s[two ? 2 * kp + 1 : 0] * db[cur], hi[1], lo[1]);
-        dh = pair_operand(hi[0], hi[1]), dl = pair_operand(lo[0], lo[1]);
+        const f32x4 a = s[2 * kp] * da[cur], b = two ? s[two ? 2 * kp + 1 : 0] * db[cur] : zero;  // dS, times the row sum
+        if constexpr (TIGHT) {
+            bf16x4 hi[2], lo[2];
+            hi[1] = lo[1] = as_bf16x4(uint2{0u, 0u});
+            split_hi_lo_dot(a, hi[0], lo[0]);
+            if (two) split_hi_lo_dot(b, hi[1], lo[1]);
+            dh = __builtin_bit_cast(u32x4, pair_operand(hi[0], hi[1])), dl = __builtin_bit_cast(u32x4, pair_operand(lo[0], lo[1]));
+        } else {
+            if (2 * kp + 2 < NB) da[nxt] = mfma_bf16(o0, gop, nd);
+            if (2 * kp + 3 < NB) db[nxt] = mfma_bf16(o1, gop, nd);
+            if (2 * kp + 4 < NB) o0 = v_rows(2 * kp + 4);
+            if (2 * kp + 5 < NB) o1 = v_rows(2 * kp + 5);
+            dh = u32x4{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), two ? pack_bf16(b[0], b[1]) : 0u, two ? pack_bf16(b[2], b[3]) : 0u};
+            ra = remainder(minus_one, uint2{dh.x, dh.y}, a);
+            rb = two ? remainder(minus_one, uint2{dh.z, dh.w}, b) : zero;
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
-    q0 = mfma_bf16(tk0, dh, q0);
-    q1 = mfma_bf16(tk1, dh, q1);
-    q0 = mfma_bf16(tk0, dl, q0);
-    q1 = mfma_bf16(tk1, dl, q1);
+    accumulate();
     const float qs = scale * inv;  // the lane's query row: dQ_i = scale / sum_i * (the products above)
     lo2 = u32x2{pack_bf16(q0[0] * qs, q0[1] * qs), pack_bf16(q0[2] * qs, q0[3] * qs)};
     hi2 = u32x2{pack_bf16(q1[0] * qs, q1[1] * qs), pack_bf16(q1[2] * qs, q1[3] * qs)};
 }
-__device__ __forceinline__ u32x2 packed_row(const f32x4& q) { return u32x2{pack_bf16(q[0], q[1]), pack_bf16(q[2], q[3])}; }
 // -inf for the keys of the last block beyond L; the running maximum m takes a block's scores in
 template <int NB>
 __device__ __forceinline__ void pad_and_max(f32x4& x, int jb, int L, int g, float& m) {
@@ -300,19 +231,19 @@ constexpr size_t rows_lds() {
     return (size_t)2 * 2 * 16 * NB * kLargeStride * 16 + (size_t)2 * 16 * NB * 4 + (size_t)rows_waves(NB) * 16 * 80;
 }
 
-// Waves per SIMD that the registers leave room for: said where the compiler would take a few more and lose one (81 tokens, labels
-// per window, 1656 windows, 3 heads: 46 us with four, 52 with three).
-constexpr int rows_per_simd(int nb, bool bm, bool pw) { return nb <= 6 ? (bm ? 4 : 5) : nb == 7 ? (pw ? 3 : 4) : nb <= 12 ? (bm || nb == 12 ? 3 : 4) : (bm ? 2 : 3); }
+// Waves per SIMD, said where the compiler would take two registers too many and lose one (112 tokens, bias, 690 windows, 3 heads:
+// 42.7 us with four, 45.3 with three; elsewhere its own choice is as fast, and without a term at 81 to 96 and 193 to 224 tokens 3 to 7 %
+// faster than one wave more).
+constexpr int rows_per_simd(int nb, bool bm, bool pw) { return nb == 7 && bm && !pw ? 4 : 1; }
 
-// Kernels whose waves per SIMD leave no registers for the longer pipeline (11 to 40 of them spilled): they take every row around its
-// maximum and split dS where it is made.
-constexpr bool rows_tight(int nb, bool bm, bool pw) { return pw ? nb <= 6 || nb == 11 || nb == 12 : bm && nb == 12; }
+// Kernels whose three waves per SIMD leave no registers for the longer pipeline (16 to 19 of them spilled): 192 tokens, labels per window,
+// 232 windows, 3 heads 44.4 us against 56.4, with dBias 52.9 against 64.4, 161 tokens with dBias 54.9 against 65.8.
+constexpr bool rows_tight(int nb, bool pw) { return pw && (nb == 11 || nb == 12); }
 
 template <int NB, bool BM, bool PW>
 __global__ void __launch_bounds__(64 * rows_waves(NB), rows_per_simd(NB, BM, PW)) bwd_bf16_rows_kernel(BwdArgs p, LargeGeom gm) {
     constexpr int W = rows_waves(NB);
     constexpr int ROWS = 16 * NB;
-    constexpr bool TIGHT = rows_tight(NB, BM, PW);
     constexpr int PASSES = (ROWS + 16 * W - 1) / (16 * W);  // the workgroup moves 16 W slab rows per pass
     constexpr uint32_t STRIDE = kLargeStride, SROW = STRIDE * 8;
     constexpr uint32_t SLAB = ROWS * STRIDE;                // in uint4
@@ -416,98 +347,32 @@ __global__ void __launch_bounds__(64 * rows_waves(NB), rows_per_simd(NB, BM, PW)
             f32x4 s[NB];
             const int* const lab = llab + buf * ROWS;
             const AddendRegsLabels<NB> with_labels = {add, lab, PW ? lab[16 * qb + n] : 0, mv, g};
-            auto k_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lk[opd + 16 * jb * STRIDE]); };
-            auto v_rows = [&](int jb) { return __builtin_bit_cast(bf16x8, lv[opd + 16 * jb * STRIDE]); };
-            auto scaled = [&](int jb) {
-                const f32x4 t = PW ? with_labels.block(jb) : (BM ? add[jb] : zero);
-                f32x4 x;
+            // all K operands are asked for at once (they are as large as the scores that replace them), and the
+            // products run two blocks ahead of the vector work on them
+            float m = -INFINITY;
+            bf16x8 ok[NB];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    x[r] = BM ? fmaf(s[jb][r], sl2, t[r]) : s[jb][r] * sl2;
-                    if (jb == NB - 1 && 16 * jb + 4 * g + r >= L) x[r] = -INFINITY;
+            for (int jb = 0; jb < NB; ++jb) ok[jb] = __builtin_bit_cast(bf16x8, lk[opd + 16 * jb * STRIDE]);
+#pragma unroll
+            for (int jb = 0; jb < NB + 2; ++jb) {
+                if (jb < NB) s[jb] = mfma_bf16(ok[jb], qop, zero);
+                if (jb >= 2) {
+                    const int c = jb - 2;
+                    const f32x4 t = PW ? with_labels.block(c) : (BM ? add[c] : zero);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) s[c][r] = BM ? fmaf(s[c][r], sl2, t[r]) : s[c][r] * sl2;
+                    pad_and_max<NB>(s[c], c, L, g, m);
                 }
-                return x;
-            };
-            auto next_loads = [&](int i) {
+                if (jb & 1) __builtin_amdgcn_sched_barrier(0);
+            }
+            rows_block<NB, rows_tight(NB, PW)>(s, m, gop, lk, lv, opd, trs, minus_one, p.scale, M, nd, lo, hi, [&](int i) {
                 // the next window's loads one pair at a time: issued in one go they queue at the CU's address unit
                 // and hold the wave up
 #pragma unroll
                 for (int t = 0; t < PASSES; ++t)
                     if (i == 2 * t) request_slab(buf ^ 1u, t);
                 if (i == 3) request_rest(w + step, has_next);
-            };
-            if constexpr (!TIGHT) {
-                f32x4 q0, q1;
-                // The exponentials are taken of the scores as they are: what the row maximum would keep in range is in range for any
-                // scores but the largest, and a maximum has to wait for the last product of the row.  The row is
-                // made again around its maximum where that does not hold (see below).
-                float sum = 0.f, delta = 0.f;
-                f32x4 dp[2];
-                bf16x8 ok = k_rows(2), ov = v_rows(1);
-                s[0] = mfma_bf16(k_rows(0), qop, zero);
-                dp[0] = mfma_bf16(v_rows(0), gop, zero);
-                s[1] = mfma_bf16(k_rows(1), qop, zero);
-#pragma unroll
-                for (int jb = 0; jb < NB; ++jb) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    next_loads(jb);
-                    if (jb + 2 < NB) s[jb + 2] = mfma_bf16(ok, qop, zero);
-                    if (jb + 1 < NB) dp[(jb + 1) & 1] = mfma_bf16(ov, gop, zero);
-                    if (jb + 3 < NB) ok = k_rows(jb + 3);
-                    if (jb + 2 < NB) ov = v_rows(jb + 2);
-                    const f32x4 x = scaled(jb);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float e = __builtin_amdgcn_exp2f(x[r]);
-                        s[jb][r] = e;
-                        sum += e;
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) delta = fmaf(s[jb][r], dp[jb & 1][r], delta);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                rows_gradient<NB>(s, 0.f, sum, delta, gop, lk, lv, opd, trs, minus_one, p.scale, M, nd, q0, q1);
-                // In range: a sum of at least 2^-10 (so that no probability that counts was lost below 2^-126) and at most 2^40, and
-                // nothing in dQ that is not finite (a product with an exponential of up to 2^40 may overflow where one with a
-                // probability does not).
-                float rest = 0.f;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) rest = fmaf(q0[r], 0.f, rest), rest = fmaf(q1[r], 0.f, rest);
-                const bool good = fabsf(M + rest - 15.f) <= 25.f;
-                if (__builtin_expect(__any(!good && 16 * qb + n < L), 0)) {
-                    float m = -INFINITY;
-#pragma unroll
-                    for (int jb = 0; jb < NB; ++jb) {
-                        __builtin_amdgcn_sched_barrier(0);
-                        s[jb] = mfma_bf16(k_rows(jb), qop, zero);
-                        s[jb] = scaled(jb);
-                        m = fmaxf(fmaxf(m, s[jb][0]), s[jb][1]);
-                        m = fmaxf(fmaxf(m, s[jb][2]), s[jb][3]);
-                    }
-                    rows_block<NB>(s, m, gop, lk, lv, opd, trs, minus_one, p.scale, M, nd, q0, q1, [](int) {});
-                }
-                lo = packed_row(q0), hi = packed_row(q1);
-            } else {
-                float m = -INFINITY;
-                // all K operands are asked for at once (they are as large as the scores that replace them), and the
-                // products run two blocks ahead of the vector work on them
-                bf16x8 ok[NB];
-#pragma unroll
-                for (int jb = 0; jb < NB; ++jb) ok[jb] = k_rows(jb);
-#pragma unroll
-                for (int jb = 0; jb < NB + 2; ++jb) {
-                    if (jb < NB) s[jb] = mfma_bf16(ok[jb], qop, zero);
-                    if (jb >= 2) {
-                        const int c = jb - 2;
-                        const f32x4 t = PW ? with_labels.block(c) : (BM ? add[c] : zero);
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) s[c][r] = BM ? fmaf(s[c][r], sl2, t[r]) : s[c][r] * sl2;
-                        pad_and_max<NB>(s[c], c, L, g, m);
-                    }
-                    if (jb & 1) __builtin_amdgcn_sched_barrier(0);
-                }
-                rows_block_tight<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, next_loads);
-            }
+            });
         } else {  // an idle wave moves its share all the same
 #pragma unroll
             for (int t = 0; t < PASSES; ++t) request_slab(buf ^ 1u, t);
@@ -670,7 +535,7 @@ __global__ void __launch_bounds__(64 * stream_waves(NB)) bwd_bf16_rows_stream_ke
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb) pad_and_max<NB>(s[jb], jb, L, g, m);
             u32x2 lo, hi;
-            rows_block_tight<NB>(s, m, gop, lk, lv, opd, trs, p.scale, M, nd, lo, hi, [](int) {});
+            rows_block<NB, true>(s, m, gop, lk, lv, opd, trs, bf16x4{0, 0, 0, 0}, p.scale, M, nd, lo, hi, [](int) {});
             if (has_next && qb + W >= NB) request(w + gm.G);  // the wave's last block of this window
             store_stats<NB>(p, tile_d, row_d, qb, n, g, M, nd);
             store_rows(reinterpret_cast<char*>(patch), lo, hi, make_rsrc((char*)p.dq + tile_d, tile_bytes_d), qb, row_d, lane);
@@ -755,8 +620,8 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
     }
 
     // The Q and dO slabs of the next window go straight from memory into the other LDS buffer (no registers, no LDS
-    // writes), requested at the top of a window; its statistics (wave 0: M, wave 1: -delta, 16 bytes per lane), its
-    // labels and the wave's own K and V rows wait in registers.  Rows beyond L are never loaded: zeros from the start.
+    // writes), requested over the first half of a window's blocks; its statistics (wave 0: M, wave 1: -delta, 16 bytes per lane), its
+    // labels and the wave's own K and V rows are requested at block REST_AT and wait in registers.  Rows beyond L are never loaded: zeros from the start.
     static_assert(W >= 3, "wave 2 fetches the labels");
     const uint32_t off_q = ((uint32_t)lane >> 2) * row_bytes + ((uint32_t)lane & 3u) * 16u, off_g = ((uint32_t)lane >> 2) * row_g + ((uint32_t)lane & 3u) * 16u;
     static_assert(4 * SLAB * 16 <= 65536, "direct loads reach the first 64 KB");

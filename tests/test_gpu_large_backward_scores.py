@@ -1,6 +1,5 @@
-"""The backward above 64 tokens at the edges of its score arithmetic.  One kernel takes the exponentials of the scores as they are
-and makes a row again around its maximum where their sum leaves [2^-10, 2^40] or dQ is not finite; the other makes the scores again and
-subtracts what the first found.  A constant added to every score of a row changes nothing, which is the reference here; the scale may
+"""The backward above 64 tokens at the edges of its score arithmetic.  One kernel finds the maximum
+and the sum of every row, the other makes the scores again and subtracts what the first found.  A constant added to every score of a row changes nothing, which is the reference here; the scale may
 be zero."""
 import numpy as np
 import pytest
@@ -46,10 +45,10 @@ def _draw(L, heads, N, kind):
     return w, x, bias, mask, labels
 
 
-def _check(got, ref, what, unit=1.0):
+def _check(got, ref, what):
     for name, a, b in zip(("dq", "dk", "dv"), got, ref):
         assert np.isfinite(a).all(), (what, name)
-        check_bf16_output(a / unit, b, f"{what} {name}")
+        check_bf16_output(a, b, f"{what} {name}")
 
 
 @pytest.mark.parametrize("dbias", [False, True])
@@ -57,7 +56,7 @@ def _check(got, ref, what, unit=1.0):
 def test_rows_far_from_zero(oracle, L, heads, N, kind, dbias):
     w, x, bias, mask, labels = _draw(L, heads, N, kind)
     ref = oracle.backward(x["q"], x["k"], x["v"], x["d_o"], heads, w.scale, bias, mask, want_dbias=dbias)
-    # rows of one block: both sides of the two limits (in units of ln 2), some blocks untouched
+    # rows of one block near zero and far from it on both sides (in units of ln 2), some blocks untouched
     shift = np.zeros((1, L, 1), np.float32)
     shift[0, :, 0] = np.resize(np.float32([0, 24, 40, 400, -14, -20, -300, 0]) * np.float32(0.6931472), L)
     shift[0, 32:64] = 0
@@ -81,18 +80,22 @@ def test_scales(oracle, L, heads, N, kind, scale):
     assert np.abs(got[3] - ref[3]).max() <= 2e-4
 
 
-@pytest.mark.parametrize("L,heads,N,kind", [SHAPES[1], SHAPES[4]], ids=["L100", "L256"])
-def test_gradients_of_any_size(oracle, L, heads, N, kind):
-    """dO of 2^100 overflows beside exponentials of up to 2^40 (rows with a shift of 38), where it does not beside probabilities."""
+@pytest.mark.parametrize("dbias", [False, True])
+@pytest.mark.parametrize("L,heads,N,kind", [SHAPES[1], SHAPES[3], SHAPES[4]], ids=["L100", "L193", "L256"])
+def test_gradients_of_any_size(oracle, L, heads, N, kind, dbias):
+    """dO of 2^100 and 2^-90, beside rows whose scores lie 20 (28.9 in units of ln 2) above the others': what a kernel keeps of a row
+    before it divides by the row's sum may neither overflow nor vanish.  With dBias the pair of kernels takes every one of these calls."""
     import torch
     w, x, bias, mask, labels = _draw(L, heads, N, kind)
-    ref = oracle.backward(x["q"], x["k"], x["v"], x["d_o"], heads, w.scale, bias, mask, want_dbias=False)
+    ref = oracle.backward(x["q"], x["k"], x["v"], x["d_o"], heads, w.scale, bias, mask, want_dbias=dbias)
     shift = np.zeros((1, L, 1), np.float32)
     shift[0, 16:48] = np.float32(20.0)
     for power in (100, -90):
         g = to_device(x, w, "d_o") * torch.tensor(2.0 ** power, device="cuda").to(torch.bfloat16)
-        got = _call(x, w, bias + shift, mask, labels, w.scale, False, g)
-        _check(got, ref, f"L={L} dO 2^{power}", 2.0 ** power)
+        got = _call(x, w, bias + shift, mask, labels, w.scale, dbias, g)
+        _check([a / 2.0 ** power for a in got[:3]], ref, f"L={L} dO 2^{power}")
+        if dbias:
+            assert np.abs(got[3] / 2.0 ** power - ref[3]).max() <= 2e-4 * max(1.0, np.sqrt(N))
 
 
 @pytest.mark.parametrize("value", [-1e4, -1e9, -1e38])
