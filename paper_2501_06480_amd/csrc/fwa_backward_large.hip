@@ -562,10 +562,11 @@ constexpr size_t keys_lds() {  // two buffers of: Q, dO slabs; then two of: M, -
     return (size_t)2 * 2 * 16 * NB * kLargeStride * 16 + (size_t)2 * 3 * 16 * NB * 4 + (size_t)keys_waves(NB) * 16 * 80;
 }
 
-// Waves per SIMD: two at least, more where the registers and the LDS have room for them.
-constexpr int keys_per_simd(int nb, int term, bool db) {
-    return (nb == 9 && term == kTermLabels && !db) || (nb == 7 && term == kTermStreamMask) ? 3 : 2;
-}
+// Waves per SIMD: two at least; more said for 65 to 80 tokens, where a workgroup is small and the compiler takes a few registers too many.
+// Four against three there: no term, dBias, 2048 windows of 65 tokens, 3 heads 67.9 us against 75.6, labels per window without dBias 70.2
+// against 87.3.  Three against two: dense mask per window, dBias 91.8 against 94.7.  Three elsewhere only spill: 100 tokens, mask alone per
+// window 70.8 against 67.8, 161 tokens, no term 53.5 against 45.8, 81 tokens, labels per window 112 against 69.
+constexpr int keys_per_simd(int nb, int term, bool db) { return nb > 5 ? 2 : term == kTermNone || !db ? 4 : 3; }
 
 template <int NB, int TERM, bool DB>
 __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, DB)) bwd_bf16_keys_kernel(BwdArgs p, LargeGeom gm) {
@@ -574,10 +575,13 @@ __global__ void __launch_bounds__(64 * keys_waves(NB), keys_per_simd(NB, TERM, D
     constexpr bool PW = TERM == kTermLabels;
     constexpr bool KEEPB = TERM == kTermStream && NB <= 12;  // the bias in registers all the same
     constexpr bool HB = TERM == kTermStream && !KEEPB;
-    // the block during which the next window's rows and statistics are requested: late, while they wait they take registers,
-    // but ahead of the loads of a term that is read for every window
-    constexpr int REST_AT = STREAM ? NB / 2 : NB == 5 || (NB >= 15 && PW) ? NB - 1 : NB - 3;
-    // the products of the lower parts with those of the upper ones, not a block later: fewer registers
+    // The block during which the next window's rows and statistics are requested: late, while they wait they take registers,
+    // but ahead of the loads of a term that is read for every window.  At 65 to 80 tokens the last one is the third: there the last but
+    // two would be the first half (bias without dBias 63.8 us against 78.6; labels per window with dBias the other way round, 91.6
+    // against 85.9), and 225 to 256 tokens with labels per window have few registers (55.4 against 56.1).
+    constexpr int REST_AT = STREAM ? NB / 2 : (NB == 5 && !(PW && DB)) || (NB >= 15 && PW) ? NB - 1 : NB - 3;
+    // The products of the lower parts with those of the upper ones, not a block later: fewer registers (65 tokens, bias without dBias 63.8 us
+    // against 78.1; mask per window at 97 to 112 tokens 70.8 against 72.7, elsewhere -1 to +1 %).
     constexpr bool EARLY = NB == 5 || STREAM;
     constexpr uint32_t PARTS = (uint32_t)keys_parts(NB);
     constexpr int W = keys_waves(NB);
