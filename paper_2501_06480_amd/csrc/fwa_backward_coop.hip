@@ -110,7 +110,11 @@ __global__ void __launch_bounds__(kCoopBoundThreads) bwd_bf16_coop_kernel(BwdArg
     for (int jb = 0; jb < NB; ++jb) dbacc[jb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    const bf16x4 minus_one = minus_identity(g, n);
+    // Remainders of the splits of P and dS from the matrix core: above 49 tokens, where they save 2 to 7 % (128 windows of 64 tokens, 32
+    // heads, labels 48.8 -> 46.0 us), and at 49 with dBias (Swin-T stage 1 with bias and mask 127.7 -> 126.7).  At 49 without dBias the last
+    // block holds one key, and they cost 1 to 6 % (4096 windows, 12 heads, bias 248 -> 263); fewer blocks would lose a wave per SIMD.
+    constexpr bool MATRIX = NB == 4 && (KT == 4 || DB);
+    [[maybe_unused]] const bf16x4 minus_one = minus_identity(g, n);
 
     // slab movement: thread -> (row, 16-byte column); 4 hpb threads per row and 64 NB hpb threads: one pass covers
     // the slab.  (rip < ROWS holds for every thread; without the branches on it the compiler mixes the stores with what
@@ -240,28 +244,30 @@ __global__ void __launch_bounds__(kCoopBoundThreads) bwd_bf16_coop_kernel(BwdArg
                     dp[jb][r] = (jb == NB - 1 && r >= KT) ? 0.f : s[jb][r] * (dp[jb][r] - delta);  // dS
                 if (DB) dbacc[jb] += dp[jb];
             }
-            // hi + lo bf16 parts of P and dS: rows of this block into the LDS tiles for phase B.  Above 48 tokens what remains after
-            // the upper parts comes from the matrix core, for all blocks before the first is packed (Swin-T stage 1 with bias, mask
-            // and dBias 127.7 -> 126.7 us, 128 windows of 64 tokens with 32 heads and labels 48.8 -> 46.0); the kernels for fewer blocks would lose a wave per SIMD to it.
-            bf16x4 p_hi[NB], p_lo[NB], ds_hi[NB], ds_lo[NB];
+            // hi + lo bf16 parts of P and dS: rows of this block into the LDS tiles for phase B.  MATRIX: what remains after the upper
+            // parts comes from the matrix core, for all blocks before the first is packed.
+            bf16x4 p_hi[NB], ds_hi[NB], ds_lo[NB];
+            if constexpr (MATRIX) {
 #pragma unroll
-            for (int jb = 0; jb < NB; ++jb) {
-                if constexpr (NB == 4) {
+                for (int jb = 0; jb < NB; ++jb) {
                     p_hi[jb] = packed4(s[jb]);
                     s[jb] = remainder(minus_one, p_hi[jb], s[jb]);
                     ds_hi[jb] = packed4(dp[jb]);
                     dp[jb] = remainder(minus_one, ds_hi[jb], dp[jb]);
-                } else {
-                    split_hi_lo(s[jb], p_hi[jb], p_lo[jb]);
-                    split_hi_lo(dp[jb], ds_hi[jb], ds_lo[jb]);
                 }
             }
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb) {
-                if constexpr (NB == 4) p_lo[jb] = packed4(s[jb]), ds_lo[jb] = packed4(dp[jb]);
+                bf16x4 p_lo;
+                if constexpr (MATRIX) {
+                    p_lo = packed4(s[jb]), ds_lo[jb] = packed4(dp[jb]);
+                } else {
+                    split_hi_lo(s[jb], p_hi[jb], p_lo);
+                    split_hi_lo(dp[jb], ds_hi[jb], ds_lo[jb]);
+                }
                 uint16_t* cell = ex + (16 * qb + n) * XS + ((jb ^ (n & 3)) << 4) + ((g ^ ((n >> 2) & 3)) << 2);
                 *reinterpret_cast<uint2*>(cell + 0 * XT) = __builtin_bit_cast(uint2, p_hi[jb]);
-                *reinterpret_cast<uint2*>(cell + 1 * XT) = __builtin_bit_cast(uint2, p_lo[jb]);
+                *reinterpret_cast<uint2*>(cell + 1 * XT) = __builtin_bit_cast(uint2, p_lo);
                 *reinterpret_cast<uint2*>(cell + 2 * XT) = __builtin_bit_cast(uint2, ds_hi[jb]);
                 *reinterpret_cast<uint2*>(cell + 3 * XT) = __builtin_bit_cast(uint2, ds_lo[jb]);
             }
@@ -360,8 +366,11 @@ __global__ void __launch_bounds__(kCoopBoundThreads) bwd_bf16_coop_kernel(BwdArg
         // partial sums in register order: [slot][head][qb][jb][lane] float4 -- contiguous 16-byte stores
         f32x4* dst = reinterpret_cast<f32x4*>(p.partial) + ((size_t)bw * p.heads + h) * (NB * NB * 64) + lane;
 #pragma unroll
-        for (int jb = 0; jb < NB; ++jb)
-            if (16 * role + n < L && (jb < NB - 1 || 16 * jb + 4 * g < L)) dst[(role * NB + jb) * 64] = dbacc[jb];  // the rest is never read
+        for (int jb = 0; jb < NB; ++jb) {
+            // What lies beyond L is never read.  Above 48 tokens it is not stored either (38 % at 49); below, asking costs more than it saves
+            // (8192 windows of 25 tokens, 8 heads 171 -> 176 us).
+            if (NB < 4 || (16 * role + n < L && (jb < NB - 1 || 16 * jb + 4 * g < L))) dst[(role * NB + jb) * 64] = dbacc[jb];
+        }
     }
 }
 
