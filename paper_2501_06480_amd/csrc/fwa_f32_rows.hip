@@ -51,7 +51,12 @@ constexpr uint32_t kRowV = 144;  // bytes from row to row of a V that is not spl
 template <int NB>
 constexpr size_t f32_rows_lds() { return (size_t)6 * 16 * NB * 64 + 16; }
 
-template <int NB, bool BM, int W>
+// Splits with the remainders from the matrix core -- but not with an additive term at up to 7 blocks, where 168 registers would spill more
+// (2304 tiles of 10 x 10 tokens 45.0 -> 46.8 us; of 9 x 9 3456 tiles 48.5 -> 47.2 but 48 tiles 5.38 -> 5.63), and at 9 (2048 tiles of
+// 12 x 12 even, 48 tiles 7.03 -> 7.20).
+constexpr bool f32_rows_matrix(int nb, bool bm, int w) { return !(bm && w < nb && (nb <= 7 || nb == 9)); }
+
+template <int NB, bool BM, int W, bool MATRIX>
 __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)) ? 3 : 2) fwd_f32_rows_kernel(FwdArgs p, uint32_t parts, uint32_t tiles) {
     constexpr int ROWS = 16 * NB;
     constexpr int PASSES = (ROWS + 8 * W - 1) / (8 * W);  // the workgroup moves 8 W slab rows per pass
@@ -69,10 +74,7 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
     int* const flag = reinterpret_cast<int*>(ldsb + 6 * SLAB);
     const uint32_t srow = (uint32_t)tid >> 3, scol = (uint32_t)tid & 7u;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    // Splits with the remainders from the matrix core, those of the next pair's weights beside the products of this one -- but not
-    // with an additive term at up to 7 blocks, where 168 registers would spill more (2304 tiles of 10 x 10 tokens 45.0 -> 46.8 us; of
-    // 9 x 9 3456 tiles 48.5 -> 47.2 but 48 tiles 5.38 -> 5.63), and at 9 (2048 tiles of 12 x 12 even, 48 tiles 7.03 -> 7.20).
-    constexpr bool MATRIX = !(BM && W < NB && (NB <= 7 || NB == 9));
+    // MATRIX: splits with the remainders from the matrix core, those of the next pair's weights beside the products of this one
     const bf16x4 minus_one = minus_identity(g, n);
     auto split = [&](const f32x4& x) {
         if constexpr (MATRIX) return split3(minus_one, x);
@@ -330,11 +332,11 @@ __global__ void __launch_bounds__(64 * W, W < NB && (NB <= 7 || (NB == 8 && !BM)
     }
 }
 
-template <int NB, bool BM, int W>
+template <int NB, bool BM, int W, bool MATRIX = f32_rows_matrix(NB, BM, W)>
 hipError_t launch_rows_w(const FwdArgs& a, hipStream_t st) {
     static std::atomic<int> once{0};
     int per_cu = 1;
-    const hipError_t e = workgroups_per_cu(reinterpret_cast<const void*>(&fwd_f32_rows_kernel<NB, BM, W>), 64u * W, f32_rows_lds<NB>(), once, per_cu);
+    const hipError_t e = workgroups_per_cu(reinterpret_cast<const void*>(&fwd_f32_rows_kernel<NB, BM, W, MATRIX>), 64u * W, f32_rows_lds<NB>(), once, per_cu);
     if (e != hipSuccess) return e;
     // While the chip holds several workgroups per tile: the query blocks of a tile over them, each with its own copy of K and V
     // (150 tiles of 196 tokens 15.4 -> 13.9 us), down to one block per SIMD (with two for half of them 8.7 -> 11.1).
@@ -342,7 +344,7 @@ hipError_t launch_rows_w(const FwdArgs& a, hipStream_t st) {
     const long long parts = W > f32_rows_waves(NB, BM) ? 1LL : std::max(1LL, std::min(resident / pairs, (long long)(NB + 3) / 4));
     const long long tiles = pairs * parts;
     const unsigned grid = (unsigned)std::min(tiles, resident);
-    hipLaunchKernelGGL((fwd_f32_rows_kernel<NB, BM, W>), dim3(grid), dim3(64u * W), f32_rows_lds<NB>(), st, a, (uint32_t)parts, (uint32_t)tiles);
+    hipLaunchKernelGGL((fwd_f32_rows_kernel<NB, BM, W, MATRIX>), dim3(grid), dim3(64u * W), f32_rows_lds<NB>(), st, a, (uint32_t)parts, (uint32_t)tiles);
     return hipGetLastError();
 }
 template <int NB, bool BM>
@@ -354,6 +356,11 @@ hipError_t launch_rows_bm(const FwdArgs& a, hipStream_t st) {
         // (At 5, 6 and 8 blocks the two workgroups were no slower than the fp32 instruction; here they were, 7.9 us.)
         const long long pairs = a.N * a.heads;
         if (2 * pairs > cu_count() && pairs <= cu_count()) return launch_rows_w<NB, BM, NB>(a, st);
+    }
+    if constexpr (!BM && (NB == 6 || NB == 7)) {
+        // Up to half a tile per CU a wave has one block and nothing to make beside its products: the remainder's way through the matrix
+        // core shows (64 tiles of 112 tokens 4.89 us with it, 4.70 without; 192 tiles 6.07 and 6.17, 1536 tiles 28.0 and 29.3).
+        if (2 * a.N * a.heads <= cu_count()) return launch_rows_w<NB, BM, f32_rows_waves(NB, BM), false>(a, st);
     }
     return launch_rows_w<NB, BM, f32_rows_waves(NB, BM)>(a, st);
 }
