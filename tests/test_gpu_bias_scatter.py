@@ -25,9 +25,10 @@ def test_scatter(heads, k):
     assert np.array_equal(got[0], got[1])
 
 
-@pytest.mark.parametrize("heads,k", [(1, 1), (3, 2), (5, 7), (12, 8), (33, 9), (40, 16)])
+@pytest.mark.parametrize("heads,k", [(1, 1), (3, 2), (29, 3), (5, 7), (12, 8), (7, 9), (33, 12), (40, 16), (2100, 4)])
 def test_gather(oracle, heads, k):
-    """One row per workgroup and several (more than 8192 rows), rows shorter and longer than a workgroup."""
+    """One row per workgroup and up to 256 of them, the last workgroup cut, whole and ragged powers of two of columns, several turns of
+    a workgroup (more rows than 8192 workgroups hold)."""
     import torch
     import paper_2501_06480_amd as fwa
     table = np.random.default_rng(200 * heads + k).standard_normal((heads, (2 * k - 1) ** 2)).astype(np.float32)
