@@ -39,10 +39,6 @@ struct FusedGeom {
 constexpr int fused_waves(int nb) { return nb <= 10 ? 4 : 8; }
 // slab rows in 16-byte units: 64 bytes of data and no padding (reads run at the same rate with 16 bytes of it)
 constexpr uint32_t kFusedStride = 4;
-__device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
-    const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
-    return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
-}
 
 // HB: no bias (0) or an fp32 bias (1; a bf16 bias arrives as an fp32 copy made once per call); HM: no mask (0), a dense
 // mask (1), or region labels from which the mask values are formed in registers (2).  What is absent costs neither

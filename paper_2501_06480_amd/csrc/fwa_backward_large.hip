@@ -97,10 +97,6 @@ __device__ __forceinline__ void store_rows(char* cell, const u32x2 lo, const u32
     __builtin_amdgcn_raw_buffer_store_b128(rows, dst, (uint32_t)(16 * blk + r) * row_d + 16u * c, 0, 0);
 }
 
-__device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
-    const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
-    return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
-}
 // What follows the scores in the query orientation, shared by the two rows kernels: s holds the scaled scores (with
 // the additive term, -inf beyond L), m their maximum over the lane's keys; on return the block's dQ rows are packed in
 // lo2, hi2, and M, neg_delta are its statistics.  lk, lv: the K and V slabs; opd / trs: the lane's offsets for row
@@ -535,6 +531,7 @@ __global__ void __launch_bounds__(64 * stream_waves(NB)) bwd_bf16_rows_stream_ke
 #pragma unroll
             for (int jb = 0; jb < NB; ++jb) pad_and_max<NB>(s[jb], jb, L, g, m);
             u32x2 lo, hi;
+            // in the tight form: the longer pipeline gives up to 1 % from 145 tokens on, but 97 tokens take 75.6 us with it, 72.5 without
             rows_block<NB, true>(s, m, gop, lk, lv, opd, trs, bf16x4{0, 0, 0, 0}, p.scale, M, nd, lo, hi, [](int) {});
             if (has_next && qb + W >= NB) request(w + gm.G);  // the wave's last block of this window
             store_stats<NB>(p, tile_d, row_d, qb, n, g, M, nd);

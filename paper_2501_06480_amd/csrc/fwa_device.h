@@ -204,6 +204,11 @@ __device__ __forceinline__ uint32_t lower_halves(uint32_t a, uint32_t b) { retur
 __device__ __forceinline__ uint32_t upper_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
 
 __device__ __forceinline__ bf16x4 as_bf16x4(uint2 u) { return __builtin_bit_cast(bf16x4, u); }
+// two blocks of four values as one operand of the K = 32 matrix instruction
+__device__ __forceinline__ bf16x8 pair_operand(bf16x4 a, bf16x4 b) {
+    const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
+    return as_bf16x8(u32x4{ua.x, ua.y, ub.x, ub.y});
+}
 
 // fp32 values that are exactly bf16 (results of a product with a 0/1 matrix) -> packed bf16
 __device__ __forceinline__ uint2 pack_exact_u2(const f32x4& x) {
