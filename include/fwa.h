@@ -116,6 +116,9 @@ int fwa_forward_strided(const void* q, const void* k, const void* v, void* o,
  *                may be NULL when dbias is NULL, unless L > 64 and the bias is
  *                bf16.  Contents on entry are ignored and undefined on exit.
  * Results are bit-reproducible from run to run for fixed arguments.
+ * For L > 64 a row that finite additive terms of about -1.2e7 or less shut to every key enters dk, dv and
+ * dbias with up to L times its weight (fp32 cannot hold the logarithm of its sum beside such a maximum);
+ * its dq is not affected, nor is anything where its d_o is zero.
  */
 int fwa_backward(const void* q, const void* k, const void* v, const void* d_o,
                  void* dq, void* dk, void* dv, float* dbias,

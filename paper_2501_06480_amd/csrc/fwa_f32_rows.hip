@@ -24,7 +24,7 @@
 // the remainders of the splits come from the matrix core (1056 tiles of 14 x 14 68.6 -> 65.8, 4096 of 12 x 12 without a term
 // 87.4 -> 82.2); 264 tiles of 14 x 14 41 -> 25; 64 windows of 12 x 12, 3 heads 12.5 -> 10.  A wave spends its time in thirds on scores, on probabilities and their
 // products, and on stores, splits and barriers, which two or three waves per SIMD overlap in part: in the first case the
-// vector ALU is busy for 35 % of the cycles, the matrix cores for 25 %, the LDS for 23 %.
+// vector ALU is busy for 32 % of the cycles, the matrix cores for 32 %, the LDS for 24 %.
 #include "fwa_device.h"
 #include "fwa_internal.h"
 #include "fwa_softmax.h"
