@@ -36,6 +36,18 @@ def test_forward(oracle, L, N, heads, form):
     assert max_abs(to_f64(o), want) <= TOL["f32"]
 
 
+@pytest.mark.parametrize("L", [81, 96, 97, 112])
+def test_both_sides_of_half_a_tile_per_cu(L):
+    """6 and 7 blocks without a term split their values in one way up to half the 256 CUs and in another beyond: the same bits."""
+    import torch
+    import paper_2501_06480_amd as fwa
+    g = torch.Generator(device="cuda").manual_seed(L)
+    q, k, v = (torch.randn(129, L, 32, device="cuda", generator=g) for _ in range(3))
+    many = fwa.fwa_forward(q, k, v, 1, 32 ** -0.5)
+    few = fwa.fwa_forward(q[:128], k[:128], v[:128], 1, 32 ** -0.5)
+    assert torch.equal(few, many[:128])
+
+
 @pytest.mark.parametrize("L", [97, 100, 112])
 @pytest.mark.parametrize("tiles", [128, 129, 256, 257])
 @pytest.mark.parametrize("form", ["none", "bias"])

@@ -25,6 +25,15 @@ CASES = [
     ("beyond_L65", 65, 24, 100, 50, True, True),
     ("beyond_L65_no_bias", 65, 24, 100, 50, False, True),
     ("beyond_L81_no_dbias", 81, 24, 100, 50, True, False),
+    # block counts whose kernels state their waves per SIMD or take the tight form
+    ("beyond_L80", 80, 24, 100, 50, True, True),
+    ("beyond_L80_no_dbias", 80, 24, 100, 50, True, False),
+    ("beyond_L96", 96, 24, 60, 60, True, True),
+    ("beyond_L112", 112, 24, 44, 44, False, True),
+    ("beyond_L144_no_dbias", 144, 16, 40, 40, True, False),
+    ("beyond_L161", 161, 16, 36, 36, True, True),
+    ("beyond_L176_no_dbias", 176, 16, 36, 36, True, False),
+    ("beyond_L192", 192, 16, 36, 36, True, True),
     ("beyond_L177", 177, 16, 40, 40, True, True),
     ("beyond_L256", 256, 12, 24, 24, True, True),
     ("beyond_L256_mask_alone", 256, 12, 24, 24, False, False),
